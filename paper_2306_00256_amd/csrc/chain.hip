@@ -39,20 +39,18 @@ __device__ __forceinline__ Raw<V, MODE, READ_Y> load_raw(const ChainArgs& A, int
 template <typename V, int MODE, bool EXCH_Y, bool READ_Y>
 __device__ __forceinline__ void agent_terms(const ChainArgs& A, const Raw<V, MODE, READ_Y>& r, int agent,
                                             int64_t col, V& xs, V& ys, V& v) {
-  // no fused multiply-add here or in message_only: a message must have the same bits whether its
-  // own stretch or a neighbouring one computes it, so results do not depend on the launch shape
+  // no contraction of the compiler's choosing here or in message_only: a message must have the same bits whether
+  // its own stretch or a neighbouring one computes it, so results do not depend on the launch shape
 #pragma clang fp contract(off)
   const V z = EXCH_Y ? r.y : r.x;
   if (MODE == MODE_GOSSIP) {
     xs = r.x; ys = r.y; v = z;
   } else if (MODE == MODE_QUAD) {
     V e = z - r.aux;
-    if (A.noise_std != 0.0f) e += A.noise_std * noise_group<V>(col, noise_keys(A.seed, A.k, (uint32_t)agent));
-    const V ge = A.lr * e;
-    xs = r.x - ge; ys = r.y - ge; v = z - ge;
+    if (A.noise_std != 0.0f) e = add_noise<V>(e, A.noise_std, col, noise_keys(A.seed, A.k, (uint32_t)agent));
+    xs = half_step(r.x, A.lr, e); ys = half_step(r.y, A.lr, e); v = EXCH_Y ? ys : xs;
   } else if (MODE == MODE_GRAD) {
-    const V ge = A.lr * r.aux;
-    xs = r.x - ge; ys = r.y - ge; v = z - ge;
+    xs = half_step(r.x, A.lr, r.aux); ys = half_step(r.y, A.lr, r.aux); v = EXCH_Y ? ys : xs;
   } else {  // MODE_FROMV: aux = v, so -lr e = v - z
     v = r.aux;
     const V dz = v - z;
@@ -69,11 +67,10 @@ __device__ __forceinline__ V message_only(const ChainArgs& A, int agent, int64_t
   if (MODE == MODE_FROMV) return ld_plain<V>(A.aux + (int64_t)agent * A.ldaux + col);
   const V z = ld_plain<V>((EXCH_Y ? A.yin : A.xin) + off);
   if (MODE == MODE_GOSSIP) return z;
-  if (MODE == MODE_GRAD) return z - A.lr * ld_plain<V>(A.aux + (int64_t)agent * A.ldaux + col);
+  if (MODE == MODE_GRAD) return half_step(z, A.lr, ld_plain<V>(A.aux + (int64_t)agent * A.ldaux + col));
   V e = z - ld_plain<V>(A.aux + (int64_t)agent * A.ldaux + col);
-  if (A.noise_std != 0.0f) e += A.noise_std * noise_group<V>(col, noise_keys(A.seed, A.k, (uint32_t)agent));
-  const V ge = A.lr * e;
-  return z - ge;
+  if (A.noise_std != 0.0f) e = add_noise<V>(e, A.noise_std, col, noise_keys(A.seed, A.k, (uint32_t)agent));
+  return half_step(z, A.lr, e);
 }
 
 // Per-thread walk state: where the thread is on its cycle and the message of the row before.

@@ -136,13 +136,6 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h) {
   h ^= h >> 16;
   return h;
 }
-__device__ __forceinline__ uint32_t noise_word(uint32_t c, uint32_t k0, uint32_t k1) {
-  uint32_t h = c ^ k0;
-  h ^= h >> 16; h *= 0x7feb352du;
-  h ^= h >> 15; h += k1; h *= 0x846ca68bu;
-  h ^= h >> 16;
-  return h;
-}
 struct NoiseKeys { uint32_t k0, k1; };
 __device__ __forceinline__ NoiseKeys noise_keys(uint32_t seed, uint32_t k, uint32_t agent) {
   NoiseKeys nk;
@@ -150,31 +143,59 @@ __device__ __forceinline__ NoiseKeys noise_keys(uint32_t seed, uint32_t k, uint3
   nk.k1 = mix32(nk.k0 + 0x85ebca6bu);
   return nk;
 }
-__device__ __forceinline__ void normal_pair(uint32_t q, NoiseKeys nk, float& e0, float& e1) {
-  const uint32_t w1 = noise_word(2u * q, nk.k0, nk.k1);
-  const uint32_t w2 = noise_word(2u * q + 1u, nk.k0, nk.k1);
-  const float u1 = (float)((w1 >> 8) + 1u) * 0x1p-24f;   // (0, 1], exact in fp32
-  const float u2 = (float)(w2 >> 8) * 0x1p-24f;          // [0, 1), exact in fp32
-  // -2 ln u1 = (-2 ln 2) log2 u1
-  const float rad = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u1));
-  e0 = rad * __builtin_amdgcn_cosf(u2);
-  e1 = rad * __builtin_amdgcn_sinf(u2);
+// The noise is what bounds the fused iterations, so its instructions are counted: integer multiplies run at
+// the full vector rate on gfx950 (32 against 34 T lane-operations/s for a three-operand fused multiply-add),
+// the transcendental units at half of it, and every other instruction costs the same.  The words of a group
+// of four columns therefore share the first two steps of the hash, the conversions keep no instruction that
+// is not exact anyway, and std * eps reaches e by one fused multiply-add per column.
+//
+// First two steps of word(c): c ^ k0, then h ^= h >> 16.  Columns that differ in their low two bits only
+// differ there in those bits only, because h >> 16 does not see them.
+__device__ __forceinline__ uint32_t noise_head(uint32_t c, NoiseKeys nk) {
+  const uint32_t h = c ^ nk.k0;
+  return h ^ (h >> 16);
 }
-template <typename V> __device__ __forceinline__ V noise_group(int64_t col, NoiseKeys nk);
-template <> __device__ __forceinline__ vf4 noise_group<vf4>(int64_t col, NoiseKeys nk) {
-  vf4 e;
-  float a, b;
-  const uint32_t q = (uint32_t)(col >> 1);     // col is a multiple of 4 on this path
-  normal_pair(q, nk, a, b);
-  e.x = a; e.y = b;
-  normal_pair(q + 1u, nk, a, b);
-  e.z = a; e.w = b;
+// The remaining steps; the upper 24 bits of the word.
+__device__ __forceinline__ uint32_t noise_tail24(uint32_t head, NoiseKeys nk) {
+  uint32_t h = head * 0x7feb352du;
+  h ^= h >> 15; h += nk.k1; h *= 0x846ca68bu;
+  return (h >> 8) ^ (h >> 24);                           // (h ^ (h >> 16)) >> 8
+}
+// std * radius and the angle (in turns) of a column pair from its two words.
+__device__ __forceinline__ void noise_polar(uint32_t w1, uint32_t w2, float std, float& rad, float& turns) {
+#pragma clang fp contract(off)
+  const float u1 = __builtin_fmaf((float)w1, 0x1p-24f, 0x1p-24f);    // (w1 + 1) / 2^24 in (0, 1], exact in fp32
+  turns = (float)w2 * 0x1p-24f;                          // [0, 1), exact in fp32
+  // -2 ln u1 = (2 ln 2) (-log2 u1); the factor's root goes with std, which is the same for every column
+  rad = (std * 1.1774100225154747f) * __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
+}
+// e + std * eps of the group's columns
+template <typename V> __device__ __forceinline__ V add_noise(V e, float std, int64_t col, NoiseKeys nk);
+template <> __device__ __forceinline__ vf4 add_noise<vf4>(vf4 e, float std, int64_t col, NoiseKeys nk) {
+  const uint32_t h = noise_head((uint32_t)col, nk);      // col is a multiple of 4 on this path
+  float r0, t0, r1, t1;
+  noise_polar(noise_tail24(h, nk), noise_tail24(h ^ 1u, nk), std, r0, t0);
+  noise_polar(noise_tail24(h ^ 2u, nk), noise_tail24(h ^ 3u, nk), std, r1, t1);
+  e.x = __builtin_fmaf(r0, __builtin_amdgcn_cosf(t0), e.x);
+  e.y = __builtin_fmaf(r0, __builtin_amdgcn_sinf(t0), e.y);
+  e.z = __builtin_fmaf(r1, __builtin_amdgcn_cosf(t1), e.z);
+  e.w = __builtin_fmaf(r1, __builtin_amdgcn_sinf(t1), e.w);
   return e;
 }
-template <> __device__ __forceinline__ float noise_group<float>(int64_t col, NoiseKeys nk) {
-  float a, b;
-  normal_pair((uint32_t)(col >> 1), nk, a, b);
-  return (col & 1) ? b : a;
+template <> __device__ __forceinline__ float add_noise<float>(float e, float std, int64_t col, NoiseKeys nk) {
+  const uint32_t h = noise_head((uint32_t)col & ~1u, nk);
+  float r, t;
+  noise_polar(noise_tail24(h, nk), noise_tail24(h ^ 1u, nk), std, r, t);
+  return __builtin_fmaf(r, (col & 1) ? __builtin_amdgcn_sinf(t) : __builtin_amdgcn_cosf(t), e);
+}
+
+// z - lr e, the half step: one fused multiply-add, the same wherever it is evaluated.
+__device__ __forceinline__ float half_step(float z, float lr, float e) { return __builtin_fmaf(-lr, e, z); }
+__device__ __forceinline__ vf4 half_step(vf4 z, float lr, vf4 e) {
+  vf4 o;
+  o.x = half_step(z.x, lr, e.x); o.y = half_step(z.y, lr, e.y);
+  o.z = half_step(z.z, lr, e.z); o.w = half_step(z.w, lr, e.w);
+  return o;
 }
 
 // w * self + wp * msg, with one fixed rounding order wherever it is evaluated: the product with self is

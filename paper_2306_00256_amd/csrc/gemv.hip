@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kBlock) void halfstep_kernel(const GemvArgs G) {
 #pragma unroll
     for (int jj = 0; jj < kRowGroup; ++jj) e += coef[j0 + jj] * r[jj];
   }
-  if (G.noise_std != 0.0f) e += G.noise_std * noise_group<V>(col, noise_keys(G.seed, G.k, (uint32_t)agent));
+  if (G.noise_std != 0.0f) e = add_noise<V>(e, G.noise_std, col, noise_keys(G.seed, G.k, (uint32_t)agent));
   const V z = ld_plain<V>(G.zin + (int64_t)agent * G.ld + col);
   *reinterpret_cast<V*>(G.v + (int64_t)agent * G.ldv + col) = z - G.lr * e;
 }
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
       vf4 e = vf4(0.0f);
 #pragma unroll
       for (int j = 0; j < BMAX; ++j) e += coef[j] * a[j][u];
-      if (P.noise_std != 0.0f) e += P.noise_std * noise_group<vf4>(col[u], noise_keys(P.seed, P.k, (uint32_t)agent));
+      if (P.noise_std != 0.0f) e = add_noise<vf4>(e, P.noise_std, col[u], noise_keys(P.seed, P.k, (uint32_t)agent));
       if (on[u]) *reinterpret_cast<vf4*>(P.v + (int64_t)agent * P.ldv + col[u]) = z[u] - P.lr * e;
     }
   }
@@ -376,7 +376,7 @@ void grad_chunked_kernel(const GemvArgs P) {
 #pragma unroll
   for (int u = 0; u < G; ++u) {
     V ee = e[u];
-    if (P.noise_std != 0.0f) ee += P.noise_std * noise_group<V>(col[u], noise_keys(P.seed, P.k, (uint32_t)agent));
+    if (P.noise_std != 0.0f) ee = add_noise<V>(ee, P.noise_std, col[u], noise_keys(P.seed, P.k, (uint32_t)agent));
     const V v = z[u] - P.lr * ee;
     if (FUSE == 2) {
       // half-step rows for the next iteration's combine: the travelling variable becomes the message itself,

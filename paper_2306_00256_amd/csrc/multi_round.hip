@@ -166,7 +166,7 @@ void multi_round_kernel(const MultiArgs M) {
 // Eqs. (8), (9)), `rounds` times.  20 bytes per agent-parameter for any number of iterations.  The
 // arithmetic per iteration is that of the single-step kernel, operation for operation.
 // ---------------------------------------------------------------------------------------------
-template <int VEC, int RT, int THREADS>
+template <int VEC, int RT, int THREADS, bool NOISY>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(multi_round_waves<THREADS>())))
 void multi_step_kernel(const StepsArgs S) {
 #pragma clang fp contract(off)
@@ -211,40 +211,69 @@ void multi_step_kernel(const StepsArgs S) {
   const bool last_mine = rg + L * M.row_lanes < M.n;
   const int slot_last = last_mine ? tid + L * THREADS : (M.n - 1) * lanes + cg;
   const int wrap = M.n * lanes;
-  const bool alternate = M.row_lanes == 1;         // one port: my rows share rg's parity unless consecutive
-  const bool rg_odd = (rg & 1) != 0;
+  const bool odd0 = (rg & 1) != 0;                 // one port: see multi_round_kernel
+  const bool odd1 = M.row_lanes == 1 ? !odd0 : odd0;
+  const bool odd_last = ((min(rg + L * M.row_lanes, M.n - 1)) & 1) != 0;
+  const int slot0 = min(tid, wrap - 1);
+  // The noise keys of an iteration depend on the agent alone: each is worked out once per iteration and
+  // workgroup, for the iteration to come, and read back by every thread that holds a row of that agent (a
+  // row's keys are 14 of the 86 instructions its noise took per four columns).
+  NoiseKeys* keys = reinterpret_cast<NoiseKeys*>(lds_z + ((wrap * VEC + 1) & ~1));
+  auto make_keys = [&](uint32_t k) {
+    for (int i = tid; i < M.n; i += THREADS) keys[i] = noise_keys(S.seed, k, (uint32_t)i);
+  };
+  if (NOISY) {
+    make_keys(S.k0);
+    __syncthreads();
+  }
   for (int t = 0; t < M.rounds; ++t) {
     const MultiRound R = M.round[t];
-    // Local step of row k at z (its x or y): both x and y move by lr * e (Algorithm 1; x - lr e and
+    // Local step of row k at z (its x or y): both x and y move by -lr * e (Algorithm 1; x - lr e and
     // y - lr e are what Eqs. (8), (9) combine), and the moved z is the message v.
+    NoiseKeys nk[THREADS > 256 ? 1 : RT];          // all requested before the first is used where registers allow
+    if (NOISY && THREADS == 256) {
+#pragma unroll
+      for (int k = 0; k < RT; ++k) nk[k] = keys[min(rg + k * M.row_lanes, M.n - 1)];
+    }
     auto local_step = [&](int k, const V& z) {
-      const int i = min(rg + k * M.row_lanes, M.n - 1);
       V e = z - c[k];
-      if (S.noise_std != 0.0f) e += S.noise_std * noise_group<V>(col, noise_keys(S.seed, S.k0 + (uint32_t)t, (uint32_t)i));
-      const V ge = S.lr * e;
-      x[k] = x[k] - ge;
-      y[k] = y[k] - ge;
+      if (NOISY) e = add_noise<V>(e, S.noise_std, col, THREADS > 256 ? keys[min(rg + k * M.row_lanes, M.n - 1)] : nk[THREADS > 256 ? 0 : k]);
+      x[k] = half_step(x[k], S.lr, e);
+      y[k] = half_step(y[k], S.lr, e);
     };
     // the round's flags are the same for every thread: branches, not per-element selects
     if (R.exch_y) {
 #pragma unroll
       for (int k = 0; k < RT; ++k) {
-        local_step(k, y[k]);
-        if (k < L) zs[tid + k * THREADS] = y[k];
-        else if (last_mine) zs[slot_last] = y[k];
+        if (k < L || last_mine) {
+          local_step(k, y[k]);
+          zs[tid + k * THREADS] = y[k];
+        }
         if (THREADS > 256) __builtin_amdgcn_sched_barrier(0);     // row by row where registers are short
       }
     } else {
 #pragma unroll
       for (int k = 0; k < RT; ++k) {
-        local_step(k, x[k]);
-        if (k < L) zs[tid + k * THREADS] = x[k];
-        else if (last_mine) zs[slot_last] = x[k];
+        if (k < L || last_mine) {
+          local_step(k, x[k]);
+          zs[tid + k * THREADS] = x[k];
+        }
         if (THREADS > 256) __builtin_amdgcn_sched_barrier(0);     // row by row where registers are short
       }
     }
-    __syncthreads();
+    // b = 0: from y = -0 the combine below gives b_peer * z to the bit (see multi_round_kernel)
+    if (!R.read_y) {
+#pragma unroll
+      for (int k = 0; k < RT; ++k) y[k] = V(-0.0f);
+    }
     const int back = R.shift * lanes;
+    const int fwd = M.port == 2 ? -back : back;
+    PeerSlots P;
+    P.base[0] = wrap_slot(slot0 + (odd0 ? -back : fwd), wrap);
+    P.base[1] = wrap_slot(slot0 + (odd1 ? -back : fwd), wrap);
+    P.last = wrap_slot(slot_last + (odd_last ? -back : fwd), wrap);
+    __syncthreads();
+    if (NOISY) make_keys(S.k0 + (uint32_t)t + 1u);   // this iteration's keys have been read
     // rows whose messages are read from LDS together: all of them, or two at a time where registers are short
     constexpr int KB = (THREADS > 256 && RT > 2) ? 2 : RT;
 #pragma unroll
@@ -253,32 +282,15 @@ void multi_step_kernel(const StepsArgs S) {
 #pragma unroll
       for (int j = 0; j < KB; ++j) {
         const int k = k0 + j;
-        if (k < RT) {
-          const int s = (k == L) ? slot_last : tid + k * THREADS;
-          int q;
-          if (M.port == 2) {
-            q = s - back;
-            if (q < 0) q += wrap;
-          } else {
-            const bool odd = alternate ? ((k & 1) != 0) : rg_odd;   // even rows look ahead, odd rows back (Eq. (7))
-            q = odd ? s - back : s + back;
-            if (q < 0) q += wrap;
-            if (q >= wrap) q -= wrap;
-          }
-          zp[j] = zs[q];
-        }
+        if (k < RT) zp[j] = zs[k == L ? P.last : peer_slot<THREADS>(P, k, wrap)];
       }
 #pragma unroll
-      for (int j = 0; j < KB; ++j)
-        if (k0 + j < RT) x[k0 + j] = combine(R.a, x[k0 + j], R.ap, zp[j]);
-      if (R.read_y) {
-#pragma unroll
-        for (int j = 0; j < KB; ++j)
-          if (k0 + j < RT) y[k0 + j] = combine(R.b, y[k0 + j], R.bp, zp[j]);
-      } else {
-#pragma unroll
-        for (int j = 0; j < KB; ++j)
-          if (k0 + j < RT) y[k0 + j] = R.bp * zp[j];
+      for (int j = 0; j < KB; ++j) {
+        const int k = k0 + j;
+        if (k < L || (k == L && last_mine)) {
+          x[k] = combine(R.a, x[k], R.ap, zp[j]);
+          y[k] = combine(R.b, y[k], R.bp, zp[j]);
+        }
       }
       if (KB < RT) __builtin_amdgcn_sched_barrier(0);    // keep the batches apart
     }
@@ -300,13 +312,13 @@ void multi_step_kernel(const StepsArgs S) {
 
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_steps(const StepsArgs& ss, unsigned blocks, size_t lds, hipStream_t st) {
+  const auto fn = ss.noise_std != 0.0f ? &multi_step_kernel<VEC, RT, THREADS, true> : &multi_step_kernel<VEC, RT, THREADS, false>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&multi_step_kernel<VEC, RT, THREADS>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  multi_step_kernel<VEC, RT, THREADS><<<dim3(blocks), dim3(THREADS), lds, st>>>(ss);
+  fn<<<dim3(blocks), dim3(THREADS), lds, st>>>(ss);
   return hipGetLastError();
 }
 
@@ -350,7 +362,8 @@ hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st) {
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   StepsArgs ss = s;
   ss.m.xcd_tiles = xcd_run(lanes * (vec4 ? 16 : 4), &blocks);
-  const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
+  size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
+  if (s.noise_std != 0.0f) lds = ((lds + 7) & ~(size_t)7) + (size_t)m.n * sizeof(uint64_t);   // the noise keys behind the tile
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_steps_256<1>(ss, (unsigned)blocks, lds, st);
   if (threads == 256) return launch_steps_256<4>(ss, (unsigned)blocks, lds, st);
