@@ -198,6 +198,16 @@ __device__ __forceinline__ vf4 half_step(vf4 z, float lr, vf4 e) {
   return o;
 }
 
+// A value that every lane shares, in a vector register.  On gfx950 the plain fp32 and integer instructions (add,
+// multiply, fused multiply-add, xor, and, shift) issue about 1.7 times as fast when all their operands are vector
+// registers or constants as with one scalar-register operand (57 against 35 T lane-operations/s for a fused
+// multiply-add), so factors that a loop applies to many elements are worth a vector register each.
+__device__ __forceinline__ float in_vgpr(float uniform) {
+  float v;
+  asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(uniform));
+  return v;
+}
+
 // w * self + wp * msg, with one fixed rounding order wherever it is evaluated: the product with self is
 // rounded, then the peer's term is added by a fused multiply-add.  In this order the result can replace
 // self in its own register (multiply in place, accumulate in place): kernels that carry self across a loop

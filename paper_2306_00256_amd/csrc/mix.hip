@@ -60,7 +60,7 @@ void mix_rounds_kernel(const MixArgs M) {
   int spec = M.k0 % M.period;
   for (int t = 0; t < M.rounds; ++t) {
     const int j0 = M.start[spec], j1 = M.start[spec + 1];
-    const float ws = M.w_self[spec];
+    const float ws = in_vgpr(M.w_self[spec]);
     if (j1 > j0) {                                  // a round without peers is the identity
 #pragma unroll
       for (int k = 0; k < L; ++k) xs[tid + k * THREADS] = x[k];
@@ -74,7 +74,7 @@ void mix_rounds_kernel(const MixArgs M) {
       for (int k = 0; k < RT; ++k) x[k] = ws * x[k];
       for (int j = j0; j < j1; ++j) {
         const int back = M.shift[j] * lanes;
-        const float w = M.w[j];
+        const float w = in_vgpr(M.w[j]);
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
           int q = ((k == L) ? slot_last : tid + k * THREADS) - back;

@@ -122,6 +122,7 @@ void multi_round_kernel(const MultiArgs M) {
     P.base[0] = wrap_slot(slot0 + (odd0 ? -back : fwd), wrap);
     P.base[1] = wrap_slot(slot0 + (odd1 ? -back : fwd), wrap);
     P.last = wrap_slot(slot_last + (odd_last ? -back : fwd), wrap);
+    const float wa = in_vgpr(R.a), wap = in_vgpr(R.ap), wb = in_vgpr(R.b), wbp = in_vgpr(R.bp);
     __syncthreads();
 #pragma unroll
     for (int k0 = 0; k0 < RT; k0 += KB) {
@@ -136,8 +137,8 @@ void multi_round_kernel(const MultiArgs M) {
       for (int j = 0; j < KB; ++j) {
         const int k = k0 + j;
         if (k < RT) {
-          x[k] = combine(R.a, x[k], R.ap, zp[j]);
-          y[k] = combine(R.b, y[k], R.bp, zp[j]);
+          x[k] = combine(wa, x[k], wap, zp[j]);
+          y[k] = combine(wb, y[k], wbp, zp[j]);
         }
       }
       if (KB < RT) __builtin_amdgcn_sched_barrier(0);    // keep the batches apart
@@ -222,6 +223,7 @@ void multi_step_kernel(const StepsArgs S) {
   auto make_keys = [&](uint32_t k) {
     for (int i = tid; i < M.n; i += THREADS) keys[i] = noise_keys(S.seed, k, (uint32_t)i);
   };
+  const float lr = in_vgpr(S.lr), std = in_vgpr(S.noise_std);
   if (NOISY) {
     make_keys(S.k0);
     __syncthreads();
@@ -237,9 +239,9 @@ void multi_step_kernel(const StepsArgs S) {
     }
     auto local_step = [&](int k, const V& z) {
       V e = z - c[k];
-      if (NOISY) e = add_noise<V>(e, S.noise_std, col, THREADS > 256 ? keys[min(rg + k * M.row_lanes, M.n - 1)] : nk[THREADS > 256 ? 0 : k]);
-      x[k] = half_step(x[k], S.lr, e);
-      y[k] = half_step(y[k], S.lr, e);
+      if (NOISY) e = add_noise<V>(e, std, col, THREADS > 256 ? keys[min(rg + k * M.row_lanes, M.n - 1)] : nk[THREADS > 256 ? 0 : k]);
+      x[k] = half_step(x[k], lr, e);
+      y[k] = half_step(y[k], lr, e);
     };
     // the round's flags are the same for every thread: branches, not per-element selects
     if (R.exch_y) {
@@ -272,6 +274,7 @@ void multi_step_kernel(const StepsArgs S) {
     P.base[0] = wrap_slot(slot0 + (odd0 ? -back : fwd), wrap);
     P.base[1] = wrap_slot(slot0 + (odd1 ? -back : fwd), wrap);
     P.last = wrap_slot(slot_last + (odd_last ? -back : fwd), wrap);
+    const float wa = in_vgpr(R.a), wap = in_vgpr(R.ap), wb = in_vgpr(R.b), wbp = in_vgpr(R.bp);
     __syncthreads();
     if (NOISY) make_keys(S.k0 + (uint32_t)t + 1u);   // this iteration's keys have been read
     // rows whose messages are read from LDS together: all of them, or two at a time where registers are short
@@ -288,8 +291,8 @@ void multi_step_kernel(const StepsArgs S) {
       for (int j = 0; j < KB; ++j) {
         const int k = k0 + j;
         if (k < L || (k == L && last_mine)) {
-          x[k] = combine(R.a, x[k], R.ap, zp[j]);
-          y[k] = combine(R.b, y[k], R.bp, zp[j]);
+          x[k] = combine(wa, x[k], wap, zp[j]);
+          y[k] = combine(wb, y[k], wbp, zp[j]);
         }
       }
       if (KB < RT) __builtin_amdgcn_sched_barrier(0);    // keep the batches apart
