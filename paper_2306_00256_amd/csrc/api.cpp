@@ -483,9 +483,22 @@ TileShape mix_tile(int32_t n, bool vec4, bool heavy) {
 // agents, 512-thread ones up to 768 (n = 520: torus 0.81 -> 0.72 ms, ring 0.59 -> 0.53 against 1024 threads),
 // 1024-thread ones beyond, with up to 8 rows per thread so that the rows of the tile stay 64 bytes wide up to
 // 2048 agents (n = 2048 ring: 1.13 -> 0.70 ms against 6 rows and 32-byte rows).
-TileShape graph_tile(int32_t n, bool vec4) {
+TileShape graph_tile(int32_t n, bool vec4, int32_t m, bool fixed) {
+  // One graph for the whole call and few neighbours: the table lives in registers, what is left is bound by the
+  // LDS reads of the values.  Torus (four neighbours) and hypercube (up to eight), 2^27 elements: up to 128 agents
+  // 256 threads x at most 5 rows (n = 64: 213 us against 232 with 9 rows, n = 128: 241 against 267), up to 256
+  // agents 9 rows (n = 130: 318 against 370 with 5).  Beyond, rows of the tile that are 64 bytes or wider count:
+  // 512 threads x 9 rows up to 1152 agents (n = 258: 395 against 449 with 256 threads, n = 1026: 531 against 860
+  // with 1024), 1024 threads after that (n = 2050: 742 against 2170).  More than four neighbours fit 8 rows.
+  if (fixed && vec4 && m <= ceca::kGraphFixedDegree) {
+    const int32_t wide = ceca::graph_fixed_rows(512, m);
+    const TileShape t = pick_tile(n, vec4, 4, ceca::kGraphRows, 9,
+                                  [wide](int32_t k) { return k <= 256 ? ceca::kBlock : (k <= wide * 128 ? 512 : 1024); },
+                                  [n, wide](int32_t threads) { return threads == ceca::kBlock ? (n <= 128 ? 5 : 9) : wide; });
+    if (t.ok && t.row_bytes(true) >= 64) return t;
+  }
   return pick_tile(n, vec4, 4, ceca::kGraphRows, 8,
-                   [](int32_t m) { return m <= 384 ? ceca::kBlock : (m <= 768 ? 512 : 1024); },
+                   [](int32_t k) { return k <= 384 ? ceca::kBlock : (k <= 768 ? 512 : 1024); },
                    [n](int32_t threads) {
                      if (threads == ceca::kBlock) return n <= 192 ? 8 : ceca::kGraphRows;
                      return 8;
@@ -1196,13 +1209,15 @@ int32_t ceca_graph_rounds(const float* X_in, float* X_out, int32_t n, int64_t d,
   if (overlaps(nbr, entries * 4, X_out, bytes) || overlaps(w, entries * 4, X_out, bytes) ||
       overlaps(w_self, (int64_t)period * n * 4, X_out, bytes))
     return fail(CECA_EINVAL, "the graph tables overlap X_out");
-  const TileShape tv = graph_tile(n, true), ts = graph_tile(n, false);
+  const bool fixed = (period == 1 || rounds == 1) && !g_tuning.graph_tables_in_memory;
+  const TileShape tv = graph_tile(n, true, m, fixed), ts = graph_tile(n, false, m, fixed);
   if (!tv.ok || !ts.ok) return fail(CECA_EINVAL, "internal: no tile holds n = %d agents", n);
   ceca::GraphArgs g{};
   g.xin = X_in;  g.xout = X_out;  g.ld = ld;
   g.nbr = nbr;  g.w = w;  g.w_self = w_self;
   g.n = n;  g.m = m;  g.rounds = rounds;  g.period = period;  g.k0 = k0 % period;
   g.stage = !g_tuning.graph_tables_in_memory;
+  g.fixed = fixed;
   hipStream_t st = (hipStream_t)hip_stream;
   const bool can_vec = aligned16(X_in) && aligned16(X_out) && ld % 4 == 0;
   const int64_t d4 = can_vec ? d / 4 : 0;

@@ -125,8 +125,111 @@ void graph_rounds_kernel(const GraphArgs M) {
   }
 }
 
+// The lane's value as its quad's lane j holds it (a quad permute on the vector pipe, no LDS traffic); j is a
+// compile-time constant in every use.
+__device__ __forceinline__ int quad_lane(int v, int j) {
+  switch (j & 3) {
+    case 0: return __builtin_amdgcn_update_dpp(0, v, 0x00, 0xf, 0xf, true);
+    case 1: return __builtin_amdgcn_update_dpp(0, v, 0x55, 0xf, 0xf, true);
+    case 2: return __builtin_amdgcn_update_dpp(0, v, 0xaa, 0xf, 0xf, true);
+    default: return __builtin_amdgcn_update_dpp(0, v, 0xff, 0xf, 0xf, true);
+  }
+}
+
+// The same rounds over one fixed graph (one table for every round) with at most 4 * MQ neighbours, on tiles whose
+// rows are at least 64 bytes wide: the table is read once and stays in registers.  The four lanes of a quad hold
+// the same rows of the tile, so lane c of the quad keeps entries c, c + 4, ... of each row -- 2 * MQ registers per
+// row -- and a neighbour's slot and weight reach the other three by quad permutes.
+// What bounds it is LDS bandwidth: m reads and one write of 16 bytes per row and round.  Reading the table
+// entries from LDS at every look-up (the kernel above) adds half as many bytes again and an LDS round trip
+// in front of every value.  Torus, tau rounds: n = 130, d = 2^20 554 -> 333 us, n = 1026, d = 2^17 1050 -> 531 us.
+template <int RT, int THREADS, int MQ>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(graph_waves<THREADS>())))
+void graph_fixed_kernel(const GraphArgs M) {
+#pragma clang fp contract(off)
+  extern __shared__ float lds_x[];                 // [n][lanes] groups of 4 floats
+  const int lanes = THREADS / M.row_lanes;         // a multiple of 4
+  const int tid = threadIdx.x;
+  const int cg = tid % lanes;
+  const int rg = tid / lanes;
+  int64_t tile = blockIdx.x;
+  if (M.xcd_tiles > 0) tile = (int64_t)(blockIdx.x & 7) * M.xcd_tiles + (blockIdx.x >> 3);   // see mix_rounds_kernel
+  const int64_t g = tile * lanes + cg;
+  const bool on = g < M.ngroups;
+  const int64_t col = M.col0 + (on ? g : 0) * 4;   // lanes past the last column shadow column group 0
+
+  vf4 x[RT];
+  float ws[RT], wt[RT][MQ];
+  int off[RT][MQ];                                 // byte offset of the neighbour's row in the tile
+#pragma unroll
+  for (int k = 0; k < RT; ++k) {
+    const int row = min(rg + k * M.row_lanes, M.n - 1);            // a row past the last agent shadows it (never published or stored)
+    x[k] = ld_stream<vf4>(M.xin + (int64_t)row * M.ld + col);
+  }
+#pragma unroll
+  for (int k = 0; k < RT; ++k) {
+    const int64_t row = (int64_t)M.k0 * M.n + min(rg + k * M.row_lanes, M.n - 1);
+    ws[k] = M.w_self[row];
+#pragma unroll
+    for (int q = 0; q < MQ; ++q) {
+      const int64_t e = row * M.m + min((cg & 3) + 4 * q, M.m - 1);
+      off[k][q] = min(max(M.nbr[e], 0), M.n - 1) * lanes * 16;     // indices outside [0, n) are clamped, not followed
+      wt[k][q] = M.w[e];
+    }
+  }
+  // neighbours read from LDS together: all rows' or a few at a time where registers are short
+  constexpr int KB = RT <= (THREADS > 256 ? 5 : 8) ? RT : 4;
+  vf4* xs = reinterpret_cast<vf4*>(lds_x);
+  const char* mine = reinterpret_cast<const char*>(lds_x) + cg * 16;
+  constexpr int L = RT - 1;                        // rows_per_thread is the least that covers n: only row L can be a shadow
+  const bool last_mine = rg + L * M.row_lanes < M.n;
+  for (int t = 0; t < M.rounds; ++t) {
+#pragma unroll
+    for (int k = 0; k < L; ++k) xs[tid + k * THREADS] = x[k];      // row i, group c sits in slot i * lanes + c = tid + k * THREADS
+    if (last_mine) xs[tid + L * THREADS] = x[L];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < RT; ++k) x[k] = ws[k] * x[k];             // the new x grows in the registers of the old one
+#pragma unroll
+    for (int j = 0; j < 4 * MQ; ++j) {
+      if (j < M.m) {                               // the same for every thread
+#pragma unroll
+        for (int k0 = 0; k0 < RT; k0 += KB) {
+          vf4 z[KB];
+#pragma unroll
+          for (int k = k0; k < RT && k < k0 + KB; ++k) z[k - k0] = *reinterpret_cast<const vf4*>(mine + quad_lane(off[k][j >> 2], j));
+#pragma unroll
+          for (int k = k0; k < RT && k < k0 + KB; ++k)
+            x[k] = fma_rows(__int_as_float(quad_lane(__float_as_int(wt[k][j >> 2]), j)), z[k - k0], x[k]);
+          if (KB < RT) __builtin_amdgcn_sched_barrier(0);          // keep the batches apart
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (!on) return;
+#pragma unroll
+  for (int k = 0; k < RT; ++k) {
+    const int i = rg + k * M.row_lanes;
+    if (i < M.n) st_stream<vf4>(M.xout + (int64_t)i * M.ld + col, x[k]);
+  }
+}
+
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_graph(const GraphArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
+  if constexpr (VEC == 4) {
+    const int lanes = THREADS / mm.row_lanes;
+    if (mm.fixed && lanes % 4 == 0 && mm.m <= kGraphFixedDegree && RT <= graph_fixed_rows(THREADS, mm.m)) {
+      const auto fixed = mm.m <= 4 ? &graph_fixed_kernel<RT, THREADS, 1>
+                       : mm.m <= 8 ? &graph_fixed_kernel<RT, THREADS, 2> : &graph_fixed_kernel<RT, THREADS, 3>;
+      if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fixed), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+      }
+      fixed<<<dim3(blocks), dim3(THREADS), lds, st>>>(mm);
+      return hipGetLastError();
+    }
+  }
   // small tables are staged in LDS behind the tile
   const int64_t entries = (int64_t)mm.n * mm.m;
   const size_t staged = ((lds + 7) & ~(size_t)7) + (size_t)entries * sizeof(int2);
@@ -157,12 +260,14 @@ static hipError_t launch_graph_256(const GraphArgs& mm, unsigned blocks, size_t 
   return hipErrorInvalidValue;
 }
 
-// wider workgroups (16-byte groups only): 6 rows per thread fit their 128 registers, 8 spill a little
+// wider workgroups (16-byte groups only): with the table in registers 9 rows per thread (8 or 7 with more than four
+// or eight neighbours) fit their 128 registers; otherwise 6 rows do, 8 spill a little
 template <int THREADS>
 static hipError_t launch_graph_wide(const GraphArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
   switch (mm.rows_per_thread) {
 #define CECA_RT(RT) case RT: return launch_graph<4, RT, THREADS>(mm, blocks, lds, st)
     CECA_RT(1); CECA_RT(2); CECA_RT(3); CECA_RT(4); CECA_RT(5); CECA_RT(6); CECA_RT(7); CECA_RT(8);
+    CECA_RT(9);
 #undef CECA_RT
   }
   return hipErrorInvalidValue;

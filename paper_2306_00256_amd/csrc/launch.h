@@ -164,6 +164,9 @@ struct MixArgs {
 };
 
 constexpr int kGraphRows = 16;      // most rows of x a thread of the graph-gossip kernel keeps in registers
+constexpr int kGraphFixedDegree = 12;  // most neighbours of the form with the table in registers
+// most rows per thread of that form: what fits the registers of the workgroup
+constexpr int graph_fixed_rows(int threads, int m) { return threads == 256 ? kGraphRows : (m <= 4 ? 9 : m <= 8 ? 8 : threads == 512 ? 7 : 6); }
 constexpr int kGraphMaxDegree = 64; // most neighbours per vertex and round
 constexpr int kGraphStageEntries = 12;   // a round's table is staged in LDS when each thread copies at most this many entries
 
@@ -181,6 +184,7 @@ struct GraphArgs {
   int32_t row_lanes;        // power of two, row_lanes * rows_per_thread >= n
   int32_t threads;          // threads per workgroup: 0 = 256, or 512 / 1024 (16-byte groups only)
   int32_t stage;            // 1: stage small tables in LDS (0: always read them from memory)
+  int32_t fixed;            // 1: every round of the call uses table k0, which may be kept in registers
   int32_t xcd_tiles;        // set by the launcher
 };
 

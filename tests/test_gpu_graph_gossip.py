@@ -147,3 +147,42 @@ def test_indices_outside_the_graph_are_clamped_and_errors(env):
     with pytest.raises(P.CecaError):                                      # partial overlap of input and output
         flat = torch.zeros(2 * n * d, device="cuda")
         P.ceca_graph_rounds(flat[: n * d].view(n, d), flat[d: d + n * d].view(n, d), n, d, tn, tw, ts, 1)
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 4), (5, 3), (128, 4), (129, 5), (256, 8), (257, 9), (640, 12), (897, 12), (1024, 8), (1025, 8), (1152, 4),
+                                 (1153, 4), (1537, 12), (2048, 4), (2049, 4), (2304, 1), (2305, 4), (130, 13)])
+def test_fixed_graph_with_any_table(env, n, m):
+    """One table for every round (the form that keeps it in registers, up to 12 neighbours and 64-byte tile rows)
+    at the edges of its tiles, with arbitrary weights and indices on both sides of the valid range (clamped):
+    same bits as the tables read from memory, and the fp64 sums to 1e-6 of the largest entry (3 rounds of at
+    most 14 fp32 operations with weights that sum to at most 1: 42 half-ulps = 2.5e-6 at worst, random signs)."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    rng = np.random.default_rng(n * 16 + m)
+    d = 4 * 33 + 3
+    period, rounds = 3, 3
+    nbr = rng.integers(-2, n + 2, size=(period, n, m)).astype(np.int32)
+    w = (rng.uniform(-1, 1, size=(period, n, m)) / (m + 1)).astype(np.float32)
+    ws = (rng.uniform(-1, 1, size=(period, n)) / (m + 1)).astype(np.float32)
+    x0 = WL.initial_state(n, d, seed=n)
+    dev = [torch.from_numpy(a).cuda() for a in (nbr, w, ws)]
+
+    def call(tables, rounds, k0):
+        X = torch.from_numpy(x0).cuda()
+        P.ceca_graph_rounds(X, X, n, d, *tables, rounds, k0=k0)
+        return X
+
+    one = [a[1:2].contiguous() for a in dev]
+    got = [call(one, rounds, 5), call(dev, 1, 4)]            # a single table; a single round of several tables
+    try:
+        P.ceca_set_option(Bn.OPT_GRAPH_STAGE, 0)
+        assert torch.equal(got[0], call(one, rounds, 5)) and torch.equal(got[1], call(dev, 1, 4))
+    finally:
+        P.ceca_set_option(Bn.OPT_GRAPH_STAGE, 1)
+    idx = np.clip(nbr[1], 0, n - 1)
+    x = x0.astype(np.float64)
+    for t in range(rounds):
+        x = ws[1].astype(np.float64)[:, None] * x + sum(w[1][:, j].astype(np.float64)[:, None] * x[idx[:, j]] for j in range(m))
+        if t == 0:
+            assert np.abs(got[1].cpu().numpy() - x).max() <= 1e-6 * np.abs(x0).max()
+    assert np.abs(got[0].cpu().numpy() - x).max() <= 1e-6 * np.abs(x0).max()
