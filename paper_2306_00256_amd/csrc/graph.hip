@@ -40,8 +40,7 @@ void graph_rounds_kernel(const GraphArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  int64_t tile = blockIdx.x;
-  if (M.xcd_tiles > 0) tile = (int64_t)(blockIdx.x & 7) * M.xcd_tiles + (blockIdx.x >> 3);   // see mix_rounds_kernel
+  const int64_t tile = tile_of_block(M.xcd_runs);
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
@@ -152,8 +151,7 @@ void graph_fixed_kernel(const GraphArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  int64_t tile = blockIdx.x;
-  if (M.xcd_tiles > 0) tile = (int64_t)(blockIdx.x & 7) * M.xcd_tiles + (blockIdx.x >> 3);   // see mix_rounds_kernel
+  const int64_t tile = tile_of_block(M.xcd_runs);
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * 4;   // lanes past the last column shadow column group 0
@@ -287,11 +285,7 @@ hipError_t launch_graph_rounds(const GraphArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   GraphArgs mm = m;
-  mm.xcd_tiles = 0;
-  if (lanes * (vec4 ? 16 : 4) < 128 && blocks >= 1024 && !g_tuning.plain_tile_order) {
-    mm.xcd_tiles = (int32_t)((blocks + 7) / 8);
-    blocks = (int64_t)mm.xcd_tiles * 8;            // tiles past the last one find no columns and leave
-  }
+  mm.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_graph_256<1>(mm, (unsigned)blocks, lds, st);

@@ -7,6 +7,8 @@
 
 namespace ceca {
 
+constexpr uint32_t kXcdRun = 16;     // adjacent column tiles that one XCD takes in a row (device_util.h, tile_of_block)
+
 // What an agent contributes in one iteration (Algorithm 1): its "self" terms x_i - lr e_i and
 // y_i - lr e_i, and the message v_i = z_i - lr e_i it sends.
 enum ChainMode : int {
@@ -61,7 +63,7 @@ struct MultiArgs {
   int64_t col0;
   int64_t ngroups;
   int32_t n, port, rounds;
-  int32_t xcd_tiles;        // > 0: workgroup b takes tile (b % 8) * xcd_tiles + b / 8 (set by the launcher)
+  int32_t xcd_runs;         // 1: tiles go to the XCDs in runs (tile_of_block; set by the launcher)
   int32_t rows_per_thread;  // 1 to 16 rows of (x, y) in a thread's registers
   int32_t row_lanes;   // power of two, row_lanes * rows_per_thread >= n: threads of a workgroup that share a column group
   int32_t threads;     // threads per workgroup of the gossip-rounds kernel: 0 = 256, or 512 / 1024 (16-byte groups only);
@@ -156,7 +158,7 @@ struct MixArgs {
   int32_t rows_per_thread;  // rows of x in a thread's registers: 1 to 32, the least that covers n
   int32_t row_lanes;        // power of two, row_lanes * rows_per_thread >= n
   int32_t threads;          // threads per workgroup: 0 = 256, or 512 / 1024 (16-byte groups only, at most 16 rows per thread)
-  int32_t xcd_tiles;        // > 0: workgroup b takes tile (b % 8) * xcd_tiles + b / 8 (set by the launcher)
+  int32_t xcd_runs;         // 1: tiles go to the XCDs in runs (tile_of_block; set by the launcher)
   int32_t start[kMixMaxPeriod + 1];
   float w_self[kMixMaxPeriod];
   int32_t shift[kMixMaxPeers];
@@ -185,7 +187,7 @@ struct GraphArgs {
   int32_t threads;          // threads per workgroup: 0 = 256, or 512 / 1024 (16-byte groups only)
   int32_t stage;            // 1: stage small tables in LDS (0: always read them from memory)
   int32_t fixed;            // 1: every round of the call uses table k0, which may be kept in registers
-  int32_t xcd_tiles;        // set by the launcher
+  int32_t xcd_runs;         // set by the launcher
 };
 
 // Launch-shape overrides of the calling thread, set through the test and measurement interface
@@ -238,6 +240,16 @@ hipError_t launch_stream_probe(const float* a, const float* b, const float* c, f
                                int reads, int writes, hipStream_t st);
 // out[10] = out[0] + out[5] (11 doubles on the device)
 hipError_t launch_phi(double* out, hipStream_t st);
+
+// Whether a register-tile kernel numbers its tiles in runs per XCD (device_util.h, tile_of_block): rows of the tile
+// narrower than a 128-byte line and enough tiles to matter (small launches measured better in plain order).
+// Rounds *blocks up to whole runs on every XCD (workgroups past the last tile find no columns and leave).
+inline int32_t xcd_runs(int row_bytes, int64_t* blocks) {
+  if (row_bytes >= 128 || *blocks < 1024 || g_tuning.plain_tile_order) return 0;
+  const int64_t whole = 8 * (int64_t)kXcdRun;
+  *blocks = (*blocks + whole - 1) / whole * whole;
+  return 1;
+}
 
 constexpr int kBlock = 256;          // threads per workgroup: 4 wavefronts of 64
 constexpr int kChunkGroups = 1;      // column groups per thread in the margins kernel

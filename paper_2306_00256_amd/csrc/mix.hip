@@ -34,11 +34,7 @@ void mix_rounds_kernel(const MixArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  // workgroups go round-robin over the 8 XCDs, each with its own L2: when a row of the tile is
-  // narrower than a 128-byte line, neighbouring tiles should meet in one L2, so every XCD takes a
-  // contiguous run of tiles (xcd_tiles = tiles per XCD, 0 = plain order)
-  int64_t tile = blockIdx.x;
-  if (M.xcd_tiles > 0) tile = (int64_t)(blockIdx.x & 7) * M.xcd_tiles + (blockIdx.x >> 3);
+  const int64_t tile = tile_of_block(M.xcd_runs);
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
@@ -151,11 +147,7 @@ hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MixArgs mm = m;
-  mm.xcd_tiles = 0;
-  if (lanes * (vec4 ? 16 : 4) < 128 && blocks >= 1024 && !g_tuning.plain_tile_order) {
-    mm.xcd_tiles = (int32_t)((blocks + 7) / 8);
-    blocks = (int64_t)mm.xcd_tiles * 8;            // tiles past the last one find no columns and leave
-  }
+  mm.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_mix_256<1>(mm, (unsigned)blocks, lds, st);

@@ -14,16 +14,6 @@ namespace ceca {
 // independent instances of the recursion (Sec. 3.1), and every round uses the same combine() as the
 // single-round kernel, so the result has the same bits as `rounds` separate calls.
 // ---------------------------------------------------------------------------------------------
-// Tiles per XCD for the XCD-contiguous workgroup order (rows of the tile narrower than a 128-byte line
-// and enough tiles to matter), 0 for the plain order; rounds *blocks up to 8 runs of that many tiles
-// (workgroups past the last tile find no columns and leave).
-static int32_t xcd_run(int row_bytes, int64_t* blocks) {
-  if (row_bytes >= 128 || *blocks < 1024 || g_tuning.plain_tile_order) return 0;   // small launches measured better in plain order
-  const int64_t per = (*blocks + 7) / 8;
-  *blocks = per * 8;
-  return (int32_t)per;
-}
-
 // Wavefronts per SIMD the kernel is compiled for: workgroups wider than 256 threads hold many agents'
 // rows and must fit 128 registers per thread (four wavefronts per SIMD: one 1024-thread workgroup or two
 // 512-thread ones per compute unit); 256-thread workgroups take what their rows need.
@@ -62,10 +52,7 @@ void multi_round_kernel(const MultiArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;                      // my column group inside the tile
   const int rg = tid / lanes;                      // my first row; I own rows rg, rg + row_lanes, ...
-  // narrow tiles: every XCD (workgroups go round-robin over 8 of them, each with its own L2) takes a
-  // contiguous run of tiles, so that the two halves of a 128-byte line meet in one L2
-  int64_t tile = blockIdx.x;
-  if (M.xcd_tiles > 0) tile = (int64_t)(blockIdx.x & 7) * M.xcd_tiles + (blockIdx.x >> 3);
+  const int64_t tile = tile_of_block(M.xcd_runs);
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
@@ -178,10 +165,7 @@ void multi_step_kernel(const StepsArgs S) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  // narrow tiles: every XCD (workgroups go round-robin over 8 of them, each with its own L2) takes a
-  // contiguous run of tiles, so that the two halves of a 128-byte line meet in one L2
-  int64_t tile = blockIdx.x;
-  if (M.xcd_tiles > 0) tile = (int64_t)(blockIdx.x & 7) * M.xcd_tiles + (blockIdx.x >> 3);
+  const int64_t tile = tile_of_block(M.xcd_runs);
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
@@ -364,7 +348,7 @@ hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   StepsArgs ss = s;
-  ss.m.xcd_tiles = xcd_run(lanes * (vec4 ? 16 : 4), &blocks);
+  ss.m.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
   size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (s.noise_std != 0.0f) lds = ((lds + 7) & ~(size_t)7) + (size_t)m.n * sizeof(uint64_t);   // the noise keys behind the tile
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
@@ -412,7 +396,7 @@ hipError_t launch_multi_round(const MultiArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MultiArgs mm = m;
-  mm.xcd_tiles = xcd_run(lanes * (vec4 ? 16 : 4), &blocks);
+  mm.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_rounds_rt<1, 256>(mm, (unsigned)blocks, lds, st);
