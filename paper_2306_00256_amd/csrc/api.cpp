@@ -223,11 +223,12 @@ int32_t check_loss(const ceca_loss_t* loss, int64_t d, bool need_batch, const in
   }
 }
 
-// Consensus observables come in three forms (all deterministic, fp64 accumulation):
+// Consensus observables come in four forms (all deterministic, fp64 accumulation):
+//   GROUP     one pass, a long-lived workgroup holds a column strip of every agent: up to 3072 agents, 16-byte layouts
 //   WAVE      one pass, a wavefront holds a column strip of every agent (no LDS): up to 64 x 32 agents
 //   TILE      one pass, a workgroup holds a column tile of every agent and reduces through LDS
 //   TWO_PASS  column sums, mean, then per-agent squared deviations (x read twice)
-enum ConsForm { CONS_TWO_PASS = 1, CONS_TILE = 2, CONS_WAVE = 3 };
+enum ConsForm { CONS_TWO_PASS = 1, CONS_TILE = 2, CONS_WAVE = 3, CONS_GROUP = 4 };
 
 // Partial sums of the WAVE form are capped at this many bytes whatever the launch shape, so that the
 // workspace bound does not depend on the calling thread's tuning.
@@ -247,6 +248,9 @@ struct ConsPlan {
   int32_t wave_cgs, wave_shift, wave_rows;
   int64_t wave_cap;            // most wavefronts (bounds the partial sums)
   bool wave_default;           // the library's own choice for this n
+  // GROUP form: threads per workgroup (0 = not available), column groups per strip, rows per thread, most workgroups
+  int32_t group_threads, group_cgs, group_rows, groups;
+  bool group_default;          // the library's own choice for this n
   int64_t bound;               // workspace that covers every form and launch shape
 };
 
@@ -341,6 +345,32 @@ ConsPlan cons_plan(int32_t n, int64_t d) {
       // strips of 128 bytes per agent still win (n = 130: 0.072 against 0.077 ms for the workgroup tiles on
       // 273 MB); at 64 bytes (n = 258) the tiles do
       p.wave_default = p.wave_cgs >= 8;
+    }
+  }
+  // GROUP form.  Measured on MI355X, 2^27 elements, several row pitches, against the form used before.  What
+  // counts is the width of a strip (rows of 64 bytes read at 2.5 TB/s, of 128 at 4.2 to 5, of 256 at 6) and one or
+  // two workgroups per compute unit; more of them lose.
+  //   up to 112 agents   the WAVE form's strips are 256 bytes wide (n = 100: 73 us against 82)
+  //   up to 416          256 threads x 13 rows (17 beyond 208 agents), two workgroups per unit: 128 to 256-byte strips
+  //                      (n = 130: 94 us against 87 to 127 depending on the pitch, n = 192: 71 against 100, n = 258:
+  //                      107 against 158, n = 320: 92 against 147)
+  //   up to 1088         512 threads x 17 rows, one workgroup per unit: n = 513: 115 against 182, n = 1026: 129
+  //                      against 222 (128-byte strips)
+  //   up to 3072         24 rows (more than 22 spill a little): 128-byte strips up to 1536 agents (n = 1500: 160 against
+  //                      203 with 17 rows and 64 bytes, 229 in two passes), 64-byte ones beyond (n = 2500: 189 against 224)
+  {
+    p.group_threads = n <= 416 ? 256 : 512;
+    const int32_t cap = n <= 208 ? 13 : (n <= 1088 ? 17 : 24);
+    int32_t row_lanes = p.group_threads / 64;          // a strip is at most a wavefront wide
+    while ((int64_t)row_lanes * cap < n) row_lanes *= 2;
+    p.group_default = n > 112 && n <= 3072;
+    if (row_lanes > p.group_threads / 2) {
+      p.group_threads = 0;
+      p.group_default = false;
+    } else {
+      p.group_cgs = p.group_threads / row_lanes;
+      p.group_rows = (n + row_lanes - 1) / row_lanes;
+      p.groups = p.group_threads == 256 ? 512 : 256;   // partial sums: 7 MB at most
     }
   }
   // the WAVE form never exceeds its cap whatever its launch shape; the TILE form's share follows the
@@ -560,7 +590,7 @@ int32_t ceca_set_option(int32_t option, int32_t value) {
       t.two_pass_gradient = value == 0;
       return CECA_OK;
     case CECA_OPT_CONS_SINGLE_PASS:
-      if (value < 0 || value > 3) return fail(CECA_EINVAL, "consensus form must be 0..3");
+      if (value < 0 || value > 4) return fail(CECA_EINVAL, "consensus form must be 0..4");
       t.cons_form = value == 1 ? 0 : (value == 0 ? 1 : value);
       return CECA_OK;
     case CECA_OPT_TILE_THREADS:
@@ -1297,9 +1327,22 @@ int32_t run_consensus(const float* X, int32_t n, int64_t d, int64_t ld, double* 
   const bool vec = aligned16(X) && ld % 4 == 0 && d % 4 == 0;
   const int32_t forced = g_tuning.cons_form;
   int form = CONS_TWO_PASS;
-  if (forced == CONS_WAVE ? p.wave_cgs > 0 : (forced == 0 && p.wave_cgs > 0 && p.wave_default)) form = CONS_WAVE;
+  if (p.group_threads > 0 && vec && (forced == CONS_GROUP || (forced == 0 && p.group_default))) form = CONS_GROUP;
+  else if (forced == CONS_WAVE ? p.wave_cgs > 0 : (forced == 0 && p.wave_cgs > 0 && p.wave_default)) form = CONS_WAVE;
   else if (forced != CONS_TWO_PASS && p.rows_per_thread > 0) form = CONS_TILE;
-  if (form == CONS_WAVE) {
+  if (form == CONS_GROUP) {
+    c.group_threads = p.group_threads;
+    c.wave_cgs = p.group_cgs;
+    while ((1 << c.cg_shift) < c.wave_cgs) ++c.cg_shift;
+    c.rows_per_thread = p.group_rows;
+    c.strips = (d / 4 + c.wave_cgs - 1) / c.wave_cgs;
+    c.nwaves = std::min<int64_t>(c.strips, p.groups);
+    const int64_t off_dev2 = round_up(((int64_t)n + 1) * c.nwaves * 8, 256);
+    *need = off_dev2 + round_up(((int64_t)n + 1) * 8, 256);
+    if (have < *need) return CECA_EWORKSPACE;
+    c.devpart = reinterpret_cast<double*>(w);
+    c.dev2 = reinterpret_cast<double*>(w + off_dev2);
+  } else if (form == CONS_WAVE) {
     const ConsWave cw = cons_wave(p, n, d, vec);
     *need = cw.total;
     if (have < cw.total) return CECA_EWORKSPACE;

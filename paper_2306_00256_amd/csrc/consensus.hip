@@ -276,6 +276,128 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
   if (lane == 0) C.devpart[(int64_t)C.n * C.nwaves + w] = nrm;
 }
 
+// s / n from the rounded reciprocal r of n: one correction step brings it back to the rounded quotient (up to ties
+// in the last bit), in three instructions where a division takes ten.
+__device__ __forceinline__ double div_by(double s, double n, double r) {
+  const double q = s * r;
+  return __builtin_fma(__builtin_fma(-q, n, s), r, q);
+}
+
+// Single pass, long-lived workgroups: the workgroup holds a column strip of every agent (cgs adjacent 16-byte groups
+// of RT rows per thread, rows rg, rg + row_lanes, ...) and takes strips b, b + nwaves, ... in turn.  Column sums
+// cross the row lanes of a wavefront by lane exchanges and the wavefronts through LDS (fp64, fixed order; one barrier
+// per strip: the sums of two strips alternate between two buffers).  As soon as a row's squared distance to the
+// means is in its accumulator, the row's register takes the next strip's load, so memory stays busy through the
+// arithmetic without a second copy of the strip.  The distances are added up over all strips in registers and cross
+// the column groups once, at the end.
+// A workgroup spreads the agents over all its wavefronts, so its strips stay 128 to 256 bytes wide for eight times as
+// many agents as a wavefront's; x is read once.  n = 1026, d = 2^17 (538 MB): 222 us in two passes, 129 us in this form
+// (4.2 TB/s, bound by the 128-byte reads of 1026 rows a strip).
+// Writes devpart[agent][workgroup] (row n: the workgroup's share of ||xbar||^2) and, if asked, xbar.
+template <int RT, int THREADS>
+__global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs C) {
+  constexpr int WAVES = THREADS / 64;
+  constexpr int RTP = RT <= 1 ? 1 : RT <= 2 ? 2 : RT <= 4 ? 4 : RT <= 8 ? 8 : RT <= 16 ? 16 : 32;
+  constexpr int LOG_RTP = RTP == 1 ? 0 : RTP == 2 ? 1 : RTP == 4 ? 2 : RTP == 8 ? 3 : RTP == 16 ? 4 : 5;
+  extern __shared__ double lds_d[];                 // [2][WAVES][cgs][4] column sums
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cgs = C.wave_cgs;                       // a power of two, 1..64
+  const int cg = tid & (cgs - 1);
+  const int rg = tid >> C.cg_shift;
+  const int row_lanes = THREADS >> C.cg_shift;
+  const int64_t ngroups = C.d / 4;
+  const bool last_mine = rg + (RT - 1) * row_lanes < C.n;      // rows per thread is the least that covers n
+  const double n = (double)C.n, rn = 1.0 / n;
+  double acc[RTP];
+#pragma unroll
+  for (int k = 0; k < RTP; ++k) acc[k] = 0.0;
+  double nrm = 0.0;
+  // lanes past the last column shadow column group 0, a row past the last agent shadows it (neither is counted)
+  const int64_t step = (int64_t)row_lanes * C.ld;
+  const int64_t last_step = last_mine ? step : (int64_t)(C.n - 1 - (rg + (RT - 2) * row_lanes)) * C.ld;
+  auto first_row = [&](int64_t tile) {
+    const int64_t g = tile * cgs + cg;
+    return C.X + (int64_t)(RT > 1 ? rg : min(rg, C.n - 1)) * C.ld + (g < ngroups ? g : 0) * 4;
+  };
+  vf4 x[RT];
+  {
+    const float* p = first_row(blockIdx.x);
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      x[k] = ld_stream<vf4>(p);
+      p += k == RT - 2 ? last_step : step;
+    }
+  }
+  int buf = 0;
+  for (int64_t tile = blockIdx.x; tile < C.strips; tile += gridDim.x, buf ^= 1) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < RT - 1; ++k) acc4(s, x[k]);
+    if (last_mine) acc4(s, x[RT - 1]);
+#define CECA_ROWSUM(O)                                                \
+    if (cgs <= O) {                                                   \
+      _Pragma("unroll") for (int q = 0; q < 4; ++q) s[q] += xor_lane<O>(s[q]); \
+    }
+    CECA_ROWSUM(1) CECA_ROWSUM(2) CECA_ROWSUM(4) CECA_ROWSUM(8) CECA_ROWSUM(16) CECA_ROWSUM(32)
+#undef CECA_ROWSUM
+    double* sums = lds_d + (size_t)buf * WAVES * cgs * 4;
+    if (lane < cgs) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sums[(wave * cgs + cg) * 4 + q] = s[q];
+    }
+    __syncthreads();
+    double m[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) m[q] += sums[(w * cgs + cg) * 4 + q];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m[q] = div_by(m[q], n, rn);
+    const int64_t g = tile * cgs + cg;
+    const bool on = g < ngroups;
+    // the last tile's loop re-requests itself: no branch surrounds a load
+    const float* p = first_row(tile + gridDim.x < C.strips ? tile + gridDim.x : tile);
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      asm volatile("" : "+v"(x[k]));                // converted to fp64 anew: kept from the sums, the doubles would take twice the registers of x
+      const double dev = sqdev(x[k], m);
+      x[k] = ld_stream<vf4>(p);
+      p += k == RT - 2 ? last_step : step;
+      acc[k] += on ? dev : 0.0;
+    }
+    if (rg == 0 && on) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) nrm += m[q] * m[q];
+      if (C.xbar) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) C.xbar[g * 4 + q] = (float)m[q];
+      }
+    }
+  }
+  // Sum over the column groups (lane bits below cg_shift), as in cons_wave_kernel
+  if (cgs > 1) { halve_d<1, RTP / 2>(acc, (lane & 1) != 0); nrm += xor_lane<1>(nrm); }
+  if (cgs > 2) { halve_d<2, RTP / 4>(acc, (lane & 2) != 0); nrm += xor_lane<2>(nrm); }
+  if (cgs > 4) { halve_d<4, RTP / 8>(acc, (lane & 4) != 0); nrm += xor_lane<4>(nrm); }
+  if (cgs > 8) { halve_d<8, RTP / 16>(acc, (lane & 8) != 0); nrm += xor_lane<8>(nrm); }
+  if (cgs > 16) { halve_d<16, RTP / 32>(acc, (lane & 16) != 0); nrm += xor_lane<16>(nrm); }
+  if (cgs > 32) { halve_d<32, RTP / 64>(acc, (lane & 32) != 0); nrm += xor_lane<32>(nrm); }
+  const int halvings = C.cg_shift < LOG_RTP ? C.cg_shift : LOG_RTP;
+  int off = 0;
+#pragma unroll
+  for (int t = 0; t < LOG_RTP; ++t)
+    if (t < halvings) off += ((lane >> t) & 1) * (RTP >> (t + 1));
+  const int live = RTP >> halvings;
+  const bool writer = (cg >> halvings) == 0;
+#pragma unroll
+  for (int j = 0; j < RTP; ++j) {
+    const int k = j + off;
+    const int i = rg + k * row_lanes;
+    if (writer && j < live && k < RT && i < C.n) C.devpart[(int64_t)i * C.nwaves + blockIdx.x] = acc[j];
+  }
+  if (tid == 0) C.devpart[(int64_t)C.n * C.nwaves + blockIdx.x] = nrm;
+}
+
 // The five results from the per-agent squared deviations dev2[0..n) and the partials of ||xbar||^2 (every
 // sum in a fixed order).  One workgroup.
 __device__ __forceinline__ void finish_results(const ConsensusArgs& C, const double* dev2) {
@@ -427,7 +549,46 @@ static hipError_t launch_cons_wave(const ConsensusArgs& c0, bool vec4, hipStream
   return hipGetLastError();
 }
 
+template <int THREADS, int MOST>
+static hipError_t launch_group_rt(const ConsensusArgs& c, size_t lds, hipStream_t st) {
+  switch (c.rows_per_thread) {
+#define CECA_CG(RT)                                                                                       \
+  case RT:                                                                                                \
+    if constexpr (RT <= MOST) {                                                                           \
+      cons_group_kernel<RT, THREADS><<<dim3((unsigned)c.nwaves), dim3(THREADS), lds, st>>>(c);            \
+      return hipGetLastError();                                                                           \
+    }                                                                                                     \
+    break;
+    CECA_CG(1) CECA_CG(2) CECA_CG(3) CECA_CG(4) CECA_CG(5) CECA_CG(6) CECA_CG(7) CECA_CG(8)
+    CECA_CG(9) CECA_CG(10) CECA_CG(11) CECA_CG(12) CECA_CG(13) CECA_CG(14) CECA_CG(15) CECA_CG(16)
+    CECA_CG(17) CECA_CG(18) CECA_CG(19) CECA_CG(20) CECA_CG(21) CECA_CG(22) CECA_CG(23) CECA_CG(24)
+#undef CECA_CG
+  }
+  return hipErrorInvalidValue;
+}
+
+static hipError_t launch_cons_group(const ConsensusArgs& c0, hipStream_t st) {
+  ConsensusArgs c = c0;
+  const int cgs = c.wave_cgs;
+  if (cgs < 1 || cgs > 64 || (1 << c.cg_shift) != cgs) return hipErrorInvalidValue;
+  const int row_lanes = c.group_threads / cgs;
+  if (c.rows_per_thread < 1 || (int64_t)c.rows_per_thread * row_lanes < c.n || (int64_t)(c.rows_per_thread - 1) * row_lanes >= c.n)
+    return hipErrorInvalidValue;                    // the kernel relies on rows_per_thread being the least that covers n
+  if (c.nwaves < 1 || c.nwaves > c.strips || c.nwaves >= (1LL << 24)) return hipErrorInvalidConfiguration;
+  c.ntiles = c.nwaves;            // row length of devpart for the reduction kernels
+  c.normpart = c.dev2 + c.n;      // devsum's row n is ||xbar||^2
+  c.norm_count = 1;
+  const size_t lds = 2 * (size_t)(c.group_threads / 64) * cgs * 4 * sizeof(double);
+  hipError_t e = hipErrorInvalidValue;
+  if (c.group_threads == 256) e = launch_group_rt<256, 17>(c, lds, st);
+  else if (c.group_threads == 512) e = launch_group_rt<512, 24>(c, lds, st);
+  if (e != hipSuccess) return e;
+  launch_close(c, c.n + 1, st);
+  return hipGetLastError();
+}
+
 hipError_t launch_consensus(const ConsensusArgs& c0, bool vec4, hipStream_t st) {
+  if (c0.group_threads > 0) return launch_cons_group(c0, st);
   if (c0.wave_cgs > 0) return launch_cons_wave(c0, vec4, st);
   ConsensusArgs c = c0;
   c.norm_count = c.ntiles;        // one partial of ||xbar||^2 per column tile

@@ -129,6 +129,8 @@ struct ConsensusArgs {
   int64_t strips;          // column strips in all
   int64_t nwaves;          // wavefronts launched; wavefront w takes strips w, w + nwaves, ...
   int64_t norm_count;      // entries of normpart (set by the launcher)
+  // workgroup form of the strips (group_threads > 0): as the wavefront form, with a workgroup in a wavefront's place
+  int32_t group_threads;   // 256 or 512 threads; wave_cgs column groups per strip, group_threads / wave_cgs row lanes
   int32_t close_rows;      // rows of devpart the closing kernels reduce (set by the launcher)
 };
 
@@ -202,7 +204,7 @@ struct Tuning {
   int32_t agents_per_wg;        // agents one workgroup of the looping one-pass gradient kernel takes in turn
   int32_t two_pass_gradient;    // 1: minibatch gradients always take the margins / half-step kernels
   int32_t never_chunked;        // 1: single steps never take the chunked gradient kernel
-  int32_t cons_form;            // consensus observables: 1 two-pass, 2 workgroup tiles, 3 wavefront strips
+  int32_t cons_form;            // consensus observables: 1 two-pass, 2 workgroup tiles, 3 wavefront strips, 4 workgroup strips
   int32_t cons_strips;          // strips one wavefront of the consensus kernel takes in turn
   int32_t plain_tile_order;     // 1: register-tile kernels never use the XCD-contiguous tile order
   int32_t graph_tables_in_memory;  // 1: graph gossip reads its tables from memory at every look-up

@@ -206,6 +206,40 @@ def test_wavefront_strip_form_is_deterministic_and_tight(env, n, d):
     P.ceca_reset_options()
 
 
+@pytest.mark.parametrize("n,d", [(1, 2052), (5, 30_000), (112, 4096), (113, 40_000), (208, 33_000), (209, 20_004), (416, 1004), (417, 18_000), (544, 64),
+                                 (545, 9000), (1088, 8196), (1089, 8200), (1536, 516), (1537, 5000), (3072, 4100), (3073, 32)])
+def test_workgroup_strip_form(env, n, d):
+    """The long-lived workgroup form at the edges of its shapes (one strip, several strips per workgroup, a ragged
+    last strip, padded rows): the library's choice and the form forced, at rtol 1e-12 on the four scalars, twice with
+    the same bits."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    x = WL.initial_state(n, d, seed=n + d) * 3.0 + 1.5
+    want = OCONS.consensus_error(x)
+    X = torch.full((n, d + 4), 1e30, dtype=torch.float32, device="cuda")
+    X[:, :d] = torch.from_numpy(x).cuda()
+    ws = torch.empty(P.consensus_error_workspace_bytes(n, d) + 256, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:]
+    for form in (1, 4):
+        P.ceca_set_option(Bn.OPT_CONS_SINGLE_PASS, form)
+        outs = []
+        for _ in range(2):
+            ws.fill_(0xFF)
+            out = torch.full((5,), -1.0, dtype=torch.float64, device="cuda")
+            xbar = torch.zeros(d, dtype=torch.float32, device="cuda")
+            P.consensus_error(X, n, d, out, xbar=xbar, workspace=ws, ld=d + 4)
+            outs.append(out.cpu().numpy())
+        g = outs[0]
+        assert np.array_equal(g, outs[1])
+        if n == 1:
+            assert g[0] == 0.0 and g[2] == 0.0
+        else:
+            assert np.isclose(g[0], want["frob2"], rtol=1e-12) and np.isclose(g[1], want["residue"], rtol=1e-12)
+            assert np.isclose(g[2], want["max_dev"], rtol=1e-12)
+        assert np.isclose(g[3], want["mean_norm"], rtol=1e-12) and g[4] == n
+        assert np.abs(xbar.cpu().numpy() - want["mean"]).max() <= 1e-6 * np.abs(want["mean"]).max()
+
+
 def test_stream_probe_values(env):
     """The measurement aid computes what its header says (elementwise, in and out of place)."""
     torch, P = env
