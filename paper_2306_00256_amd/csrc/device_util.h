@@ -224,6 +224,15 @@ __device__ __forceinline__ float in_vgpr(float uniform) {
   return v;
 }
 
+// LDS by its own 32-bit addresses, so that a kernel can keep one as an integer and let a constant distance ride in
+// the load instruction.
+__device__ __forceinline__ uint32_t lds_address(const void* shared) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)shared;
+}
+template <typename V> __device__ __forceinline__ V lds_load(uint32_t address) {
+  return *(__attribute__((address_space(3))) const V*)(uintptr_t)address;
+}
+
 // w * self + wp * msg, with one fixed rounding order wherever it is evaluated: the product with self is
 // rounded, then the peer's term is added by a fused multiply-add.  In this order the result can replace
 // self in its own register (multiply in place, accumulate in place): kernels that carry self across a loop

@@ -48,11 +48,11 @@ void mix_rounds_kernel(const MixArgs M) {
   V* xs = reinterpret_cast<V*>(lds_x);
   // Row i, column group c sits in LDS slot i * lanes + c, so my row k is slot tid + k * THREADS
   // (row_lanes * lanes = THREADS).  rows_per_thread is the least that covers n, so only my last row can
-  // lie past the last agent: it then shadows agent n - 1 and is never published.
+  // lie past the last agent: it then holds what agent n - 1 does and is never published.
   constexpr int L = RT - 1;
   const bool last_mine = rg + L * M.row_lanes < M.n;
-  const int slot_last = last_mine ? tid + L * THREADS : (M.n - 1) * lanes + cg;
-  const int wrap = M.n * lanes;
+  const int wrap = in_vgpr(M.n * lanes * (int)sizeof(V));
+  const uint32_t slot = lds_address(lds_x) + tid * sizeof(V), end = lds_address(lds_x) + wrap - sizeof(V);
   int spec = M.k0 % M.period;
   for (int t = 0; t < M.rounds; ++t) {
     const int j0 = M.start[spec], j1 = M.start[spec + 1];
@@ -60,7 +60,7 @@ void mix_rounds_kernel(const MixArgs M) {
     if (j1 > j0) {                                  // a round without peers is the identity
 #pragma unroll
       for (int k = 0; k < L; ++k) xs[tid + k * THREADS] = x[k];
-      if (last_mine) xs[slot_last] = x[L];
+      if (last_mine) xs[tid + L * THREADS] = x[L];
       __syncthreads();
       // peer by peer, all of the thread's rows at once: the RT LDS reads of a peer are independent and
       // issue back to back (row by row they would each wait for the one before).  Per row the order of
@@ -69,14 +69,25 @@ void mix_rounds_kernel(const MixArgs M) {
 #pragma unroll
       for (int k = 0; k < RT; ++k) x[k] = ws * x[k];
       for (int j = j0; j < j1; ++j) {
-        const int back = M.shift[j] * lanes;
+        // The peer of row rg + k * row_lanes is `shift` rows back on the circle: from the near address while that is
+        // inside the tile, from the far end otherwise.  One comparison and one select per row, with the rows'
+        // distances constants of the load instructions: an addition and a wrap took four instructions and, with
+        // their slower forms (a scalar operand, a minimum), more than the row's multiply-adds.
+        const int shift = M.shift[j];
+        const int past = shift - rg;               // rows k with k * row_lanes < past start from the far end
+        uint32_t near = slot - shift * (lanes * (uint32_t)sizeof(V)), far = near + wrap;
+        asm volatile("" : "+v"(near), "+v"(far));  // two addresses to select from, not one and a distance to add
         const float w = in_vgpr(M.w[j]);
+        V z[RT];
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
-          int q = ((k == L) ? slot_last : tid + k * THREADS) - back;
-          if (q < 0) q += wrap;
-          x[k] = fma_each(w, xs[q], x[k]);
+          uint32_t q = k * M.row_lanes < past ? far : near;
+          if (k == L) q = min(q + L * THREADS * (uint32_t)sizeof(V), end) - L * THREADS * (uint32_t)sizeof(V);   // a shadow row stays inside the tile
+          z[k] = lds_load<V>(q + k * THREADS * (uint32_t)sizeof(V));
         }
+        __builtin_amdgcn_sched_barrier(0);         // every read is issued before the first value is used
+#pragma unroll
+        for (int k = 0; k < RT; ++k) x[k] = fma_each(w, z[k], x[k]);
       }
       __syncthreads();
     }
