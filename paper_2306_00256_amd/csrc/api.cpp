@@ -912,6 +912,38 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   const bool lay = ld % 4 == 0 && aligned16(loss->A) && loss->lda % 4 == 0 && d % 4 == 0;
   const bool vec = lay && aligned16(S_in);
   const bool same_layout = vec == (lay && aligned16(S_out));
+  // Small problems: the whole window in one kernel, whose workgroups hold the state in registers and pass messages and
+  // partial margins through the workspace (the words fit it except for some odd lengths in chunks).  From two iterations
+  // on it is never more launches than the forms below.
+  ceca::RunShape shape{};
+  if (same_layout && n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
+      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, vec, st, &shape) &&
+      ceca::run_kernel_words(shape, n, d, loss->B) * 8 <= need) {
+    ceca::RunArgs a{};
+    a.xin = S_in;  a.yin = S_in + (int64_t)n * ld;
+    a.xout = S_out;  a.yout = S_out + (int64_t)n * ld;
+    a.ld = ld;
+    a.A = loss->A;  a.lda = loss->lda;  a.t = loss->t;
+    a.batch_idx = batch_idx;
+    a.words = reinterpret_cast<unsigned long long*>(workspace);
+    a.d = d;
+    a.n = n;  a.N = loss->N;  a.B = loss->B;  a.kind = loss->kind;
+    a.nchunks = shape.nchunks;  a.port = port;  a.iters = iters;
+    a.tau = tau;  a.r0 = r0;
+    a.lr = lr;
+    a.scale = loss->grad_scale > 0.0f ? loss->grad_scale : 1.0f / (float)loss->B;
+    a.noise_std = loss->noise_std;
+    a.seed = loss->seed;  a.k = loss->k;
+    for (int32_t t = 0; t < tau; ++t) {
+      ceca::fill_round(n, t, port, &rd);
+      ceca::MultiRound& R = a.round[t];
+      R.shift = rd.shift;  R.exch_y = rd.exchange_y;  R.read_y = rd.b_num != 0;
+      R.a = rd.a;  R.ap = rd.a_peer;  R.b = rd.b;  R.bp = rd.b_peer;
+    }
+    const hipError_t e = ceca::launch_run(a, shape, vec, st);
+    if (e != hipSuccess) return hip_fail(e, "window kernel launch");
+    return CECA_OK;
+  }
   const bool fused = same_layout && n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
                      ceca::grad_fused_covers(n, d, loss->B, vec);
   // Shapes whose single step takes the two-pass gradient (margins, then half step): the combine of the

@@ -3,6 +3,7 @@
 
 #include "ceca.h"
 #include "device_util.h"
+#include "gemv_util.h"
 #include "launch.h"
 
 namespace ceca {
@@ -89,13 +90,6 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
     for (int w = 0; w < kBlock / 64; ++w) t += red[w][threadIdx.x];
     G.partial[((int64_t)agent * G.nchunks + chunk) * G.B + j0 + threadIdx.x] = t;
   }
-}
-
-// Loss derivative at margin m with target / label t, already divided by the batch size.
-__device__ __forceinline__ float loss_coef(int kind, float m, float t, float scale) {
-  // LOGISTIC: -t * sigma(-t m) with sigma(-u) = 1 / (1 + e^u); e^u = inf gives 0, e^u = 0 gives 1
-  const float cf = (kind == CECA_LOSS_LSQ) ? (m - t) : (-t / (1.0f + expf(t * m)));
-  return cf * scale;
 }
 
 // v_i = z_i - lr * e_i with e_i = sum_j coef_j a_ij; coef_j folds the loss derivative and the 1/B.

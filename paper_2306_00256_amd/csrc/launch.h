@@ -105,6 +105,35 @@ struct GemvArgs {
   int32_t p_first;        // half-step form only: 1 = no iteration before (px, py are x, y themselves)
 };
 
+// A window of minibatch iterations in one kernel (run.hip).
+constexpr int kRunMaxTau = 16;
+constexpr int kRunParts = 2048;      // most chunks x samples of an agent
+
+struct RunShape {
+  int32_t threads;         // per workgroup: 64, 256 or 1024
+  int32_t bmax;            // sampled rows in registers
+  int32_t nchunks;         // workgroups per agent
+  int32_t wg_per_cu;       // workgroups a compute unit holds at least
+};
+
+struct RunArgs {
+  const float* xin;        // row 0 of x, y in S_in
+  const float* yin;
+  float* xout;             // in S_out (may be S_in: a workgroup touches only its own rows and columns)
+  float* yout;
+  int64_t ld;
+  const float* A;
+  int64_t lda;
+  const float* t;
+  const int32_t* batch_idx;   // [iters][n][B]
+  unsigned long long* words;  // {tag, value} words: two message slots [n][d], then two slots of partial margins [n][nchunks][B]
+  int64_t d;
+  int32_t n, N, B, kind, nchunks, port, iters, tau, r0;
+  float lr, scale, noise_std;
+  uint32_t seed, k;
+  MultiRound round[kRunMaxTau];
+};
+
 struct ConsensusArgs {
   const float* X;
   int64_t ld;
@@ -225,6 +254,11 @@ bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec4);
 // the fused form with the state in half-step rows between iterations: reads px, py (pitch ld), writes ox, oy
 // (pitch ldo, another buffer unless p_first); false when the shape is not covered
 bool launch_grad_half(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
+// a whole window of iterations as one kernel whose workgroups wait for each other: the shape for this problem, false
+// where it does not apply; the 8-byte words it needs as scratch; the launch
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, bool vec4, hipStream_t st, RunShape* out);
+int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B);
+hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_t st);
 // single-step gradient for layouts that are not 16-byte aligned (rows up to 1024 columns); false otherwise
 bool launch_grad_scalar(const GemvArgs& g, hipStream_t st, hipError_t* err);
 hipError_t launch_multi_round(const MultiArgs& m, bool vec4, hipStream_t st);

@@ -139,3 +139,41 @@ def test_two_pass_shapes_for_every_parity_of_the_iteration_count(env, iters, n, 
         B_ = A_ if inplace else torch.full_like(A_, float("nan"))
         P.dsgd_ceca_run(A_, B_, n, d, loss, idxd, lr, 1 % tau, iters, port, workspace=ws)
         assert torch.equal(B_, S), (iters, inplace)
+
+
+@pytest.mark.parametrize("n,port,d,B", [(2, 1, 4, 1), (3, 2, 1024, 8), (8, 1, 1020, 9), (96, 2, 1024, 16), (97, 2, 1024, 16), (64, 1, 512, 17),
+                                        (5, 2, 600, 32), (4, 1, 1024, 33), (32, 2, 1000, 64), (7, 2, 1028, 8), (32, 1, 4096, 16), (33, 2, 4096, 9),
+                                        (5, 2, 4096, 17), (8, 1, 4100, 9), (3, 2, 16000, 64), (512, 1, 64, 16), (513, 2, 63, 17), (2, 2, 1, 64),
+                                        (9, 2, 65, 16), (128, 2, 255, 17), (10, 1, 257, 33), (32, 2, 1023, 64), (5, 2, 1025, 16), (3, 2, 4099, 40)])
+def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B):
+    """Windows of many iterations (every message slot is used again and again), at the edges of workgroup sizes, batch
+    tiles, chunk counts and resident agents: the bits of the form with one or two kernels per iteration, twice on the
+    same workspace, and two windows on two streams at once."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    N, iters, lr = max(B // 2, 3), 61, 0.02 / (d * B) ** 0.5
+    gen = torch.Generator(device="cuda").manual_seed(n * d + B)
+    A = torch.randn((n, N, d), generator=gen, device="cuda")
+    t = torch.randn((n, N), generator=gen, device="cuda").sign()
+    idx = torch.randint(0, N, (iters, n, B), dtype=torch.int32, device="cuda", generator=gen)
+    S = torch.randn((2 * n, d), generator=gen, device="cuda")
+    loss = Bn.make_minibatch_loss(Bn.LOSS_LOGISTIC, A, t, N, B, noise_std=0.01, seed=5)
+    nbytes = P.dsgd_ceca_run_workspace_bytes(n, d, loss)
+    ws = [torch.full((nbytes + 256,), 255, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    ws = [w[(-w.data_ptr()) % 256:][:nbytes] for w in ws]
+    ref, got = torch.empty_like(S), [torch.full_like(S, float("nan")) for _ in range(2)]
+    P.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 0)
+    P.dsgd_ceca_run(S, ref, n, d, loss, idx, lr, 1 % OS.num_rounds(n), iters, port, workspace=ws[0])
+    P.ceca_reset_options()
+    assert bool(torch.isfinite(ref).all())
+    for _ in range(2):
+        P.dsgd_ceca_run(S, got[0], n, d, loss, idx, lr, 1 % OS.num_rounds(n), iters, port, workspace=ws[0])
+        assert torch.equal(got[0], ref)
+    torch.cuda.synchronize()
+    got[0].fill_(float("nan"))
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for s, w, g in zip(streams, ws, got):
+        P.dsgd_ceca_run(S, g, n, d, loss, idx, lr, 1 % OS.num_rounds(n), iters, port, workspace=w, stream=s)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], ref) and torch.equal(got[1], ref)
