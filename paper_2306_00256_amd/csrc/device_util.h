@@ -56,17 +56,29 @@ __device__ __forceinline__ double wave_max(double v) {
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
   return v;
 }
-// v + (v of lane ^ XOR).  Distances 1 and 2 are quad permutes on the data-parallel-primitive path (no
-// LDS traffic); 4, 8 and 16 are swizzles inside each half of the wavefront; 32 is a lane exchange.
+// v + (v of lane ^ XOR), all in the vector unit: a trip through the LDS pipe (swizzle, lane exchange) costs about a
+// hundred cycles in the reductions' dependent chains.  Distances 1 and 2 are quad permutes, 4 is a shift by four
+// lanes up for the even banks of a row of 16 and down for the odd ones, 8 a rotation of the row by half; 16 and 32
+// swap rows or halves between two registers that both hold v: one ends up with the lower, the other with the upper
+// one's value in both places, and their sum is the pair's sum.
 template <int XOR>
 __device__ __forceinline__ float xor_add(float v) {
   const int bits = __builtin_bit_cast(int, v);
-  int moved;
-  if constexpr (XOR == 1) moved = __builtin_amdgcn_update_dpp(0, bits, 0xB1, 0xf, 0xf, false);        // quad_perm [1, 0, 3, 2]
-  else if constexpr (XOR == 2) moved = __builtin_amdgcn_update_dpp(0, bits, 0x4E, 0xf, 0xf, false);   // quad_perm [2, 3, 0, 1]
-  else if constexpr (XOR == 32) moved = __shfl_xor(bits, 32, 64);
-  else moved = __builtin_amdgcn_ds_swizzle(bits, (XOR << 10) | 0x1f);                                  // xor mask, all lanes kept
-  return v + __builtin_bit_cast(float, moved);
+  if constexpr (XOR == 16 || XOR == 32) {
+    typedef unsigned int pair __attribute__((ext_vector_type(2)));
+    const pair s = XOR == 16 ? __builtin_amdgcn_permlane16_swap(bits, bits, false, false)
+                             : __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  } else {
+    int moved;
+    if constexpr (XOR == 1) moved = __builtin_amdgcn_update_dpp(0, bits, 0xB1, 0xf, 0xf, false);        // quad_perm [1, 0, 3, 2]
+    else if constexpr (XOR == 2) moved = __builtin_amdgcn_update_dpp(0, bits, 0x4E, 0xf, 0xf, false);   // quad_perm [2, 3, 0, 1]
+    else if constexpr (XOR == 4) {
+      moved = __builtin_amdgcn_update_dpp(0, bits, 0x104, 0xf, 0x5, false);                              // row_shl:4 into banks 0 and 2
+      moved = __builtin_amdgcn_update_dpp(moved, bits, 0x114, 0xf, 0xa, false);                          // row_shr:4 into banks 1 and 3
+    } else moved = __builtin_amdgcn_update_dpp(0, bits, 0x128, 0xf, 0xf, false);                        // row_ror:8
+    return v + __builtin_bit_cast(float, moved);
+  }
 }
 // One level of the halving butterfly below: every lane adds its partner's copy of each of the 2H values
 // it still carries, then keeps the H values that belong to its side (`up`); with one value left (H = 0)
@@ -140,7 +152,12 @@ __device__ __forceinline__ void halve_d(double (&v)[N], bool up) {
 }
 
 __device__ __forceinline__ float dot_v(vf4 a, vf4 b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
-__device__ __forceinline__ float dot_v(float a, float b) { return a * b; }
+// (the product is rounded by itself: fused into the first addition of a wavefront sum in one kernel and not in
+// another, the same margin would get different bits)
+__device__ __forceinline__ float dot_v(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 
 // ---------------------------------------------------------------------------------------------
 // Counter-based Gaussian noise (definition in ceca.h): one 32-bit word per uniform, Box-Muller

@@ -78,7 +78,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_wav
 void run_kernel(const RunArgs P) {
   using V = typename VecOf<VEC>::T;
   constexpr int WAVES = THREADS / 64;
-  constexpr int CH = kRowGroup;            // samples per wavefront sum, as in the single-step kernels
+  constexpr int CH = kRowGroup;            // rows are requested and added up in groups, as in the single-step kernels
+  constexpr int MG = BMAX < 16 ? BMAX : 16;    // samples per wavefront sum (any number gives the same bits)
   static_assert(BMAX % CH == 0 && BMAX <= 64, "whole groups of samples, one lane per sample");
   __shared__ float red[2][WAVES][BMAX];    // alternating between iterations
   __shared__ float part[CHUNKS ? kRunParts : 1];                  // partial margins of every chunk of the agent
@@ -101,6 +102,8 @@ void run_kernel(const RunArgs P) {
   const int64_t nb = (int64_t)P.n * P.B;
   int32_t myidx = min(max(idx[0], 0), P.N - 1);
   V a[BMAX];
+#pragma unroll
+  for (int j = 0; j < BMAX; ++j) a[j] = V(0.0f);      // groups past B are never requested
   float tmine;
   auto request_rows = [&]() {
     tmine = tbase[myidx];
@@ -129,21 +132,15 @@ void run_kernel(const RunArgs P) {
     if (t >= 2 && on) ack = peek(seen);
 
     const V z = on ? (R.exch_y ? y : x) : V(0.0f);
+    // every group of the tile, also those past B (zeros): without branches the groups' chains overlap
 #pragma unroll
-    for (int c0 = 0; c0 < BMAX; c0 += CH) {
-      if (c0 < P.B) {
-        float m[CH];
+    for (int c0 = 0; c0 < BMAX; c0 += MG) {
+      float m[MG];
 #pragma unroll
-        for (int j = 0; j < CH; ++j) {
-          // (the one-pass kernels start from a zero, the two-pass ones from the product: with one column per thread
-          // the product may fuse into the wavefront sum's first addition, which rounds differently)
-          m[j] = 0.0f;
-          m[j] = CHUNKS ? dot_v(a[c0 + j], z) : m[j] + dot_v(a[c0 + j], z);
-        }
-        int jrow;
-        const float msum = wave_sum_many<CH>(m, lane, jrow);
-        if (lane < CH) red[par][wave][c0 + jrow] = msum;
-      }
+      for (int j = 0; j < MG; ++j) m[j] = dot_v(a[c0 + j], z);
+      int jrow;
+      const float msum = wave_sum_many<MG>(m, lane, jrow);
+      if (lane < MG) red[par][wave][c0 + jrow] = msum;
     }
     __syncthreads();
     float mj = 0.0f;
