@@ -81,8 +81,9 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
 #pragma unroll
   for (int jj = 0; jj < kRowGroup; ++jj) acc[jj] = dot_v(a[jj], z);
   int jj;
-  const float s = wave_sum_many<kRowGroup>(acc, lane, jj);
-  if (lane < kRowGroup) red[wave][jj] = s;
+  bool owner;
+  const float s = wave_sum_many<kRowGroup>(acc, lane, jj, owner);
+  if (owner) red[wave][jj] = s;
   __syncthreads();
   if ((int)threadIdx.x < kRowGroup && j0 + (int)threadIdx.x < G.B) {
     float t = 0.0f;
@@ -200,8 +201,9 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
 #pragma unroll
       for (int k = 0; k < CH; ++k) part[k] = m[c0 + k];
       int jrow;
-      const float msum = wave_sum_many<CH>(part, lane, jrow);
-      if (lane < CH) red[turn][wave][c0 + jrow] = msum;
+      bool owner;
+      const float msum = wave_sum_many<CH>(part, lane, jrow, owner);
+      if (owner) red[turn][wave][c0 + jrow] = msum;
     }
     __syncthreads();
     // every wavefront turns the margins into coefficients for itself (lane j: sample j, same summation
@@ -350,8 +352,9 @@ void grad_chunked_kernel(const GemvArgs P) {
       for (int u = 0; u < G; ++u) m[j] += dot_v(a[j][u], z[u]);
     }
     int jrow;
-    const float msum = wave_sum_many<CH>(m, lane, jrow);
-    if (lane < CH) red[turn][wave][jrow] = msum;
+    bool owner;
+    const float msum = wave_sum_many<CH>(m, lane, jrow, owner);
+    if (owner) red[turn][wave][jrow] = msum;
     __syncthreads();
     // lane c0 + j of every wavefront turns margin j of this chunk into its coefficient
     const int jm = min(max(lane - c0, 0), CH - 1);

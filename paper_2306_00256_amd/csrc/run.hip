@@ -86,7 +86,7 @@ void run_kernel(const RunArgs P) {
   const int agent = CHUNKS ? (int)(blockIdx.x / (uint32_t)P.nchunks) : (int)blockIdx.x;
   const int chunk = CHUNKS ? (int)(blockIdx.x % (uint32_t)P.nchunks) : 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // lanes past the last column read column 0 instead and carry z = 0; they publish and wait for nothing
+  // lanes past the last column carry z = 0; they publish and wait for nothing
   const int64_t c = ((int64_t)chunk * THREADS + tid) * VEC;
   const bool on = c < P.d;
   const int64_t col = on ? c : 0;
@@ -96,7 +96,10 @@ void run_kernel(const RunArgs P) {
 
   V x = ld_plain<V>(P.xin + (int64_t)agent * P.ld + col);
   V y = ld_plain<V>(P.yin + (int64_t)agent * P.ld + col);
-  const float* Abase = P.A + (int64_t)agent * P.N * P.lda + col;
+  // a row's address is a scalar (its distance computed once per batch, lane j for sample j) plus the thread's own
+  // 32-bit offset: two lane reads and one 64-bit scalar addition in front of a load
+  const char* Abase = reinterpret_cast<const char*>(P.A + (int64_t)agent * P.N * P.lda + (int64_t)chunk * THREADS * VEC);
+  const uint32_t voff = on ? (uint32_t)tid * VEC * 4 : 0;        // lanes past the last column read the chunk's first one
   const float* tbase = P.t + (int64_t)agent * P.N;
   const int32_t* idx = P.batch_idx + (int64_t)agent * P.B + min(lane, P.B - 1);    // samples past B repeat the last
   const int64_t nb = (int64_t)P.n * P.B;
@@ -107,12 +110,16 @@ void run_kernel(const RunArgs P) {
   float tmine;
   auto request_rows = [&]() {
     tmine = tbase[myidx];
+    const int64_t dist = (int64_t)myidx * P.lda * (int64_t)sizeof(float);
+    const int lo = (int)(uint32_t)dist, hi = (int)(dist >> 32);
 #pragma unroll
     for (int c0 = 0; c0 < BMAX; c0 += CH) {
       if (c0 < P.B) {                      // the same for every thread
 #pragma unroll
-        for (int j = c0; j < c0 + CH; ++j)
-          a[j] = ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, j) * P.lda);
+        for (int j = c0; j < c0 + CH; ++j) {
+          const int64_t off = ((int64_t)__builtin_amdgcn_readlane(hi, j) << 32) | (uint32_t)__builtin_amdgcn_readlane(lo, j);
+          a[j] = ld_plain<V>(reinterpret_cast<const float*>(Abase + off + voff));
+        }
       }
     }
   };
@@ -139,8 +146,9 @@ void run_kernel(const RunArgs P) {
 #pragma unroll
       for (int j = 0; j < MG; ++j) m[j] = dot_v(a[c0 + j], z);
       int jrow;
-      const float msum = wave_sum_many<MG>(m, lane, jrow);
-      if (lane < MG) red[par][wave][c0 + jrow] = msum;
+      bool owner;
+      const float msum = wave_sum_many<MG>(m, lane, jrow, owner);
+      if (owner) red[par][wave][c0 + jrow] = msum;
     }
     __syncthreads();
     float mj = 0.0f;
@@ -153,11 +161,18 @@ void run_kernel(const RunArgs P) {
         publish(ring + chunk * P.B + tid, tag, s);
       }
       const int count = P.nchunks * P.B;   // at most kRunParts
-      for (int i = tid; i < count; i += THREADS) {
-        Word w = peek(ring + i);
+      for (int i0 = tid; i0 < count; i0 += 2 * THREADS) {
+        const int i1 = min(i0 + THREADS, count - 1);             // two words in flight; past the end the last one again
+        Word w0, w1;
+        bool here;
         wait.begin();
-        while ((uint32_t)(w >> 32) != tag && wait.again()) w = peek(ring + i);
-        part[i] = (uint32_t)(w >> 32) == tag ? __uint_as_float((uint32_t)w) : __builtin_nanf("");
+        do {
+          w0 = peek(ring + i0);
+          w1 = peek(ring + i1);
+          here = (uint32_t)(w0 >> 32) == tag && (uint32_t)(w1 >> 32) == tag;
+        } while (!here && wait.again());
+        part[i0] = (uint32_t)(w0 >> 32) == tag ? __uint_as_float((uint32_t)w0) : __builtin_nanf("");
+        part[i1] = (uint32_t)(w1 >> 32) == tag ? __uint_as_float((uint32_t)w1) : __builtin_nanf("");
       }
       __syncthreads();
       const int j = min(lane, P.B - 1);
@@ -202,10 +217,11 @@ void run_kernel(const RunArgs P) {
 #pragma unroll
       for (int u = 0; u < VEC; ++u) publish(slot + u * plane, tag, Parts<VEC>::get(v, u));
     }
-    // the next iteration's rows travel while the message does
+    // the next iteration's rows travel while the message does; a batch of the same rows (full gradients) is there
     if (t + 1 < P.iters) {
+      const int32_t now = myidx;
       myidx = min(max(idx_next, 0), P.N - 1);
-      request_rows();
+      if (__any(now != myidx)) request_rows();                   // the same in every wavefront
       idx_next = idx[(int64_t)min(t + 2, P.iters - 1) * nb];
     }
     V msg = V(0.0f);
