@@ -917,7 +917,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   // on it is never more launches than the forms below.
   ceca::RunShape shape{};
   if (same_layout && n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
-      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, vec, st, &shape) &&
+      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, loss->N, loss->lda, vec, st, &shape) &&
       ceca::run_kernel_words(shape, n, d, loss->B) * 8 <= need) {
     ceca::RunArgs a{};
     a.xin = S_in;  a.yin = S_in + (int64_t)n * ld;

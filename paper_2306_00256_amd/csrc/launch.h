@@ -256,7 +256,7 @@ bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec4);
 bool launch_grad_half(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
 // a whole window of iterations as one kernel whose workgroups wait for each other: the shape for this problem, false
 // where it does not apply; the 8-byte words it needs as scratch; the launch
-bool run_kernel_shape(int32_t n, int64_t d, int32_t B, bool vec4, hipStream_t st, RunShape* out);
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out);
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B);
 hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_t st);
 // single-step gradient for layouts that are not 16-byte aligned (rows up to 1024 columns); false otherwise

@@ -96,8 +96,8 @@ void run_kernel(const RunArgs P) {
 
   V x = ld_plain<V>(P.xin + (int64_t)agent * P.ld + col);
   V y = ld_plain<V>(P.yin + (int64_t)agent * P.ld + col);
-  // a row's address is a scalar (its distance computed once per batch, lane j for sample j) plus the thread's own
-  // 32-bit offset: two lane reads and one 64-bit scalar addition in front of a load
+  // a row's address is the agent's base in scalar registers plus 32 bits (the host sees to it that they are enough):
+  // the row's distance, computed once per batch in lane j for sample j, and the thread's own offset
   const char* Abase = reinterpret_cast<const char*>(P.A + (int64_t)agent * P.N * P.lda + (int64_t)chunk * THREADS * VEC);
   const uint32_t voff = on ? (uint32_t)tid * VEC * 4 : 0;        // lanes past the last column read the chunk's first one
   const float* tbase = P.t + (int64_t)agent * P.N;
@@ -110,16 +110,13 @@ void run_kernel(const RunArgs P) {
   float tmine;
   auto request_rows = [&]() {
     tmine = tbase[myidx];
-    const int64_t dist = (int64_t)myidx * P.lda * (int64_t)sizeof(float);
-    const int lo = (int)(uint32_t)dist, hi = (int)(dist >> 32);
+    const uint32_t dist = (uint32_t)myidx * (uint32_t)P.lda * (uint32_t)sizeof(float);
 #pragma unroll
     for (int c0 = 0; c0 < BMAX; c0 += CH) {
       if (c0 < P.B) {                      // the same for every thread
 #pragma unroll
-        for (int j = c0; j < c0 + CH; ++j) {
-          const int64_t off = ((int64_t)__builtin_amdgcn_readlane(hi, j) << 32) | (uint32_t)__builtin_amdgcn_readlane(lo, j);
-          a[j] = ld_plain<V>(reinterpret_cast<const float*>(Abase + off + voff));
-        }
+        for (int j = c0; j < c0 + CH; ++j)
+          a[j] = ld_plain<V>(reinterpret_cast<const float*>(Abase + (voff + (uint32_t)__builtin_amdgcn_readlane((int)dist, j))));
       }
     }
   };
@@ -297,9 +294,9 @@ int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B) {
 // stream's compute units have for it, so that eight such kernels fit beside each other (a process has four
 // hardware queues); kernels of any other kind end by themselves and make room.  A stream restricted to some compute
 // units counts those only.
-bool run_kernel_shape(int32_t n, int64_t d, int32_t B, bool vec4, hipStream_t st, RunShape* out) {
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out) {
   const RunShape s = run_shape(n, d, B, vec4);
-  if (s.threads == 0) return false;
+  if (s.threads == 0 || lda >= (1LL << 30) / N) return false;    // an agent's rows within 32-bit distances: 4 GB
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
     (void)hipGetLastError();
