@@ -855,6 +855,18 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
   g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (gemv_vec ? 4 : 1);
   g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
   hipError_t e = hipSuccess;
+  // small problems: one launch, in which every agent's workgroup also evaluates its peer's message (out of place only:
+  // in place a peer's rows could be written before they are read)
+  if (n > 1 && S_in != S_out && (!gemv_vec || state_vec) && !g_tuning.two_pass_gradient && g_tuning.agents_per_wg == 0 &&
+      !g_tuning.no_half_step) {
+    g.px = a.xin;  g.py = a.yin;
+    g.ox = a.xout;  g.oy = a.yout;
+    g.ldo = ld;
+    g.p_shift = rd.shift;  g.p_port = port;
+    g.p_exch_y = a.exch_y;  g.p_read_y = a.read_y;
+    g.pa = a.a;  g.pap = a.ap;  g.pb = a.b;  g.pbp = a.bp;
+    if (ceca::launch_pair_step(g, gemv_vec, st, &e)) return e == hipSuccess ? CECA_OK : hip_fail(e, "step kernel launch");
+  }
   const bool onepass = !g_tuning.two_pass_gradient &&
                        (gemv_vec ? ceca::launch_grad_onepass(g, st, &e) : ceca::launch_grad_scalar(g, st, &e));
   if (onepass) {

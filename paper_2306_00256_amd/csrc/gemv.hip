@@ -486,6 +486,118 @@ bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err) {
   return false;
 }
 
+// A whole iteration of a small problem in one launch.  The gradient kernel and the combine cost a launch each (about
+// 5 us) at sizes whose work takes one or two, and what separates them is that the combine needs a peer's message.  Here
+// a workgroup of 2 x THREADS threads evaluates two messages side by side: the first half its own agent's, the second
+// half that agent's peer's, which passes through LDS.  Every gradient is taken twice, so the rule in launch_pair_step
+// keeps to problems whose rows cost less than the launch saved.
+// Arithmetic and order of summation: the one-pass kernels' and the combine kernel's, operation for operation.
+template <int VEC, int THREADS, int BMAX>
+__global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P) {
+  using V = typename VecOf<VEC>::T;
+  constexpr int WAVES = THREADS / 64;
+  constexpr int CH = kRowGroup;
+  constexpr int MG = BMAX < 16 ? BMAX : 16;            // samples per wavefront sum (any number gives the same bits)
+  __shared__ float red[2][WAVES][BMAX];
+  __shared__ V msg_s[THREADS];
+  const int tid = threadIdx.x % THREADS, lane = threadIdx.x & 63;
+  const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / THREADS);        // the same for a whole wavefront
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int p;
+  if (P.p_port == 2) {
+    p = (int)blockIdx.x - P.p_shift; if (p < 0) p += P.n;
+  } else {
+    p = (blockIdx.x & 1) ? (int)blockIdx.x - P.p_shift : (int)blockIdx.x + P.p_shift;
+    if (p < 0) p += P.n;
+    if (p >= P.n) p -= P.n;
+  }
+  const int agent = half ? p : (int)blockIdx.x;
+  const int64_t c = (int64_t)tid * VEC;
+  const bool on = c < P.d;                             // d is a multiple of VEC
+  const int64_t col = on ? c : 0;
+  // lane j holds sample j; samples past B repeat the last
+  const int32_t myidx = min(max(P.batch_idx[(int64_t)agent * P.B + min(lane, P.B - 1)], 0), P.N - 1);
+  const float tmine = P.t[(int64_t)agent * P.N + myidx];
+  const float* Abase = P.A + (int64_t)agent * P.N * P.lda + col;
+  V a[BMAX];
+#pragma unroll
+  for (int j = 0; j < BMAX; ++j) a[j] = V(0.0f);       // groups past B are never requested
+#pragma unroll
+  for (int c0 = 0; c0 < BMAX; c0 += CH) {
+    if (c0 < P.B) {
+#pragma unroll
+      for (int j = c0; j < c0 + CH; ++j) a[j] = ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, j) * P.lda);
+    }
+  }
+  const int64_t off = (int64_t)agent * P.ld + col;
+  const V x = ld_plain<V>(P.px + off);
+  const V y = P.p_read_y || P.p_exch_y ? ld_plain<V>(P.py + off) : V(0.0f);
+  const V z = on ? (P.p_exch_y ? y : x) : V(0.0f);
+#pragma unroll
+  for (int c0 = 0; c0 < BMAX; c0 += MG) {
+    float m[MG];
+#pragma unroll
+    for (int j = 0; j < MG; ++j) m[j] = dot_v(a[c0 + j], z);
+    int jrow;
+    bool owner;
+    const float msum = wave_sum_many<MG>(m, lane, jrow, owner);
+    if (owner) red[half][wave][c0 + jrow] = msum;
+  }
+  __syncthreads();
+  float mj = 0.0f;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) mj += red[half][w][min(lane, BMAX - 1)];
+  const float cmine = lane < P.B ? loss_coef(P.kind, mj, tmine, P.scale) : 0.0f;
+  V e = V(0.0f);
+#pragma unroll
+  for (int c0 = 0; c0 < BMAX; c0 += CH) {
+    if (c0 < P.B) {
+#pragma unroll
+      for (int j = c0; j < c0 + CH; ++j) {
+        const float cj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cmine), j));
+        e += cj * a[j];
+      }
+    }
+  }
+  if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, col, noise_keys(P.seed, P.k, (uint32_t)agent));
+  const V v = z - P.lr * e;
+  if (half) msg_s[tid] = v;
+  __syncthreads();
+  if (half || !on) return;
+  {
+#pragma clang fp contract(off)
+    const V msg = msg_s[tid];
+    const V dz = v - z;                                // -lr e
+    const V xs = P.p_exch_y ? x + dz : v;
+    const V ys = P.p_exch_y ? v : y + dz;
+    const int64_t oo = (int64_t)agent * P.ldo + col;
+    *reinterpret_cast<V*>(P.ox + oo) = combine(P.pa, xs, P.pap, msg);
+    *reinterpret_cast<V*>(P.oy + oo) = P.p_read_y ? combine(P.pb, ys, P.pbp, msg) : P.pbp * msg;
+  }
+}
+
+// Where the pair form applies: rows that one 64- or 256-thread workgroup takes in one pass, and few enough of them --
+// 8 MB in all, 1.5 us of streaming, twice -- that taking every gradient twice costs less than a launch.
+bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
+  if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20) || g.px == g.ox) return false;
+  const dim3 grid((unsigned)g.n);
+#define CECA_PAIR(VEC, T, BM)                                                \
+  if (vec4 == (VEC == 4) && g.d <= (int64_t)T * VEC && g.B <= BM) {          \
+    pair_step_kernel<VEC, T, BM><<<grid, dim3(2 * T), 0, st>>>(g);           \
+    *err = hipGetLastError();                                                \
+    return true;                                                             \
+  }
+  CECA_PAIR(4, 256, 8)
+  CECA_PAIR(4, 256, 16)
+  CECA_PAIR(4, 256, 32)
+  CECA_PAIR(1, 64, 16)
+  CECA_PAIR(1, 64, 64)
+  CECA_PAIR(1, 256, 16)
+  CECA_PAIR(1, 256, 64)
+#undef CECA_PAIR
+  return false;
+}
+
 hipError_t launch_margins(const GemvArgs& g, bool vec4, hipStream_t st) {
   if (g.nchunks < 1 || g.n > 65535) return hipErrorInvalidConfiguration;
   dim3 grid((unsigned)g.nchunks, (unsigned)g.n, (unsigned)((g.B + kRowGroup - 1) / kRowGroup)), block(kBlock);

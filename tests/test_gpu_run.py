@@ -177,3 +177,31 @@ def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B):
         P.dsgd_ceca_run(S, g, n, d, loss, idx, lr, 1 % OS.num_rounds(n), iters, port, workspace=w, stream=s)
     torch.cuda.synchronize()
     assert torch.equal(got[0], ref) and torch.equal(got[1], ref)
+
+
+@pytest.mark.parametrize("kind", ["lsq", "logistic"])
+@pytest.mark.parametrize("n,port,d,B", [(2, 1, 4, 1), (3, 2, 1024, 8), (6, 1, 1020, 9), (70, 2, 1024, 16), (5, 2, 256, 17), (63, 2, 1024, 32),
+                                        (64, 1, 1024, 32), (65, 2, 1024, 32), (258, 1, 10, 50), (2, 2, 1, 64), (9, 2, 64, 16), (9, 2, 65, 17),
+                                        (4, 1, 255, 16), (7, 2, 253, 64), (6, 2, 1024, 33), (5, 2, 257, 8)])
+def test_single_launch_step_equals_the_two_kernel_form(env, kind, n, port, d, B):
+    """One out-of-place step whose workgroups also evaluate their peer's message, at the edges of its workgroup sizes,
+    batch tiles and size limit (and just past them), every round of a cycle: the bits of gradient kernel + combine."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    N, lr = max(B // 2, 3), 0.02 / (d * B) ** 0.5
+    gen = torch.Generator(device="cuda").manual_seed(n * d + B)
+    A = torch.randn((n, N, d), generator=gen, device="cuda")
+    t = torch.randn((n, N), generator=gen, device="cuda").sign()
+    idx = torch.randint(-1, N + 1, (n, B), dtype=torch.int32, device="cuda", generator=gen)      # out-of-range numbers are clamped
+    S = torch.randn((2 * n, d), generator=gen, device="cuda")
+    for r in range(OS.num_rounds(n)):
+        loss = Bn.make_minibatch_loss(Bn.LOSS_LSQ if kind == "lsq" else Bn.LOSS_LOGISTIC, A, t, N, B, noise_std=0.01, seed=5, k=r)
+        ws = _aligned(torch, P.dsgd_ceca_workspace_bytes(n, d, loss))
+        one, two, inplace = torch.full_like(S, float("nan")), torch.full_like(S, float("nan")), S.clone()
+        P.dsgd_ceca_step(S, one, n, d, loss, idx, lr, r, port, workspace=ws)
+        P.dsgd_ceca_step(inplace, inplace, n, d, loss, idx, lr, r, port, workspace=ws)
+        P.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 0)
+        P.dsgd_ceca_step(S, two, n, d, loss, idx, lr, r, port, workspace=ws)
+        P.ceca_reset_options()
+        assert bool(torch.isfinite(two).all())
+        assert torch.equal(one, two) and torch.equal(inplace, two), r
