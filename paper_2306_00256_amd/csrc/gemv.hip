@@ -577,7 +577,10 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
 }
 
 // Where the pair form applies: rows that one 64- or 256-thread workgroup takes in one pass, and few enough of them --
-// 8 MB in all, 1.5 us of streaming, twice -- that taking every gradient twice costs less than a launch.
+// 8 MB in all, 1.5 us of streaming, twice -- that taking every gradient twice costs less than a launch.  Per step in a
+// captured graph, two kernels against this one: n = 6, d = 1000, B = 8: 6.4 -> 3.2 us; n = 258, d = 10, B = 50: 9.3 ->
+// 5.4; and at the limit n = 64, d = 1024, B = 32: 7.8 -> 5.7; n = 2000, d = 64, B = 16: 12.3 -> 5.5; n = 4000,
+// d = 10, B = 50: 18.2 -> 14.6.
 bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
   if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20) || g.px == g.ox) return false;
   const dim3 grid((unsigned)g.n);
@@ -587,6 +590,9 @@ bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* 
     *err = hipGetLastError();                                                \
     return true;                                                             \
   }
+  CECA_PAIR(4, 64, 8)                      // (the 256-thread kernels' other wavefronts would add zeros)
+  CECA_PAIR(4, 64, 16)
+  CECA_PAIR(4, 64, 32)
   CECA_PAIR(4, 256, 8)
   CECA_PAIR(4, 256, 16)
   CECA_PAIR(4, 256, 32)

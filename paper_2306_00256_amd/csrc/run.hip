@@ -26,8 +26,12 @@ namespace ceca {
 // kept off the device for kGiveUpTicks), it gives up: NaN takes the place of the missing values, and the call ends.
 //
 // What bounds it: the latency of the chain rows -> margins -> barrier -> coefficients -> message -> peer, once per
-// iteration.  Per iteration, one launch (or two) each before and here: n = 5, d = 1000, B = 8: 3.9 -> 2.1 us;
-// n = 258, d = 10, B = 50 with noise: 7.6 -> 4.7 us; n = 6, d = 10000, B = 32 in ten chunks: 13.4 -> 6.9 us.
+// iteration (an exchange between workgroups takes about 1.3 us), and a compute unit's intake of sampled rows, 75 GB/s.
+// Per iteration, one launch (two in chunks) each before and here: n = 5, d = 1000, B = 8: 3.9 -> 1.9 us; n = 258, d = 10,
+// B = N = 50 with noise: 7.6 -> 2.5 us; n = 6, d = 10000, B = 32 in ten chunks: 13.4 -> 5.9 us; n = 256, d = 256, B = 32:
+// 8.4 -> 2.6 us.
+// Messages packed as four floats in three words were slower (n = 5: 2.2 -> 2.5 us in the same loop), and 128-thread
+// workgroups with a margin word per wavefront too (n = 6, d = 10000, B = 32: 5.9 -> 6.6 us: four times the polling).
 //
 // Arithmetic and order of summation are those of the single-step kernels (gemv.hip), operation for operation: per
 // sample the dot product over a thread's columns, the wavefront butterfly 8 samples at a time, wavefronts in order,
@@ -270,7 +274,8 @@ static RunShape run_shape(int32_t n, int64_t d, int32_t B, bool vec4) {
   if (n < 2 || B < 1 || B > 64) return s;
   const int64_t groups = vec4 ? d / 4 : d;
   if (vec4) {
-    if (groups <= 256) s.threads = 256;
+    if (groups <= 64) s.threads = 64;                            // (the single step's other wavefronts add zeros)
+    else if (groups <= 256) s.threads = 256;
     else if (groups <= 1024 && B <= 16) s.threads = 1024;
     else if (grad_fused_covers(n, d, B, true)) return s;         // wider rows in one workgroup
     else s.threads = 256;
@@ -335,6 +340,7 @@ hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_
   if (e != hipSuccess) return e;
   switch ((vec4 ? 1 << 20 : 0) + s.threads * 64 + s.bmax - 1) {
 #define CECA_RUN(VEC, T, BM) case (VEC == 4 ? 1 << 20 : 0) + T * 64 + BM - 1: return launch<VEC, T, BM>(a, st)
+    CECA_RUN(4, 64, 8); CECA_RUN(4, 64, 16); CECA_RUN(4, 64, 32); CECA_RUN(4, 64, 64);
     CECA_RUN(4, 256, 8); CECA_RUN(4, 256, 16); CECA_RUN(4, 256, 32); CECA_RUN(4, 256, 64);
     CECA_RUN(4, 1024, 8); CECA_RUN(4, 1024, 16);
     CECA_RUN(1, 64, 16); CECA_RUN(1, 64, 64);

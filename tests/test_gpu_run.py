@@ -144,7 +144,7 @@ def test_two_pass_shapes_for_every_parity_of_the_iteration_count(env, iters, n, 
 @pytest.mark.parametrize("n,port,d,B", [(2, 1, 4, 1), (3, 2, 1024, 8), (8, 1, 1020, 9), (96, 2, 1024, 16), (97, 2, 1024, 16), (64, 1, 512, 17),
                                         (5, 2, 600, 32), (4, 1, 1024, 33), (32, 2, 1000, 64), (7, 2, 1028, 8), (32, 1, 4096, 16), (33, 2, 4096, 9),
                                         (5, 2, 4096, 17), (8, 1, 4100, 9), (3, 2, 16000, 64), (512, 1, 64, 16), (513, 2, 63, 17), (2, 2, 1, 64),
-                                        (9, 2, 65, 16), (128, 2, 255, 17), (10, 1, 257, 33), (32, 2, 1023, 64), (5, 2, 1025, 16), (3, 2, 4099, 40)])
+                                        (9, 2, 65, 16), (512, 1, 256, 8), (257, 2, 252, 9), (256, 2, 256, 32), (128, 1, 64, 33), (9, 2, 260, 40), (128, 2, 255, 17), (10, 1, 257, 33), (32, 2, 1023, 64), (5, 2, 1025, 16), (3, 2, 4099, 40)])
 def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B):
     """Windows of many iterations (every message slot is used again and again), at the edges of workgroup sizes, batch
     tiles, chunk counts and resident agents: the bits of the form with one or two kernels per iteration, twice on the
@@ -182,7 +182,7 @@ def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B):
 @pytest.mark.parametrize("kind", ["lsq", "logistic"])
 @pytest.mark.parametrize("n,port,d,B", [(2, 1, 4, 1), (3, 2, 1024, 8), (6, 1, 1020, 9), (70, 2, 1024, 16), (5, 2, 256, 17), (63, 2, 1024, 32),
                                         (64, 1, 1024, 32), (65, 2, 1024, 32), (258, 1, 10, 50), (2, 2, 1, 64), (9, 2, 64, 16), (9, 2, 65, 17),
-                                        (4, 1, 255, 16), (7, 2, 253, 64), (6, 2, 1024, 33), (5, 2, 257, 8)])
+                                        (4, 1, 255, 16), (7, 2, 253, 64), (6, 2, 1024, 33), (5, 2, 257, 8), (9, 2, 256, 8), (9, 2, 252, 32), (9, 2, 260, 9)])
 def test_single_launch_step_equals_the_two_kernel_form(env, kind, n, port, d, B):
     """One out-of-place step whose workgroups also evaluate their peer's message, at the edges of its workgroup sizes,
     batch tiles and size limit (and just past them), every round of a cycle: the bits of gradient kernel + combine."""
