@@ -181,11 +181,13 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
 /* `iters` consecutive DSGD-CECA iterations with a minibatch loss (LSQ or LOGISTIC) in one call.
  * Iteration t (t = 0 .. iters-1) uses round (r0 + t) mod tau, the noise counter loss->k + t, the batch
  * rows batch_idx + t * n * B (device, iters * n * B int32) and the one step size lr; the result has the
- * same bits as `iters` calls of dsgd_ceca_step.  Small problems -- all workgroups resident in an eighth of
- * the device (512 agents at d <= 64, 128 to 512 at d <= 256, a few dozen at d <= 4096, about six at d = 16000; not the wide rows of
- * small batches that one workgroup takes, d > 4096 with B <= 8) -- run the whole window as one kernel whose workgroups wait for each
- * other's messages (a stream restricted to some compute units counts those; should a workgroup's peers
- * stay off the device for 30 s, it gives up and the result is NaN).  For the others: where a workgroup can take an agent's whole rows
+ * same bits as `iters` calls of dsgd_ceca_step.  Small problems run the
+ * whole window as one kernel whose workgroups wait for each other's messages: those whose workgroups are
+ * all resident in an eighth of the device (512 agents at d <= 64, 128 to 512 at d <= 256, a few dozen at
+ * d <= 4096, about six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096
+ * with B <= 8; a stream restricted to some compute units counts those).  Should a workgroup's peers stay
+ * off the device for 30 s, it gives up and the result is NaN.  For the others: where a workgroup
+ * can take an agent's whole rows
  * (16-byte aligned layouts with d <= 16384 and either n >= 128 with d > 1024 or a batch that fits a
  * register tile: B <= 32 at d <= 1024, 16 at 4096, 8 at 8192, 4 at 16384; any other layout with
  * d <= 1024) each iteration after the first is ONE kernel: the workgroup that takes agent i's gradient

@@ -237,7 +237,8 @@ struct Tuning {
   int32_t cons_strips;          // strips one wavefront of the consensus kernel takes in turn
   int32_t plain_tile_order;     // 1: register-tile kernels never use the XCD-contiguous tile order
   int32_t graph_tables_in_memory;  // 1: graph gossip reads its tables from memory at every look-up
-  int32_t no_half_step;         // 1: dsgd_ceca_run keeps full states and message buffers between fused iterations
+  int32_t no_half_step;         // 1: dsgd_ceca_run keeps full states and message buffers between fused iterations (and small
+                                // problems take neither the window kernel nor the single-launch step)
   int32_t lean_tiles;           // gossip-rounds kernel with 256 threads: 4, 5, 6 = the register-lean form for that many wavefronts per SIMD
   int32_t probe_variant;        // 3-read / 2-write probe: policy * 100 + threads code * 10 + column groups per thread
   int32_t probe_waves;          // probe kernels: that many long-lived wavefronts instead of one thread per column group
