@@ -855,9 +855,9 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
   g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (gemv_vec ? 4 : 1);
   g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
   hipError_t e = hipSuccess;
-  // small problems: one launch, in which every agent's workgroup also evaluates its peer's message (out of place only:
-  // in place a peer's rows could be written before they are read)
-  if (n > 1 && S_in != S_out && (!gemv_vec || state_vec) && !g_tuning.two_pass_gradient && g_tuning.agents_per_wg == 0 &&
+  // small problems: one launch, in which every agent's workgroup also evaluates its peer's message (with two ports out
+  // of place only: in place a peer's rows could be written before they are read)
+  if (n > 1 && (!gemv_vec || state_vec) && !g_tuning.two_pass_gradient && g_tuning.agents_per_wg == 0 &&
       !g_tuning.no_half_step) {
     g.px = a.xin;  g.py = a.yin;
     g.ox = a.xout;  g.oy = a.yout;

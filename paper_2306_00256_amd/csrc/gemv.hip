@@ -489,8 +489,9 @@ bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err) {
 // A whole iteration of a small problem in one launch.  The gradient kernel and the combine cost a launch each (about
 // 5 us) at sizes whose work takes one or two, and what separates them is that the combine needs a peer's message.  Here
 // a workgroup of 2 x THREADS threads evaluates two messages side by side: the first half its own agent's, the second
-// half that agent's peer's, which passes through LDS.  Every gradient is taken twice, so the rule in launch_pair_step
-// keeps to problems whose rows cost less than the launch saved.
+// half that agent's peer's, which passes through LDS.  With one port the two are each other's peers, so a workgroup
+// finishes both (also in place); with two ports every gradient is taken twice, and the rule in launch_pair_step keeps
+// to problems whose rows cost less than the launch saved.
 // Arithmetic and order of summation: the one-pass kernels' and the combine kernel's, operation for operation.
 template <int VEC, int THREADS, int BMAX>
 __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P) {
@@ -499,19 +500,19 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
   constexpr int CH = kRowGroup;
   constexpr int MG = BMAX < 16 ? BMAX : 16;            // samples per wavefront sum (any number gives the same bits)
   __shared__ float red[2][WAVES][BMAX];
-  __shared__ V msg_s[THREADS];
+  __shared__ V msg_s[2][THREADS];
   const int tid = threadIdx.x % THREADS, lane = threadIdx.x & 63;
   const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x / THREADS);        // the same for a whole wavefront
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool both = P.p_port == 1;                     // an even agent and the odd one it is paired with (Eq. (7))
+  const int first = both ? 2 * (int)blockIdx.x : (int)blockIdx.x;
   int p;
-  if (P.p_port == 2) {
-    p = (int)blockIdx.x - P.p_shift; if (p < 0) p += P.n;
+  if (both) {
+    p = first + P.p_shift; if (p >= P.n) p -= P.n;
   } else {
-    p = (blockIdx.x & 1) ? (int)blockIdx.x - P.p_shift : (int)blockIdx.x + P.p_shift;
-    if (p < 0) p += P.n;
-    if (p >= P.n) p -= P.n;
+    p = first - P.p_shift; if (p < 0) p += P.n;
   }
-  const int agent = half ? p : (int)blockIdx.x;
+  const int agent = half ? p : first;
   const int64_t c = (int64_t)tid * VEC;
   const bool on = c < P.d;                             // d is a multiple of VEC
   const int64_t col = on ? c : 0;
@@ -561,12 +562,12 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
   }
   if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, col, noise_keys(P.seed, P.k, (uint32_t)agent));
   const V v = z - P.lr * e;
-  if (half) msg_s[tid] = v;
+  msg_s[half][tid] = v;
   __syncthreads();
-  if (half || !on) return;
+  if ((half && !both) || !on) return;
   {
 #pragma clang fp contract(off)
-    const V msg = msg_s[tid];
+    const V msg = msg_s[half ^ 1][tid];
     const V dz = v - z;                                // -lr e
     const V xs = P.p_exch_y ? x + dz : v;
     const V ys = P.p_exch_y ? v : y + dz;
@@ -582,8 +583,10 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
 // 5.4; and at the limit n = 64, d = 1024, B = 32: 7.8 -> 5.7; n = 2000, d = 64, B = 16: 12.3 -> 5.5; n = 4000,
 // d = 10, B = 50: 18.2 -> 14.6.
 bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
-  if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20) || g.px == g.ox) return false;
-  const dim3 grid((unsigned)g.n);
+  const bool both = g.p_port == 1;
+  if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20)) return false;
+  if (both ? (g.n & 1) || !(g.p_shift & 1) : g.px == g.ox) return false;       // two ports: out of place only
+  const dim3 grid((unsigned)(both ? g.n / 2 : g.n));
 #define CECA_PAIR(VEC, T, BM)                                                \
   if (vec4 == (VEC == 4) && g.d <= (int64_t)T * VEC && g.B <= BM) {          \
     pair_step_kernel<VEC, T, BM><<<grid, dim3(2 * T), 0, st>>>(g);           \

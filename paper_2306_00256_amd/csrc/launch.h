@@ -260,7 +260,7 @@ bool launch_grad_half(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* 
 bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out);
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B);
 hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_t st);
-// gradient, message and combine of one iteration as one kernel, S_in and S_out different (px, py -> ox, oy); false
+// gradient, message and combine of one iteration as one kernel (px, py -> ox, oy; two ports: another buffer); false
 // where it does not apply
 bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
 // single-step gradient for layouts that are not 16-byte aligned (rows up to 1024 columns); false otherwise
