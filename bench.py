@@ -316,7 +316,10 @@ def run_minibatch(torch, P, Bn, sp, steps, warmup):
     tm.final = consensus_report(torch, P, S[:n], n, d, ld)      # after warmup + steps iterations from x(0) = 0
     one_kernel_gradient = (d % 4 == 0 and ((n >= 128 and 1024 < d <= 16384) or (B <= 32 and d <= 1024) or (B <= 16 and d <= 4096)
                                            or (B <= 8 and d <= 8192) or (B <= 4 and d <= 16384))) or (d % 4 != 0 and d <= 1024)
-    launches = 2 if one_kernel_gradient else 3
+    # small problems: gradient, messages and combine in one kernel
+    vec = d % 4 == 0
+    one_launch = B <= (32 if vec else 64) and d <= (1024 if vec else 256) and n * B * d * 4 <= 8 << 20
+    launches = 1 if one_launch else 2 if one_kernel_gradient else 3
     if EAGER_ONLY:
         return tm, launches, minibatch_bytes(B)
     # launch-bound loops: the same iterations captured once as a HIP graph and replayed

@@ -580,7 +580,7 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
 // Where the pair form applies: rows that one 64- or 256-thread workgroup takes in one pass, and few enough of them --
 // 8 MB in all, 1.5 us of streaming, twice -- that taking every gradient twice costs less than a launch.  Per step in a
 // captured graph, two kernels against this one: n = 6, d = 1000, B = 8: 6.4 -> 3.2 us; n = 258, d = 10, B = 50: 9.3 ->
-// 5.4; and at the limit n = 64, d = 1024, B = 32: 7.8 -> 5.7; n = 2000, d = 64, B = 16: 12.3 -> 5.5; n = 4000,
+// 5.4 (one port 4.6); and at the limit n = 64, d = 1024, B = 32: 7.8 -> 5.7 (one port 5.6); n = 2000, d = 64, B = 16: 12.3 -> 5.5; n = 4000,
 // d = 10, B = 50: 18.2 -> 14.6.
 bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
   const bool both = g.p_port == 1;
