@@ -277,10 +277,12 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
 }
 
 // s / n from the rounded reciprocal r of n: one correction step brings it back to the rounded quotient (up to ties
-// in the last bit), in three instructions where a division takes ten.
+// in the last bit), in six instructions where a division takes a dozen.  The correction of an infinite quotient would be
+// inf - inf; it stays as it is, as in the forms that divide.
 __device__ __forceinline__ double div_by(double s, double n, double r) {
   const double q = s * r;
-  return __builtin_fma(__builtin_fma(-q, n, s), r, q);
+  const double c = __builtin_fma(__builtin_fma(-q, n, s), r, q);
+  return __builtin_isinf(q) ? q : c;
 }
 
 // Single pass, long-lived workgroups: the workgroup holds a column strip of every agent (cgs adjacent 16-byte groups

@@ -240,6 +240,30 @@ def test_workgroup_strip_form(env, n, d):
         assert np.abs(xbar.cpu().numpy() - want["mean"]).max() <= 1e-6 * np.abs(want["mean"]).max()
 
 
+@pytest.mark.parametrize("n,d", [(60, 2052), (112, 4096), (113, 4096), (130, 1001), (130, 5000), (600, 4096), (1026, 2052), (1600, 516)])
+@pytest.mark.parametrize("entries", [((3, 5, np.inf),), ((0, 0, -np.inf), (7, 129, np.inf)), ((2, 17, np.inf), (9, 17, -np.inf)), ((11, 77, np.nan),)])
+def test_entries_that_are_not_finite(env, n, d, entries):
+    """A column with one infinite entry has an infinite mean, one with both signs or a NaN has none, and the others keep
+    theirs (to one fp32 rounding); the norm of the mean and the distances follow.  The same in every form."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    x = WL.initial_state(n, d, seed=n + d) * 3.0 + 1.5
+    for i, j, v in entries:
+        x[i, j] = v
+    with np.errstate(invalid="ignore"):
+        mean = x.astype(np.float64).mean(axis=0)
+        norm = np.sqrt((mean ** 2).sum())
+    X = torch.from_numpy(x).cuda()
+    for form in range(5):
+        P.ceca_set_option(Bn.OPT_CONS_SINGLE_PASS, form)
+        got, xbar = _consensus(torch, P, X, n, d)
+        finite = np.isfinite(mean)
+        assert np.array_equal(xbar[~finite], mean[~finite].astype(np.float32), equal_nan=True), form
+        assert np.abs(xbar[finite] - mean[finite]).max() <= 2.0 ** -24 * np.abs(mean[finite]).max() * (1 + 1e-6), form
+        assert np.array_equal(got[3], norm, equal_nan=True), form
+        assert np.isnan(got[0]) and np.isnan(got[1]) and got[4] == n, form       # the entry's own row is at inf - inf
+
+
 def test_stream_probe_values(env):
     """The measurement aid computes what its header says (elementwise, in and out of place)."""
     torch, P = env
