@@ -68,6 +68,18 @@ int32_t ceca_set_option(int32_t option, int32_t value);
 /* Every option of the calling thread back to the library default. */
 int32_t ceca_reset_options(void);
 
+/* The form that the calling thread's last successful dsgd_ceca_step or dsgd_ceca_run with a minibatch loss took
+ * (CECA_FORM_NONE before the first): every form gives the same bits, so a test that means one of them asks here
+ * whether it ran.
+ *   STEP_SINGLE  one launch per step         STEP_ONE_PASS / STEP_TWO_PASS  gradient in one or two kernels, then combine
+ *   RUN_WINDOW  the whole window in one kernel
+ *   RUN_HALF_STEPS / RUN_MESSAGES  one kernel per iteration, the state between them in half-step form or with message buffers
+ *   RUN_TWO_PASS  two kernels per iteration  RUN_STEPS  dsgd_ceca_step in a loop */
+enum { CECA_FORM_NONE = 0, CECA_FORM_STEP_SINGLE = 1, CECA_FORM_STEP_ONE_PASS = 2, CECA_FORM_STEP_TWO_PASS = 3,
+       CECA_FORM_RUN_WINDOW = 4, CECA_FORM_RUN_HALF_STEPS = 5, CECA_FORM_RUN_MESSAGES = 6, CECA_FORM_RUN_TWO_PASS = 7,
+       CECA_FORM_RUN_STEPS = 8 };
+int32_t ceca_last_form(void);
+
 /* Launch shape the library picks (under the calling thread's overrides) for the state-updating kernel of one
  * ceca_gossip_round (kind = 0), of one dsgd_ceca_step with the quadratic-centre loss (kind = 1) or of one
  * dsgd_ceca_step with a minibatch loss (kind = 2: the combine from stored messages) on a 16-byte aligned

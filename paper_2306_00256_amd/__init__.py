@@ -14,6 +14,7 @@ from .binding import (  # noqa: F401
     ceca_gossip_round,
     ceca_gossip_rounds,
     ceca_graph_rounds,
+    ceca_last_form,
     ceca_mix_rounds,
     ceca_reset_options,
     ceca_schedule,

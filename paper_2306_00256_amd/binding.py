@@ -15,13 +15,15 @@ OPT_SEGMENT, OPT_ROWS, OPT_BAND, OPT_WG_PER_CU, OPT_ONEPASS, OPT_AGENTS_PER_WG, 
 OPT_GRAPH_STAGE, OPT_CHUNKED_GRADIENT, OPT_CONS_STRIPS, OPT_PROBE_WAVES, OPT_LEAN_TILES, OPT_PROBE_VARIANT, OPT_HALF_STEP_RUN = 11, 12, 13, 14, 15, 16, 17
 TOPO_RING, TOPO_STATIC_EXP, TOPO_ONE_PEER_EXP = 0, 1, 2
 MIX_MAX = 16
+# forms of the minibatch calls, as ceca_last_form (ceca_test.h) names them
+FORM_NONE, FORM_STEP_SINGLE, FORM_STEP_ONE_PASS, FORM_STEP_TWO_PASS, FORM_RUN_WINDOW, FORM_RUN_HALF_STEPS, FORM_RUN_MESSAGES, FORM_RUN_TWO_PASS, FORM_RUN_STEPS = range(9)
 
 EXPORTS = (
     "ceca_tau", "ceca_schedule", "ceca_gossip_round", "ceca_gossip_rounds", "ceca_average", "dsgd_ceca_workspace_bytes", "dsgd_ceca_step", "dsgd_ceca_steps", "dsgd_ceca_run_workspace_bytes", "dsgd_ceca_run",
     "consensus_error_workspace_bytes", "consensus_error", "consensus_error_noalloc", "ceca_state_consensus", "ceca_topology_round", "ceca_mix_rounds", "ceca_graph_rounds", "ceca_last_error", "ceca_last_hip_error",
 )
 # include/ceca_test.h: launch-shape overrides and probe kernels for tests and measurement, not the product ABI
-TEST_EXPORTS = ("ceca_set_option", "ceca_reset_options", "ceca_stream_probe", "ceca_describe_step_launch")
+TEST_EXPORTS = ("ceca_set_option", "ceca_reset_options", "ceca_stream_probe", "ceca_describe_step_launch", "ceca_last_form")
 
 
 class CecaError(RuntimeError):
@@ -112,6 +114,8 @@ def lib():
         L.ceca_describe_step_launch.argtypes = [C.c_int32, C.c_int64, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                                 C.POINTER(C.c_int32)]
         L.ceca_describe_step_launch.restype = C.c_int32
+        L.ceca_last_form.argtypes = []
+        L.ceca_last_form.restype = C.c_int32
         L.ceca_reset_options.argtypes = []
         L.ceca_reset_options.restype = C.c_int32
         L.ceca_last_error.restype = C.c_char_p
@@ -264,6 +268,11 @@ def ceca_describe_step_launch(n: int, d: int, ld: int, r: int, port: int, kind: 
     out = (C.c_int32 * 6)()
     _check(lib().ceca_describe_step_launch(n, d, ld, r, port, int(kind), int(in_place), out))
     return dict(zip(("rows", "band", "wg_per_cu", "stretch", "stretches_per_cycle", "vec"), list(out)))
+
+
+def ceca_last_form() -> int:
+    """The form (FORM_*) that this thread's last minibatch step or run took (ceca_test.h)."""
+    return int(lib().ceca_last_form())
 
 
 def ceca_set_option(option: int, value: int) -> None:

@@ -23,6 +23,7 @@ using ceca::g_tuning;
 
 thread_local char g_msg[256] = "";
 thread_local int32_t g_hip = 0;
+thread_local int32_t g_form = CECA_FORM_NONE;     // ceca_last_form
 
 int32_t fail(int32_t code, const char* fmt, ...) {
   va_list ap;
@@ -644,6 +645,8 @@ int32_t ceca_reset_options(void) {
   return CECA_OK;
 }
 
+int32_t ceca_last_form(void) { return g_form; }
+
 int32_t ceca_tau(int32_t n) {
   if (n < 1) return fail(CECA_EINVAL, "n = %d: need at least one agent", n);
   return ceca::tau_of(n);
@@ -865,7 +868,11 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
     g.p_shift = rd.shift;  g.p_port = port;
     g.p_exch_y = a.exch_y;  g.p_read_y = a.read_y;
     g.pa = a.a;  g.pap = a.ap;  g.pb = a.b;  g.pbp = a.bp;
-    if (ceca::launch_pair_step(g, gemv_vec, st, &e)) return e == hipSuccess ? CECA_OK : hip_fail(e, "step kernel launch");
+    if (ceca::launch_pair_step(g, gemv_vec, st, &e)) {
+      if (e != hipSuccess) return hip_fail(e, "step kernel launch");
+      g_form = CECA_FORM_STEP_SINGLE;
+      return CECA_OK;
+    }
   }
   const bool onepass = !g_tuning.two_pass_gradient &&
                        (gemv_vec ? ceca::launch_grad_onepass(g, st, &e) : ceca::launch_grad_scalar(g, st, &e));
@@ -880,6 +887,7 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
 
   a.aux = g.v;
   a.ldaux = g.ldv;
+  g_form = onepass ? CECA_FORM_STEP_ONE_PASS : CECA_FORM_STEP_TWO_PASS;
   return run_chain(a, ceca::MODE_FROMV, d, state_vec, rd, port, st);
 }
 
@@ -954,6 +962,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     }
     const hipError_t e = ceca::launch_run(a, shape, vec, st);
     if (e != hipSuccess) return hip_fail(e, "window kernel launch");
+    g_form = CECA_FORM_RUN_WINDOW;
     return CECA_OK;
   }
   const bool fused = same_layout && n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
@@ -1020,6 +1029,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     set_weights(prev, n, /*gossip_only=*/false, &a);
     a.aux = V2[(iters - 1) & 1];
     a.ldaux = p.ldv;
+    g_form = CECA_FORM_RUN_TWO_PASS;
     return run_chain(a, ceca::MODE_FROMV, d, vec && aligned16(S_out) && ld % 4 == 0, prev, port, st);
   }
   ceca_loss_t one = *loss;
@@ -1031,6 +1041,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
                           n == 1 ? 0 : (r0 + t) % tau, port, w + p.v_bytes, p.v_bytes + p.partial_bytes, st);
       if (rc != CECA_OK) return rc;
     }
+    g_form = CECA_FORM_RUN_STEPS;
     return CECA_OK;
   }
   if (copy_fits && !g_tuning.no_half_step) {
@@ -1080,6 +1091,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     a.ld = ld;
     a.n = n;
     set_weights(prev, n, /*gossip_only=*/true, &a);
+    g_form = CECA_FORM_RUN_HALF_STEPS;
     return run_chain(a, ceca::MODE_GOSSIP, d, vec && aligned16(S_out), prev, port, st);
   }
   float* V[2] = {reinterpret_cast<float*>(w), reinterpret_cast<float*>(w + p.v_bytes)};
@@ -1136,6 +1148,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   set_weights(prev, n, /*gossip_only=*/false, &a);
   a.aux = V[(iters - 1) & 1];
   a.ldaux = p.ldv;
+  g_form = CECA_FORM_RUN_MESSAGES;
   return run_chain(a, ceca::MODE_FROMV, d, aligned16(S_out) && ld % 4 == 0, prev, port, st);
 }
 

@@ -217,12 +217,14 @@ def test_concurrent_calls_on_two_streams_from_two_threads(env):
             assert np.array_equal(outs[i][0], serial[i]), i
 
 
-def test_graph_of_a_run_on_the_two_pass_gradient(env):
-    """dsgd_ceca_run on a shape whose gradient takes two passes (the state alternates between S_out and a copy
-    in the workspace): captured once, every replay continues the eager trajectory."""
+@pytest.mark.parametrize("n,d,form", [(8, 20000, "FORM_RUN_TWO_PASS"), (6, 10000, "FORM_RUN_WINDOW")])
+def test_graph_of_a_run_on_the_two_pass_gradient(env, n, d, form):
+    """dsgd_ceca_run on shapes whose gradient takes two passes: with two kernels per iteration (the state alternates
+    between S_out and a copy in the workspace) and as one kernel in chunks.  Captured once, every replay continues the
+    eager trajectory."""
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
-    n, d, N, B, iters, port = 6, 10000, 20, 32, 5, 2
+    N, B, iters, port = 20, 32, 5, 2
     A, t, _ = WL.logistic_data_sparse(n, N, d, seed=5, density=0.5)
     idx = torch.from_numpy(WL.batch_indices(n, N, B, iters, seed=5)).cuda()
     Ad, td = torch.from_numpy(A).cuda(), torch.from_numpy(t).cuda()
@@ -248,6 +250,7 @@ def test_graph_of_a_run_on_the_two_pass_gradient(env):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         P.dsgd_ceca_run(S2, S2, n, d, loss, idx, 0.01, 0, iters, port, workspace=ws)
+    assert P.ceca_last_form() == getattr(Bn, form)
     S2.copy_(make_state(torch, x0))
     for rep in range(replays):
         graph.replay()

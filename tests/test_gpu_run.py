@@ -118,7 +118,7 @@ def test_single_iteration_and_argument_errors(env):
 
 
 @pytest.mark.parametrize("iters", [2, 3, 4, 5])
-@pytest.mark.parametrize("n,port,d,B", [(6, 2, 10000, 32), (6, 1, 2051, 9)])
+@pytest.mark.parametrize("n,port,d,B", [(8, 2, 20000, 32), (6, 1, 2051, 9)])
 def test_two_pass_shapes_for_every_parity_of_the_iteration_count(env, iters, n, port, d, B):
     """Shapes on the two-pass gradient alternate the state between S_out and a copy in the workspace: the
     result must land in S_out for odd and even iteration counts, in place and out of place."""
@@ -138,17 +138,22 @@ def test_two_pass_shapes_for_every_parity_of_the_iteration_count(env, iters, n, 
         A_ = make_state(torch, x0)
         B_ = A_ if inplace else torch.full_like(A_, float("nan"))
         P.dsgd_ceca_run(A_, B_, n, d, loss, idxd, lr, 1 % tau, iters, port, workspace=ws)
+        assert P.ceca_last_form() == Bn.FORM_RUN_TWO_PASS
         assert torch.equal(B_, S), (iters, inplace)
 
 
-@pytest.mark.parametrize("n,port,d,B", [(2, 1, 4, 1), (3, 2, 1024, 8), (8, 1, 1020, 9), (96, 2, 1024, 16), (97, 2, 1024, 16), (64, 1, 512, 17),
-                                        (5, 2, 600, 32), (4, 1, 1024, 33), (32, 2, 1000, 64), (7, 2, 1028, 8), (32, 1, 4096, 16), (33, 2, 4096, 9),
-                                        (5, 2, 4096, 17), (8, 1, 4100, 9), (3, 2, 16000, 64), (512, 1, 64, 16), (513, 2, 63, 17), (2, 2, 1, 64),
-                                        (9, 2, 65, 16), (512, 1, 256, 8), (257, 2, 252, 9), (256, 2, 256, 32), (128, 1, 64, 33), (9, 2, 260, 40), (128, 2, 255, 17), (10, 1, 257, 33), (32, 2, 1023, 64), (5, 2, 1025, 16), (3, 2, 4099, 40)])
-def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B):
+@pytest.mark.parametrize("n,port,d,B,window", [
+    (2, 1, 4, 1, True), (3, 2, 1024, 8, True), (8, 1, 1020, 9, True), (96, 2, 1024, 16, True), (97, 2, 1024, 16, False), (64, 1, 512, 17, True),
+    (5, 2, 600, 32, True), (4, 1, 1024, 33, True), (32, 2, 1000, 64, True), (7, 2, 1028, 8, True), (32, 1, 4096, 16, True), (33, 2, 4096, 9, False),
+    (5, 2, 4096, 17, True), (8, 1, 4100, 9, True), (6, 2, 9984, 32, False), (2, 2, 9000, 64, True), (384, 1, 64, 16, True), (385, 2, 64, 16, False),
+    (512, 1, 63, 16, True), (512, 2, 64, 64, False), (512, 2, 63, 17, True), (513, 2, 63, 17, False), (2, 2, 1, 64, True), (9, 2, 65, 16, True),
+    (512, 1, 256, 8, True), (257, 2, 252, 9, True), (256, 2, 256, 32, True), (128, 1, 64, 33, True), (129, 2, 256, 64, False), (9, 2, 260, 40, True),
+    (128, 2, 255, 17, True), (10, 1, 257, 33, True), (32, 2, 1023, 64, True), (4, 1, 1999, 4, True), (2, 2, 1025, 9, True), (3, 2, 2049, 8, False)])
+def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B, window):
     """Windows of many iterations (every message slot is used again and again), at the edges of workgroup sizes, batch
-    tiles, chunk counts and resident agents: the bits of the form with one or two kernels per iteration, twice on the
-    same workspace, and two windows on two streams at once."""
+    tiles, chunk counts, resident agents and the words that fit the workspace: the bits of the form with one or two
+    kernels per iteration, twice on the same workspace, and two windows on two streams at once; the one-kernel form
+    inside those edges and another one outside."""
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
     N, iters, lr = max(B // 2, 3), 61, 0.02 / (d * B) ** 0.5
@@ -165,9 +170,10 @@ def test_long_windows_at_the_edges_of_the_shapes(env, n, port, d, B):
     P.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 0)
     P.dsgd_ceca_run(S, ref, n, d, loss, idx, lr, 1 % OS.num_rounds(n), iters, port, workspace=ws[0])
     P.ceca_reset_options()
-    assert bool(torch.isfinite(ref).all())
+    assert bool(torch.isfinite(ref).all()) and P.ceca_last_form() != Bn.FORM_RUN_WINDOW
     for _ in range(2):
         P.dsgd_ceca_run(S, got[0], n, d, loss, idx, lr, 1 % OS.num_rounds(n), iters, port, workspace=ws[0])
+        assert (P.ceca_last_form() == Bn.FORM_RUN_WINDOW) == window
         assert torch.equal(got[0], ref)
     torch.cuda.synchronize()
     got[0].fill_(float("nan"))
@@ -199,9 +205,11 @@ def test_single_launch_step_equals_the_two_kernel_form(env, kind, n, port, d, B)
         ws = _aligned(torch, P.dsgd_ceca_workspace_bytes(n, d, loss))
         one, two, inplace = torch.full_like(S, float("nan")), torch.full_like(S, float("nan")), S.clone()
         P.dsgd_ceca_step(S, one, n, d, loss, idx, lr, r, port, workspace=ws)
+        assert (P.ceca_last_form() == Bn.FORM_STEP_SINGLE) == (B <= (64 if d % 4 else 32) and d <= (256 if d % 4 else 1024) and n * B * d <= 2 << 20)
         P.dsgd_ceca_step(inplace, inplace, n, d, loss, idx, lr, r, port, workspace=ws)
         P.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 0)
         P.dsgd_ceca_step(S, two, n, d, loss, idx, lr, r, port, workspace=ws)
         P.ceca_reset_options()
+        assert P.ceca_last_form() in (Bn.FORM_STEP_ONE_PASS, Bn.FORM_STEP_TWO_PASS)
         assert bool(torch.isfinite(two).all())
         assert torch.equal(one, two) and torch.equal(inplace, two), r
