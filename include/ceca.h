@@ -182,11 +182,24 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * Iteration t (t = 0 .. iters-1) uses round (r0 + t) mod tau, the noise counter loss->k + t, the batch
  * rows batch_idx + t * n * B (device, iters * n * B int32) and the one step size lr; the result has the
  * same bits as `iters` calls of dsgd_ceca_step.  Small problems run the
- * whole window as one kernel whose workgroups wait for each other's messages: those whose workgroups are
- * all resident in an eighth of the device (512 agents at d <= 64, 128 to 512 at d <= 256, a few dozen at
- * d <= 4096, about six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096
- * with B <= 8; a stream restricted to some compute units counts those).  Should a workgroup's peers stay
- * off the device for 30 s, it gives up and the result is NaN.  For the others: where a workgroup
+ * whole window as one kernel whose workgroups wait for each other's messages: those whose workgroups fit an
+ * eighth of the device's 256 compute units (16-byte aligned layouts with d <= 256: 512, 384, 256 and 128
+ * agents for B <= 8, 16, 32 and 64; other layouts with d <= 64: 512; a few dozen agents at d <= 4096, about
+ * six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096 with B <= 8; a
+ * stream restricted to some compute units counts those).  Where several workgroups share an agent's columns
+ * (16-byte layouts with d > 1024 and B > 16 or d > 4096, others with d > 1024) their words also have to fit
+ * the workspace, which depends on the length: up to B = 16 nine in ten 16-byte lengths do, at B = 32 two in
+ * three (d = 10000 but not 9984), at B = 64 fewer than half; of the lengths that are not multiples of 4 one in
+ * five at B = 4, one in fifty at B = 8 and none from B = 16 on.
+ * All workgroups of that kernel have to be on the device at once.  When some of them are not after about
+ * 12 ms of waiting -- kernels that do not end hold their places, a captured call is replayed on a stream with
+ * fewer compute units than the capturing one, the process was given fewer by other means than the stream's
+ * mask, more than eight such windows run at the same time (of all processes on the device together) -- the
+ * window is given up before anything is stored, and one workgroup does all of it alone: the same bits, but
+ * slowly (tens of milliseconds where the window takes 0.05 to 0.6).  Only a workspace that something else
+ * writes to during the call can make workgroups that are all there miss a message; after half a minute
+ * the result is NaN then.
+ * For the others: where a workgroup
  * can take an agent's whole rows
  * (16-byte aligned layouts with d <= 16384 and either n >= 128 with d > 1024 or a batch that fits a
  * register tile: B <= 32 at d <= 1024, 16 at 4096, 8 at 8192, 4 at 16384; any other layout with
@@ -198,7 +211,8 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * 64; beyond that, and when S_in and S_out differ in 16-byte alignment, the call loops over
  * dsgd_ceca_step).
  * S_out may be S_in or disjoint from it; when disjoint, S_in is left unchanged.
- * workspace: device, 256-byte aligned, at least dsgd_ceca_run_workspace_bytes(); contents are scratch. */
+ * workspace: device, 256-byte aligned, at least dsgd_ceca_run_workspace_bytes() (256 bytes less are taken
+ * too; the one-kernel window may then not fit); contents are scratch. */
 int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int64_t ld,
                       const ceca_loss_t* loss, const int32_t* batch_idx, float lr, int32_t r0,
                       int32_t iters, int32_t port, void* workspace, int64_t workspace_bytes,

@@ -53,6 +53,8 @@ extern "C" {
  *   CECA_OPT_HALF_STEP_RUN  1 (default): dsgd_ceca_run keeps the state in half-step form between fused iterations
  *                     (no message buffers); 0: it keeps full states and two message buffers.  0 also keeps small
  *                     problems off the one-kernel window and the single-launch step
+ *   CECA_OPT_WINDOW_MISSING  that many workgroups (all but one at most) of a one-kernel window are never launched: the
+ *                     others wait for them in vain, give the window up after some 12 ms and one does it alone
  *   CECA_OPT_PROBE_VARIANT  the 3-read / 2-write probe in another shape: 100 * policy (0 streaming loads and stores,
  *                     1 plain loads, 2 plain stores, 3 both plain) + 10 * threads code (1 = 256, 2 = 512,
  *                     4 = 1024 per workgroup) + column groups per thread (1, 2, 4, 8 with 256 threads)
@@ -62,7 +64,8 @@ extern "C" {
 enum { CECA_OPT_SEGMENT = 1, CECA_OPT_ROWS = 2, CECA_OPT_BAND = 3, CECA_OPT_WG_PER_CU = 4, CECA_OPT_ONEPASS = 5,
        CECA_OPT_AGENTS_PER_WG = 7, CECA_OPT_CONS_SINGLE_PASS = 8, CECA_OPT_XCD_TILE_ORDER = 9,
        CECA_OPT_TILE_THREADS = 10, CECA_OPT_GRAPH_STAGE = 11, CECA_OPT_CHUNKED_GRADIENT = 12,
-       CECA_OPT_CONS_STRIPS = 13, CECA_OPT_PROBE_WAVES = 14, CECA_OPT_LEAN_TILES = 15, CECA_OPT_PROBE_VARIANT = 16, CECA_OPT_HALF_STEP_RUN = 17 };
+       CECA_OPT_CONS_STRIPS = 13, CECA_OPT_PROBE_WAVES = 14, CECA_OPT_LEAN_TILES = 15, CECA_OPT_PROBE_VARIANT = 16, CECA_OPT_HALF_STEP_RUN = 17,
+       CECA_OPT_WINDOW_MISSING = 18 };
 int32_t ceca_set_option(int32_t option, int32_t value);
 
 /* Every option of the calling thread back to the library default. */

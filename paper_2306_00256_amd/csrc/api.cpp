@@ -185,6 +185,8 @@ void set_weights(const ceca_round_t& rd, int32_t n, bool gossip_only, ceca::Chai
 // dsgd_ceca_run's copy of the state: 2n rows at the caller's pitch, for pitches up to round_up(d, 64)
 int64_t run_state_bytes(int32_t n, int64_t d) { return round_up(2 * (int64_t)n * round_up(d, 64) * (int64_t)sizeof(float), 256); }
 
+constexpr int64_t kRollBytes = 256;      // the one-kernel window's word of who is there
+
 struct GemvPlan {
   int64_t ldv, v_bytes, partial_bytes;
   int32_t nchunks_max;
@@ -619,6 +621,10 @@ int32_t ceca_set_option(int32_t option, int32_t value) {
     case CECA_OPT_HALF_STEP_RUN:
       t.no_half_step = value == 0;
       return CECA_OK;
+    case CECA_OPT_WINDOW_MISSING:
+      if (value < 0) return fail(CECA_EINVAL, "missing workgroups must be >= 0");
+      t.window_missing = value;
+      return CECA_OK;
     case CECA_OPT_LEAN_TILES:
       if (value != 0 && value != 1 && (value < 4 || value > 6)) return fail(CECA_EINVAL, "lean tiles must be 0, 1, 4, 5 or 6");
       t.lean_tiles = value;
@@ -899,8 +905,9 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
     return fail(CECA_EINVAL, "dsgd_ceca_run takes minibatch losses (LSQ, LOGISTIC)");
   const GemvPlan p = gemv_plan(n, d, loss->B);
   // two message buffers (iterations alternate) + partial margins + a copy of the state (iterations on the
-  // two-pass gradient kernels alternate between it and S_out)
-  return 2 * p.v_bytes + p.partial_bytes + run_state_bytes(n, d);
+  // two-pass gradient kernels alternate between it and S_out) + room for the roll of the one-kernel window, whose
+  // words may take all of the rest
+  return 2 * p.v_bytes + p.partial_bytes + run_state_bytes(n, d) + kRollBytes;
 }
 
 int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int64_t ld, const ceca_loss_t* loss,
@@ -915,7 +922,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     return fail(CECA_EINVAL, "dsgd_ceca_run takes minibatch losses (LSQ, LOGISTIC)");
   if (iters < 1) return fail(CECA_EINVAL, "iters = %d: need at least one", iters);
   const GemvPlan p = gemv_plan(n, d, loss->B);
-  const int64_t need = 2 * p.v_bytes + p.partial_bytes + run_state_bytes(n, d);
+  const int64_t need = 2 * p.v_bytes + p.partial_bytes + run_state_bytes(n, d);       // (the roll is asked for below)
   if (!workspace || workspace_bytes < need)
     return fail(CECA_EWORKSPACE, "workspace of %lld bytes needed, %lld given", (long long)need,
                 (long long)(workspace ? workspace_bytes : 0));
@@ -932,13 +939,20 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   const bool lay = ld % 4 == 0 && aligned16(loss->A) && loss->lda % 4 == 0 && d % 4 == 0;
   const bool vec = lay && aligned16(S_in);
   const bool same_layout = vec == (lay && aligned16(S_out));
+  // (a workspace of the size before the roll was added to it is still taken, with another form where the words fill it)
+  auto window_roll_fits = [&](int64_t words) {
+    return words + 8 <= workspace_bytes && !overlaps(workspace, words + 8, S_out, sbytes) && !overlaps(workspace, words + 8, S_in, sbytes);
+  };
   // Small problems: the whole window in one kernel, whose workgroups hold the state in registers and pass messages and
-  // partial margins through the workspace (the words fit it except for some odd lengths in chunks).  From two iterations
-  // on it is never more launches than the forms below.
+  // partial margins through the workspace.  From two iterations on it is never more launches than the forms below.
+  // Its words have to fit the space that the other forms need.  They do with one workgroup per agent; in chunks the
+  // partial margins are 16 n chunks B bytes of words against 4 n B ceil(d / 256) bytes and what padding rows to 64
+  // floats leaves, so it depends on the length.  Of all lengths to 12,000 with up to 40 agents: 87 % or more of the
+  // 16-byte ones to B = 16, 68 % at B = 32, 43 % at B = 64; of the others 21 % at B = 4, 2 % at B = 8, none from B = 16.
   ceca::RunShape shape{};
   if (same_layout && n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
       !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, loss->N, loss->lda, vec, st, &shape) &&
-      ceca::run_kernel_words(shape, n, d, loss->B) * 8 <= need) {
+      ceca::run_kernel_words(shape, n, d, loss->B) * 8 <= need && window_roll_fits(ceca::run_kernel_words(shape, n, d, loss->B) * 8)) {
     ceca::RunArgs a{};
     a.xin = S_in;  a.yin = S_in + (int64_t)n * ld;
     a.xout = S_out;  a.yout = S_out + (int64_t)n * ld;

@@ -127,8 +127,10 @@ struct RunArgs {
   const float* t;
   const int32_t* batch_idx;   // [iters][n][B]
   unsigned long long* words;  // {tag, value} words: two message slots [n][d], then two slots of partial margins [n][nchunks][B]
+  unsigned long long* roll;   // the word after them: who is there (set by the launcher)
   int64_t d;
   int32_t n, N, B, kind, nchunks, port, iters, tau, r0;
+  int32_t roll_call;          // workgroups that have to be there (set by the launcher)
   float lr, scale, noise_std;
   uint32_t seed, k;
   MultiRound round[kRunMaxTau];
@@ -239,6 +241,7 @@ struct Tuning {
   int32_t graph_tables_in_memory;  // 1: graph gossip reads its tables from memory at every look-up
   int32_t no_half_step;         // 1: dsgd_ceca_run keeps full states and message buffers between fused iterations (and small
                                 // problems take neither the window kernel nor the single-launch step)
+  int32_t window_missing;       // that many workgroups of a one-kernel window are never launched
   int32_t lean_tiles;           // gossip-rounds kernel with 256 threads: 4, 5, 6 = the register-lean form for that many wavefronts per SIMD
   int32_t probe_variant;        // 3-read / 2-write probe: policy * 100 + threads code * 10 + column groups per thread
   int32_t probe_waves;          // probe kernels: that many long-lived wavefronts instead of one thread per column group
@@ -256,7 +259,7 @@ bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec4);
 // (pitch ldo, another buffer unless p_first); false when the shape is not covered
 bool launch_grad_half(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
 // a whole window of iterations as one kernel whose workgroups wait for each other: the shape for this problem, false
-// where it does not apply; the 8-byte words it needs as scratch; the launch
+// where it does not apply; the 8-byte words it needs as scratch (one more behind them for the roll); the launch
 bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out);
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B);
 hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_t st);

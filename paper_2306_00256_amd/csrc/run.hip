@@ -22,8 +22,14 @@ namespace ceca {
 // partial margins need no such look, because a workgroup takes the next iteration's margins from every chunk of its
 // agent, and each of those published them after it had consumed the old ones.
 // Every wait is for something published one iteration earlier, or for this iteration's words of workgroups that wait
-// only on earlier ones: with every workgroup resident (the host's rule) every wait ends.  Should one not (workgroups
-// kept off the device for kGiveUpTicks), it gives up: NaN takes the place of the missing values, and the call ends.
+// only on earlier ones: once every workgroup is on the device every wait ends.  The host's rule makes that likely but
+// cannot promise it (other processes, replays of a captured call on a narrower stream), so the workgroups keep a roll
+// in one word of memory: each adds itself when it starts, and one that has waited for kRollCallPolls polls while the
+// roll is not full marks the window as given up -- one compare-and-swap, so the window is either complete or given up for
+// good, the same for everybody.  Results are stored only by a window that is complete.  From one that was given up the
+// workgroups leave as they come to the end, and the last one to leave does the whole window alone (run_alone), from
+// the untouched state and with the same bits.  Off the hot path: the roll costs one atomic per workgroup and a look at
+// the end.
 //
 // What bounds it: the latency of the chain rows -> margins -> barrier -> coefficients -> message -> peer, once per
 // iteration (an exchange between workgroups takes about 1.3 us), and a compute unit's intake of sampled rows, 75 GB/s.
@@ -39,27 +45,40 @@ namespace ceca {
 // ---------------------------------------------------------------------------------------------
 typedef unsigned long long Word;
 
-constexpr long long kGiveUpTicks = 30LL * 100 * 1000 * 1000;     // 30 s of the 100 MHz clock
+// Waits are counted in polls, a quarter of a microsecond each: they stand still while the process is off the device.
+// 12 ms: what a window done alone takes (n = 5, d = 1000, B = 8, 200 iterations: 2 ms; n = 258, d = 10, B = 50, 20
+// iterations: 40 ms; n = 6, d = 10000, B = 32, 100 iterations: 80 ms).
+constexpr uint32_t kRollCallPolls = 64 * 1024;
+// With the roll full no wait lasts; this bound is for a workspace that something else writes to during the call: NaN
+// takes the place of what never came, and the call ends.
+constexpr uint32_t kGiveUpPolls = 128 * 1024 * 1024;             // half a minute
+constexpr uint32_t kLost = 1u << 31;
+// the roll: workgroups that came (low half), workgroups that left a window given up (bits 32 to 62), the mark
+constexpr Word kLeft = 1ULL << 32, kGivenUp = 1ULL << 63;
 
 __device__ __forceinline__ Word peek(const Word* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void publish(Word* p, uint32_t tag, float v) {
   __hip_atomic_store(p, ((Word)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// A bounded wait: false once it has been given up, then for good.
+// A bounded wait: false once the window has been given up, then for good.
 struct Patience {
-  bool lost = false;
-  uint32_t polls = 0;
-  long long since = 0;
-  __device__ __forceinline__ void begin() { polls = 0; }
+  Word* roll;
+  uint32_t all;                            // workgroups on a full roll
+  uint32_t polls = 0;                      // of this wait; from kLost on: given up
+  __device__ __forceinline__ Patience(const RunArgs& P) : roll(P.roll), all((uint32_t)P.roll_call) {}
+  __device__ __forceinline__ void begin() { polls &= kLost; }
   __device__ __forceinline__ bool again() {
-    if (lost) return false;
-    if ((++polls & 1023u) == 0) {
-      const long long now = wall_clock64();
-      if (polls == 1024u) since = now;
-      else if (now - since > kGiveUpTicks) { lost = true; return false; }
-    }
-    return true;
+    if ((++polls & 1023u) == 0 && hopeless()) polls = kLost;
+    return polls < kLost;
   }
+  __device__ __forceinline__ bool hopeless() {
+    Word w = peek(roll);
+    if (w & kGivenUp) return true;
+    if ((uint32_t)w == all) return polls >= kGiveUpPolls;
+    // fails if the roll has changed meanwhile: then the next look decides
+    return polls >= kRollCallPolls && __hip_atomic_compare_exchange_strong(roll, &w, w | kGivenUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ bool settled(Word w) const { return (w & kGivenUp) || (uint32_t)w == all; }
 };
 
 template <int VEC> struct Parts;
@@ -76,6 +95,100 @@ template <> struct Parts<4> {
 // columns and about 70 more registers per thread, nothing spilled
 template <int VEC, int THREADS, int BMAX>
 constexpr int run_waves() { return THREADS == 1024 || VEC == 1 || BMAX <= 8 ? 4 : BMAX <= 16 ? 3 : BMAX <= 32 ? 2 : 1; }
+
+// Whose message an agent reads (Eqs. (6), (7)).
+__device__ __forceinline__ int peer_of(const RunArgs& P, const MultiRound& R, int agent) {
+  int p = P.port == 2 || (agent & 1) ? agent - R.shift : agent + R.shift;
+  if (p < 0) p += P.n;
+  if (p >= P.n) p -= P.n;
+  return p;
+}
+
+// The whole window by one workgroup: iteration by iteration every agent's message, then every agent's combine, with the
+// state in the output rows and the messages in the workspace.  Operation for operation what the workgroups of run_kernel
+// do together; `red` and `part` are theirs.
+template <int VEC, int THREADS, int BMAX, bool CHUNKS>
+__device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THREADS / 64][BMAX], float* part) {
+  using V = typename VecOf<VEC>::T;
+  constexpr int WAVES = THREADS / 64;
+  constexpr int CH = kRowGroup;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));                                  // nothing derived from it waits in run_kernel's registers
+  const int lane = tid & 63, wave = tid >> 6;
+  float* msgs = reinterpret_cast<float*>(P.words);               // n rows of d
+  int r = P.r0;
+  for (int t = 0; t < P.iters; ++t) {
+    const MultiRound& R = P.round[r];
+    const float* xin = t == 0 ? P.xin : P.xout;
+    const float* yin = t == 0 ? P.yin : P.yout;
+    const float* zin = R.exch_y ? yin : xin;
+    for (int agent = 0; agent < P.n; ++agent) {
+      const int32_t myidx = min(max(P.batch_idx[((int64_t)t * P.n + agent) * P.B + min(lane, P.B - 1)], 0), P.N - 1);
+      const float tmine = P.t[(int64_t)agent * P.N + myidx];
+      const float* Abase = P.A + (int64_t)agent * P.N * P.lda;
+      float mj = 0.0f;
+      for (int chunk = 0; chunk < P.nchunks; ++chunk) {
+        const int64_t first = (int64_t)chunk * THREADS * VEC, c = first + tid * VEC;
+        const bool on = c < P.d;
+        const V z = on ? ld_plain<V>(zin + (int64_t)agent * P.ld + c) : V(0.0f);
+        for (int c0 = 0; c0 < P.B; c0 += CH) {
+          float m[CH];
+#pragma unroll
+          for (int j = 0; j < CH; ++j)
+            m[j] = dot_v(ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c : first)), z);
+          int jrow;
+          bool owner;
+          const float msum = wave_sum_many<CH>(m, lane, jrow, owner);
+          if (owner) red[0][wave][c0 + jrow] = msum;
+        }
+        __syncthreads();
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) s += red[0][w][min(lane, P.B - 1)];
+        if (!CHUNKS) mj = s;
+        else if (tid < P.B) part[chunk * P.B + tid] = s;
+        __syncthreads();
+      }
+      if (CHUNKS)
+        for (int ch = 0; ch < P.nchunks; ++ch) mj += part[ch * P.B + min(lane, P.B - 1)];
+      const float cmine = lane < P.B ? loss_coef(P.kind, mj, tmine, P.scale) : 0.0f;
+      for (int chunk = 0; chunk < P.nchunks; ++chunk) {
+        const int64_t first = (int64_t)chunk * THREADS * VEC, c = first + tid * VEC;
+        const bool on = c < P.d;
+        const V z = on ? ld_plain<V>(zin + (int64_t)agent * P.ld + c) : V(0.0f);
+        V e = V(0.0f);
+        for (int c0 = 0; c0 < P.B; c0 += CH) {
+#pragma unroll
+          for (int j = 0; j < CH; ++j) {
+            const V a = ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c : first));
+            const float cj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cmine), c0 + j));
+            e += cj * a;
+          }
+        }
+        if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, on ? c : 0, noise_keys(P.seed, P.k + (uint32_t)t, (uint32_t)agent));
+        const V v = z - P.lr * e;
+        if (on) *reinterpret_cast<V*>(msgs + (int64_t)agent * P.d + c) = v;
+      }
+    }
+    __syncthreads();
+    for (int agent = 0; agent < P.n; ++agent) {
+      const int p = peer_of(P, R, agent);
+      for (int64_t c = (int64_t)tid * VEC; c < P.d; c += (int64_t)THREADS * VEC) {
+#pragma clang fp contract(off)
+        const int64_t off = (int64_t)agent * P.ld + c;
+        const V x = ld_plain<V>(xin + off), y = ld_plain<V>(yin + off), z = R.exch_y ? y : x;
+        const V v = ld_plain<V>(msgs + (int64_t)agent * P.d + c), msg = ld_plain<V>(msgs + (int64_t)p * P.d + c);
+        const V dz = v - z;
+        const V xs = R.exch_y ? x + dz : v;
+        const V ys = R.exch_y ? v : y + dz;
+        *reinterpret_cast<V*>(P.xout + off) = combine(R.a, xs, R.ap, msg);
+        *reinterpret_cast<V*>(P.yout + off) = R.read_y ? combine(R.b, ys, R.bp, msg) : R.bp * msg;
+      }
+    }
+    __syncthreads();
+    r = r + 1 == P.tau ? 0 : r + 1;
+  }
+}
 
 template <int VEC, int THREADS, int BMAX, bool CHUNKS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_waves<VEC, THREADS, BMAX>(), 8)))
@@ -126,7 +239,10 @@ void run_kernel(const RunArgs P) {
   };
   request_rows();
   int32_t idx_next = idx[P.iters > 1 ? nb : 0];
-  Patience wait;
+  // on the roll; behind the first rows' requests, so that they do not wait for it
+  if (tid == 0) (void)__hip_atomic_fetch_add(P.roll, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  Patience wait(P);
+  Word roll = 0;
   int r = P.r0;
   int reader = agent;                      // who read my message two iterations ago (after the shifts below)
   int reader1 = agent;                     // and one iteration ago
@@ -172,8 +288,8 @@ void run_kernel(const RunArgs P) {
           w1 = peek(ring + i1);
           here = (uint32_t)(w0 >> 32) == tag && (uint32_t)(w1 >> 32) == tag;
         } while (!here && wait.again());
-        part[i0] = (uint32_t)(w0 >> 32) == tag ? __uint_as_float((uint32_t)w0) : __builtin_nanf("");
-        part[i1] = (uint32_t)(w1 >> 32) == tag ? __uint_as_float((uint32_t)w1) : __builtin_nanf("");
+        part[i0] = here ? __uint_as_float((uint32_t)w0) : __builtin_nanf("");
+        part[i1] = here ? __uint_as_float((uint32_t)w1) : __builtin_nanf("");
       }
       __syncthreads();
       const int j = min(lane, P.B - 1);
@@ -199,16 +315,9 @@ void run_kernel(const RunArgs P) {
     if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, col, noise_keys(P.seed, P.k + (uint32_t)t, (uint32_t)agent));
     const V v = z - P.lr * e;
 
-    int p, to;                             // whose message I read, and who reads mine (Eqs. (6), (7))
-    if (P.port == 2) {
-      p = agent - R.shift; if (p < 0) p += P.n;
-      to = agent + R.shift; if (to >= P.n) to -= P.n;
-    } else {
-      p = (agent & 1) ? agent - R.shift : agent + R.shift;
-      if (p < 0) p += P.n;
-      if (p >= P.n) p -= P.n;
-      to = p;
-    }
+    const int p = peer_of(P, R, agent);    // whose message I read, and who reads mine
+    int to = p;
+    if (P.port == 2) { to = agent + R.shift; if (to >= P.n) to -= P.n; }
     if (t >= 2 && on) {
       wait.begin();
       while ((uint32_t)(ack >> 32) < (uint32_t)t && wait.again()) ack = peek(seen);
@@ -224,6 +333,8 @@ void run_kernel(const RunArgs P) {
       myidx = min(max(idx_next, 0), P.N - 1);
       if (__any(now != myidx)) request_rows();                   // the same in every wavefront
       idx_next = idx[(int64_t)min(t + 2, P.iters - 1) * nb];
+    } else {
+      roll = peek(P.roll);                 // full long ago, as a rule
     }
     V msg = V(0.0f);
     if (on) {
@@ -240,7 +351,7 @@ void run_kernel(const RunArgs P) {
       } while (!here && wait.again());
 #pragma unroll
       for (int u = 0; u < VEC; ++u)
-        Parts<VEC>::set(msg, u, (uint32_t)(w[u] >> 32) == tag ? __uint_as_float((uint32_t)w[u]) : __builtin_nanf(""));
+        Parts<VEC>::set(msg, u, here ? __uint_as_float((uint32_t)w[u]) : __builtin_nanf(""));
     }
     {
 #pragma clang fp contract(off)
@@ -254,10 +365,27 @@ void run_kernel(const RunArgs P) {
     reader1 = to;
     r = r + 1 == P.tau ? 0 : r + 1;
   }
-  if (on) {
-    *reinterpret_cast<V*>(P.xout + (int64_t)agent * P.ld + col) = x;
-    *reinterpret_cast<V*>(P.yout + (int64_t)agent * P.ld + col) = y;
+  wait.begin();
+  while (!wait.settled(roll)) {
+    (void)wait.again();
+    roll = peek(P.roll);
   }
+  if (!(roll & kGivenUp)) {
+    if (on) {
+      *reinterpret_cast<V*>(P.xout + (int64_t)agent * P.ld + col) = x;
+      *reinterpret_cast<V*>(P.yout + (int64_t)agent * P.ld + col) = y;
+    }
+    return;
+  }
+  // given up (the same for every thread): nothing has been stored; my own words are behind me before I leave
+  __shared__ bool last_s;
+  __threadfence();
+  __syncthreads();
+  if (tid == 0) last_s = (uint32_t)((__hip_atomic_fetch_add(P.roll, kLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kGivenUp) >> 32) + 1 == gridDim.x;
+  __syncthreads();
+  if (!last_s) return;
+  __threadfence();
+  run_alone<VEC, THREADS, BMAX, CHUNKS>(P, red, part);
 }
 
 // No word may carry a tag of this call before it is published.
@@ -295,10 +423,10 @@ int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B) {
   return 2 * (int64_t)n * d + (s.nchunks > 1 ? 2 * (int64_t)n * s.nchunks * B : 0);
 }
 
-// Every workgroup of the kernel has to be resident, whatever else runs: it may take an eighth of the places that the
-// stream's compute units have for it, so that eight such kernels fit beside each other (a process has four
-// hardware queues); kernels of any other kind end by themselves and make room.  A stream restricted to some compute
-// units counts those only.
+// Every workgroup of the kernel should be resident, whatever else runs (else the window is given up, see above): it may
+// take an eighth of the places that the stream's compute units have for it, so that eight such kernels of a like shape
+// fit beside each other; kernels of any other kind end by themselves and make room.  A stream restricted to some
+// compute units counts those only.
 bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out) {
   const RunShape s = run_shape(n, d, B, vec4);
   if (s.threads == 0 || lda >= (1LL << 30) / N) return false;    // an agent's rows within 32-bit distances: 4 GB
@@ -323,15 +451,19 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, b
 
 template <int VEC, int THREADS, int BMAX>
 static hipError_t launch(const RunArgs& a, hipStream_t st) {
-  const dim3 grid((unsigned)(a.n * a.nchunks)), block(THREADS);
+  const int32_t kept = a.roll_call - g_tuning.window_missing;
+  const dim3 grid((unsigned)(kept < 1 ? 1 : kept)), block(THREADS);
   if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false><<<grid, block, 0, st>>>(a);
   else if constexpr (THREADS == 256) run_kernel<VEC, THREADS, BMAX, true><<<grid, block, 0, st>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_t st) {
-  const int64_t words = run_kernel_words(s, a.n, a.d, a.B);
+hipError_t launch_run(const RunArgs& a0, const RunShape& s, bool vec4, hipStream_t st) {
+  RunArgs a = a0;
+  a.roll_call = a.n * a.nchunks;
+  a.roll = a.words + run_kernel_words(s, a.n, a.d, a.B);
+  const int64_t words = run_kernel_words(s, a.n, a.d, a.B) + 1;
   const int64_t blocks = (words + kBlock - 1) / kBlock;
   if (s.threads == 0 || a.B > s.bmax || a.nchunks != s.nchunks || a.tau < 1 || a.tau > kRunMaxTau || blocks > 0x7fffffffLL)
     return hipErrorInvalidValue;

@@ -213,3 +213,55 @@ def test_single_launch_step_equals_the_two_kernel_form(env, kind, n, port, d, B)
         assert P.ceca_last_form() in (Bn.FORM_STEP_ONE_PASS, Bn.FORM_STEP_TWO_PASS)
         assert bool(torch.isfinite(two).all())
         assert torch.equal(one, two) and torch.equal(inplace, two), r
+
+
+@pytest.mark.parametrize("missing,iters", [(1, 2), (1, 40), (3, 9), (1 << 20, 9)])
+@pytest.mark.parametrize("n,port,d,B,noise", [(5, 2, 1000, 8, 0.0), (6, 1, 250, 64, 0.01), (40, 1, 24, 50, 0.01), (6, 2, 10000, 32, 0.0), (2, 2, 9000, 64, 0.01),
+                                              (12, 2, 4096, 16, 0.0), (9, 2, 255, 20, 0.01), (12, 1, 63, 9, 0.0), (3, 2, 1000, 40, 0.0), (4, 1, 1999, 4, 0.01)])
+def test_window_whose_workgroups_are_not_all_there(env, n, port, d, B, noise, missing, iters):
+    """Workgroups that never reach the device: the others give the window up (none of them stores anything) and one does
+    it alone -- the bits of the whole window, in place and out of place; the next call runs normally."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    N, lr, tau = max(B // 2, 3), 0.02 / (d * B) ** 0.5, OS.num_rounds(n)
+    gen = torch.Generator(device="cuda").manual_seed(n * d + B)
+    A = torch.randn((n, N, d), generator=gen, device="cuda")
+    t = torch.randn((n, N), generator=gen, device="cuda").sign()
+    idx = torch.randint(-1, N + 1, (iters, n, B), dtype=torch.int32, device="cuda", generator=gen)
+    S = torch.randn((2 * n, d), generator=gen, device="cuda")
+    loss = Bn.make_minibatch_loss(Bn.LOSS_LOGISTIC if port == 2 else Bn.LOSS_LSQ, A, t, N, B, noise_std=noise, seed=5, k=3)
+    ws = _aligned(torch, P.dsgd_ceca_run_workspace_bytes(n, d, loss))
+    ref, got, inplace = torch.empty_like(S), torch.full_like(S, float("nan")), S.clone()
+    P.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 0)
+    P.dsgd_ceca_run(S, ref, n, d, loss, idx, lr, 1 % tau, iters, port, workspace=ws)
+    P.ceca_reset_options()
+    P.ceca_set_option(Bn.OPT_WINDOW_MISSING, missing)
+    for out in (got, inplace):
+        P.dsgd_ceca_run(inplace if out is inplace else S, out, n, d, loss, idx, lr, 1 % tau, iters, port, workspace=ws)
+        assert P.ceca_last_form() == Bn.FORM_RUN_WINDOW
+        torch.cuda.synchronize()
+    P.ceca_reset_options()
+    assert bool(torch.isfinite(ref).all()) and torch.equal(got, ref) and torch.equal(inplace, ref)
+    P.dsgd_ceca_run(S, got.fill_(float("nan")), n, d, loss, idx, lr, 1 % tau, iters, port, workspace=ws)
+    assert torch.equal(got, ref)
+
+
+def test_workspace_without_room_for_the_roll(env):
+    """The size that dsgd_ceca_run took before the window kept a roll is still taken; where the window's words fill it, with
+    another form and the same bits."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    for n, d, B, fits in [(2, 18240, 4, False), (6, 10000, 32, True)]:
+        N, iters = 5, 4
+        A, t, idx, Ad, td, idxd, code = _problem(torch, Bn, "logistic", n, N, d, B, iters, seed=n)
+        loss = Bn.make_minibatch_loss(code, Ad, td, N, B)
+        ws = _aligned(torch, P.dsgd_ceca_run_workspace_bytes(n, d, loss))
+        S = make_state(torch, 0.05 * WL.initial_state(n, d, seed=3))
+        outs = []
+        for w, form in ((ws, True), (ws[:-256], fits)):
+            outs.append(torch.full_like(S, float("nan")))
+            P.dsgd_ceca_run(S, outs[-1], n, d, loss, idxd, 0.003, 0, iters, 2, workspace=w)
+            assert (P.ceca_last_form() == Bn.FORM_RUN_WINDOW) == form
+        assert torch.equal(*outs)
+        with pytest.raises(P.CecaError):
+            P.dsgd_ceca_run(S, outs[0], n, d, loss, idxd, 0.003, 0, iters, 2, workspace=ws[:-257])
