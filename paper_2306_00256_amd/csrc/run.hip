@@ -436,6 +436,9 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, b
     return false;
   }
   if ((int64_t)n * s.nchunks * 8 > (int64_t)cus * s.wg_per_cu) return false;
+  // (the handles of the legacy and the per-thread default stream are not pointers to a stream object, and nothing says
+  // that the query takes them; like the null stream they carry no mask of their own)
+  if (st == hipStreamLegacy || st == hipStreamPerThread) st = nullptr;
   uint32_t mask[32] = {};
   if (hipExtStreamGetCUMask(st, 32, mask) != hipSuccess) {
     (void)hipGetLastError();

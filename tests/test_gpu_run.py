@@ -265,3 +265,36 @@ def test_workspace_without_room_for_the_roll(env):
         assert torch.equal(*outs)
         with pytest.raises(P.CecaError):
             P.dsgd_ceca_run(S, outs[0], n, d, loss, idxd, 0.003, 0, iters, 2, workspace=ws[:-257])
+
+
+def test_window_on_streams_of_every_kind(env):
+    """The one-kernel window on the null stream, the per-thread default stream and streams restricted to 32 compute
+    units, where a window of 16 workgroups of 256 threads (an eighth of 32 x 4) still runs as one kernel and 17 do not."""
+    import ctypes
+    from types import SimpleNamespace
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    masked = ctypes.c_void_p()
+    bits = (ctypes.c_uint32 * 8)(0xFFFFFFFF)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(masked), ctypes.c_uint32(8), bits) == 0
+    try:
+        for n in (16, 17):
+            d, B, N, iters, lr = 1000, 8, 20, 9, 0.001
+            A, t, idx, Ad, td, idxd, code = _problem(torch, Bn, "lsq", n, N, d, B, iters, seed=n)
+            loss = Bn.make_minibatch_loss(code, Ad, td, N, B, noise_std=0.1, seed=2)
+            ws = _aligned(torch, P.dsgd_ceca_run_workspace_bytes(n, d, loss))
+            S = make_state(torch, 0.05 * WL.initial_state(n, d, seed=3))
+            ref = torch.full_like(S, float("nan"))
+            P.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 0)
+            P.dsgd_ceca_run(S, ref, n, d, loss, idxd, lr, 0, iters, 2, workspace=ws)
+            P.ceca_reset_options()
+            for handle, window in ((0, True), (2, True), (masked.value, n == 16)):          # 2: hipStreamPerThread
+                out = torch.full_like(S, float("nan"))
+                torch.cuda.synchronize()
+                P.dsgd_ceca_run(S, out, n, d, loss, idxd, lr, 0, iters, 2, workspace=ws, stream=SimpleNamespace(cuda_stream=handle))
+                torch.cuda.synchronize()
+                assert (P.ceca_last_form() == Bn.FORM_RUN_WINDOW) == window, (n, handle)
+                assert torch.equal(out, ref), (n, handle)
+    finally:
+        assert hip.hipStreamDestroy(masked) == 0
