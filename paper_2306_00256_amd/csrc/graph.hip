@@ -41,6 +41,7 @@ void graph_rounds_kernel(const GraphArgs M) {
   const int cg = tid % lanes;
   const int rg = tid / lanes;
   const int64_t tile = tile_of_block(M.xcd_runs);
+  if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
@@ -152,6 +153,7 @@ void graph_fixed_kernel(const GraphArgs M) {
   const int cg = tid % lanes;
   const int rg = tid / lanes;
   const int64_t tile = tile_of_block(M.xcd_runs);
+  if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * 4;   // lanes past the last column shadow column group 0

@@ -286,7 +286,7 @@ hipError_t launch_phi(double* out, hipStream_t st);
 
 // Whether a register-tile kernel numbers its tiles in runs per XCD (device_util.h, tile_of_block): rows of the tile
 // narrower than a 128-byte line and enough tiles to matter (small launches measured better in plain order).
-// Rounds *blocks up to whole runs on every XCD (workgroups past the last tile find no columns and leave).
+// Rounds *blocks up to whole runs on every XCD (workgroups past the last tile leave before they load anything).
 inline int32_t xcd_runs(int row_bytes, int64_t* blocks) {
   if (row_bytes >= 128 || *blocks < 1024 || g_tuning.plain_tile_order) return 0;
   const int64_t whole = 8 * (int64_t)kXcdRun;

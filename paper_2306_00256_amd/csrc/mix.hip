@@ -35,6 +35,7 @@ void mix_rounds_kernel(const MixArgs M) {
   const int cg = tid % lanes;
   const int rg = tid / lanes;
   const int64_t tile = tile_of_block(M.xcd_runs);
+  if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0

@@ -53,6 +53,7 @@ void multi_round_kernel(const MultiArgs M) {
   const int cg = tid % lanes;                      // my column group inside the tile
   const int rg = tid / lanes;                      // my first row; I own rows rg, rg + row_lanes, ...
   const int64_t tile = tile_of_block(M.xcd_runs);
+  if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
@@ -166,6 +167,7 @@ void multi_step_kernel(const StepsArgs S) {
   const int cg = tid % lanes;
   const int rg = tid / lanes;
   const int64_t tile = tile_of_block(M.xcd_runs);
+  if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
   const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0

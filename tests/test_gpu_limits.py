@@ -167,6 +167,33 @@ def test_xcd_tile_order_does_not_change_results(env):
     assert max(rel_err(gx, x)) <= 1e-5 and max(rel_err(gy, y)) <= 1e-5
 
 
+@pytest.mark.parametrize("d", [16 * 1024, 16 * 1025, 16 * 1152 - 4])
+def test_tiles_past_the_last_column(env, d):
+    """Launches whose grid is rounded up to whole runs of tiles (none, 127 and no workgroups too many, the last with a
+    ragged tile), in place and out of place: the plain order's bits, also for both graph kernels."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    n, port = 1026, 2
+    S = make_state(torch, WL.initial_state(n, d, seed=3))
+    c = torch.from_numpy(WL.quad_centers(n, d, 4)).cuda()
+    exp = [P.ceca_topology_round(Bn.TOPO_STATIC_EXP, n)]
+    tables = [torch.from_numpy(t[None].copy()).cuda() for t in WL.graph_table(n, WL.edges_of("torus", n, 27))]
+    outs = []
+    for order in (1, 0):
+        P.ceca_set_option(Bn.OPT_XCD_TILE_ORDER, order)
+        out = [torch.full_like(S, float("nan")), S.clone(), torch.full_like(S, float("nan"))]
+        P.ceca_gossip_rounds(S, out[0], n, d, 4, port)
+        P.dsgd_ceca_steps(out[1], out[1], n, d, Bn.make_quad_center_loss(c, 0.01, 1, 0), 0.1, 0, 3, port)
+        P.ceca_mix_rounds(S[:n], out[2][:n], n, d, exp, 2)
+        P.ceca_graph_rounds(S[n:], out[2][n:], n, d, *tables, 2)
+        P.ceca_set_option(Bn.OPT_GRAPH_STAGE, 0)
+        P.ceca_graph_rounds(out[2][:n], out[2][:n], n, d, *tables, 2)
+        P.ceca_set_option(Bn.OPT_GRAPH_STAGE, 1)
+        outs.append(out)
+    assert all(bool(torch.isfinite(o).all()) for o in outs[0])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
 def test_more_rounds_than_one_kernel_takes(env):
     """ceca_gossip_rounds beyond 64 rounds (several kernels of whole cycles, in place after the first) and
     ceca_mix_rounds with hundreds of rounds in one kernel: same bits as the calls split into shorter runs,
