@@ -358,14 +358,16 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
     for (int q = 0; q < 4; ++q) m[q] = div_by(m[q], n, rn);
     const int64_t g = tile * cgs + cg;
     const bool on = g < ngroups;
-    // the last tile's loop re-requests itself: no branch surrounds a load
-    const float* p = first_row(tile + gridDim.x < C.strips ? tile + gridDim.x : tile);
+    // no branch surrounds a load: after the last strip every request goes to the thread's own first entry, which is cached
+    const bool more = tile + gridDim.x < C.strips;
+    const float* p = first_row(more ? tile + gridDim.x : tile);
+    const int64_t to_next = more ? step : 0, to_last = more ? last_step : 0;
 #pragma unroll
     for (int k = 0; k < RT; ++k) {
       asm volatile("" : "+v"(x[k]));                // converted to fp64 anew: kept from the sums, the doubles would take twice the registers of x
       const double dev = sqdev(x[k], m);
       x[k] = ld_stream<vf4>(p);
-      p += k == RT - 2 ? last_step : step;
+      p += k == RT - 2 ? to_last : to_next;
       acc[k] += on ? dev : 0.0;
     }
     if (rg == 0 && on) {
