@@ -444,7 +444,7 @@ __global__ __launch_bounds__(kBlock) void devsum_kernel(const ConsensusArgs C) {
 
 __global__ __launch_bounds__(kBlock) void finish_kernel(const ConsensusArgs C) { finish_results(C, C.dev2); }
 
-// Few partials in all (small problems, where every launch counts): one workgroup sums the rows of devpart in
+// Few rows and partials (small problems, where every launch counts): one workgroup sums the rows of devpart in
 // turn (same order of additions as devsum_kernel) and finishes, in one launch.
 __global__ __launch_bounds__(kBlock) void close_small_kernel(const ConsensusArgs C) {
   __shared__ double red[kBlock / 64];
@@ -467,10 +467,12 @@ __global__ __launch_bounds__(kBlock) void close_small_kernel(const ConsensusArgs
 }
 
 // Closes a consensus call: dev2 from the partials of `rows` rows (n, or n + 1 with ||xbar||^2 as the last), then
-// the results.
+// the results.  The rows cost the single workgroup 0.6 us each (0.3 us with a handful of partials), one after the other,
+// against 2 us for the second launch: per call at n = 5 / 9 / 12 / 24 / 130, d = 4096 one launch takes 10.7 / 12.6 / 14.7 /
+// 22.6 / 82 us, two take 12.9 us at every n; at d = 64, n = 12 / 14 / 24 one takes 11.3 / 13.0 / 16.4.
 static void launch_close(ConsensusArgs& c, int rows, hipStream_t st) {
   c.close_rows = rows;
-  if ((int64_t)rows * c.ntiles <= 16384) {
+  if (rows <= (c.ntiles <= 8 ? 14 : 11) && (int64_t)rows * c.ntiles <= 16384) {
     close_small_kernel<<<dim3(1), dim3(kBlock), 0, st>>>(c);
   } else {
     devsum_kernel<<<dim3((unsigned)rows), dim3(kBlock), 0, st>>>(c);

@@ -28,7 +28,7 @@ def _consensus(torch, P, X, n, d, want_mean=True):
 
 
 @pytest.mark.parametrize("n,d", [(1, 5), (2, 1), (5, 1000), (6, 1027), (31, 4096), (100, 3000), (1023, 4096),
-                                 (3, 70001)])
+                                 (3, 70001), (10, 2052), (11, 2052), (13, 32), (14, 32), (14, 31), (130, 4096)])
 def test_matches_oracle(env, n, d):
     torch, P = env
     x = WL.initial_state(n, d, seed=n + d) * 3.0 + 1.5
