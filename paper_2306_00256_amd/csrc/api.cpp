@@ -414,7 +414,11 @@ TileShape shape_tile(int32_t n, bool vec4, int32_t threads, int32_t cap) {
 template <typename Threads, typename Cap>
 TileShape pick_tile(int32_t n, bool vec4, int32_t cap_lo, int32_t cap_hi_256, int32_t cap_hi_wide, Threads threads_for, Cap cap_for) {
   const int32_t dflt_threads = vec4 ? threads_for(n) : ceca::kBlock;
-  const TileShape dflt = shape_tile(n, vec4, dflt_threads, cap_for(dflt_threads));
+  // a default tile that outgrows the LDS gets narrower rows (mixing rounds on 2561 to 3328 agents: 13 rows per thread
+  // leave 64-byte rows, 208 KB)
+  int32_t dflt_cap = cap_for(dflt_threads);
+  TileShape dflt = shape_tile(n, vec4, dflt_threads, dflt_cap);
+  while (!dflt.ok && dflt_cap > 1) dflt = shape_tile(n, vec4, dflt_threads, dflt_cap = (dflt_cap + 1) / 2);
   int32_t threads = vec4 ? g_tuning.tile_threads : ceca::kBlock;
   if (threads == 0) threads = dflt_threads;
   int32_t cap = g_tuning.rows;

@@ -74,10 +74,10 @@ def test_fused_iterations_around_the_agent_limit(env, n, port):
         assert max(rel_err(gx, x)) <= 1e-4 and max(rel_err(gy, y)) <= 1e-4
 
 
-def test_mixing_rounds_at_the_agent_limit(env):
+@pytest.mark.parametrize("n,d", [(4096, 29), (2560, 36), (2561, 36), (3000, 20), (3328, 12), (3329, 12)])
+def test_mixing_rounds_at_the_agent_limit(env, n, d):
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
-    n, d = 4096, 29
     x0 = WL.initial_state(n, d, seed=4)
     X = torch.from_numpy(x0).cuda()
     for kind, want in [(Bn.TOPO_STATIC_EXP, [OT.static_exponential(n)]), (Bn.TOPO_RING, [OT.ring(n)])]:
