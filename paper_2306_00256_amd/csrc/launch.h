@@ -237,7 +237,7 @@ struct Tuning {
   int32_t never_chunked;        // 1: single steps never take the chunked gradient kernel
   int32_t cons_form;            // consensus observables: 1 two-pass, 2 workgroup tiles, 3 wavefront strips, 4 workgroup strips
   int32_t cons_strips;          // strips one wavefront of the consensus kernel takes in turn
-  int32_t plain_tile_order;     // 1: register-tile kernels never use the XCD-contiguous tile order
+  int32_t plain_tile_order;     // 1: register-tile kernels number their tiles plainly, not in runs per XCD
   int32_t graph_tables_in_memory;  // 1: graph gossip reads its tables from memory at every look-up
   int32_t no_half_step;         // 1: dsgd_ceca_run keeps full states and message buffers between fused iterations (and small
                                 // problems take neither the window kernel nor the single-launch step)

@@ -24,7 +24,8 @@ constexpr int mix_waves() { return THREADS > 256 ? 4 : 1; }
 // Same tiling as the fused CECA rounds: a workgroup keeps a column tile of every agent's x in
 // registers (RT rows per thread) and publishes it in LDS once per round, where each row picks up its
 // peers.  One read and one write of x for any number of rounds.
-template <int VEC, int RT, int THREADS>
+// SCALAR: weights in scalar instead of vector registers, see launch_mix.
+template <int VEC, int RT, int THREADS, bool SCALAR>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(mix_waves<THREADS>())))
 void mix_rounds_kernel(const MixArgs M) {
 #pragma clang fp contract(off)
@@ -57,7 +58,7 @@ void mix_rounds_kernel(const MixArgs M) {
   int spec = M.k0 % M.period;
   for (int t = 0; t < M.rounds; ++t) {
     const int j0 = M.start[spec], j1 = M.start[spec + 1];
-    const float ws = in_vgpr(M.w_self[spec]);
+    const float ws = SCALAR ? M.w_self[spec] : in_vgpr(M.w_self[spec]);
     if (j1 > j0) {                                  // a round without peers is the identity
 #pragma unroll
       for (int k = 0; k < L; ++k) xs[tid + k * THREADS] = x[k];
@@ -78,7 +79,7 @@ void mix_rounds_kernel(const MixArgs M) {
         const int past = shift - rg;               // rows k with k * row_lanes < past start from the far end
         uint32_t near = slot - shift * (lanes * (uint32_t)sizeof(V)), far = near + wrap;
         asm volatile("" : "+v"(near), "+v"(far));  // two addresses to select from, not one and a distance to add
-        const float w = in_vgpr(M.w[j]);
+        const float w = SCALAR ? M.w[j] : in_vgpr(M.w[j]);
         V z[RT];
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
@@ -106,15 +107,22 @@ void mix_rounds_kernel(const MixArgs M) {
 }
 
 
+// Vector registers for the weights are the rule (static exponential, 2^26 elements, vector against scalar: n = 258
+// 304 us against 355, n = 600 336 against 385, n = 1026 427 against 539).  512-thread tiles with 32-byte rows and 6 or 7 rows
+// per thread, which many peers per round take from 1281 to 1792 agents, are the exception, over five pitches: n = 1300
+// 380 to 660 against 348 to 571, n = 1500 402 to 529 against 359 to 481, n = 1660 464 to 566 against 425 to 521 (1281: 327
+// to 522 against 344 to 548).
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_mix(const MixArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
+  auto fn = &mix_rounds_kernel<VEC, RT, THREADS, false>;
+  if constexpr (VEC == 4 && THREADS == 512 && (RT == 6 || RT == 7))
+    if (THREADS / mm.row_lanes * 16 < 64) fn = &mix_rounds_kernel<VEC, RT, THREADS, true>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mix_rounds_kernel<VEC, RT, THREADS>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  mix_rounds_kernel<VEC, RT, THREADS><<<dim3(blocks), dim3(THREADS), lds, st>>>(mm);
+  fn<<<dim3(blocks), dim3(THREADS), lds, st>>>(mm);
   return hipGetLastError();
 }
 
