@@ -250,8 +250,9 @@ __device__ __forceinline__ vf4 half_step(vf4 z, float lr, vf4 e) {
 // multiply, fused multiply-add, xor, and, shift) issue about 1.7 times as fast when all their operands are vector
 // registers or constants as with one scalar-register operand (57 against 35 T lane-operations/s for a fused
 // multiply-add), so factors that a loop applies to many elements are worth a vector register each.
-__device__ __forceinline__ float in_vgpr(float uniform) {
-  float v;
+template <typename T> __device__ __forceinline__ T in_vgpr(T uniform) {
+  static_assert(sizeof(T) == 4, "one register");
+  T v;
   asm("v_mov_b32 %0, %1" : "=v"(v) : "s"(uniform));
   return v;
 }
