@@ -254,6 +254,7 @@ struct ConsPlan {
   // GROUP form: threads per workgroup (0 = not available), column groups per strip, rows per thread, most workgroups
   int32_t group_threads, group_cgs, group_rows, groups;
   bool group_default;          // the library's own choice for this n
+  bool group_spills;           // ... unless two passes fit the workspace: large and more rows than its registers hold
   int64_t bound;               // workspace that covers every form and launch shape
 };
 
@@ -360,13 +361,18 @@ ConsPlan cons_plan(int32_t n, int64_t d) {
   //   up to 1088         512 threads x 17 rows, one workgroup per unit: n = 513: 115 against 182, n = 1026: 129
   //                      against 222 (128-byte strips)
   //   up to 3072         24 rows (more than 22 spill a little): 128-byte strips up to 1536 agents (n = 1500: 160 against
-  //                      203 with 17 rows and 64 bytes, 229 in two passes), 64-byte ones beyond (n = 2500: 189 against 224)
+  //                      203 with 17 rows and 64 bytes, 229 in two passes), 64-byte ones beyond.  Against two passes, 2^24
+  //                      to 2^27 elements: 0.91 to 1.5 times as fast up to 2688 agents (21 rows), 1.1 times on average;
+  //                      slower beyond (2816: 0.88 to 1.16, 2900: 0.82 to 1.02, 3072: 0.74 to 0.9), where it only takes
+  //                      problems to 2^24 elements (before, workgroup tiles: n = 2944 87 us against 65) and those whose
+  //                      two-pass partial sums do not fit the workspace
   {
     p.group_threads = n <= 416 ? 256 : 512;
     const int32_t cap = n <= 208 ? 13 : (n <= 1088 ? 17 : 24);
     int32_t row_lanes = p.group_threads / 64;          // a strip is at most a wavefront wide
     while ((int64_t)row_lanes * cap < n) row_lanes *= 2;
     p.group_default = n > 112 && n <= 3072;
+    p.group_spills = n > 21 * 128 && (int64_t)n * d > (1LL << 24);
     if (row_lanes > p.group_threads / 2) {
       p.group_threads = 0;
       p.group_default = false;
@@ -1403,7 +1409,8 @@ int32_t run_consensus(const float* X, int32_t n, int64_t d, int64_t ld, double* 
   const bool vec = aligned16(X) && ld % 4 == 0 && d % 4 == 0;
   const int32_t forced = g_tuning.cons_form;
   int form = CONS_TWO_PASS;
-  if (p.group_threads > 0 && vec && (forced == CONS_GROUP || (forced == 0 && p.group_default))) form = CONS_GROUP;
+  const bool by_default = p.group_default && !(p.group_spills && have >= p.two_pass_total);
+  if (p.group_threads > 0 && vec && (forced == CONS_GROUP || (forced == 0 && by_default))) form = CONS_GROUP;
   else if (forced == CONS_WAVE ? p.wave_cgs > 0 : (forced == 0 && p.wave_cgs > 0 && p.wave_default)) form = CONS_WAVE;
   else if (forced != CONS_TWO_PASS && p.rows_per_thread > 0) form = CONS_TILE;
   if (form == CONS_GROUP) {

@@ -264,6 +264,25 @@ def test_entries_that_are_not_finite(env, n, d, entries):
         assert np.isnan(got[0]) and np.isnan(got[1]) and got[4] == n, form       # the entry's own row is at inf - inf
 
 
+@pytest.mark.parametrize("n,d", [(2688, 6400), (2689, 6236), (2689, 6400), (2800, 80_000), (3072, 5464)])
+def test_many_agents_around_the_line_to_two_passes(env, n, d):
+    """Where the workgroup form ends for large problems: the library's choice with a workspace and without one (whose 16 MiB
+    hold only the workgroup form's partial sums at n = 2800, d = 80,000) against both forms forced, rtol 1e-12."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    X = torch.randn((n, d), generator=torch.Generator(device="cuda").manual_seed(n), device="cuda") + 0.5
+    outs = []
+    for form in (1, 0, 4):
+        P.ceca_set_option(Bn.OPT_CONS_SINGLE_PASS, form)
+        outs.append(_consensus(torch, P, X, n, d)[0])
+    P.ceca_reset_options()
+    out = torch.zeros(5, dtype=torch.float64, device="cuda")
+    P.consensus_error_noalloc(X, n, d, out)
+    outs.append(out.cpu().numpy())
+    for o in outs[1:]:
+        assert np.allclose(o, outs[0], rtol=1e-12, atol=0.0)
+
+
 def test_stream_probe_values(env):
     """The measurement aid computes what its header says (elementwise, in and out of place)."""
     torch, P = env
