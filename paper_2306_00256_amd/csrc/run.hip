@@ -412,6 +412,8 @@ static RunShape run_shape(int32_t n, int64_t d, int32_t B, bool vec4) {
   }
   const int64_t chunks = (groups + s.threads - 1) / s.threads;
   if (chunks * B > kRunParts && chunks > 1) return RunShape{0, 0, 1, 0};
+  // single columns in chunks: from B = 16 on the words never fit the space of the other forms (see dsgd_ceca_run)
+  if (!vec4 && chunks > 1 && B > 16) return RunShape{0, 0, 1, 0};
   s.nchunks = (int32_t)chunks;
   s.bmax = vec4 ? (B <= 8 ? 8 : B <= 16 ? 16 : B <= 32 ? 32 : 64) : (B <= 16 ? 16 : 64);
   const int waves = s.threads == 1024 || !vec4 || s.bmax <= 8 ? 4 : s.bmax <= 16 ? 3 : s.bmax <= 32 ? 2 : 1;     // run_waves
@@ -457,7 +459,7 @@ static hipError_t launch(const RunArgs& a, hipStream_t st) {
   const int32_t kept = a.roll_call - g_tuning.window_missing;
   const dim3 grid((unsigned)(kept < 1 ? 1 : kept)), block(THREADS);
   if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false><<<grid, block, 0, st>>>(a);
-  else if constexpr (THREADS == 256) run_kernel<VEC, THREADS, BMAX, true><<<grid, block, 0, st>>>(a);
+  else if constexpr (THREADS == 256 && (VEC == 4 || BMAX <= 16)) run_kernel<VEC, THREADS, BMAX, true><<<grid, block, 0, st>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
