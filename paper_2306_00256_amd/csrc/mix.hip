@@ -109,14 +109,14 @@ void mix_rounds_kernel(const MixArgs M) {
 
 // Vector registers for the weights are the rule (static exponential, 2^26 elements, vector against scalar: n = 258
 // 304 us against 355, n = 600 336 against 385, n = 1026 427 against 539).  512-thread tiles with 32-byte rows and 6 or 7 rows
-// per thread, which many peers per round take from 1281 to 1792 agents, are the exception, over five pitches: n = 1300
-// 380 to 660 against 348 to 571, n = 1500 402 to 529 against 359 to 481, n = 1660 464 to 566 against 425 to 521 (1281: 327
-// to 522 against 344 to 548).
+// per thread, which many peers per round take from 1281 agents on, are the exception up to 1664 agents, over five pitches:
+// n = 1300 380 to 660 against 348 to 571, n = 1500 402 to 529 against 359 to 481, n = 1660 464 to 566 against 425 to 521
+// (1281: 327 to 522 against 344 to 548); beyond, vector registers win again (n = 1700 465 to 555 against 496 to 604).
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_mix(const MixArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
   auto fn = &mix_rounds_kernel<VEC, RT, THREADS, false>;
   if constexpr (VEC == 4 && THREADS == 512 && (RT == 6 || RT == 7))
-    if (THREADS / mm.row_lanes * 16 < 64) fn = &mix_rounds_kernel<VEC, RT, THREADS, true>;
+    if (THREADS / mm.row_lanes * 16 < 64 && mm.n <= 13 * 128) fn = &mix_rounds_kernel<VEC, RT, THREADS, true>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
