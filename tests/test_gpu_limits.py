@@ -74,7 +74,8 @@ def test_fused_iterations_around_the_agent_limit(env, n, port):
         assert max(rel_err(gx, x)) <= 1e-4 and max(rel_err(gy, y)) <= 1e-4
 
 
-@pytest.mark.parametrize("n,d", [(4096, 29), (2560, 36), (2561, 36), (3000, 20), (3328, 12), (3329, 12)])
+@pytest.mark.parametrize("n,d", [(4096, 29), (2560, 36), (2561, 36), (3000, 20), (3328, 12), (3329, 12), (1152, 70), (1153, 70), (1280, 68), (1281, 68), (1536, 37),
+                                 (1537, 36), (1664, 36), (1665, 36)])
 def test_mixing_rounds_at_the_agent_limit(env, n, d):
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
