@@ -392,7 +392,7 @@ def run_consensus(torch, P, Bn, steps=20, warmup=3):
         ms, gbs = probe(torch, P, (flat, None, None, flat, None), n * ld, 1, 0)
         e["read_only_probe_GBs"] = gbs
         if 4.0 * n * d < 64e6:
-            e["bound"] = "launch latency (two launches, 17 MB): microseconds, not a bandwidth fraction"
+            e["bound"] = "launch latency (three launches, 17 MB): microseconds, not a bandwidth fraction"
         out.append(e)
         del X, ws
         torch.cuda.empty_cache()

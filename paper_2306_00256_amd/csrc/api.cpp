@@ -356,9 +356,9 @@ ConsPlan cons_plan(int32_t n, int64_t d) {
   // two workgroups per compute unit; more of them lose.
   //   up to 112 agents   the WAVE form's strips are 256 bytes wide (n = 100: 73 us against 82)
   //   up to 416          256 threads x 13 rows (17 beyond 208 agents), two workgroups per unit: 128 to 256-byte strips
-  //                      (n = 130: 94 us against 87 to 127 depending on the pitch, n = 192: 71 against 100, n = 258:
+  //                      (n = 130: 90 to 95 us against 92 to 125 depending on the pitch, n = 192: 71 against 100, n = 258:
   //                      107 against 158, n = 320: 92 against 147)
-  //   up to 1088         512 threads x 17 rows, one workgroup per unit: n = 513: 115 against 182, n = 1026: 129
+  //   up to 1088         512 threads x 17 rows, one workgroup per unit: n = 513: 115 against 182, n = 1026: 126
   //                      against 222 (128-byte strips)
   //   up to 3072         24 rows (more than 22 spill a little): 128-byte strips up to 1536 agents (n = 1500: 160 against
   //                      203 with 17 rows and 64 bytes, 229 in two passes), 64-byte ones beyond.  Against two passes, 2^24

@@ -293,8 +293,9 @@ __device__ __forceinline__ double div_by(double s, double n, double r) {
 // arithmetic without a second copy of the strip.  The distances are added up over all strips in registers and cross
 // the column groups once, at the end.
 // A workgroup spreads the agents over all its wavefronts, so its strips stay 128 to 256 bytes wide for eight times as
-// many agents as a wavefront's; x is read once.  n = 1026, d = 2^17 (538 MB): 222 us in two passes, 129 us in this form
-// (4.2 TB/s, bound by the 128-byte reads of 1026 rows a strip).
+// many agents as a wavefront's; x is read once (FETCH_SIZE 1.006 of its bytes).  n = 1026, d = 2^17 (538 MB): 222 us per
+// call in two passes, 126 us in this form (122 us for the kernel, 4.4 TB/s, bound by the 128-byte reads of 1026 rows a
+// strip).
 // Writes devpart[agent][workgroup] (row n: the workgroup's share of ||xbar||^2) and, if asked, xbar.
 template <int RT, int THREADS>
 __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs C) {

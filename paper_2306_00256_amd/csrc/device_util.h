@@ -10,7 +10,6 @@
 
 namespace ceca {
 
-
 typedef float vf4 __attribute__((ext_vector_type(4)));
 
 template <int VEC> struct VecOf;

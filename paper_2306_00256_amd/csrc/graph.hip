@@ -140,9 +140,10 @@ __device__ __forceinline__ int quad_lane(int v, int j) {
 // rows are at least 64 bytes wide: the table is read once and stays in registers.  The four lanes of a quad hold
 // the same rows of the tile, so lane c of the quad keeps entries c, c + 4, ... of each row -- 2 * MQ registers per
 // row -- and a neighbour's slot and weight reach the other three by quad permutes.
-// What bounds it is LDS bandwidth: m reads and one write of 16 bytes per row and round.  Reading the table
+// What bounds it first is the LDS, busy for 0.6 of the time on a torus: m reads and one write of 16 bytes per row and round.  Reading the table
 // entries from LDS at every look-up (the kernel above) adds half as many bytes again and an LDS round trip
-// in front of every value.  Torus, tau rounds: n = 130, d = 2^20 554 -> 333 us, n = 1026, d = 2^17 1050 -> 531 us.
+// in front of every value.  Torus, tau rounds: n = 130, d = 2^20 554 -> 333 us, n = 1026, d = 2^17 1050 -> 462 us (the
+// latter with the tile order of tile_of_block).
 template <int RT, int THREADS, int MQ>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(graph_waves<THREADS>())))
 void graph_fixed_kernel(const GraphArgs M) {
