@@ -53,8 +53,8 @@ extern "C" {
  *   CECA_OPT_HALF_STEP_RUN  1 (default): dsgd_ceca_run keeps the state in half-step form between fused iterations
  *                     (no message buffers); 0: it keeps full states and two message buffers.  0 also keeps small
  *                     problems off the one-kernel window and the single-launch step
- *   CECA_OPT_WINDOW_MISSING  that many workgroups (all but one at most) of a one-kernel window are never launched: the
- *                     others wait for them in vain, give the window up after some 12 ms and one does it alone
+ *   CECA_OPT_WINDOW_MISSING  that many workgroups (not the one that calls the roll) of a one-kernel window are never
+ *                     launched: the others wait for them in vain, give the window up after some 12 ms and one does it alone
  *   CECA_OPT_PROBE_VARIANT  the 3-read / 2-write probe in another shape: 100 * policy (0 streaming loads and stores,
  *                     1 plain loads, 2 plain stores, 3 both plain) + 10 * threads code (1 = 256, 2 = 512,
  *                     4 = 1024 per workgroup) + column groups per thread (1, 2, 4, 8 with 256 threads)

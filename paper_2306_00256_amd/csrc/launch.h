@@ -127,10 +127,9 @@ struct RunArgs {
   const float* t;
   const int32_t* batch_idx;   // [iters][n][B]
   unsigned long long* words;  // {tag, value} words: two message slots [n][d], then two slots of partial margins [n][nchunks][B]
-  unsigned long long* roll;   // the word after them: who is there (set by the launcher)
+  unsigned long long* roll;   // the word after them: complete or given up (set by the launcher)
   int64_t d;
   int32_t n, N, B, kind, nchunks, port, iters, tau, r0;
-  int32_t roll_call;          // workgroups that have to be there (set by the launcher)
   float lr, scale, noise_std;
   uint32_t seed, k;
   MultiRound round[kRunMaxTau];

@@ -23,13 +23,14 @@ namespace ceca {
 // agent, and each of those published them after it had consumed the old ones.
 // Every wait is for something published one iteration earlier, or for this iteration's words of workgroups that wait
 // only on earlier ones: once every workgroup is on the device every wait ends.  The host's rule makes that likely but
-// cannot promise it (other processes, replays of a captured call on a narrower stream), so the workgroups keep a roll
-// in one word of memory: each adds itself when it starts, and one that has waited for kRollCallPolls polls while the
-// roll is not full marks the window as given up -- one compare-and-swap, so the window is either complete or given up for
-// good, the same for everybody.  Results are stored only by a window that is complete.  From one that was given up the
-// workgroups leave as they come to the end, and the last one to leave does the whole window alone (run_alone), from
-// the untouched state and with the same bits.  Off the hot path: the roll costs one atomic per workgroup and a look at
-// the end.
+// cannot promise it (other processes, replays of a captured call on a narrower stream), so one more workgroup calls the
+// roll: when it has seen the first words of every other it marks the window as complete.  A workgroup that has waited for
+// kRollCallPolls polls while it is not complete marks it as given up.  Both are a compare-and-swap on one word that is
+// zero before, so the window is one or the other for good, the same for everybody.  Results are stored only by a
+// complete window.  From one given up the workgroups leave as they come to the end, and the last one to leave does
+// the whole window alone (run_alone), from the untouched state and with the same bits.  The others pay a look at that
+// word after their last exchange (requested inside the loop it costs every iteration 0.4 us: the compiler waits for it before
+// the next rows' requests).  With a count that every workgroup adds itself to, the atomics on one word took 3 us of a call with 426 agents, 73 -> 76 us.
 //
 // What bounds it: the latency of the chain rows -> margins -> barrier -> coefficients -> message -> peer, once per
 // iteration (an exchange between workgroups takes about 1.3 us), and a compute unit's intake of sampled rows, 75 GB/s.
@@ -47,14 +48,14 @@ typedef unsigned long long Word;
 
 // Waits are counted in polls, a quarter of a microsecond each: they stand still while the process is off the device.
 // 12 ms: what a window done alone takes (n = 5, d = 1000, B = 8, 200 iterations: 2 ms; n = 258, d = 10, B = 50, 20
-// iterations: 40 ms; n = 6, d = 10000, B = 32, 100 iterations: 80 ms).
+// iterations: 40 ms; n = 6, d = 10000, B = 32, 100 iterations: 46 ms).
 constexpr uint32_t kRollCallPolls = 64 * 1024;
-// With the roll full no wait lasts; this bound is for a workspace that something else writes to during the call: NaN
+// In a complete window no wait lasts; this bound is for a workspace that something else writes to during the call: NaN
 // takes the place of what never came, and the call ends.
 constexpr uint32_t kGiveUpPolls = 128 * 1024 * 1024;             // half a minute
 constexpr uint32_t kLost = 1u << 31;
-// the roll: workgroups that came (low half), workgroups that left a window given up (bits 32 to 62), the mark
-constexpr Word kLeft = 1ULL << 32, kGivenUp = 1ULL << 63;
+// the word of the roll: its two marks, and a count of the workgroups that left a window given up (bits 32 to 62)
+constexpr Word kComplete = 1, kLeft = 1ULL << 32, kGivenUp = 1ULL << 63;
 
 __device__ __forceinline__ Word peek(const Word* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void publish(Word* p, uint32_t tag, float v) {
@@ -63,9 +64,8 @@ __device__ __forceinline__ void publish(Word* p, uint32_t tag, float v) {
 // A bounded wait: false once the window has been given up, then for good.
 struct Patience {
   Word* roll;
-  uint32_t all;                            // workgroups on a full roll
   uint32_t polls = 0;                      // of this wait; from kLost on: given up
-  __device__ __forceinline__ Patience(const RunArgs& P) : roll(P.roll), all((uint32_t)P.roll_call) {}
+  __device__ __forceinline__ Patience(const RunArgs& P) : roll(P.roll) {}
   __device__ __forceinline__ void begin() { polls &= kLost; }
   __device__ __forceinline__ bool again() {
     if ((++polls & 1023u) == 0 && hopeless()) polls = kLost;
@@ -74,11 +74,23 @@ struct Patience {
   __device__ __forceinline__ bool hopeless() {
     Word w = peek(roll);
     if (w & kGivenUp) return true;
-    if ((uint32_t)w == all) return polls >= kGiveUpPolls;
-    // fails if the roll has changed meanwhile: then the next look decides
-    return polls >= kRollCallPolls && __hip_atomic_compare_exchange_strong(roll, &w, w | kGivenUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (w & kComplete) return polls >= kGiveUpPolls;
+    // fails if the word has changed meanwhile: then the next look decides
+    return polls >= kRollCallPolls && settle(roll, kGivenUp);
   }
-  __device__ __forceinline__ bool settled(Word w) const { return (w & kGivenUp) || (uint32_t)w == all; }
+  static __device__ __forceinline__ bool settle(Word* roll, Word mark) {
+    Word w = 0;
+    return __hip_atomic_compare_exchange_strong(roll, &w, mark, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // waits for one of the marks, from word w on; true if the window is complete
+  __device__ __forceinline__ bool complete(Word w) {
+    begin();
+    while (!(w & (kComplete | kGivenUp))) {
+      (void)again();
+      w = peek(roll);
+    }
+    return !(w & kGivenUp);
+  }
 };
 
 template <int VEC> struct Parts;
@@ -190,16 +202,30 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
   }
 }
 
+// The roll: a workgroup is there when its first word has a tag -- the margin of sample 0 of its chunk, or the first word
+// of its agent's message.  True if the window is complete.
+template <int THREADS, bool CHUNKS>
+__device__ __forceinline__ bool call_roll(const RunArgs& P) {
+  Patience wait(P);
+  bool here = true;
+  for (int i = threadIdx.x; i < P.n * P.nchunks && here; i += THREADS) {
+    const Word* first = P.words + (CHUNKS ? 2 * (int64_t)P.n * P.d + (int64_t)i * P.B : (int64_t)i * P.d);
+    wait.begin();
+    do here = (peek(first) >> 32) != 0;
+    while (!here && wait.again());
+  }
+  if (__syncthreads_and(here) && threadIdx.x == 0) (void)Patience::settle(P.roll, kComplete);
+  return wait.complete(0);
+}
+
+// A workgroup's part of the window.  True if the window is complete and the results are stored.
 template <int VEC, int THREADS, int BMAX, bool CHUNKS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_waves<VEC, THREADS, BMAX>(), 8)))
-void run_kernel(const RunArgs P) {
+__device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THREADS / 64][BMAX], float* part) {
   using V = typename VecOf<VEC>::T;
   constexpr int WAVES = THREADS / 64;
   constexpr int CH = kRowGroup;            // rows are requested and added up in groups, as in the single-step kernels
   constexpr int MG = BMAX < 16 ? BMAX : 16;    // samples per wavefront sum (any number gives the same bits)
   static_assert(BMAX % CH == 0 && BMAX <= 64, "whole groups of samples, one lane per sample");
-  __shared__ float red[2][WAVES][BMAX];    // alternating between iterations
-  __shared__ float part[CHUNKS ? kRunParts : 1];                  // partial margins of every chunk of the agent
   const int agent = CHUNKS ? (int)(blockIdx.x / (uint32_t)P.nchunks) : (int)blockIdx.x;
   const int chunk = CHUNKS ? (int)(blockIdx.x % (uint32_t)P.nchunks) : 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -239,10 +265,7 @@ void run_kernel(const RunArgs P) {
   };
   request_rows();
   int32_t idx_next = idx[P.iters > 1 ? nb : 0];
-  // on the roll; behind the first rows' requests, so that they do not wait for it
-  if (tid == 0) (void)__hip_atomic_fetch_add(P.roll, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   Patience wait(P);
-  Word roll = 0;
   int r = P.r0;
   int reader = agent;                      // who read my message two iterations ago (after the shifts below)
   int reader1 = agent;                     // and one iteration ago
@@ -333,8 +356,6 @@ void run_kernel(const RunArgs P) {
       myidx = min(max(idx_next, 0), P.N - 1);
       if (__any(now != myidx)) request_rows();                   // the same in every wavefront
       idx_next = idx[(int64_t)min(t + 2, P.iters - 1) * nb];
-    } else {
-      roll = peek(P.roll);                 // full long ago, as a rule
     }
     V msg = V(0.0f);
     if (on) {
@@ -365,23 +386,25 @@ void run_kernel(const RunArgs P) {
     reader1 = to;
     r = r + 1 == P.tau ? 0 : r + 1;
   }
-  wait.begin();
-  while (!wait.settled(roll)) {
-    (void)wait.again();
-    roll = peek(P.roll);
+  if (!wait.complete(peek(P.roll))) return false;                // marked long ago, as a rule
+  if (on) {
+    *reinterpret_cast<V*>(P.xout + (int64_t)agent * P.ld + col) = x;
+    *reinterpret_cast<V*>(P.yout + (int64_t)agent * P.ld + col) = y;
   }
-  if (!(roll & kGivenUp)) {
-    if (on) {
-      *reinterpret_cast<V*>(P.xout + (int64_t)agent * P.ld + col) = x;
-      *reinterpret_cast<V*>(P.yout + (int64_t)agent * P.ld + col) = y;
-    }
-    return;
-  }
+  return true;
+}
+
+template <int VEC, int THREADS, int BMAX, bool CHUNKS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_waves<VEC, THREADS, BMAX>(), 8)))
+void run_kernel(const RunArgs P) {
+  __shared__ float red[2][THREADS / 64][BMAX];                   // alternating between iterations
+  __shared__ float part[CHUNKS ? kRunParts : 1];                 // partial margins of every chunk of the agent
+  if (blockIdx.x + 1 == gridDim.x ? call_roll<THREADS, CHUNKS>(P) : take_part<VEC, THREADS, BMAX, CHUNKS>(P, red, part)) return;
   // given up (the same for every thread): nothing has been stored; my own words are behind me before I leave
   __shared__ bool last_s;
   __threadfence();
   __syncthreads();
-  if (tid == 0) last_s = (uint32_t)((__hip_atomic_fetch_add(P.roll, kLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kGivenUp) >> 32) + 1 == gridDim.x;
+  if (threadIdx.x == 0) last_s = (uint32_t)((__hip_atomic_fetch_add(P.roll, kLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kGivenUp) >> 32) + 1 == gridDim.x;
   __syncthreads();
   if (!last_s) return;
   __threadfence();
@@ -456,8 +479,8 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, b
 
 template <int VEC, int THREADS, int BMAX>
 static hipError_t launch(const RunArgs& a, hipStream_t st) {
-  const int32_t kept = a.roll_call - g_tuning.window_missing;
-  const dim3 grid((unsigned)(kept < 1 ? 1 : kept)), block(THREADS);
+  const int32_t kept = a.n * a.nchunks - g_tuning.window_missing;
+  const dim3 grid((unsigned)(kept < 0 ? 0 : kept) + 1), block(THREADS);       // the last one calls the roll
   if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false><<<grid, block, 0, st>>>(a);
   else if constexpr (THREADS == 256 && (VEC == 4 || BMAX <= 16)) run_kernel<VEC, THREADS, BMAX, true><<<grid, block, 0, st>>>(a);
   else return hipErrorInvalidValue;
@@ -466,7 +489,6 @@ static hipError_t launch(const RunArgs& a, hipStream_t st) {
 
 hipError_t launch_run(const RunArgs& a0, const RunShape& s, bool vec4, hipStream_t st) {
   RunArgs a = a0;
-  a.roll_call = a.n * a.nchunks;
   a.roll = a.words + run_kernel_words(s, a.n, a.d, a.B);
   const int64_t words = run_kernel_words(s, a.n, a.d, a.B) + 1;
   const int64_t blocks = (words + kBlock - 1) / kBlock;
