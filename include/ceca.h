@@ -192,7 +192,7 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * three (d = 10000 but not 9984), at B = 64 fewer than half; of the lengths that are not multiples of 4 one in
  * five at B = 4, one in fifty at B = 8 and none from B = 16 on.
  * All workgroups of that kernel have to be on the device at once.  When some of them are not after about
- * 12 ms of waiting -- kernels that do not end hold their places, a captured call is replayed on a stream with
+ * 12 ms of waiting -- other kernels hold their places for that long, a captured call is replayed on a stream with
  * fewer compute units than the capturing one, the process was given fewer by other means than the stream's
  * mask, more than eight such windows run at the same time (of all processes on the device together) -- the
  * window is given up before anything is stored, and one workgroup does all of it alone: the same bits, but

@@ -29,8 +29,9 @@ namespace ceca {
 // zero before, so the window is one or the other for good, the same for everybody.  Results are stored only by a
 // complete window.  From one given up the workgroups leave as they come to the end, and the last one to leave does
 // the whole window alone (run_alone), from the untouched state and with the same bits.  The others pay a look at that
-// word after their last exchange (requested inside the loop it costs every iteration 0.4 us: the compiler waits for it before
-// the next rows' requests).  With a count that every workgroup adds itself to, the atomics on one word took 3 us of a call with 426 agents, 73 -> 76 us.
+// word after their last exchange (requested inside the loop it costs every iteration 0.4 us: the compiler waits for it
+// before the next rows' requests).  With a count that every workgroup adds itself to, the atomics on one word took 3 us of
+// a call with 426 agents, 73 -> 76 us.
 //
 // What bounds it: the latency of the chain rows -> margins -> barrier -> coefficients -> message -> peer, once per
 // iteration (an exchange between workgroups takes about 1.3 us), and a compute unit's intake of sampled rows, 75 GB/s.
