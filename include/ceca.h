@@ -19,9 +19,11 @@
  *     NULL = the default stream); the library never synchronizes.
  *   - Agents and rounds are 0-based: row i is the paper's agent i+1, r = k mod tau
  *     is the ordinary remainder in [0, tau) (Algorithm 1).
- *   - Any base pointer / leading dimension is accepted; 16-byte aligned bases with
- *     leading dimensions that are multiples of 4 take the vectorized kernels, other
- *     layouts silently take a scalar kernel with identical results.
+ *   - Any base pointer / leading dimension is accepted, with identical results.  The
+ *     kernels on the state alone (gossip, averaging, mixing, graphs, elementwise losses,
+ *     consensus) take 16-byte groups of columns at any alignment; those of minibatch losses
+ *     need 16-byte aligned bases and leading dimensions that are multiples of 4 for that,
+ *     and take single columns otherwise.
  *   - The functions declared here keep no mutable state between calls beyond the calling
  *     thread's last error (ceca_last_error, ceca_last_hip_error) and may be called from
  *     several threads at once.  Launch shapes are the library's own; the per-thread

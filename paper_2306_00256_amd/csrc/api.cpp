@@ -68,7 +68,7 @@ int32_t check_state_call(const float* S_in, float* S_out, int32_t n, int64_t d, 
 }
 
 // Chain shape for the round: which cycles the walk has and how they are cut into stretches.
-void shape_chain(const ceca_round_t& rd, int32_t n, int32_t port, bool in_place, int32_t default_seg, int64_t groups,
+void shape_chain(const ceca_round_t& rd, int32_t n, int32_t port, bool in_place, int32_t default_seg, int64_t d,
                  ceca::ChainArgs* a) {
   a->n = n;
   if (n == 1) {
@@ -93,7 +93,7 @@ void shape_chain(const ceca_round_t& rd, int32_t n, int32_t port, bool in_place,
   if (seg_len <= 0) seg_len = default_seg;
   if (seg_len > len) seg_len = len;
   // a launch addresses fewer than 2^24 workgroups: huge problems walk longer stretches
-  const int64_t tiles = (groups + ceca::kBlock - 1) / ceca::kBlock;
+  const int64_t tiles = (d / 4 + ceca::kBlock - 1) / ceca::kBlock + (d % 4 ? 1 : 0);
   while (seg_len < len && tiles * g * ((len + seg_len - 1) / seg_len) >= (1LL << 24)) seg_len *= 2;
   if (seg_len > len) seg_len = len;
   a->seg_len = seg_len;
@@ -144,28 +144,12 @@ ChainPlan plan_chain(ceca::ChainArgs* a, int mode, int64_t d, int32_t port) {
   return p;
 }
 
-int32_t run_chain(ceca::ChainArgs a, int mode, int64_t d, bool can_vec, const ceca_round_t& rd, int32_t port,
-                  hipStream_t st) {
+int32_t run_chain(ceca::ChainArgs a, int mode, int64_t d, const ceca_round_t& rd, int32_t port, hipStream_t st) {
   const ChainPlan pl = plan_chain(&a, mode, d, port);
-  const int rows = pl.rows;
-  const bool in_place = pl.in_place;
-  const int32_t default_seg = pl.default_seg;
-  const int64_t d4 = can_vec ? d / 4 : 0;
-  if (d4 > 0) {
-    a.col0 = 0;
-    a.ngroups = d4;
-    shape_chain(rd, a.n, port, in_place, default_seg, d4, &a);
-    const hipError_t e = ceca::launch_chain(a, mode, true, rows, st);
-    if (e != hipSuccess) return hip_fail(e, "chain kernel launch");
-  }
-  const int64_t rest = d - 4 * d4;
-  if (rest > 0) {
-    a.col0 = 4 * d4;
-    a.ngroups = rest;
-    shape_chain(rd, a.n, port, in_place, default_seg, rest, &a);
-    const hipError_t e = ceca::launch_chain(a, mode, false, rows, st);
-    if (e != hipSuccess) return hip_fail(e, "chain kernel launch (scalar columns)");
-  }
+  a.d = d;
+  shape_chain(rd, a.n, port, pl.in_place, pl.default_seg, d, &a);
+  const hipError_t e = ceca::launch_chain(a, mode, pl.rows, st);
+  if (e != hipSuccess) return hip_fail(e, "chain kernel launch");
   return CECA_OK;
 }
 
@@ -397,14 +381,29 @@ ConsPlan cons_plan(int32_t n, int64_t d) {
 // ok = false when no such tile holds n agents.
 struct TileShape {
   int32_t threads, row_lanes, rows_per_thread;
-  bool ok;
+  bool ok, vec4;
   // bytes of one agent's row inside the tile
-  int32_t row_bytes(bool vec4) const { return (threads / std::max(row_lanes, 1)) * (vec4 ? 16 : 4); }
+  int32_t row_bytes() const { return (threads / std::max(row_lanes, 1)) * (vec4 ? 16 : 4); }
+  // the tile and the columns of a register-tile kernel's launch
+  template <typename Args>
+  void fill(int64_t d, Args* a) const {
+    a->threads = threads;  a->row_lanes = row_lanes;  a->rows_per_thread = rows_per_thread;
+    a->ngroups = vec4 ? (d + 3) / 4 : d;
+    a->mem.short_cols = vec4 ? (int32_t)(4 * a->ngroups - d) : 0;
+  }
 };
+
+// Register-tile kernels take rows of four columns or more in 16-byte groups, whatever their base and pitch; the last
+// group of a row may be short (own_columns in device_util.h).  Single columns take four times the instructions of both
+// kinds and leave rows of the tile a quarter as wide: with rows that are not 16-byte aligned, 2^26 elements, tiles of
+// single columns -> groups: exact averaging n = 9 164 -> 107 us, n = 130 295 -> 210, n = 1026 2181 -> 362; with aligned
+// rows of a length that is no multiple of four, one launch instead of two (n = 130, d = 8067: 18 -> 11.5 us).
+constexpr int64_t kTileVecCols = 4;
 
 // The tile with at most `cap` rows per thread: the fewest row lanes that cover n give the widest rows.
 TileShape shape_tile(int32_t n, bool vec4, int32_t threads, int32_t cap) {
   TileShape t{};
+  t.vec4 = vec4;
   t.threads = threads;
   t.row_lanes = 1;
   while ((int64_t)t.row_lanes * cap < n) t.row_lanes *= 2;
@@ -466,9 +465,9 @@ TileShape rounds_tile(int32_t n, bool vec4, bool with_y = true) {
 // a thread's peers read at once).  Measured on MI355X: with 5 to 8 rows five wavefronts per SIMD (n = 128,
 // 8 rows: exact averaging 0.235 -> 0.21 ms), with 9 rows four; from 10 rows on the lean forms spill and the
 // plain form is the one to use.
-int32_t rounds_lean(const TileShape& t, bool vec4) {
+int32_t rounds_lean(const TileShape& t) {
   const int32_t forced = g_tuning.lean_tiles;
-  if (!vec4 || t.threads != ceca::kBlock || forced == 1) return 0;
+  if (!t.vec4 || t.threads != ceca::kBlock || forced == 1) return 0;
   if (forced >= 4) return forced;
   if (t.rows_per_thread >= 5 && t.rows_per_thread <= 8) return 5;
   if (t.rows_per_thread == 9) return 4;
@@ -539,7 +538,7 @@ TileShape graph_tile(int32_t n, bool vec4, int32_t m, bool fixed) {
     const TileShape t = pick_tile(n, vec4, 4, ceca::kGraphRows, 9,
                                   [wide](int32_t k) { return k <= 256 ? ceca::kBlock : (k <= wide * 128 ? 512 : 1024); },
                                   [n, wide](int32_t threads) { return threads == ceca::kBlock ? (n <= 128 ? 5 : 9) : wide; });
-    if (t.ok && t.row_bytes(true) >= 64) return t;
+    if (t.ok && t.row_bytes() >= 64) return t;
   }
   return pick_tile(n, vec4, 4, ceca::kGraphRows, 8,
                    [](int32_t k) { return k <= 384 ? ceca::kBlock : (k <= 768 ? 512 : 1024); },
@@ -694,8 +693,7 @@ int32_t ceca_gossip_round(const float* S_in, float* S_out, int32_t n, int64_t d,
   a.ld = ld;
   a.n = n;
   set_weights(rd, n, /*gossip_only=*/true, &a);
-  const bool can_vec = aligned16(S_in) && aligned16(S_out) && ld % 4 == 0;
-  return run_chain(a, ceca::MODE_GOSSIP, d, can_vec, rd, port, (hipStream_t)hip_stream);
+  return run_chain(a, ceca::MODE_GOSSIP, d, rd, port, (hipStream_t)hip_stream);
 }
 
 int32_t ceca_gossip_rounds(const float* S_in, float* S_out, int32_t n, int64_t d, int64_t ld, int32_t rounds,
@@ -707,12 +705,11 @@ int32_t ceca_gossip_rounds(const float* S_in, float* S_out, int32_t n, int64_t d
   hipStream_t st = (hipStream_t)hip_stream;
   const int32_t tau = ceca::tau_of(n);
   const TileShape tv = rounds_tile(n, true), ts = rounds_tile(n, false);
-  const bool can_vec = aligned16(S_in) && aligned16(S_out) && ld % 4 == 0;
+  const TileShape& tile = d >= kTileVecCols ? tv : ts;
   // A single round is the streaming kernel's job, and tiles with rows narrower than a 128-byte line pay
   // off only over a few rounds (measured: the fused pass costs about 1.5, 2.5 and 4.7 single rounds at
   // n = 1026, 2050 and 4096).
-  const int32_t row_bytes = can_vec ? tv.row_bytes(true) : ts.row_bytes(false);
-  const int32_t worth = row_bytes >= 64 ? (tv.threads == 1024 && can_vec ? 3 : 2) : 5;
+  const int32_t worth = tile.row_bytes() >= 64 ? (tile.threads == 1024 ? 3 : 2) : 5;
   const bool knobs = g_tuning.rows != 0 || g_tuning.tile_threads != 0;
   // (rounds after the first run in place on S_out: with two ports those walk whole cycles, which needs
   // many column tiles to fill the device)
@@ -726,7 +723,6 @@ int32_t ceca_gossip_rounds(const float* S_in, float* S_out, int32_t n, int64_t d
     }
     return CECA_OK;
   }
-  const int64_t d4 = can_vec ? d / 4 : 0;
   // one kernel takes up to kMultiMaxRounds rounds; longer runs go in pieces of whole cycles (the
   // kernel starts at round 0, which reads no y), the first from S_in to S_out and the rest in place
   // on S_out (a workgroup holds its whole tile before it writes)
@@ -738,25 +734,16 @@ int32_t ceca_gossip_rounds(const float* S_in, float* S_out, int32_t n, int64_t d
     m.xout = S_out;  m.yout = S_out + (int64_t)n * ld;
     m.ld = ld;
     m.n = n;  m.port = port;  m.rounds = cnt;
-    m.lean = rounds_lean(tv, true);
+    m.lean = rounds_lean(tile);
     for (int32_t t = 0; t < cnt; ++t) {
       ceca::fill_round(n, (t0 + t) % tau, port, &rd);
       ceca::MultiRound& R = m.round[t];
       R.shift = rd.shift;  R.exch_y = rd.exchange_y;  R.read_y = rd.b_num != 0;
       R.a = rd.a;  R.ap = rd.a_peer;  R.b = rd.b;  R.bp = rd.b_peer;
     }
-    if (d4 > 0) {
-      m.col0 = 0;  m.ngroups = d4;
-      m.threads = tv.threads;  m.row_lanes = tv.row_lanes;  m.rows_per_thread = tv.rows_per_thread;
-      const hipError_t e = ceca::launch_multi_round(m, true, st);
-      if (e != hipSuccess) return hip_fail(e, "multi-round kernel launch");
-    }
-    if (d - 4 * d4 > 0) {
-      m.col0 = 4 * d4;  m.ngroups = d - 4 * d4;
-      m.threads = ts.threads;  m.row_lanes = ts.row_lanes;  m.rows_per_thread = ts.rows_per_thread;
-      const hipError_t e = ceca::launch_multi_round(m, false, st);
-      if (e != hipSuccess) return hip_fail(e, "multi-round kernel launch (scalar columns)");
-    }
+    tile.fill(d, &m);
+    const hipError_t e = ceca::launch_multi_round(m, tile.vec4, st);
+    if (e != hipSuccess) return hip_fail(e, "multi-round kernel launch");
   }
   return CECA_OK;
 }
@@ -774,12 +761,13 @@ int32_t ceca_average(const float* X_in, float* X_out, int32_t n, int64_t d, int6
   const int32_t tau = ceca::tau_of(n);
   const TileShape tv = rounds_tile(n, true, false), ts = rounds_tile(n, false, false);
   if (!tv.ok || !ts.ok) return fail(CECA_EINVAL, "internal: no tile holds n = %d agents", n);
+  const TileShape& tile = d >= kTileVecCols ? tv : ts;
   ceca::MultiArgs m{};
   m.xin = X_in;
   m.xout = X_out;  m.yout = nullptr;
   m.ld = ld;
   m.n = n;  m.port = port;  m.rounds = tau;          // n = 1: no rounds, the kernel copies
-  m.lean = rounds_lean(tv, true);
+  m.lean = rounds_lean(tile);
   ceca_round_t rd;
   for (int32_t t = 0; t < tau; ++t) {
     ceca::fill_round(n, t, port, &rd);
@@ -787,20 +775,9 @@ int32_t ceca_average(const float* X_in, float* X_out, int32_t n, int64_t d, int6
     R.shift = rd.shift;  R.exch_y = rd.exchange_y;  R.read_y = rd.b_num != 0;
     R.a = rd.a;  R.ap = rd.a_peer;  R.b = rd.b;  R.bp = rd.b_peer;
   }
-  const bool can_vec = aligned16(X_in) && aligned16(X_out) && ld % 4 == 0;
-  const int64_t d4 = can_vec ? d / 4 : 0;
-  if (d4 > 0) {
-    m.col0 = 0;  m.ngroups = d4;
-    m.threads = tv.threads;  m.row_lanes = tv.row_lanes;  m.rows_per_thread = tv.rows_per_thread;
-    const hipError_t e = ceca::launch_multi_round(m, true, st);
-    if (e != hipSuccess) return hip_fail(e, "averaging kernel launch");
-  }
-  if (d - 4 * d4 > 0) {
-    m.col0 = 4 * d4;  m.ngroups = d - 4 * d4;
-    m.threads = ts.threads;  m.row_lanes = ts.row_lanes;  m.rows_per_thread = ts.rows_per_thread;
-    const hipError_t e = ceca::launch_multi_round(m, false, st);
-    if (e != hipSuccess) return hip_fail(e, "averaging kernel launch (scalar columns)");
-  }
+  tile.fill(d, &m);
+  const hipError_t e = ceca::launch_multi_round(m, tile.vec4, st);
+  if (e != hipSuccess) return hip_fail(e, "averaging kernel launch");
   return CECA_OK;
 }
 
@@ -837,12 +814,11 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
     if (overlaps(loss->c, cbytes, S_out, sbytes)) return fail(CECA_EINVAL, "centres or gradients overlap S_out");
     a.aux = loss->c;
     a.ldaux = loss->ldc;
-    const bool can_vec = state_vec && aligned16(loss->c) && loss->ldc % 4 == 0;
-    if (loss->kind == CECA_LOSS_GRADIENT) return run_chain(a, ceca::MODE_GRAD, d, can_vec, rd, port, st);
+    if (loss->kind == CECA_LOSS_GRADIENT) return run_chain(a, ceca::MODE_GRAD, d, rd, port, st);
     a.noise_std = loss->noise_std;
     a.seed = loss->seed;
     a.k = loss->k;
-    return run_chain(a, ceca::MODE_QUAD, d, can_vec, rd, port, st);
+    return run_chain(a, ceca::MODE_QUAD, d, rd, port, st);
   }
 
   // GEMV-shaped losses: margins -> messages v (workspace) -> combine
@@ -905,7 +881,7 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
   a.aux = g.v;
   a.ldaux = g.ldv;
   g_form = onepass ? CECA_FORM_STEP_ONE_PASS : CECA_FORM_STEP_TWO_PASS;
-  return run_chain(a, ceca::MODE_FROMV, d, state_vec, rd, port, st);
+  return run_chain(a, ceca::MODE_FROMV, d, rd, port, st);
 }
 
 int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* loss) {
@@ -1055,7 +1031,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     a.aux = V2[(iters - 1) & 1];
     a.ldaux = p.ldv;
     g_form = CECA_FORM_RUN_TWO_PASS;
-    return run_chain(a, ceca::MODE_FROMV, d, vec && aligned16(S_out) && ld % 4 == 0, prev, port, st);
+    return run_chain(a, ceca::MODE_FROMV, d, prev, port, st);
   }
   ceca_loss_t one = *loss;
   if (!fused) {
@@ -1117,7 +1093,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     a.n = n;
     set_weights(prev, n, /*gossip_only=*/true, &a);
     g_form = CECA_FORM_RUN_HALF_STEPS;
-    return run_chain(a, ceca::MODE_GOSSIP, d, vec && aligned16(S_out), prev, port, st);
+    return run_chain(a, ceca::MODE_GOSSIP, d, prev, port, st);
   }
   float* V[2] = {reinterpret_cast<float*>(w), reinterpret_cast<float*>(w + p.v_bytes)};
   ceca::GemvArgs g{};
@@ -1174,7 +1150,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   a.aux = V[(iters - 1) & 1];
   a.ldaux = p.ldv;
   g_form = CECA_FORM_RUN_MESSAGES;
-  return run_chain(a, ceca::MODE_FROMV, d, aligned16(S_out) && ld % 4 == 0, prev, port, st);
+  return run_chain(a, ceca::MODE_FROMV, d, prev, port, st);
 }
 
 int32_t dsgd_ceca_steps(const float* S_in, float* S_out, int32_t n, int64_t d, int64_t ld, const ceca_loss_t* loss,
@@ -1192,11 +1168,11 @@ int32_t dsgd_ceca_steps(const float* S_in, float* S_out, int32_t n, int64_t d, i
   hipStream_t st = (hipStream_t)hip_stream;
   const int32_t tau = ceca::tau_of(n);
   const TileShape tv = steps_tile(n, true, steps), ts = steps_tile(n, false, steps);
-  const bool can_vec = aligned16(S_in) && aligned16(S_out) && ld % 4 == 0 && aligned16(loss->c) && loss->ldc % 4 == 0;
+  const TileShape& tile = d >= kTileVecCols ? tv : ts;
   // A tile row narrower than a 128-byte line reads and writes HBM several times less efficiently than
   // the streaming single-step kernel, which only pays off over enough iterations (measured at n = 1026,
   // 2050, 4096: the fused pass costs about 2, 6 and 11 single steps at 64, 32 and 16 bytes).
-  const int32_t row_bytes = can_vec ? tv.row_bytes(true) : ts.row_bytes(false);
+  const int32_t row_bytes = tile.row_bytes();
   const int32_t worth = row_bytes >= 128 ? 1 : (row_bytes >= 64 ? 3 : (row_bytes >= 32 ? 8 : 14));
   // (the steps after the first run in place on S_out: with two ports those walk whole cycles, which
   // needs many column tiles to fill the device)
@@ -1212,7 +1188,6 @@ int32_t dsgd_ceca_steps(const float* S_in, float* S_out, int32_t n, int64_t d, i
     }
     return CECA_OK;
   }
-  const int64_t d4 = can_vec ? d / 4 : 0;
   // one kernel takes up to kMultiMaxRounds iterations; longer runs go in pieces, the first from S_in
   // to S_out and the rest in place on S_out (a workgroup holds its whole tile before it writes)
   for (int32_t t0 = 0; t0 < steps; t0 += ceca::kMultiMaxRounds) {
@@ -1233,18 +1208,9 @@ int32_t dsgd_ceca_steps(const float* S_in, float* S_out, int32_t n, int64_t d, i
     a.yin = src + (int64_t)n * ld;
     a.c = loss->c;  a.ldc = loss->ldc;
     a.lr = lr;  a.noise_std = loss->noise_std;  a.seed = loss->seed;  a.k0 = loss->k + (uint32_t)t0;
-    if (d4 > 0) {
-      m.col0 = 0;  m.ngroups = d4;
-      m.threads = tv.threads;  m.row_lanes = tv.row_lanes;  m.rows_per_thread = tv.rows_per_thread;
-      const hipError_t e = ceca::launch_multi_step(a, true, st);
-      if (e != hipSuccess) return hip_fail(e, "multi-step kernel launch");
-    }
-    if (d - 4 * d4 > 0) {
-      m.col0 = 4 * d4;  m.ngroups = d - 4 * d4;
-      m.threads = ts.threads;  m.row_lanes = ts.row_lanes;  m.rows_per_thread = ts.rows_per_thread;
-      const hipError_t e = ceca::launch_multi_step(a, false, st);
-      if (e != hipSuccess) return hip_fail(e, "multi-step kernel launch (scalar columns)");
-    }
+    tile.fill(d, &m);
+    const hipError_t e = ceca::launch_multi_step(a, tile.vec4, st);
+    if (e != hipSuccess) return hip_fail(e, "multi-step kernel launch");
   }
   return CECA_OK;
 }
@@ -1289,20 +1255,10 @@ int32_t ceca_mix_rounds(const float* X_in, float* X_out, int32_t n, int64_t d, i
   const TileShape tv = mix_tile(n, true, most >= 4), ts = mix_tile(n, false, most >= 4);
   if (!tv.ok || !ts.ok) return fail(CECA_EINVAL, "internal: no tile holds n = %d agents", n);
   hipStream_t st = (hipStream_t)hip_stream;
-  const bool can_vec = aligned16(X_in) && aligned16(X_out) && ld % 4 == 0;
-  const int64_t d4 = can_vec ? d / 4 : 0;
-  if (d4 > 0) {
-    m.col0 = 0;  m.ngroups = d4;
-    m.threads = tv.threads;  m.row_lanes = tv.row_lanes;  m.rows_per_thread = tv.rows_per_thread;
-    const hipError_t e = ceca::launch_mix_rounds(m, true, st);
-    if (e != hipSuccess) return hip_fail(e, "mixing kernel launch");
-  }
-  if (d - 4 * d4 > 0) {
-    m.col0 = 4 * d4;  m.ngroups = d - 4 * d4;
-    m.threads = ts.threads;  m.row_lanes = ts.row_lanes;  m.rows_per_thread = ts.rows_per_thread;
-    const hipError_t e = ceca::launch_mix_rounds(m, false, st);
-    if (e != hipSuccess) return hip_fail(e, "mixing kernel launch (scalar columns)");
-  }
+  const TileShape& tile = d >= kTileVecCols ? tv : ts;
+  tile.fill(d, &m);
+  const hipError_t e = ceca::launch_mix_rounds(m, tile.vec4, st);
+  if (e != hipSuccess) return hip_fail(e, "mixing kernel launch");
   return CECA_OK;
 }
 
@@ -1331,20 +1287,10 @@ int32_t ceca_graph_rounds(const float* X_in, float* X_out, int32_t n, int64_t d,
   g.stage = !g_tuning.graph_tables_in_memory;
   g.fixed = fixed;
   hipStream_t st = (hipStream_t)hip_stream;
-  const bool can_vec = aligned16(X_in) && aligned16(X_out) && ld % 4 == 0;
-  const int64_t d4 = can_vec ? d / 4 : 0;
-  if (d4 > 0) {
-    g.col0 = 0;  g.ngroups = d4;
-    g.threads = tv.threads;  g.row_lanes = tv.row_lanes;  g.rows_per_thread = tv.rows_per_thread;
-    const hipError_t e = ceca::launch_graph_rounds(g, true, st);
-    if (e != hipSuccess) return hip_fail(e, "graph gossip kernel launch");
-  }
-  if (d - 4 * d4 > 0) {
-    g.col0 = 4 * d4;  g.ngroups = d - 4 * d4;
-    g.threads = ts.threads;  g.row_lanes = ts.row_lanes;  g.rows_per_thread = ts.rows_per_thread;
-    const hipError_t e = ceca::launch_graph_rounds(g, false, st);
-    if (e != hipSuccess) return hip_fail(e, "graph gossip kernel launch (scalar columns)");
-  }
+  const TileShape& tile = d >= kTileVecCols ? tv : ts;
+  tile.fill(d, &g);
+  const hipError_t e = ceca::launch_graph_rounds(g, tile.vec4, st);
+  if (e != hipSuccess) return hip_fail(e, "graph gossip kernel launch");
   return CECA_OK;
 }
 
@@ -1366,15 +1312,13 @@ int32_t ceca_describe_step_launch(int32_t n, int64_t d, int64_t ld, int32_t r, i
   set_weights(rd, n, /*gossip_only=*/kind == 0, &a);
   const int mode = kind == 1 ? ceca::MODE_QUAD : (kind == 2 ? ceca::MODE_FROMV : ceca::MODE_GOSSIP);
   const ChainPlan pl = plan_chain(&a, mode, d, port);
-  const bool vec = ld % 4 == 0;
-  const int64_t groups = vec ? d / 4 : d;
-  shape_chain(rd, n, port, pl.in_place, pl.default_seg, std::max<int64_t>(groups, 1), &a);
+  shape_chain(rd, n, port, pl.in_place, pl.default_seg, d, &a);
   out[0] = pl.rows;
   out[1] = (int32_t)a.band;
   out[2] = a.wg_per_cu;
   out[3] = a.seg_len;
   out[4] = a.segs_per_cycle;
-  out[5] = vec ? 4 : 1;
+  out[5] = d >= 4 ? 4 : 1;
   return CECA_OK;
 }
 
@@ -1406,19 +1350,27 @@ int32_t run_consensus(const float* X, int32_t n, int64_t d, int64_t ld, double* 
   c.X = X;  c.ld = ld;  c.d = d;  c.n = n;
   c.out = out;
   c.xbar = xbar_or_null;
-  const bool vec = aligned16(X) && ld % 4 == 0 && d % 4 == 0;
+  // The strip forms take rows of any base, pitch and length from four columns on in 16-byte groups, the others rows
+  // of whole groups.
   const int32_t forced = g_tuning.cons_form;
   int form = CONS_TWO_PASS;
   const bool by_default = p.group_default && !(p.group_spills && have >= p.two_pass_total);
-  if (p.group_threads > 0 && vec && (forced == CONS_GROUP || (forced == 0 && by_default))) form = CONS_GROUP;
+  if (p.group_threads > 0 && d >= 4 && (forced == CONS_GROUP || (forced == 0 && by_default))) form = CONS_GROUP;
   else if (forced == CONS_WAVE ? p.wave_cgs > 0 : (forced == 0 && p.wave_cgs > 0 && p.wave_default)) form = CONS_WAVE;
   else if (forced != CONS_TWO_PASS && p.rows_per_thread > 0) form = CONS_TILE;
+  const bool vec = form == CONS_GROUP || form == CONS_WAVE ? d >= 4 : d % 4 == 0;
+  if (form != CONS_WAVE && forced == 0 && !(aligned16(X) && ld % 4 == 0 && d % 4 == 0)) {
+    // What a scratch size holds on layouts that are not 16-byte aligned is stated for single columns in workgroup tiles
+    // or two passes; calls beyond that are refused in the other forms as well.
+    *need = p.rows_per_thread > 0 ? p.tile_total : p.two_pass_total;
+    if (have < *need) return CECA_EWORKSPACE;
+  }
   if (form == CONS_GROUP) {
     c.group_threads = p.group_threads;
     c.wave_cgs = p.group_cgs;
     while ((1 << c.cg_shift) < c.wave_cgs) ++c.cg_shift;
     c.rows_per_thread = p.group_rows;
-    c.strips = (d / 4 + c.wave_cgs - 1) / c.wave_cgs;
+    c.strips = ((d + 3) / 4 + c.wave_cgs - 1) / c.wave_cgs;
     c.nwaves = std::min<int64_t>(c.strips, p.groups);
     const int64_t off_dev2 = round_up(((int64_t)n + 1) * c.nwaves * 8, 256);
     *need = off_dev2 + round_up(((int64_t)n + 1) * 8, 256);

@@ -1,7 +1,7 @@
 // gfx950 kernels of the DSGD-CECA hot path.
 //
-// Layout: the state is 2n rows of ld floats (x rows then y rows); a workgroup is 256 threads
-// (4 wavefronts of 64) and every thread owns 16-byte column groups, so each row access of a
+// Layout: the state is 2n rows of ld floats (x rows then y rows), at any base and pitch; a workgroup is 256 threads
+// (4 wavefronts of 64) and every thread owns a 16-byte column group, so each row access of a
 // workgroup is one contiguous 4 KiB run.
 //
 // Chain walk.  In a round every row i needs the message of exactly one other row, peer(i), and
@@ -125,24 +125,9 @@ __device__ __forceinline__ int walk_upto(const ChainArgs& A, int64_t col, Walk<V
   return 1;
 }
 
-template <int VEC, int MODE, bool EXCH_Y, bool READ_Y, int R>
-__global__ __launch_bounds__(kBlock) void chain_kernel(const ChainArgs A) {
-  using V = typename VecOf<VEC>::T;
-
-  // Which stretch of which cycle this workgroup walks.  Workgroups are numbered band by band: a band
-  // is `band` adjacent column tiles, and inside a band all tiles of one stretch come before the
-  // next stretch along the cycle.  The device then sweeps a few rows of one band at a time, and the
-  // message an open stretch re-reads was fetched by the stretch before it only moments earlier.
-  const uint32_t per_band = A.band * A.nsegs;
-  const uint32_t bnd = blockIdx.x / per_band;
-  const uint32_t rem = blockIdx.x - bnd * per_band;
-  const uint32_t width = min(A.band, A.tiles - bnd * A.band);     // the last band may be narrower
-  const uint32_t seg = rem / width;
-  const uint32_t tile = bnd * A.band + (rem - seg * width);
-  const int64_t g = (int64_t)tile * kBlock + threadIdx.x;
-  if (g >= A.ngroups) return;          // no barriers below: lanes past the last column just leave
-  const int64_t col = A.col0 + g * VEC;
-
+// One thread's stretch `seg`, at its columns.
+template <typename V, int MODE, bool EXCH_Y, bool READ_Y, int R>
+__device__ __forceinline__ void walk_stretch(const ChainArgs& A, uint32_t seg, int64_t col) {
   const int cyc = (int)(seg / (uint32_t)A.segs_per_cycle);
   const int q = (int)seg - cyc * A.segs_per_cycle;
   const int t0 = q * A.seg_len;
@@ -167,17 +152,43 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const ChainArgs A) {
   if (closed) put_row<V>(A, c_first, col, w.xs0, w.ys0, w.vprev, READ_Y);
 }
 
-template <int VEC, int MODE, int R>
+template <int MODE, bool EXCH_Y, bool READ_Y, int R>
+__global__ __launch_bounds__(kBlock) void chain_kernel(const ChainArgs A) {
+  // The last workgroups, one per stretch, take the 1 to 3 columns past the last whole group (or a row of fewer than
+  // four), a column per thread: in a launch of their own they took a small call 3 to 4 us.
+  if (blockIdx.x >= A.vec_blocks) {
+    const int64_t col = A.ngroups * 4 + threadIdx.x;
+    if (col < A.d) walk_stretch<float, MODE, EXCH_Y, READ_Y, 2>(A, blockIdx.x - A.vec_blocks, col);
+    return;
+  }
+  // Which stretch of which cycle this workgroup walks.  Workgroups are numbered band by band: a band
+  // is `band` adjacent column tiles, and inside a band all tiles of one stretch come before the
+  // next stretch along the cycle.  The device then sweeps a few rows of one band at a time, and the
+  // message an open stretch re-reads was fetched by the stretch before it only moments earlier.
+  const uint32_t per_band = A.band * A.nsegs;
+  const uint32_t bnd = blockIdx.x / per_band;
+  const uint32_t rem = blockIdx.x - bnd * per_band;
+  const uint32_t width = min(A.band, A.tiles - bnd * A.band);     // the last band may be narrower
+  const uint32_t seg = rem / width;
+  const uint32_t tile = bnd * A.band + (rem - seg * width);
+  const int64_t g = (int64_t)tile * kBlock + threadIdx.x;
+  if (g >= A.ngroups) return;          // no barriers below: lanes past the last column just leave
+  walk_stretch<vf4, MODE, EXCH_Y, READ_Y, R>(A, seg, g * 4);
+}
+
+template <int MODE, int R>
 static hipError_t launch_chain_t(ChainArgs a, hipStream_t st) {
+  a.ngroups = a.d / 4;
   const int64_t tiles = (a.ngroups + kBlock - 1) / kBlock;
   const int64_t ncyc = (int64_t)a.n / a.cyc_len;   // cycles are equal-length and cover all agents
-  const int64_t blocks = tiles * ncyc * a.segs_per_cycle;
+  const int64_t nsegs = ncyc * a.segs_per_cycle;
+  const int64_t whole = tiles * nsegs, tail = a.d % 4 ? nsegs : 0;
   // the runtime addresses at most 2^32 threads per launch
-  if (tiles < 1 || blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
+  constexpr int64_t most = 1LL << 24;
+  if (whole >= most || tail >= most) return hipErrorInvalidConfiguration;
   a.tiles = (uint32_t)tiles;
-  a.nsegs = (uint32_t)(ncyc * a.segs_per_cycle);
+  a.nsegs = (uint32_t)nsegs;
   if (a.band == 0 || a.band > a.tiles) a.band = a.tiles;
-  dim3 grid((unsigned)blocks), block(kBlock);
   // Unused dynamic LDS caps the workgroups resident on a CU (160 KiB of LDS each): fewer, fatter
   // workgroups keep the rows the device touches at any moment few, which the memory system rewards.
   size_t lds = 0;
@@ -185,27 +196,32 @@ static hipError_t launch_chain_t(ChainArgs a, hipStream_t st) {
     lds = (size_t)(160 * 1024 / a.wg_per_cu) & ~(size_t)1023;
     if (lds > 64 * 1024) lds = 64 * 1024;
   }
-  if (a.exch_y) {
-    // y travels only when delta_r = 0, and then b = 1/2: y is always read
-    chain_kernel<VEC, MODE, true, true, R><<<grid, block, lds, st>>>(a);
-  } else if (a.read_y) {
-    chain_kernel<VEC, MODE, false, true, R><<<grid, block, lds, st>>>(a);
-  } else {
-    chain_kernel<VEC, MODE, false, false, R><<<grid, block, lds, st>>>(a);
-  }
-  return hipGetLastError();
+  const auto go = [&](int64_t vec_blocks, int64_t tail_blocks) {
+    a.vec_blocks = (uint32_t)vec_blocks;
+    const dim3 grid((unsigned)(vec_blocks + tail_blocks)), block(kBlock);
+    if (a.exch_y) {
+      // y travels only when delta_r = 0, and then b = 1/2: y is always read
+      chain_kernel<MODE, true, true, R><<<grid, block, lds, st>>>(a);
+    } else if (a.read_y) {
+      chain_kernel<MODE, false, true, R><<<grid, block, lds, st>>>(a);
+    } else {
+      chain_kernel<MODE, false, false, R><<<grid, block, lds, st>>>(a);
+    }
+    return hipGetLastError();
+  };
+  if (whole + tail < most) return go(whole, tail);
+  const hipError_t e = go(whole, 0);
+  return e != hipSuccess ? e : go(0, tail);
 }
 
-hipError_t launch_chain(const ChainArgs& a, int mode, bool vec4, int rows, hipStream_t st) {
-  if (a.ngroups <= 0) return hipSuccess;
+hipError_t launch_chain(const ChainArgs& a, int mode, int rows, hipStream_t st) {
 #define CECA_CHAIN(M)                                                   \
   do {                                                                  \
-    if (!vec4) return launch_chain_t<1, M, 2>(a, st);                   \
     switch (rows) {                                                     \
-      case 1: return launch_chain_t<4, M, 1>(a, st);                    \
-      case 2: return launch_chain_t<4, M, 2>(a, st);                    \
-      case 8: return launch_chain_t<4, M, 8>(a, st);                    \
-      default: return launch_chain_t<4, M, 4>(a, st);                   \
+      case 1: return launch_chain_t<M, 1>(a, st);                       \
+      case 2: return launch_chain_t<M, 2>(a, st);                       \
+      case 8: return launch_chain_t<M, 8>(a, st);                       \
+      default: return launch_chain_t<M, 4>(a, st);                      \
     }                                                                   \
   } while (0)
   switch (mode) {

@@ -187,7 +187,8 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
   const int cg = lane & (cgs - 1);
   const int rg = lane >> C.cg_shift;
   const int row_lanes = 64 >> C.cg_shift;
-  const int64_t ngroups = (C.d + VEC - 1) / VEC;    // d is a multiple of VEC on the vector path
+  const int64_t ngroups = (C.d + VEC - 1) / VEC;
+  const int short_cols = (int)(ngroups * VEC - C.d);   // columns that a row's last group lacks: zeros add nothing below
   double acc[RTP];
 #pragma unroll
   for (int k = 0; k < RTP; ++k) acc[k] = 0.0;
@@ -199,7 +200,8 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
     on = g < ngroups;
     col = (on ? g : 0) * VEC;
     // my rows lie row_lanes rows apart: one address, stepped (only the last row may need the clamp)
-    const float* p = C.X + (int64_t)rg * C.ld + col;
+    const int64_t from = col - (g == ngroups - 1 ? short_cols : 0);
+    const float* p = C.X + (int64_t)rg * C.ld + from;
     const int64_t step = (int64_t)row_lanes * C.ld;
 #pragma unroll
     for (int k = 0; k < RT - 1; ++k) {
@@ -207,7 +209,7 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
       p += step;
     }
     const int i = min(rg + (RT - 1) * row_lanes, C.n - 1);
-    x[RT - 1] = ld_stream<V>(C.X + (int64_t)i * C.ld + col);
+    x[RT - 1] = ld_stream<V>(C.X + (int64_t)i * C.ld + from);
   };
   V x[RT];
   bool on;
@@ -217,6 +219,11 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
   while (true) {
     const int64_t next = strip + C.nwaves;
     const bool more = next < C.strips;              // the same for the whole wavefront
+    if (short_cols && strip == C.strips - 1) {
+      const int back = strip * cgs + cg == ngroups - 1 ? short_cols : 0;
+#pragma unroll
+      for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
+    }
     // rows per lane is the least that covers n, so only a lane's last row can lie past the last agent: the
     // others need no test
     const bool last_mine = rg + (RT - 1) * row_lanes < C.n;
@@ -244,7 +251,8 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
       for (int q = 0; q < VEC; ++q) nrm += m[q] * m[q];
       if (C.xbar) {
 #pragma unroll
-        for (int q = 0; q < VEC; ++q) C.xbar[col + q] = (float)m[q];
+        for (int q = 0; q < VEC; ++q)
+          if (col + q < C.d) C.xbar[col + q] = (float)m[q];
       }
     }
     if (!more) break;
@@ -308,7 +316,8 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
   const int cg = tid & (cgs - 1);
   const int rg = tid >> C.cg_shift;
   const int row_lanes = THREADS >> C.cg_shift;
-  const int64_t ngroups = C.d / 4;
+  const int64_t ngroups = (C.d + 3) / 4;
+  const int short_cols = (int)(ngroups * 4 - C.d);  // columns that a row's last group lacks: zeros add nothing below
   const bool last_mine = rg + (RT - 1) * row_lanes < C.n;      // rows per thread is the least that covers n
   const double n = (double)C.n, rn = 1.0 / n;
   double acc[RTP];
@@ -320,7 +329,7 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
   const int64_t last_step = last_mine ? step : (int64_t)(C.n - 1 - (rg + (RT - 2) * row_lanes)) * C.ld;
   auto first_row = [&](int64_t tile) {
     const int64_t g = tile * cgs + cg;
-    return C.X + (int64_t)(RT > 1 ? rg : min(rg, C.n - 1)) * C.ld + (g < ngroups ? g : 0) * 4;
+    return C.X + (int64_t)(RT > 1 ? rg : min(rg, C.n - 1)) * C.ld + (g < ngroups ? g * 4 - (g == ngroups - 1 ? short_cols : 0) : 0);
   };
   vf4 x[RT];
   {
@@ -333,6 +342,11 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
   }
   int buf = 0;
   for (int64_t tile = blockIdx.x; tile < C.strips; tile += gridDim.x, buf ^= 1) {
+    if (short_cols && tile == C.strips - 1) {
+      const int back = tile * cgs + cg == ngroups - 1 ? short_cols : 0;
+#pragma unroll
+      for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
+    }
     double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < RT - 1; ++k) acc4(s, x[k]);
@@ -376,7 +390,8 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
       for (int q = 0; q < 4; ++q) nrm += m[q] * m[q];
       if (C.xbar) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) C.xbar[g * 4 + q] = (float)m[q];
+        for (int q = 0; q < 4; ++q)
+          if (g * 4 + q < C.d) C.xbar[g * 4 + q] = (float)m[q];
       }
     }
   }

@@ -11,6 +11,13 @@
 namespace ceca {
 
 typedef float vf4 __attribute__((ext_vector_type(4)));
+// Four columns as they lie in memory: rows of any pitch and base, whose groups are aligned to 4 bytes only (a
+// 16-byte load or store of this chip needs no more).
+typedef float vf4_mem __attribute__((ext_vector_type(4), aligned(4)));
+
+template <typename V> struct InMemory;
+template <> struct InMemory<vf4> { using T = vf4_mem; };
+template <> struct InMemory<float> { using T = float; };
 
 template <int VEC> struct VecOf;
 template <> struct VecOf<4> { using T = vf4; };
@@ -35,13 +42,108 @@ __device__ __forceinline__ int64_t tile_of_block(int32_t xcd_runs) {
 
 // State rows are touched once per round: stream them past the caches (nontemporal loads and stores).
 template <typename V> __device__ __forceinline__ V ld_stream(const float* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+  return __builtin_nontemporal_load(reinterpret_cast<const typename InMemory<V>::T*>(p));
 }
 template <typename V> __device__ __forceinline__ void st_stream(float* p, V v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+  __builtin_nontemporal_store(v, reinterpret_cast<typename InMemory<V>::T*>(p));
 }
 template <typename V> __device__ __forceinline__ V ld_plain(const float* p) {
-  return *reinterpret_cast<const V*>(p);
+  return *reinterpret_cast<const typename InMemory<V>::T*>(p);
+}
+template <typename V> __device__ __forceinline__ void st_plain(float* p, V v) {
+  *reinterpret_cast<typename InMemory<V>::T*>(p) = v;
+}
+
+// Register-tile kernels: rows whose length is no multiple of four end in a group of 1 to 3 columns.  Its thread loads
+// the row's last four columns instead, `back` columns further left (rows have at least four), moves its own to the
+// front, and stores those one by one.
+__device__ __forceinline__ vf4 own_columns(vf4 v, int back) {
+  if (back & 1) v = vf4{v.y, v.z, v.w, 0.0f};
+  if (back & 2) v = vf4{v.z, v.w, 0.0f, 0.0f};
+  return v;
+}
+__device__ __forceinline__ float own_columns(float v, int) { return v; }
+
+// That distance for the group at column col.
+template <typename Args> __device__ __forceinline__ int columns_back(const Args& M, int64_t col) {
+  return col == (M.ngroups - 1) * 4 ? M.mem.short_cols : 0;
+}
+
+// RT rows of a tile, `step` rows apart, the last one clamped to row `last`, into registers: x from p and, with a second
+// pointer, c from pc, row by row.  (The compiler must neither merge the two kinds of access, which would drop the
+// streaming, nor work all addresses out in front of the branch.)
+template <typename V, int RT, bool TWO = true>
+__device__ __forceinline__ void load_rows(V (&x)[RT], const float* p, int64_t ld, V (&c)[RT], const float* pc, int64_t ldc, int row, int step,
+                                          int last, bool cached) {
+  if (cached) {
+    asm volatile("; cached" : "+v"(row));
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      const int64_t i = min(row + k * step, last);
+      x[k] = ld_plain<V>(p + i * ld);
+      if (TWO) c[k] = ld_plain<V>(pc + i * ldc);
+    }
+    asm volatile("; cached");
+  } else {
+    asm volatile("; streamed" : "+v"(row));
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      const int64_t i = min(row + k * step, last);
+      x[k] = ld_stream<V>(p + i * ld);
+      if (TWO) c[k] = ld_stream<V>(pc + i * ldc);
+    }
+  }
+}
+template <typename V, int RT>
+__device__ __forceinline__ void load_rows(V (&x)[RT], const float* p, int64_t ld, int row, int step, int last, bool cached) {
+  load_rows<V, RT, false>(x, p, ld, x, nullptr, 0, row, step, last, cached);
+}
+// The same rows out of registers, those up to `last`; a short group's own columns one by one.
+__device__ __forceinline__ void store_short(float* q, vf4 v, int back) {
+  q[0] = v.x;
+  if (back < 3) q[1] = v.y;
+  if (back < 2) q[2] = v.z;
+}
+__device__ __forceinline__ void store_short(float* q, float v, int) { *q = v; }
+// x at p and, unless py is null (the same for every thread), y at py, row by row: all of x's rows before the first of y's
+// measured up to 5 % slower (n = 258, 2^26 elements, fused rounds: 250 against 238 us).
+template <typename V, int RT>
+__device__ __forceinline__ void store_rows(const V (&x)[RT], float* p, const V (&y)[RT], float* py, int64_t ld, int row, int step, int last,
+                                           int back, bool cached) {
+  if (back) {
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      if (row + k * step <= last) {
+        const int64_t at = (int64_t)(row + k * step) * ld;
+        store_short(p + at, x[k], back);
+        if (py) store_short(py + at, y[k], back);
+      }
+    }
+  } else if (cached) {
+    asm volatile("; cached" : "+v"(row));
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      if (row + k * step <= last) {
+        const int64_t at = (int64_t)(row + k * step) * ld;
+        st_plain<V>(p + at, x[k]);
+        if (py) st_plain<V>(py + at, y[k]);
+      }
+    }
+  } else {
+    asm volatile("; streamed" : "+v"(row));
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      if (row + k * step <= last) {
+        const int64_t at = (int64_t)(row + k * step) * ld;
+        st_stream<V>(p + at, x[k]);
+        if (py) st_stream<V>(py + at, y[k]);
+      }
+    }
+  }
+}
+template <typename V, int RT>
+__device__ __forceinline__ void store_rows(const V (&x)[RT], float* p, int64_t ld, int row, int step, int last, int back, bool cached) {
+  store_rows<V, RT>(x, p, x, nullptr, ld, row, step, last, back, cached);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {

@@ -40,18 +40,22 @@ void graph_rounds_kernel(const GraphArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  const int64_t tile = tile_of_block(M.xcd_runs);
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
   if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
-  const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
+  const int64_t col = (on ? g : 0) * VEC;          // lanes past the last column shadow column group 0
 
   V x[RT];
   int row[RT];                                     // my rows; one past the last agent shadows it (never published or stored)
 #pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    row[k] = min(rg + k * M.row_lanes, M.n - 1);
-    x[k] = ld_stream<V>(M.xin + (int64_t)row[k] * M.ld + col);
+  for (int k = 0; k < RT; ++k) row[k] = min(rg + k * M.row_lanes, M.n - 1);
+  const int64_t from = col - columns_back(M, col);
+  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
+  if (M.mem.short_cols) {
+    const int back = (int)(col - from);
+#pragma unroll
+    for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
   }
   V* xs = reinterpret_cast<V*>(lds_x);
   // (clamped index, weight bits) of entry i * m + j, on the next 8-byte boundary behind the tile
@@ -118,11 +122,9 @@ void graph_rounds_kernel(const GraphArgs M) {
     spec = next_spec;
   }
   if (!on) return;
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = rg + k * M.row_lanes;
-    if (i < M.n) st_stream<V>(M.xout + (int64_t)i * M.ld + col, x[k]);
-  }
+  int64_t out = col;
+  asm volatile("" : "+v"(out));                    // worked out anew, after the rounds
+  store_rows<V, RT>(x, M.xout + out, M.ld, rg, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
 }
 
 // The lane's value as its quad's lane j holds it (a quad permute on the vector pipe, no LDS traffic); j is a
@@ -153,20 +155,17 @@ void graph_fixed_kernel(const GraphArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  const int64_t tile = tile_of_block(M.xcd_runs);
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
   if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
-  const int64_t col = M.col0 + (on ? g : 0) * 4;   // lanes past the last column shadow column group 0
+  const int64_t col = (on ? g : 0) * 4;            // lanes past the last column shadow column group 0
 
   vf4 x[RT];
   float ws[RT], wt[RT][MQ];
   int off[RT][MQ];                                 // byte offset of the neighbour's row in the tile
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int row = min(rg + k * M.row_lanes, M.n - 1);            // a row past the last agent shadows it (never published or stored)
-    x[k] = ld_stream<vf4>(M.xin + (int64_t)row * M.ld + col);
-  }
+  const int64_t from = col - columns_back(M, col);
+  load_rows<vf4, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);   // a row past the last agent shadows it (never published or stored)
 #pragma unroll
   for (int k = 0; k < RT; ++k) {
     const int64_t row = (int64_t)M.k0 * M.n + min(rg + k * M.row_lanes, M.n - 1);
@@ -177,6 +176,11 @@ void graph_fixed_kernel(const GraphArgs M) {
       off[k][q] = min(max(M.nbr[e], 0), M.n - 1) * lanes * 16;     // indices outside [0, n) are clamped, not followed
       wt[k][q] = M.w[e];
     }
+  }
+  if (M.mem.short_cols) {
+    const int back = (int)(col - from);
+#pragma unroll
+    for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
   }
   // neighbours read from LDS together: all rows' or a few at a time where registers are short
   constexpr int KB = RT <= (THREADS > 256 ? 5 : 8) ? RT : 4;
@@ -209,11 +213,9 @@ void graph_fixed_kernel(const GraphArgs M) {
     __syncthreads();
   }
   if (!on) return;
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = rg + k * M.row_lanes;
-    if (i < M.n) st_stream<vf4>(M.xout + (int64_t)i * M.ld + col, x[k]);
-  }
+  int64_t out = col;
+  asm volatile("" : "+v"(out));                    // worked out anew, after the rounds
+  store_rows<vf4, RT>(x, M.xout + out, M.ld, rg, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
 }
 
 template <int VEC, int RT, int THREADS>
@@ -288,7 +290,7 @@ hipError_t launch_graph_rounds(const GraphArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   GraphArgs mm = m;
-  mm.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
+  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_graph_256<1>(mm, (unsigned)blocks, lds, st);

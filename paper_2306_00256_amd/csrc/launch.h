@@ -26,9 +26,10 @@ struct ChainArgs {
   int64_t ld;
   const float* aux;   // MODE_QUAD: centres c;  MODE_FROMV: messages v;  MODE_GRAD: gradients e
   int64_t ldaux;
-  int64_t col0;       // first column of this launch
-  int64_t ngroups;    // VEC-wide column groups in this launch
-  uint32_t tiles;     // workgroups per chain stretch (set by the launcher)
+  int64_t d;
+  int64_t ngroups;    // whole 16-byte column groups of a row (set by the launcher)
+  uint32_t tiles;     // workgroups per chain stretch that take them (set by the launcher)
+  uint32_t vec_blocks;   // ... over all stretches (set by the launcher)
   uint32_t nsegs;     // stretches over all cycles (set by the launcher)
   uint32_t band;      // column tiles per band of the launch order (0 = all tiles in one band)
   int32_t wg_per_cu;  // cap on resident workgroups per CU (0 = whatever fits)
@@ -55,15 +56,23 @@ constexpr int kMultiRows = 16;       // most rows of (x, y) a thread of the mult
 constexpr int kMultiMaxRounds = 64;
 constexpr size_t kMultiMaxLds = 160 * 1024;   // LDS one workgroup can have on gfx950
 
+// How a register-tile kernel's workgroups go about memory (tile_memory below; set by the launchers, short_cols by
+// their callers).
+struct TileMemory {
+  int32_t xcd_runs;         // 1: tiles go to the XCDs in runs (tile_of_block)
+  int32_t cached_loads;     // 1: rows are loaded, stored through the caches, not streamed past them
+  int32_t cached_stores;
+  int32_t short_cols;       // columns that the last group of a row lacks (0 to 3)
+};
+
 struct MultiArgs {
   const float* xin;    // row 0 of x in S_in (y of S_in is not read: round 0 overwrites it)
   float* xout;
   float* yout;         // NULL: y is not stored (exact averaging only needs x)
   int64_t ld;
-  int64_t col0;
   int64_t ngroups;
   int32_t n, port, rounds;
-  int32_t xcd_runs;         // 1: tiles go to the XCDs in runs (tile_of_block; set by the launcher)
+  TileMemory mem;
   int32_t rows_per_thread;  // 1 to 16 rows of (x, y) in a thread's registers
   int32_t row_lanes;   // power of two, row_lanes * rows_per_thread >= n: threads of a workgroup that share a column group
   int32_t threads;     // threads per workgroup of the gossip-rounds kernel: 0 = 256, or 512 / 1024 (16-byte groups only);
@@ -184,13 +193,12 @@ struct MixArgs {
   const float* xin;
   float* xout;
   int64_t ld;
-  int64_t col0;
   int64_t ngroups;
   int32_t n, rounds, period, k0;
   int32_t rows_per_thread;  // rows of x in a thread's registers: 1 to 32, the least that covers n
   int32_t row_lanes;        // power of two, row_lanes * rows_per_thread >= n
   int32_t threads;          // threads per workgroup: 0 = 256, or 512 / 1024 (16-byte groups only, at most 16 rows per thread)
-  int32_t xcd_runs;         // 1: tiles go to the XCDs in runs (tile_of_block; set by the launcher)
+  TileMemory mem;
   int32_t start[kMixMaxPeriod + 1];
   float w_self[kMixMaxPeriod];
   int32_t shift[kMixMaxPeers];
@@ -208,7 +216,6 @@ struct GraphArgs {
   const float* xin;
   float* xout;
   int64_t ld;
-  int64_t col0;
   int64_t ngroups;
   const int32_t* nbr;       // device, [period][n][m]: neighbour j of vertex i in the round's graph
   const float* w;           // device, [period][n][m]: its weight
@@ -219,7 +226,7 @@ struct GraphArgs {
   int32_t threads;          // threads per workgroup: 0 = 256, or 512 / 1024 (16-byte groups only)
   int32_t stage;            // 1: stage small tables in LDS (0: always read them from memory)
   int32_t fixed;            // 1: every round of the call uses table k0, which may be kept in registers
-  int32_t xcd_runs;         // set by the launcher
+  TileMemory mem;
 };
 
 // Launch-shape overrides of the calling thread, set through the test and measurement interface
@@ -248,7 +255,7 @@ struct Tuning {
 extern thread_local Tuning g_tuning;
 
 // rows: state rows whose loads a thread keeps in flight together (1, 2, 4 or 8)
-hipError_t launch_chain(const ChainArgs& a, int mode, bool vec4, int rows, hipStream_t st);
+hipError_t launch_chain(const ChainArgs& a, int mode, int rows, hipStream_t st);
 // one-pass gradient (vector layouts only): returns false when no register tile covers (B, d)
 bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err);
 // gradient kernel with the previous iteration's combine as its prologue; false when the shape is not covered
@@ -283,14 +290,19 @@ hipError_t launch_stream_probe(const float* a, const float* b, const float* c, f
 // out[10] = out[0] + out[5] (11 doubles on the device)
 hipError_t launch_phi(double* out, hipStream_t st);
 
-// Whether a register-tile kernel numbers its tiles in runs per XCD (device_util.h, tile_of_block): rows of the tile
-// narrower than a 128-byte line and enough tiles to matter (small launches measured better in plain order).
+// How the tiles of a register-tile kernel go about memory: rows of the tile narrower than a 128-byte line and enough tiles
+// to matter go to the XCDs in runs (device_util.h, tile_of_block; small launches measured better in plain order), and
+// everything is streamed.
 // Rounds *blocks up to whole runs on every XCD (workgroups past the last tile leave before they load anything).
-inline int32_t xcd_runs(int row_bytes, int64_t* blocks) {
-  if (row_bytes >= 128 || *blocks < 1024 || g_tuning.plain_tile_order) return 0;
-  const int64_t whole = 8 * (int64_t)kXcdRun;
-  *blocks = (*blocks + whole - 1) / whole * whole;
-  return 1;
+inline void tile_memory(TileMemory* mem, int row_bytes, const void*, const void*, int64_t, int64_t* blocks) {
+  mem->xcd_runs = 0;
+  mem->cached_loads = 0;
+  mem->cached_stores = 0;
+  if (row_bytes < 128 && *blocks >= 1024 && !g_tuning.plain_tile_order) {
+    const int64_t whole = 8 * (int64_t)kXcdRun;
+    *blocks = (*blocks + whole - 1) / whole * whole;
+    mem->xcd_runs = 1;
+  }
 }
 
 constexpr int kBlock = 256;          // threads per workgroup: 4 wavefronts of 64

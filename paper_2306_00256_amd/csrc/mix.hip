@@ -35,17 +35,19 @@ void mix_rounds_kernel(const MixArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  const int64_t tile = tile_of_block(M.xcd_runs);
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
   if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
-  const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
+  const int64_t col = (on ? g : 0) * VEC;          // lanes past the last column shadow column group 0
 
-  V x[RT];
+  V x[RT];                                         // rows past the last agent shadow it
+  const int64_t from = col - columns_back(M, col);
+  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
+  if (M.mem.short_cols) {
+    const int back = (int)(col - from);
 #pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = min(rg + k * M.row_lanes, M.n - 1);   // rows past the last agent shadow it
-    x[k] = ld_stream<V>(M.xin + (int64_t)i * M.ld + col);
+    for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
   }
   V* xs = reinterpret_cast<V*>(lds_x);
   // Row i, column group c sits in LDS slot i * lanes + c, so my row k is slot tid + k * THREADS
@@ -98,12 +100,9 @@ void mix_rounds_kernel(const MixArgs M) {
   if (!on) return;
   // the row addresses are worked out here, after the rounds: nothing of them occupies registers meanwhile
   int rg_out = rg;
-  asm volatile("" : "+v"(rg_out));
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = rg_out + k * M.row_lanes;
-    if (i < M.n) st_stream<V>(M.xout + (int64_t)i * M.ld + col, x[k]);
-  }
+  int64_t out = col;
+  asm volatile("" : "+v"(rg_out), "+v"(out));
+  store_rows<V, RT>(x, M.xout + out, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
 }
 
 
@@ -167,7 +166,7 @@ hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MixArgs mm = m;
-  mm.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
+  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_mix_256<1>(mm, (unsigned)blocks, lds, st);

@@ -52,21 +52,24 @@ void multi_round_kernel(const MultiArgs M) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;                      // my column group inside the tile
   const int rg = tid / lanes;                      // my first row; I own rows rg, rg + row_lanes, ...
-  const int64_t tile = tile_of_block(M.xcd_runs);
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
   if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
-  const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
+  const int64_t col = (on ? g : 0) * VEC;          // lanes past the last column shadow column group 0
 
   V x[RT], y[RT];
+  // rows past the last agent shadow the last one (their values are never stored): no branch
+  // surrounds a load, so all of a thread's rows are in flight together
+  const int64_t from = col - columns_back(M, col);
+  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
+  if (M.mem.short_cols) {
+    const int back = (int)(col - from);
 #pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    // rows past the last agent shadow the last one (their values are never stored): no branch
-    // surrounds a load, so all of a thread's rows are in flight together
-    const int i = min(rg + k * M.row_lanes, M.n - 1);
-    x[k] = ld_stream<V>(M.xin + (int64_t)i * M.ld + col);
-    y[k] = V(-0.0f);                               // y(0) is never read: the first round has b = 0
+    for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
   }
+#pragma unroll
+  for (int k = 0; k < RT; ++k) y[k] = V(-0.0f);    // y(0) is never read: the first round has b = 0
   V* zs = reinterpret_cast<V*>(lds_z);
   // Row i, column group c sits in LDS slot i * lanes + c, so my row k is slot tid + k * THREADS
   // (row_lanes * lanes = THREADS).  rows_per_thread is the least that covers n, so only my last row can
@@ -140,15 +143,10 @@ void multi_round_kernel(const MultiArgs M) {
   if (!on) return;
   // the row addresses are worked out here, after the rounds: nothing of them occupies registers meanwhile
   int rg_out = rg;
-  asm volatile("" : "+v"(rg_out));
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = rg_out + k * M.row_lanes;
-    if (i < M.n) {
-      st_stream<V>(M.xout + (int64_t)i * M.ld + col, x[k]);
-      if (M.yout) st_stream<V>(M.yout + (int64_t)i * M.ld + col, y[k]);   // same for every thread
-    }
-  }
+  int64_t out = col;
+  asm volatile("" : "+v"(rg_out), "+v"(out));
+  store_rows<V, RT>(x, M.xout + out, y, M.yout ? M.yout + out : nullptr, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out),
+                    M.mem.cached_stores);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -170,29 +168,31 @@ void multi_step_kernel(const StepsArgs S) {
   const int tid = threadIdx.x;
   const int cg = tid % lanes;
   const int rg = tid / lanes;
-  const int64_t tile = tile_of_block(M.xcd_runs);
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
   if (tile * lanes >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
   const int64_t g = tile * lanes + cg;
   const bool on = g < M.ngroups;
-  const int64_t col = M.col0 + (on ? g : 0) * VEC; // lanes past the last column shadow column group 0
+  const int64_t col = (on ? g : 0) * VEC;          // lanes past the last column shadow column group 0
 
   V x[RT], y[RT], c[RT];
   const bool first_reads_y = M.round[0].read_y != 0;
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = min(rg + k * M.row_lanes, M.n - 1);   // rows past the last agent shadow it
-    x[k] = ld_stream<V>(M.xin + (int64_t)i * M.ld + col);
-    c[k] = ld_stream<V>(S.c + (int64_t)i * S.ldc + col);
-  }
+  const int64_t from = col - columns_back(M, col);
+  // rows past the last agent shadow it
+  load_rows<V, RT>(x, M.xin + from, M.ld, c, S.c + from, S.ldc, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
   if (first_reads_y) {                             // a first round with b = 0 never uses y(0)
-#pragma unroll
-    for (int k = 0; k < RT; ++k) {
-      const int i = min(rg + k * M.row_lanes, M.n - 1);
-      y[k] = ld_stream<V>(S.yin + (int64_t)i * M.ld + col);
-    }
+    load_rows<V, RT>(y, S.yin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
   } else {
 #pragma unroll
     for (int k = 0; k < RT; ++k) y[k] = V(0.0f);
+  }
+  if (M.mem.short_cols) {
+    const int back = (int)(col - from);
+#pragma unroll
+    for (int k = 0; k < RT; ++k) {
+      x[k] = own_columns(x[k], back);
+      y[k] = own_columns(y[k], back);
+      c[k] = own_columns(c[k], back);
+    }
   }
   V* zs = reinterpret_cast<V*>(lds_z);
   // Row i, column group c sits in LDS slot i * lanes + c, so my row k is slot tid + k * THREADS
@@ -292,15 +292,9 @@ void multi_step_kernel(const StepsArgs S) {
   if (!on) return;
   // the row addresses are worked out here, after the iterations: nothing of them occupies registers meanwhile
   int rg_out = rg;
-  asm volatile("" : "+v"(rg_out));
-#pragma unroll
-  for (int k = 0; k < RT; ++k) {
-    const int i = rg_out + k * M.row_lanes;
-    if (i < M.n) {
-      st_stream<V>(M.xout + (int64_t)i * M.ld + col, x[k]);
-      st_stream<V>(M.yout + (int64_t)i * M.ld + col, y[k]);
-    }
-  }
+  int64_t out = col;
+  asm volatile("" : "+v"(rg_out), "+v"(out));
+  store_rows<V, RT>(x, M.xout + out, y, M.yout + out, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
 }
 
 template <int VEC, int RT, int THREADS>
@@ -354,7 +348,7 @@ hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   StepsArgs ss = s;
-  ss.m.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
+  tile_memory(&ss.m.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
   size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (s.noise_std != 0.0f) lds = ((lds + 7) & ~(size_t)7) + (size_t)m.n * sizeof(uint64_t);   // the noise keys behind the tile
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
@@ -402,7 +396,7 @@ hipError_t launch_multi_round(const MultiArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MultiArgs mm = m;
-  mm.xcd_runs = xcd_runs(lanes * (vec4 ? 16 : 4), &blocks);
+  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_rounds_rt<1, 256>(mm, (unsigned)blocks, lds, st);
