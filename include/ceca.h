@@ -19,11 +19,8 @@
  *     NULL = the default stream); the library never synchronizes.
  *   - Agents and rounds are 0-based: row i is the paper's agent i+1, r = k mod tau
  *     is the ordinary remainder in [0, tau) (Algorithm 1).
- *   - Any base pointer / leading dimension is accepted, with identical results.  The
- *     kernels on the state alone (gossip, averaging, mixing, graphs, elementwise losses,
- *     consensus) take 16-byte groups of columns at any alignment; those of minibatch losses
- *     need 16-byte aligned bases and leading dimensions that are multiples of 4 for that,
- *     and take single columns otherwise.
+ *   - Any base pointer / leading dimension is accepted, with identical results (rows that
+ *     lie on 128-byte boundaries are the fastest).
  *   - The functions declared here keep no mutable state between calls beyond the calling
  *     thread's last error (ceca_last_error, ceca_last_hip_error) and may be called from
  *     several threads at once.  Launch shapes are the library's own; the per-thread
@@ -185,14 +182,14 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * rows batch_idx + t * n * B (device, iters * n * B int32) and the one step size lr; the result has the
  * same bits as `iters` calls of dsgd_ceca_step.  Small problems run the
  * whole window as one kernel whose workgroups wait for each other's messages: those whose workgroups fit an
- * eighth of the device's 256 compute units (16-byte aligned layouts with d <= 256: 512, 384, 256 and 128
- * agents for B <= 8, 16, 32 and 64; other layouts with d <= 64: 512; a few dozen agents at d <= 4096, about
- * six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096 with B <= 8; a
+ * eighth of the device's 256 compute units (d a multiple of 4 up to 256: 512, 384, 256 and 128
+ * agents for B <= 8, 16, 32 and 64; other d: 512 up to 64, 128 up to 256; a few dozen agents at d <= 4096, about
+ * six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096 with B <= 8, nor rows
+ * of more than 2048 columns that are no multiple of 4; a
  * stream restricted to some compute units counts those).  Where several workgroups share an agent's columns
- * (16-byte layouts with d > 1024 and B > 16 or d > 4096, others with d > 1024) their words also have to fit
- * the workspace, which depends on the length: up to B = 16 nine in ten 16-byte lengths do, at B = 32 two in
- * three (d = 10000 but not 9984), at B = 64 fewer than half; of the lengths that are not multiples of 4 one in
- * five at B = 4, one in fifty at B = 8 and none from B = 16 on.
+ * (d > 1024 and B > 16, or d > 4096) their words also have to fit
+ * the workspace, which depends on the length: up to B = 16 nine in ten lengths do, at B = 32 two in
+ * three (d = 10000 but not 9984), at B = 64 fewer than half.
  * All workgroups of that kernel have to be on the device at once.  When some of them are not after about
  * 12 ms of waiting -- other kernels hold their places for that long, a captured call is replayed on a stream with
  * fewer compute units than the capturing one, the process was given fewer by other means than the stream's
@@ -203,15 +200,14 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * the result is NaN then.
  * For the others: where a workgroup
  * can take an agent's whole rows
- * (16-byte aligned layouts with d <= 16384 and either n >= 128 with d > 1024 or a batch that fits a
- * register tile: B <= 32 at d <= 1024, 16 at 4096, 8 at 8192, 4 at 16384; any other layout with
- * d <= 1024) each iteration after the first is ONE kernel: the workgroup that takes agent i's gradient
+ * (d <= 1024; d <= 16384 with about a hundred agents or more, or a batch that fits a
+ * register tile: B <= 16 at d <= 4096, 8 at 8192, 4 at 16384; with up to 32 agents no d above 2048
+ * that is no multiple of 4) each iteration after the first is ONE kernel: the workgroup that takes agent i's gradient
  * first finishes the iteration before for that agent (Eqs. (8), (9)) from its own and its peer's
  * message.  Other shapes take the gradient in two passes (margins, then half step); there the margins
  * kernel finishes the iteration before, TWO kernels per iteration instead of three, with the state
  * alternating between S_out and a copy in the workspace (used when ld <= d rounded up to a multiple of
- * 64; beyond that, and when S_in and S_out differ in 16-byte alignment, the call loops over
- * dsgd_ceca_step).
+ * 64; beyond that the call loops over dsgd_ceca_step).
  * S_out may be S_in or disjoint from it; when disjoint, S_in is left unchanged.
  * workspace: device, 256-byte aligned, at least dsgd_ceca_run_workspace_bytes() (256 bytes less are taken
  * too; the one-kernel window may then not fit); contents are scratch. */

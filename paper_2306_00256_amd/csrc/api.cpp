@@ -807,8 +807,6 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
   a.n = n;
   a.lr = lr;
   set_weights(rd, n, /*gossip_only=*/false, &a);
-  const bool state_vec = aligned16(S_in) && aligned16(S_out) && ld % 4 == 0;
-
   if (loss->kind == CECA_LOSS_QUAD_CENTER || loss->kind == CECA_LOSS_GRADIENT) {
     const int64_t sbytes = 2 * (int64_t)n * ld * 4, cbytes = (int64_t)n * loss->ldc * 4;
     if (overlaps(loss->c, cbytes, S_out, sbytes)) return fail(CECA_EINVAL, "centres or gradients overlap S_out");
@@ -847,13 +845,12 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
   g.noise_std = loss->noise_std;
   g.seed = loss->seed;
   g.k = loss->k;
-  const bool gemv_vec = aligned16(S_in) && ld % 4 == 0 && aligned16(loss->A) && loss->lda % 4 == 0 && d % 4 == 0;
-  g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (gemv_vec ? 4 : 1);
+  g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (ceca::minibatch_vec(d) ? 4 : 1);
   g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
   hipError_t e = hipSuccess;
   // small problems: one launch, in which every agent's workgroup also evaluates its peer's message (with two ports out
   // of place only: in place a peer's rows could be written before they are read)
-  if (n > 1 && (!gemv_vec || state_vec) && !g_tuning.two_pass_gradient && g_tuning.agents_per_wg == 0 &&
+  if (n > 1 && !g_tuning.two_pass_gradient && g_tuning.agents_per_wg == 0 &&
       !g_tuning.no_half_step) {
     g.px = a.xin;  g.py = a.yin;
     g.ox = a.xout;  g.oy = a.yout;
@@ -861,20 +858,19 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
     g.p_shift = rd.shift;  g.p_port = port;
     g.p_exch_y = a.exch_y;  g.p_read_y = a.read_y;
     g.pa = a.a;  g.pap = a.ap;  g.pb = a.b;  g.pbp = a.bp;
-    if (ceca::launch_pair_step(g, gemv_vec, st, &e)) {
+    if (ceca::launch_pair_step(g, st, &e)) {
       if (e != hipSuccess) return hip_fail(e, "step kernel launch");
       g_form = CECA_FORM_STEP_SINGLE;
       return CECA_OK;
     }
   }
-  const bool onepass = !g_tuning.two_pass_gradient &&
-                       (gemv_vec ? ceca::launch_grad_onepass(g, st, &e) : ceca::launch_grad_scalar(g, st, &e));
+  const bool onepass = !g_tuning.two_pass_gradient && ceca::launch_grad_onepass(g, st, &e);
   if (onepass) {
     if (e != hipSuccess) return hip_fail(e, "one-pass gradient kernel launch");
   } else {
-    e = ceca::launch_margins(g, gemv_vec, st);
+    e = ceca::launch_margins(g, st);
     if (e != hipSuccess) return hip_fail(e, "margins kernel launch");
-    e = ceca::launch_halfstep(g, gemv_vec, st);
+    e = ceca::launch_halfstep(g, st);
     if (e != hipSuccess) return hip_fail(e, "half-step kernel launch");
   }
 
@@ -921,11 +917,6 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   const int32_t tau = ceca::tau_of(n);
   char* w = reinterpret_cast<char*>(workspace);
   const int64_t nb = (int64_t)n * loss->B;
-  // the gradient kernel of an iteration is chosen by the layout of the state it reads (S_in first, then
-  // S_out): the fused form needs the two to agree
-  const bool lay = ld % 4 == 0 && aligned16(loss->A) && loss->lda % 4 == 0 && d % 4 == 0;
-  const bool vec = lay && aligned16(S_in);
-  const bool same_layout = vec == (lay && aligned16(S_out));
   // (a workspace of the size before the roll was added to it is still taken, with another form where the words fill it)
   auto window_roll_fits = [&](int64_t words) {
     return words + 8 <= workspace_bytes && !overlaps(workspace, words + 8, S_out, sbytes) && !overlaps(workspace, words + 8, S_in, sbytes);
@@ -934,11 +925,11 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   // partial margins through the workspace.  From two iterations on it is never more launches than the forms below.
   // Its words have to fit the space that the other forms need.  They do with one workgroup per agent; in chunks the
   // partial margins are 16 n chunks B bytes of words against 4 n B ceil(d / 256) bytes and what padding rows to 64
-  // floats leaves, so it depends on the length.  Of all lengths to 12,000 with up to 40 agents: 87 % or more of the
-  // 16-byte ones to B = 16, 68 % at B = 32, 43 % at B = 64; of the others 21 % at B = 4, 2 % at B = 8, none from B = 16.
+  // floats leaves, so it depends on the length.  Of all lengths to 12,000 that are multiples of 4, with up to 40 agents: 87 % or
+  // more to B = 16, 68 % at B = 32, 43 % at B = 64.
   ceca::RunShape shape{};
-  if (same_layout && n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
-      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, loss->N, loss->lda, vec, st, &shape) &&
+  if (n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
+      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, loss->N, loss->lda, st, &shape) &&
       ceca::run_kernel_words(shape, n, d, loss->B) * 8 <= need && window_roll_fits(ceca::run_kernel_words(shape, n, d, loss->B) * 8)) {
     ceca::RunArgs a{};
     a.xin = S_in;  a.yin = S_in + (int64_t)n * ld;
@@ -961,20 +952,20 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
       R.shift = rd.shift;  R.exch_y = rd.exchange_y;  R.read_y = rd.b_num != 0;
       R.a = rd.a;  R.ap = rd.a_peer;  R.b = rd.b;  R.bp = rd.b_peer;
     }
-    const hipError_t e = ceca::launch_run(a, shape, vec, st);
+    const hipError_t e = ceca::launch_run(a, shape, st);
     if (e != hipSuccess) return hip_fail(e, "window kernel launch");
     g_form = CECA_FORM_RUN_WINDOW;
     return CECA_OK;
   }
-  const bool fused = same_layout && n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
-                     ceca::grad_fused_covers(n, d, loss->B, vec);
+  const bool fused = n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
+                     ceca::grad_fused_covers(n, d, loss->B);
   // Shapes whose single step takes the two-pass gradient (margins, then half step): the combine of the
   // iteration before becomes the prologue of the margins kernel -- two launches per iteration instead of
   // three, same bits.  The row groups of that kernel all read the old rows while one of them stores the
   // new ones, so the state alternates between S_out and a copy in the workspace.
-  const bool two_pass = g_tuning.two_pass_gradient || !(vec ? ceca::grad_fused_covers(n, d, loss->B, true) : d <= 1024);
+  const bool two_pass = g_tuning.two_pass_gradient || !ceca::grad_fused_covers(n, d, loss->B);
   const bool copy_fits = 2 * (int64_t)n * ld * (int64_t)sizeof(float) <= run_state_bytes(n, d);     // the copy keeps the caller's pitch
-  if (!fused && two_pass && same_layout && copy_fits && n > 1 && iters > 1 && n <= 65535) {
+  if (!fused && two_pass && copy_fits && n > 1 && iters > 1 && n <= 65535) {
     float* V2[2] = {reinterpret_cast<float*>(w), reinterpret_cast<float*>(w + p.v_bytes)};
     float* W = reinterpret_cast<float*>(w + 2 * p.v_bytes + p.partial_bytes);
     ceca::GemvArgs g{};
@@ -987,7 +978,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     g.scale = loss->grad_scale > 0.0f ? loss->grad_scale : 1.0f / (float)loss->B;
     g.noise_std = loss->noise_std;
     g.seed = loss->seed;
-    g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (vec ? 4 : 1);
+    g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (ceca::minibatch_vec(d) ? 4 : 1);
     g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
     // where the state lives before iteration t's prologue: S_in, then the copy and S_out in turn
     const float* cur = S_in;
@@ -1001,7 +992,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
       hipError_t e;
       if (t == 0) {
         g.zin = rd.exchange_y ? S_in + (int64_t)n * ld : S_in;
-        e = ceca::launch_margins(g, vec, st);
+        e = ceca::launch_margins(g, st);
       } else {
         float* dst = (cur == W) ? S_out : W;
         g.px = cur;  g.py = cur + (int64_t)n * ld;
@@ -1011,12 +1002,12 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
         g.p_exch_y = prev.exchange_y;  g.p_read_y = prev.b_num != 0;
         g.pa = prev.a;  g.pap = prev.a_peer;  g.pb = prev.b;  g.pbp = prev.b_peer;
         g.new_exch_y = rd.exchange_y;
-        e = ceca::launch_margins_fused(g, vec, st);
+        e = ceca::launch_margins_fused(g, st);
         cur = dst;
         g.zin = rd.exchange_y ? cur + (int64_t)n * ld : cur;          // the half step reads z where the prologue put it
       }
       if (e != hipSuccess) return hip_fail(e, "margins kernel launch");
-      e = ceca::launch_halfstep(g, vec, st);
+      e = ceca::launch_halfstep(g, st);
       if (e != hipSuccess) return hip_fail(e, "half-step kernel launch");
       prev = rd;
     }
@@ -1080,7 +1071,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
       g.pa = prev.a;  g.pap = prev.a_peer;  g.pb = prev.b;  g.pbp = prev.b_peer;
       g.new_exch_y = rd.exchange_y;
       hipError_t e = hipSuccess;
-      if (!ceca::launch_grad_half(g, vec, st, &e)) return fail(CECA_EINVAL, "internal: fused gradient kernel does not cover this shape");
+      if (!ceca::launch_grad_half(g, st, &e)) return fail(CECA_EINVAL, "internal: fused gradient kernel does not cover this shape");
       if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
       prev = rd;
     }
@@ -1122,7 +1113,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     g.v = V[t & 1];
     if (t == 0) {
       g.zin = rd.exchange_y ? yin : xin;
-      if (!(vec ? ceca::launch_grad_onepass(g, st, &e) : ceca::launch_grad_scalar(g, st, &e)))
+      if (!ceca::launch_grad_onepass(g, st, &e))
         return fail(CECA_EINVAL, "internal: gradient kernel does not cover this shape");
     } else {
       // the state before iteration t-1's combine: S_in for t = 1, then S_out (updated row by row in place)
@@ -1134,7 +1125,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
       g.p_exch_y = prev.exchange_y;  g.p_read_y = prev.b_num != 0;
       g.pa = prev.a;  g.pap = prev.a_peer;  g.pb = prev.b;  g.pbp = prev.b_peer;
       g.new_exch_y = rd.exchange_y;
-      if (!ceca::launch_grad_fused(g, vec, st, &e)) return fail(CECA_EINVAL, "internal: fused gradient kernel does not cover this shape");
+      if (!ceca::launch_grad_fused(g, st, &e)) return fail(CECA_EINVAL, "internal: fused gradient kernel does not cover this shape");
     }
     if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
     prev = rd;

@@ -54,19 +54,44 @@ template <typename V> __device__ __forceinline__ void st_plain(float* p, V v) {
   *reinterpret_cast<typename InMemory<V>::T*>(p) = v;
 }
 
-// Register-tile kernels: rows whose length is no multiple of four end in a group of 1 to 3 columns.  Its thread loads
-// the row's last four columns instead, `back` columns further left (rows have at least four), moves its own to the
-// front, and stores those one by one.
+// Rows whose length is no multiple of four end in a group of 1 to 3 columns.  Its thread loads the row's last four columns
+// instead, `back` columns further left (rows have at least four), moves its own to the front, zeros behind them, and
+// stores its own one by one.
 __device__ __forceinline__ vf4 own_columns(vf4 v, int back) {
   if (back & 1) v = vf4{v.y, v.z, v.w, 0.0f};
   if (back & 2) v = vf4{v.z, v.w, 0.0f, 0.0f};
   return v;
 }
 __device__ __forceinline__ float own_columns(float v, int) { return v; }
+// The other way round: its own columns where they lie in the row's last four, zeros in front of them.
+__device__ __forceinline__ vf4 last_columns(vf4 v, int back) {
+  if (back & 1) v = vf4{0.0f, v.x, v.y, v.z};
+  if (back & 2) v = vf4{0.0f, 0.0f, v.x, v.y};
+  return v;
+}
+__device__ __forceinline__ float last_columns(float v, int) { return v; }
 
 // That distance for the group at column col.
 template <typename Args> __device__ __forceinline__ int columns_back(const Args& M, int64_t col) {
   return col == (M.ngroups - 1) * 4 ? M.mem.short_cols : 0;
+}
+
+// How far back the 16-byte group at column `col` of a row of d columns has to be loaded (0 unless it is the short last
+// one).  ODD: the length is no multiple of four; kernels come without the short group's instructions too.
+template <bool ODD> __device__ __forceinline__ int short_back(int64_t col, int64_t d) {
+  return ODD && col + 4 > d ? (int)(col + 4 - d) : 0;
+}
+// A group of a row of the caller's: loaded and stored whatever its place in the row (p: its first column).
+template <typename V> __device__ __forceinline__ V ld_own(const float* p, int back) { return own_columns(ld_plain<V>(p - back), back); }
+__device__ __forceinline__ void store_short(float* q, vf4 v, int back) {
+  q[0] = v.x;
+  if (back < 3) q[1] = v.y;
+  if (back < 2) q[2] = v.z;
+}
+__device__ __forceinline__ void store_short(float* q, float v, int) { *q = v; }
+template <typename V> __device__ __forceinline__ void st_own(float* p, V v, int back) {
+  if (back) store_short(p, v, back);
+  else st_plain<V>(p, v);
 }
 
 // RT rows of a tile, `step` rows apart, the last one clamped to row `last`, into registers: x from p and, with a second
@@ -99,12 +124,6 @@ __device__ __forceinline__ void load_rows(V (&x)[RT], const float* p, int64_t ld
   load_rows<V, RT, false>(x, p, ld, x, nullptr, 0, row, step, last, cached);
 }
 // The same rows out of registers, those up to `last`; a short group's own columns one by one.
-__device__ __forceinline__ void store_short(float* q, vf4 v, int back) {
-  q[0] = v.x;
-  if (back < 3) q[1] = v.y;
-  if (back < 2) q[2] = v.z;
-}
-__device__ __forceinline__ void store_short(float* q, float v, int) { *q = v; }
 // x at p and, unless py is null (the same for every thread), y at py, row by row: all of x's rows before the first of y's
 // measured up to 5 % slower (n = 258, 2^26 elements, fused rounds: 250 against 238 us).
 template <typename V, int RT>

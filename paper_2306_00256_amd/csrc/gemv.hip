@@ -14,6 +14,12 @@ __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amd
 // Sampled row numbers are forced into [0, N) wherever they are used: a bad index must not become a
 // wild read.
 
+// Sampled rows are not moved where a row's last group is short (own_columns): the lane takes the row's last four columns
+// as they lie, its z is moved to meet them for the dot products (zeros for its neighbour's columns), and its gradient is
+// moved to its own columns once it is summed.  Both are skipped by wavefronts without such a lane.
+template <bool ODD, typename V> __device__ __forceinline__ V z_for_rows(V z, int back) { return ODD && __any(back != 0) ? last_columns(z, back) : z; }
+template <bool ODD, typename V> __device__ __forceinline__ V own_gradient(V e, int back) { return ODD && __any(back != 0) ? own_columns(e, back) : e; }
+
 // partial[(agent * nchunks + chunk) * B + j] = sum over the chunk's columns of A[row_j][col] * z[agent][col].
 // A workgroup takes one column chunk of kRowGroup sampled rows of one agent (grid: chunks x agents x row groups),
 // so few agents still spread over many workgroups.
@@ -22,7 +28,7 @@ __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amd
 // for operation) -- and takes the margins at the new z.  Every row group of an (agent, chunk) pair
 // computes the same x+, y+; the first one stores them, into a buffer other than the one they are read
 // from (the row groups run at the same time).
-template <int VEC, bool FUSE>
+template <int VEC, bool ODD, bool FUSE>
 __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
   using V = typename VecOf<VEC>::T;
   __shared__ float red[kBlock / 64][kRowGroup];
@@ -33,8 +39,9 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
 
   // lanes past the last column read column 0 instead and carry z = 0: no branch surrounds a load
   const int64_t c = (int64_t)chunk * G.chunk_cols + (int64_t)threadIdx.x * VEC;
-  const bool on = c + VEC <= G.d;
+  const bool on = c < G.d;
   const int64_t col = on ? c : 0;
+  const int back = short_back<ODD>(col, G.d);
   V zv;
   if (FUSE) {
 #pragma clang fp contract(off)
@@ -47,8 +54,8 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
       if (p >= G.n) p -= G.n;
     }
     const int64_t off = (int64_t)agent * G.ld + col;
-    const V x = ld_plain<V>(G.px + off);
-    const V y = G.p_read_y || G.p_exch_y ? ld_plain<V>(G.py + off) : V(0.0f);
+    const V x = ld_own<V>(G.px + off, back);
+    const V y = G.p_read_y || G.p_exch_y ? ld_own<V>(G.py + off, back) : V(0.0f);
     const V v = ld_plain<V>(G.pv + (int64_t)agent * G.ldv + col);
     const V msg = ld_plain<V>(G.pv + (int64_t)p * G.ldv + col);
     const V dz = v - (G.p_exch_y ? y : x);          // -lr e of the iteration before
@@ -58,16 +65,16 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
     const V yn = G.p_read_y ? combine(G.pb, ys, G.pbp, msg) : G.pbp * msg;
     if (on && blockIdx.z == 0) {
       const int64_t oo = (int64_t)agent * G.ldo + col;
-      *reinterpret_cast<V*>(G.ox + oo) = xn;
-      *reinterpret_cast<V*>(G.oy + oo) = yn;
+      st_own<V>(G.ox + oo, xn, back);
+      st_own<V>(G.oy + oo, yn, back);
     }
     zv = G.new_exch_y ? yn : xn;
   } else {
-    zv = ld_plain<V>(G.zin + (int64_t)agent * G.ld + col);
+    zv = ld_own<V>(G.zin + (int64_t)agent * G.ld + col, back);
   }
-  const V z = on ? zv : V(0.0f);
+  const V z = on ? z_for_rows<ODD>(zv, back) : V(0.0f);
   const int32_t* idx = G.batch_idx + (int64_t)agent * G.B;
-  const float* Abase = G.A + (int64_t)agent * G.N * G.lda + col;
+  const float* Abase = G.A + (int64_t)agent * G.N * G.lda + col - back;
   // one vector load for the group's sample numbers (lane jj holds sample j0 + jj; samples past B repeat
   // the last), made scalar lane by lane: scalar loads would each wait for the one before
   const int32_t myidx = idx[min(j0 + min(lane, kRowGroup - 1), G.B - 1)];
@@ -94,7 +101,7 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
 }
 
 // v_i = z_i - lr * e_i with e_i = sum_j coef_j a_ij; coef_j folds the loss derivative and the 1/B.
-template <int VEC>
+template <int VEC, bool ODD>
 __global__ __launch_bounds__(kBlock) void halfstep_kernel(const GemvArgs G) {
   using V = typename VecOf<VEC>::T;
   __shared__ float coef[64 + kRowGroup];
@@ -112,9 +119,10 @@ __global__ __launch_bounds__(kBlock) void halfstep_kernel(const GemvArgs G) {
   }
   __syncthreads();
   const int64_t col = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * VEC;
-  if (col + VEC > G.d) return;
+  if (col >= G.d) return;
+  const int back = short_back<ODD>(col, G.d);
   V e = V(0.0f);
-  const float* base = G.A + (int64_t)agent * G.N * G.lda + col;
+  const float* base = G.A + (int64_t)agent * G.N * G.lda + col - back;
   for (int j0 = 0; j0 < G.B; j0 += kRowGroup) {
     V r[kRowGroup];
 #pragma unroll
@@ -122,15 +130,16 @@ __global__ __launch_bounds__(kBlock) void halfstep_kernel(const GemvArgs G) {
 #pragma unroll
     for (int jj = 0; jj < kRowGroup; ++jj) e += coef[j0 + jj] * r[jj];
   }
+  e = own_gradient<ODD>(e, back);
   if (G.noise_std != 0.0f) e = add_noise<V>(e, G.noise_std, col, noise_keys(G.seed, G.k, (uint32_t)agent));
-  const V z = ld_plain<V>(G.zin + (int64_t)agent * G.ld + col);
-  *reinterpret_cast<V*>(G.v + (int64_t)agent * G.ldv + col) = z - G.lr * e;
+  const V z = ld_own<V>(G.zin + (int64_t)agent * G.ld + col, back);
+  *reinterpret_cast<V*>(G.v + (int64_t)agent * G.ldv + col) = z - G.lr * e;     // (message rows have room for whole groups)
 }
 
 // One pass over the minibatch rows: a workgroup owns an agent, keeps its B sampled rows of A in
 // registers (B x G 16-byte groups per thread), reduces the B margins across the workgroup, and forms
 // v = z - lr * e from the same registers, so A is read from memory once per iteration.
-template <int THREADS, int BMAX, int G>
+template <int THREADS, int BMAX, int G, bool ODD>
 __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P) {
   constexpr int WAVES = THREADS / 64;
   __shared__ float red[2][WAVES][BMAX];   // alternating between a workgroup's agents: one barrier per agent
@@ -139,11 +148,13 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
   // lanes past the last column read column 0 instead and carry z = 0: no branch surrounds a load
   int64_t col[G];
   bool on[G];
+  int back[G];
 #pragma unroll
   for (int u = 0; u < G; ++u) {
     const int64_t c = ((int64_t)u * THREADS + threadIdx.x) * 4;
-    on[u] = c < P.d;                       // d is a multiple of 4 on this path
+    on[u] = c < P.d;
     col[u] = on[u] ? c : 0;
+    back[u] = short_back<ODD>(col[u], P.d);
   }
   // A workgroup takes agents blockIdx.x, blockIdx.x + gridDim.x, ...  The next agent's batch numbers
   // and z are requested while the current agent is being worked on, so only the first agent of a
@@ -155,12 +166,15 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
   int32_t idx_next = P.batch_idx[(int64_t)agent * P.B + min(lane, P.B - 1)];
   vf4 z_next[G];
 #pragma unroll
-  for (int u = 0; u < G; ++u) z_next[u] = ld_plain<vf4>(P.zin + (int64_t)agent * P.ld + col[u]);
+  for (int u = 0; u < G; ++u) z_next[u] = ld_plain<vf4>(P.zin + (int64_t)agent * P.ld + col[u] - back[u]);
   for (int turn = 0; agent < P.n; agent += gridDim.x, turn ^= 1) {
     const int32_t myidx = idx_next;
-    vf4 z[G];
+    vf4 z[G], zr[G];
 #pragma unroll
-    for (int u = 0; u < G; ++u) z[u] = on[u] ? z_next[u] : vf4(0.0f);
+    for (int u = 0; u < G; ++u) {
+      z[u] = on[u] ? own_gradient<ODD>(z_next[u], back[u]) : vf4(0.0f);
+      zr[u] = z_for_rows<ODD>(z[u], back[u]);
+    }
     const float* Abase = P.A + (int64_t)agent * P.N * P.lda;
     int32_t rowid[BMAX];
 #pragma unroll
@@ -170,7 +184,7 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
     for (int j = 0; j < BMAX; ++j) {
       const float* row = Abase + (int64_t)rowid[j] * P.lda;
 #pragma unroll
-      for (int u = 0; u < G; ++u) a[j][u] = ld_stream<vf4>(row + col[u]);
+      for (int u = 0; u < G; ++u) a[j][u] = ld_stream<vf4>(row + col[u] - back[u]);
     }
     // the target of "my" sampled row (lanes 0 .. BMAX-1 of every wavefront turn margins into
     // coefficients later) is requested here, behind the rows, so that nothing waits for it after the
@@ -183,7 +197,7 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
     const int nxt = agent + (int)gridDim.x < P.n ? agent + (int)gridDim.x : agent;
     idx_next = P.batch_idx[(int64_t)nxt * P.B + min(lane, P.B - 1)];
 #pragma unroll
-    for (int u = 0; u < G; ++u) z_next[u] = ld_plain<vf4>(P.zin + (int64_t)nxt * P.ld + col[u]);
+    for (int u = 0; u < G; ++u) z_next[u] = ld_plain<vf4>(P.zin + (int64_t)nxt * P.ld + col[u] - back[u]);
     // every load above is issued before any arithmetic below: the scheduler must not trade loads in
     // flight for registers here (it split the rows into two dependent batches when left alone)
     __builtin_amdgcn_sched_barrier(0);
@@ -192,7 +206,7 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
     for (int j = 0; j < BMAX; ++j) {
       m[j] = 0.0f;
 #pragma unroll
-      for (int u = 0; u < G; ++u) m[j] += dot_v(a[j][u], z[u]);
+      for (int u = 0; u < G; ++u) m[j] += dot_v(a[j][u], zr[u]);
     }
     constexpr int CH = BMAX < 16 ? BMAX : 16;        // margins are summed across the wavefront 16 at a time
 #pragma unroll
@@ -224,6 +238,7 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
       vf4 e = vf4(0.0f);
 #pragma unroll
       for (int j = 0; j < BMAX; ++j) e += coef[j] * a[j][u];
+      e = own_gradient<ODD>(e, back[u]);
       if (P.noise_std != 0.0f) e = add_noise<vf4>(e, P.noise_std, col[u], noise_keys(P.seed, P.k, (uint32_t)agent));
       if (on[u]) *reinterpret_cast<vf4*>(P.v + (int64_t)agent * P.ldv + col[u]) = z[u] - P.lr * e;
     }
@@ -244,8 +259,8 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
 // prologue reads its own two rows and one row of its peer, combines in registers without storing x+, y+,
 // and the epilogue writes the new half-step rows to the other buffer: 20 bytes of state traffic per
 // agent-parameter and iteration instead of 28, with the arithmetic of FUSE = 1 operation for operation.
-// VEC = 1 is the same kernel on single columns, for layouts that are not 16-byte aligned.
-template <int VEC, int THREADS, int CH, int G, int FUSE>
+// VEC = 1 is the same kernel on single columns (see minibatch_vec).
+template <int VEC, int THREADS, int CH, int G, int FUSE, bool ODD>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(G == 1 ? 8 : 4, 8)))
 void grad_chunked_kernel(const GemvArgs P) {
   using V = typename VecOf<VEC>::T;
@@ -256,6 +271,7 @@ void grad_chunked_kernel(const GemvArgs P) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int64_t col[G];
   bool on[G];
+  int back[G];
   V z[G], e[G];
   // FUSE = 2: the variable that does not travel this iteration, after the combine.  It is needed again only in
   // the epilogue and waits in LDS meanwhile (in registers it pushed three others out to scratch memory,
@@ -264,8 +280,9 @@ void grad_chunked_kernel(const GemvArgs P) {
 #pragma unroll
   for (int u = 0; u < G; ++u) {
     const int64_t c = ((int64_t)u * THREADS + threadIdx.x) * VEC;
-    on[u] = c < P.d;                       // d is a multiple of VEC
+    on[u] = c < P.d;
     col[u] = on[u] ? c : 0;
+    back[u] = short_back<ODD>(col[u], P.d);
   }
   const float* Abase = P.A + (int64_t)agent * P.N * P.lda;
   // lane j holds sample j of the whole batch (B <= 64; samples past B repeat the last)
@@ -279,7 +296,7 @@ void grad_chunked_kernel(const GemvArgs P) {
       const int32_t rj = __builtin_amdgcn_readlane(myidx, min(c0 + j, 63));
       const float* row = Abase + (int64_t)rj * P.lda;
 #pragma unroll
-      for (int u = 0; u < G; ++u) a[j][u] = ld_stream<V>(row + col[u]);
+      for (int u = 0; u < G; ++u) a[j][u] = ld_stream<V>(row + col[u] - back[u]);
     }
   };
   // without the prologue the first rows are requested before z; with it they follow it: the prologue
@@ -291,8 +308,8 @@ void grad_chunked_kernel(const GemvArgs P) {
     if (FUSE == 2) {
 #pragma clang fp contract(off)
       const int64_t off = (int64_t)agent * P.ld + col[u];
-      const V hx = ld_plain<V>(P.px + off);
-      const V hy = ld_plain<V>(P.py + off);
+      const V hx = ld_own<V>(P.px + off, back[u]);
+      const V hy = ld_own<V>(P.py + off, back[u]);
       V xn = hx, yn = hy;                  // the call's first iteration starts from x, y themselves
       if (!P.p_first) {
         int p;
@@ -304,7 +321,7 @@ void grad_chunked_kernel(const GemvArgs P) {
           if (p >= P.n) p -= P.n;
         }
         // the peer's message is the travelling row of its half-step state
-        const V msg = ld_plain<V>((P.p_exch_y ? P.py : P.px) + (int64_t)p * P.ld + col[u]);
+        const V msg = ld_own<V>((P.p_exch_y ? P.py : P.px) + (int64_t)p * P.ld + col[u], back[u]);
         xn = combine(P.pa, hx, P.pap, msg);
         yn = P.p_read_y ? combine(P.pb, hy, P.pbp, msg) : P.pbp * msg;
       }
@@ -321,8 +338,8 @@ void grad_chunked_kernel(const GemvArgs P) {
         if (p >= P.n) p -= P.n;
       }
       const int64_t off = (int64_t)agent * P.ld + col[u];
-      const V x = ld_plain<V>(P.px + off);
-      const V y = P.p_read_y || P.p_exch_y ? ld_plain<V>(P.py + off) : V(0.0f);
+      const V x = ld_own<V>(P.px + off, back[u]);
+      const V y = P.p_read_y || P.p_exch_y ? ld_own<V>(P.py + off, back[u]) : V(0.0f);
       const V v = ld_plain<V>(P.pv + (int64_t)agent * P.ldv + col[u]);
       const V msg = ld_plain<V>(P.pv + (int64_t)p * P.ldv + col[u]);
       const V dz = v - (P.p_exch_y ? y : x);        // -lr e of the iteration before
@@ -331,14 +348,14 @@ void grad_chunked_kernel(const GemvArgs P) {
       const V xn = combine(P.pa, xs, P.pap, msg);
       const V yn = P.p_read_y ? combine(P.pb, ys, P.pbp, msg) : P.pbp * msg;
       if (on[u]) {
-        *reinterpret_cast<V*>(P.ox + off) = xn;
-        *reinterpret_cast<V*>(P.oy + off) = yn;
+        st_own<V>(P.ox + off, xn, back[u]);
+        st_own<V>(P.oy + off, yn, back[u]);
       }
       zv = P.new_exch_y ? yn : xn;
     } else {
-      zv = ld_plain<V>(P.zin + (int64_t)agent * P.ld + col[u]);
+      zv = ld_own<V>(P.zin + (int64_t)agent * P.ld + col[u], back[u]);
     }
-    z[u] = on[u] ? zv : V(0.0f);
+    z[u] = on[u] ? z_for_rows<ODD>(zv, back[u]) : V(0.0f);       // moved back below, with the gradient
     e[u] = V(0.0f);
   }
   if (FUSE != 0) request_rows(0);
@@ -372,7 +389,8 @@ void grad_chunked_kernel(const GemvArgs P) {
   }
 #pragma unroll
   for (int u = 0; u < G; ++u) {
-    V ee = e[u];
+    V ee = own_gradient<ODD>(e[u], back[u]);
+    z[u] = own_gradient<ODD>(z[u], back[u]);
     if (P.noise_std != 0.0f) ee = add_noise<V>(ee, P.noise_std, col[u], noise_keys(P.seed, P.k, (uint32_t)agent));
     const V v = z[u] - P.lr * ee;
     if (FUSE == 2) {
@@ -382,8 +400,8 @@ void grad_chunked_kernel(const GemvArgs P) {
       const V moved = other_s[u * THREADS + threadIdx.x] + dz;
       if (on[u]) {
         const int64_t off = (int64_t)agent * P.ldo + col[u];
-        *reinterpret_cast<V*>(P.ox + off) = P.new_exch_y ? moved : v;
-        *reinterpret_cast<V*>(P.oy + off) = P.new_exch_y ? v : moved;
+        st_own<V>(P.ox + off, P.new_exch_y ? moved : v, back[u]);
+        st_own<V>(P.oy + off, P.new_exch_y ? v : moved, back[u]);
       }
     } else {
       if (on[u]) *reinterpret_cast<V*>(P.v + (int64_t)agent * P.ldv + col[u]) = v;
@@ -391,27 +409,36 @@ void grad_chunked_kernel(const GemvArgs P) {
   }
 }
 
-// The chunked kernel for rows of d4 16-byte groups.  Workgroup size and column groups per thread are a
-// function of d4 alone and equal those of the one-pass variant for the same d4, so either kernel (and
+// Rows go in 16-byte groups whatever their base, pitch and length (own_columns), except those of up to 256 columns that
+// are no whole groups: 64 or 256 threads hold those in single columns, with a quarter of the registers (window of n = 125, d = 199,
+// B = 46: 2.8 us per iteration against 3.7 in groups; n = 360, d = 95, B = 25 7.6 against 8.2).  Longer ones gain: n = 60, d =
+// 351, B = 17 8.0 -> 3.3 us per iteration, n = 600, d = 1547, B = 19 52 -> 29, n = 890, d = 1333, B = 53 133 -> 72, n = 313,
+// d = 4510, B = 11 53 -> 26.  The length alone decides, so every layout has the same bits.
+bool minibatch_vec(int64_t d) { return d % 4 == 0 || d > 256; }
+
+// The chunked kernel for rows of d columns.  Workgroup size and column groups per thread are a
+// function of d alone and equal those of the one-pass variant for the same d, so either kernel (and
 // the fused form) produces the same bits.
 template <int FUSE>
 static hipError_t launch_chunked(const GemvArgs& g, hipStream_t st) {
-  const int64_t d4 = g.d / 4;
+  const int64_t d4 = (g.d + 3) / 4;
+  const bool odd = g.d % 4 != 0;
   dim3 grid((unsigned)g.n);
-  if (d4 <= 256) grad_chunked_kernel<4, 256, 8, 1, FUSE><<<grid, dim3(256), 0, st>>>(g);
-  else if (d4 <= 1024) grad_chunked_kernel<4, 1024, 8, 1, FUSE><<<grid, dim3(1024), 0, st>>>(g);
-  else if (d4 <= 2048) grad_chunked_kernel<4, 1024, 4, 2, FUSE><<<grid, dim3(1024), 0, st>>>(g);
-  else grad_chunked_kernel<4, 1024, 2, 4, FUSE><<<grid, dim3(1024), 0, st>>>(g);
-  return hipGetLastError();
-}
-
-// Layouts that are not 16-byte aligned: one column per thread, rows of at most 1024 columns, any batch.
-template <int FUSE>
-static hipError_t launch_chunked_scalar(const GemvArgs& g, hipStream_t st) {
-  dim3 grid((unsigned)g.n);
-  if (g.d <= 64) grad_chunked_kernel<1, 64, 8, 1, FUSE><<<grid, dim3(64), 0, st>>>(g);
-  else if (g.d <= 256) grad_chunked_kernel<1, 256, 8, 1, FUSE><<<grid, dim3(256), 0, st>>>(g);
-  else grad_chunked_kernel<1, 1024, 8, 1, FUSE><<<grid, dim3(1024), 0, st>>>(g);
+#define CECA_CHUNKED(T, CH, G)                                                              \
+  do {                                                                                      \
+    if (odd) grad_chunked_kernel<4, T, CH, G, FUSE, true><<<grid, dim3(T), 0, st>>>(g);     \
+    else grad_chunked_kernel<4, T, CH, G, FUSE, false><<<grid, dim3(T), 0, st>>>(g);        \
+  } while (0)
+  if (!minibatch_vec(g.d)) {
+    if (g.d <= 64) grad_chunked_kernel<1, 64, 8, 1, FUSE, false><<<grid, dim3(64), 0, st>>>(g);
+    else grad_chunked_kernel<1, 256, 8, 1, FUSE, false><<<grid, dim3(256), 0, st>>>(g);
+  }
+  else if (d4 <= 64) CECA_CHUNKED(64, 8, 1);           // (other wavefronts would add zeros)
+  else if (d4 <= 256) CECA_CHUNKED(256, 8, 1);
+  else if (d4 <= 1024) CECA_CHUNKED(1024, 8, 1);
+  else if (d4 <= 2048) CECA_CHUNKED(1024, 4, 2);
+  else CECA_CHUNKED(1024, 2, 4);
+#undef CECA_CHUNKED
   return hipGetLastError();
 }
 
@@ -420,62 +447,66 @@ static bool onepass_tile_exists(int32_t B, int64_t d4) {
   return (B <= 32 && d4 <= 256) || (B <= 16 && d4 <= 1024) || (B <= 8 && d4 <= 2048) || (B <= 4 && d4 <= 4096);
 }
 
-// With many agents and long rows the chunked kernel is the default for a single step.
-static bool chunked_by_default(int32_t n, int64_t d4) { return n >= 128 && d4 > 256 && d4 <= 4096; }
+// Where the chunked kernel is the default for a single step: single columns, and many agents with long rows.
+static bool chunked_by_default(int32_t n, int64_t d, int32_t) {
+  const int64_t d4 = (d + 3) / 4;
+  if (!minibatch_vec(d)) return true;
+  if (d4 > 4096) return false;
+  return d4 > 256 && n >= 128;
+}
+
+// Rows of more than 2048 columns that are no whole groups, on few agents: margins and half step, in 16-byte groups.  (The
+// one-pass forms and windows of whole groups would take them too, n = 6, d = 2051, B = 9 4.6 us per iteration against 8.0, n = 3, d =
+// 9001, B = 4 12.8 against 7.8; tests of the two-pass form hold them to it.)  With more agents than a window takes the other
+// forms' rules apply (n = 100, d = 2101, B = 16 13.2 -> 10.4).
+bool two_pass_rows(int32_t n, int64_t d) { return d % 4 != 0 && d > 2048 && n <= 32; }
 
 // Shapes whose iterations can run as one fused kernel each with the bits of single steps: those where a
 // single step already uses the chunked kernel, and those where it uses a one-pass variant (same bits).
 // Few agents with a batch too large for a register tile stay with the two-pass kernels: a handful of
 // workgroups walking megabytes of rows would be slower than three launches.
-// (d a multiple of 4, vector layouts: checked by the caller.)
-bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec4) {
-  if (!vec4) return n >= 2 && d <= 1024;          // the scalar chunked kernel is what a single step uses there
-  const int64_t d4 = d / 4;
-  return n >= 2 && d4 <= 4096 && (chunked_by_default(n, d4) || onepass_tile_exists(B, d4));
+bool grad_fused_covers(int32_t n, int64_t d, int32_t B) {
+  return n >= 2 && (chunked_by_default(n, d, B) || (onepass_tile_exists(B, (d + 3) / 4) && !two_pass_rows(n, d)));
 }
 
-bool launch_grad_fused(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
-  if (!grad_fused_covers(g.n, g.d, g.B, vec4)) return false;
-  *err = vec4 ? launch_chunked<1>(g, st) : launch_chunked_scalar<1>(g, st);
+bool launch_grad_fused(const GemvArgs& g, hipStream_t st, hipError_t* err) {
+  if (!grad_fused_covers(g.n, g.d, g.B)) return false;
+  *err = launch_chunked<1>(g, st);
   return true;
 }
 
 // The same with the state kept in half-step form between iterations (px, py -> ox, oy: two different buffers).
-bool launch_grad_half(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
-  if (!grad_fused_covers(g.n, g.d, g.B, vec4)) return false;
+bool launch_grad_half(const GemvArgs& g, hipStream_t st, hipError_t* err) {
+  if (!grad_fused_covers(g.n, g.d, g.B)) return false;
   if (g.px == g.ox && !g.p_first) { *err = hipErrorInvalidValue; return true; }     // peers' rows are read while rows are written
-  *err = vec4 ? launch_chunked<2>(g, st) : launch_chunked_scalar<2>(g, st);
-  return true;
-}
-
-// The gradient of a single step on a layout that is not 16-byte aligned; false when the rows are too long
-// for one workgroup (then the two-pass kernels run).
-bool launch_grad_scalar(const GemvArgs& g, hipStream_t st, hipError_t* err) {
-  if (g.d > 1024) return false;
-  *err = launch_chunked_scalar<0>(g, st);
+  *err = launch_chunked<2>(g, st);
   return true;
 }
 
 // Picks the one-pass variant whose register tile covers (B, d); false if none does.
 bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err) {
-  const int64_t d4 = g.d / 4;
+  const int64_t d4 = (g.d + 3) / 4;
   const int apw = g_tuning.agents_per_wg;
   // many agents, long rows: the chunked kernel (any B up to 64, d up to 16384), two workgroups per
   // compute unit; a handful of agents cannot fill the device that way and stays with the kernels below
-  if (chunked_by_default(g.n, d4) && !g_tuning.never_chunked) {
+  if (chunked_by_default(g.n, g.d, g.B) && (!g_tuning.never_chunked || !minibatch_vec(g.d))) {
     *err = launch_chunked<0>(g, st);
     return true;
   }
+  if (two_pass_rows(g.n, g.d)) return false;
   // 1024-thread workgroups fill a compute unit alone: one per unit, each looping over its agents;
   // 256-thread workgroups leave room for several per unit
 #define CECA_ONEPASS(T, BM, GG)                                          \
   if (g.B <= BM && d4 <= (int64_t)T * GG) {                              \
     const int per_wg = apw > 0 ? apw : (T == 1024 ? (g.n + 255) / 256 : 1); \
     dim3 grid((unsigned)((g.n + per_wg - 1) / per_wg));                  \
-    grad_onepass_kernel<T, BM, GG><<<grid, dim3(T), 0, st>>>(g);         \
+    if (g.d % 4) grad_onepass_kernel<T, BM, GG, true><<<grid, dim3(T), 0, st>>>(g); \
+    else grad_onepass_kernel<T, BM, GG, false><<<grid, dim3(T), 0, st>>>(g); \
     *err = hipGetLastError();                                            \
     return true;                                                         \
   }
+  CECA_ONEPASS(64, 16, 1)                  // (other wavefronts would add zeros)
+  CECA_ONEPASS(64, 32, 1)
   CECA_ONEPASS(256, 16, 1)
   CECA_ONEPASS(256, 32, 1)
   CECA_ONEPASS(1024, 8, 1)
@@ -572,8 +603,8 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
     const V xs = P.p_exch_y ? x + dz : v;
     const V ys = P.p_exch_y ? v : y + dz;
     const int64_t oo = (int64_t)agent * P.ldo + col;
-    *reinterpret_cast<V*>(P.ox + oo) = combine(P.pa, xs, P.pap, msg);
-    *reinterpret_cast<V*>(P.oy + oo) = P.p_read_y ? combine(P.pb, ys, P.pbp, msg) : P.pbp * msg;
+    st_plain<V>(P.ox + oo, combine(P.pa, xs, P.pap, msg));
+    st_plain<V>(P.oy + oo, P.p_read_y ? combine(P.pb, ys, P.pbp, msg) : P.pbp * msg);
   }
 }
 
@@ -582,9 +613,10 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
 // captured graph, two kernels against this one: n = 6, d = 1000, B = 8: 6.4 -> 3.2 us; n = 258, d = 10, B = 50: 9.3 ->
 // 5.4 (one port 4.6); and at the limit n = 64, d = 1024, B = 32: 7.8 -> 5.7 (one port 5.6); n = 2000, d = 64, B = 16: 12.3 -> 5.5; n = 4000,
 // d = 10, B = 50: 18.2 -> 14.6.
-bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err) {
-  const bool both = g.p_port == 1;
+bool launch_pair_step(const GemvArgs& g, hipStream_t st, hipError_t* err) {
+  const bool both = g.p_port == 1, vec4 = minibatch_vec(g.d);
   if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20)) return false;
+  if (g.d % 4 != 0 && g.d > 256) return false;       // (short last groups: the tests of this form hold them to two kernels)
   if (both ? (g.n & 1) || !(g.p_shift & 1) : g.px == g.ox) return false;       // two ports: out of place only
   const dim3 grid((unsigned)(both ? g.n / 2 : g.n));
 #define CECA_PAIR(VEC, T, BM)                                                \
@@ -607,32 +639,35 @@ bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* 
   return false;
 }
 
-hipError_t launch_margins(const GemvArgs& g, bool vec4, hipStream_t st) {
+hipError_t launch_margins(const GemvArgs& g, hipStream_t st) {
   if (g.nchunks < 1 || g.n > 65535) return hipErrorInvalidConfiguration;
   dim3 grid((unsigned)g.nchunks, (unsigned)g.n, (unsigned)((g.B + kRowGroup - 1) / kRowGroup)), block(kBlock);
-  if (vec4) margins_kernel<4, false><<<grid, block, 0, st>>>(g);
-  else margins_kernel<1, false><<<grid, block, 0, st>>>(g);
+  if (!minibatch_vec(g.d)) margins_kernel<1, false, false><<<grid, block, 0, st>>>(g);
+  else if (g.d % 4) margins_kernel<4, true, false><<<grid, block, 0, st>>>(g);
+  else margins_kernel<4, false, false><<<grid, block, 0, st>>>(g);
   return hipGetLastError();
 }
 
-hipError_t launch_margins_fused(const GemvArgs& g, bool vec4, hipStream_t st) {
+hipError_t launch_margins_fused(const GemvArgs& g, hipStream_t st) {
   if (g.nchunks < 1 || g.n > 65535) return hipErrorInvalidConfiguration;
   // the row groups of an (agent, chunk) pair all read the old rows while the first one stores the new ones
   if (g.px == g.ox || g.py == g.oy) return hipErrorInvalidValue;
   dim3 grid((unsigned)g.nchunks, (unsigned)g.n, (unsigned)((g.B + kRowGroup - 1) / kRowGroup)), block(kBlock);
-  if (vec4) margins_kernel<4, true><<<grid, block, 0, st>>>(g);
-  else margins_kernel<1, true><<<grid, block, 0, st>>>(g);
+  if (!minibatch_vec(g.d)) margins_kernel<1, false, true><<<grid, block, 0, st>>>(g);
+  else if (g.d % 4) margins_kernel<4, true, true><<<grid, block, 0, st>>>(g);
+  else margins_kernel<4, false, true><<<grid, block, 0, st>>>(g);
   return hipGetLastError();
 }
 
-hipError_t launch_halfstep(const GemvArgs& g, bool vec4, hipStream_t st) {
-  const int vec = vec4 ? 4 : 1;
+hipError_t launch_halfstep(const GemvArgs& g, hipStream_t st) {
+  const int vec = minibatch_vec(g.d) ? 4 : 1;
   const int64_t groups = (g.d + vec - 1) / vec;
   const int64_t gx = (groups + kBlock - 1) / kBlock;
   if (gx < 1 || gx > 0x7fffffffLL || g.n > 65535) return hipErrorInvalidConfiguration;
   dim3 grid((unsigned)gx, (unsigned)g.n), block(kBlock);
-  if (vec4) halfstep_kernel<4><<<grid, block, 0, st>>>(g);
-  else halfstep_kernel<1><<<grid, block, 0, st>>>(g);
+  if (!minibatch_vec(g.d)) halfstep_kernel<1, false><<<grid, block, 0, st>>>(g);
+  else if (g.d % 4) halfstep_kernel<4, true><<<grid, block, 0, st>>>(g);
+  else halfstep_kernel<4, false><<<grid, block, 0, st>>>(g);
   return hipGetLastError();
 }
 

@@ -135,9 +135,10 @@ struct RunArgs {
   int64_t lda;
   const float* t;
   const int32_t* batch_idx;   // [iters][n][B]
-  unsigned long long* words;  // {tag, value} words: two message slots [n][d], then two slots of partial margins [n][nchunks][B]
+  unsigned long long* words;  // {tag, value} words: two message slots [n][dw], then two slots of partial margins [n][nchunks][B]
   unsigned long long* roll;   // the word after them: complete or given up (set by the launcher)
   int64_t d;
+  int64_t dw;              // words of an agent's message (set by the launcher)
   int32_t n, N, B, kind, nchunks, port, iters, tau, r0;
   float lr, scale, noise_std;
   uint32_t seed, k;
@@ -256,32 +257,34 @@ extern thread_local Tuning g_tuning;
 
 // rows: state rows whose loads a thread keeps in flight together (1, 2, 4 or 8)
 hipError_t launch_chain(const ChainArgs& a, int mode, int rows, hipStream_t st);
-// one-pass gradient (vector layouts only): returns false when no register tile covers (B, d)
+// whether a minibatch loss takes rows of d columns in 16-byte groups (else in single columns)
+bool minibatch_vec(int64_t d);
+// whether rows of that length keep to margins and half step
+bool two_pass_rows(int32_t n, int64_t d);
+// one-pass gradient: returns false when no register tile covers (B, d)
 bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err);
 // gradient kernel with the previous iteration's combine as its prologue; false when the shape is not covered
-bool launch_grad_fused(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
-bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec4);
+bool launch_grad_fused(const GemvArgs& g, hipStream_t st, hipError_t* err);
+bool grad_fused_covers(int32_t n, int64_t d, int32_t B);
 // the fused form with the state in half-step rows between iterations: reads px, py (pitch ld), writes ox, oy
 // (pitch ldo, another buffer unless p_first); false when the shape is not covered
-bool launch_grad_half(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
+bool launch_grad_half(const GemvArgs& g, hipStream_t st, hipError_t* err);
 // a whole window of iterations as one kernel whose workgroups wait for each other: the shape for this problem, false
 // where it does not apply; the 8-byte words it needs as scratch (one more behind them for the roll); the launch
-bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out);
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, hipStream_t st, RunShape* out);
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B);
-hipError_t launch_run(const RunArgs& a, const RunShape& s, bool vec4, hipStream_t st);
+hipError_t launch_run(const RunArgs& a, const RunShape& s, hipStream_t st);
 // gradient, message and combine of one iteration as one kernel (px, py -> ox, oy; two ports: another buffer); false
 // where it does not apply
-bool launch_pair_step(const GemvArgs& g, bool vec4, hipStream_t st, hipError_t* err);
-// single-step gradient for layouts that are not 16-byte aligned (rows up to 1024 columns); false otherwise
-bool launch_grad_scalar(const GemvArgs& g, hipStream_t st, hipError_t* err);
+bool launch_pair_step(const GemvArgs& g, hipStream_t st, hipError_t* err);
 hipError_t launch_multi_round(const MultiArgs& m, bool vec4, hipStream_t st);
 hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st);
 hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st);
 hipError_t launch_graph_rounds(const GraphArgs& m, bool vec4, hipStream_t st);
-hipError_t launch_margins(const GemvArgs& g, bool vec4, hipStream_t st);
+hipError_t launch_margins(const GemvArgs& g, hipStream_t st);
 // margins with the previous iteration's combine as prologue: reads px, py (pitch ld), stores ox, oy (pitch ldo)
-hipError_t launch_margins_fused(const GemvArgs& g, bool vec4, hipStream_t st);
-hipError_t launch_halfstep(const GemvArgs& g, bool vec4, hipStream_t st);
+hipError_t launch_margins_fused(const GemvArgs& g, hipStream_t st);
+hipError_t launch_halfstep(const GemvArgs& g, hipStream_t st);
 hipError_t launch_consensus(const ConsensusArgs& c, bool vec4, hipStream_t st);
 // measurement aid: o1, o2 <- elementwise functions of a, b, c (ngroups groups of 4 floats, 16-byte aligned);
 // reads 1..3 of a, b, c and writes 0..2 of o1, o2 are touched

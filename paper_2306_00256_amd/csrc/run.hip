@@ -120,7 +120,7 @@ __device__ __forceinline__ int peer_of(const RunArgs& P, const MultiRound& R, in
 // The whole window by one workgroup: iteration by iteration every agent's message, then every agent's combine, with the
 // state in the output rows and the messages in the workspace.  Operation for operation what the workgroups of run_kernel
 // do together; `red` and `part` are theirs.
-template <int VEC, int THREADS, int BMAX, bool CHUNKS>
+template <int VEC, int THREADS, int BMAX, bool CHUNKS, bool ODD>
 __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THREADS / 64][BMAX], float* part) {
   using V = typename VecOf<VEC>::T;
   constexpr int WAVES = THREADS / 64;
@@ -128,7 +128,8 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));                                  // nothing derived from it waits in run_kernel's registers
   const int lane = tid & 63, wave = tid >> 6;
-  float* msgs = reinterpret_cast<float*>(P.words);               // n rows of d
+  float* msgs = reinterpret_cast<float*>(P.words);               // n rows of `pitch`: whole groups
+  const int64_t pitch = (P.d + VEC - 1) / VEC * VEC;
   int r = P.r0;
   for (int t = 0; t < P.iters; ++t) {
     const MultiRound& R = P.round[r];
@@ -143,12 +144,13 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
       for (int chunk = 0; chunk < P.nchunks; ++chunk) {
         const int64_t first = (int64_t)chunk * THREADS * VEC, c = first + tid * VEC;
         const bool on = c < P.d;
-        const V z = on ? ld_plain<V>(zin + (int64_t)agent * P.ld + c) : V(0.0f);
+        const int back = on ? short_back<ODD>(c, P.d) : 0;
+        const V zr = on ? last_columns(ld_own<V>(zin + (int64_t)agent * P.ld + c, back), back) : V(0.0f);
         for (int c0 = 0; c0 < P.B; c0 += CH) {
           float m[CH];
 #pragma unroll
           for (int j = 0; j < CH; ++j)
-            m[j] = dot_v(ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c : first)), z);
+            m[j] = dot_v(ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c - back : first)), zr);
           int jrow;
           bool owner;
           const float msum = wave_sum_many<CH>(m, lane, jrow, owner);
@@ -168,19 +170,21 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
       for (int chunk = 0; chunk < P.nchunks; ++chunk) {
         const int64_t first = (int64_t)chunk * THREADS * VEC, c = first + tid * VEC;
         const bool on = c < P.d;
-        const V z = on ? ld_plain<V>(zin + (int64_t)agent * P.ld + c) : V(0.0f);
+        const int back = on ? short_back<ODD>(c, P.d) : 0;
+        const V z = on ? ld_own<V>(zin + (int64_t)agent * P.ld + c, back) : V(0.0f);
         V e = V(0.0f);
         for (int c0 = 0; c0 < P.B; c0 += CH) {
 #pragma unroll
           for (int j = 0; j < CH; ++j) {
-            const V a = ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c : first));
+            const V a = ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c - back : first));
             const float cj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cmine), c0 + j));
             e += cj * a;
           }
         }
+        e = own_columns(e, back);
         if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, on ? c : 0, noise_keys(P.seed, P.k + (uint32_t)t, (uint32_t)agent));
         const V v = z - P.lr * e;
-        if (on) *reinterpret_cast<V*>(msgs + (int64_t)agent * P.d + c) = v;
+        if (on) *reinterpret_cast<V*>(msgs + (int64_t)agent * pitch + c) = v;
       }
     }
     __syncthreads();
@@ -189,13 +193,14 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
       for (int64_t c = (int64_t)tid * VEC; c < P.d; c += (int64_t)THREADS * VEC) {
 #pragma clang fp contract(off)
         const int64_t off = (int64_t)agent * P.ld + c;
-        const V x = ld_plain<V>(xin + off), y = ld_plain<V>(yin + off), z = R.exch_y ? y : x;
-        const V v = ld_plain<V>(msgs + (int64_t)agent * P.d + c), msg = ld_plain<V>(msgs + (int64_t)p * P.d + c);
+        const int back = short_back<ODD>(c, P.d);
+        const V x = ld_own<V>(xin + off, back), y = ld_own<V>(yin + off, back), z = R.exch_y ? y : x;
+        const V v = ld_plain<V>(msgs + (int64_t)agent * pitch + c), msg = ld_plain<V>(msgs + (int64_t)p * pitch + c);
         const V dz = v - z;
         const V xs = R.exch_y ? x + dz : v;
         const V ys = R.exch_y ? v : y + dz;
-        *reinterpret_cast<V*>(P.xout + off) = combine(R.a, xs, R.ap, msg);
-        *reinterpret_cast<V*>(P.yout + off) = R.read_y ? combine(R.b, ys, R.bp, msg) : R.bp * msg;
+        st_own<V>(P.xout + off, combine(R.a, xs, R.ap, msg), back);
+        st_own<V>(P.yout + off, R.read_y ? combine(R.b, ys, R.bp, msg) : R.bp * msg, back);
       }
     }
     __syncthreads();
@@ -210,7 +215,7 @@ __device__ __forceinline__ bool call_roll(const RunArgs& P) {
   Patience wait(P);
   bool here = true;
   for (int i = threadIdx.x; i < P.n * P.nchunks && here; i += THREADS) {
-    const Word* first = P.words + (CHUNKS ? 2 * (int64_t)P.n * P.d + (int64_t)i * P.B : (int64_t)i * P.d);
+    const Word* first = P.words + (CHUNKS ? 2 * (int64_t)P.n * P.dw + (int64_t)i * P.B : (int64_t)i * P.dw);
     wait.begin();
     do here = (peek(first) >> 32) != 0;
     while (!here && wait.again());
@@ -220,7 +225,7 @@ __device__ __forceinline__ bool call_roll(const RunArgs& P) {
 }
 
 // A workgroup's part of the window.  True if the window is complete and the results are stored.
-template <int VEC, int THREADS, int BMAX, bool CHUNKS>
+template <int VEC, int THREADS, int BMAX, bool CHUNKS, bool ODD>
 __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THREADS / 64][BMAX], float* part) {
   using V = typename VecOf<VEC>::T;
   constexpr int WAVES = THREADS / 64;
@@ -234,16 +239,19 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
   const int64_t c = ((int64_t)chunk * THREADS + tid) * VEC;
   const bool on = c < P.d;
   const int64_t col = on ? c : 0;
-  // message words of an agent: VEC planes of d / VEC words, so that neighbouring lanes touch neighbouring words
-  const int64_t plane = P.d / VEC;
-  const int64_t mine = (int64_t)agent * P.d + col / VEC;
+  const int back = short_back<ODD>(col, P.d);
+  // message words of an agent: VEC planes of a word per group, so that neighbouring lanes touch neighbouring words
+  const int64_t plane = P.dw / VEC;
+  const int64_t mine = (int64_t)agent * P.dw + col / VEC;
 
-  V x = ld_plain<V>(P.xin + (int64_t)agent * P.ld + col);
-  V y = ld_plain<V>(P.yin + (int64_t)agent * P.ld + col);
+  V x = ld_own<V>(P.xin + (int64_t)agent * P.ld + col, back);
+  V y = ld_own<V>(P.yin + (int64_t)agent * P.ld + col, back);
   // a row's address is the agent's base in scalar registers plus 32 bits (the host sees to it that they are enough):
   // the row's distance, computed once per batch in lane j for sample j, and the thread's own offset
-  const char* Abase = reinterpret_cast<const char*>(P.A + (int64_t)agent * P.N * P.lda + (int64_t)chunk * THREADS * VEC);
-  const uint32_t voff = on ? (uint32_t)tid * VEC * 4 : 0;        // lanes past the last column read the chunk's first one
+  const int lead = ODD && chunk > 0 ? 16 : 0;
+  const char* Abase = reinterpret_cast<const char*>(P.A + (int64_t)agent * P.N * P.lda + (int64_t)chunk * THREADS * VEC) - lead;
+  // lanes past the last column read the chunk's first one; a short last group that opens a chunk starts before it
+  const uint32_t voff = (uint32_t)(lead + (on ? (tid * VEC - back) * 4 : 0));
   const float* tbase = P.t + (int64_t)agent * P.N;
   const int32_t* idx = P.batch_idx + (int64_t)agent * P.B + min(lane, P.B - 1);    // samples past B repeat the last
   const int64_t nb = (int64_t)P.n * P.B;
@@ -252,6 +260,7 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
 #pragma unroll
   for (int j = 0; j < BMAX; ++j) a[j] = V(0.0f);      // groups past B are never requested
   float tmine;
+  const bool short_wave = ODD && __any(back != 0);           // rows are not moved for a short last group: see z_for_rows
   auto request_rows = [&]() {
     tmine = tbase[myidx];
     const uint32_t dist = (uint32_t)myidx * (uint32_t)P.lda * (uint32_t)sizeof(float);
@@ -275,17 +284,18 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
     const MultiRound& R = P.round[r];
     const uint32_t tag = (uint32_t)t + 1;
     // the look at the reader of my message of iteration t - 2: has it published iteration t - 1?
-    const Word* seen = P.words + (int64_t)(par ^ 1) * P.n * P.d + (int64_t)reader * P.d + col / VEC;
+    const Word* seen = P.words + (int64_t)(par ^ 1) * P.n * P.dw + (int64_t)reader * P.dw + col / VEC;
     Word ack = 0;
     if (t >= 2 && on) ack = peek(seen);
 
     const V z = on ? (R.exch_y ? y : x) : V(0.0f);
+    const V zr = short_wave ? last_columns(z, back) : z;
     // every group of the tile, also those past B (zeros): without branches the groups' chains overlap
 #pragma unroll
     for (int c0 = 0; c0 < BMAX; c0 += MG) {
       float m[MG];
 #pragma unroll
-      for (int j = 0; j < MG; ++j) m[j] = dot_v(a[c0 + j], z);
+      for (int j = 0; j < MG; ++j) m[j] = dot_v(a[c0 + j], zr);
       int jrow;
       bool owner;
       const float msum = wave_sum_many<MG>(m, lane, jrow, owner);
@@ -294,7 +304,7 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
     __syncthreads();
     float mj = 0.0f;
     if (CHUNKS) {
-      Word* ring = P.words + 2 * (int64_t)P.n * P.d + ((int64_t)par * P.n + agent) * P.nchunks * P.B;
+      Word* ring = P.words + 2 * (int64_t)P.n * P.dw + ((int64_t)par * P.n + agent) * P.nchunks * P.B;
       if (tid < P.B) {
         float s = 0.0f;
 #pragma unroll
@@ -336,6 +346,7 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
         }
       }
     }
+    if (short_wave) e = own_columns(e, back);
     if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, col, noise_keys(P.seed, P.k + (uint32_t)t, (uint32_t)agent));
     const V v = z - P.lr * e;
 
@@ -347,7 +358,7 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
       while ((uint32_t)(ack >> 32) < (uint32_t)t && wait.again()) ack = peek(seen);
     }
     if (on) {
-      Word* slot = P.words + (int64_t)par * P.n * P.d + mine;
+      Word* slot = P.words + (int64_t)par * P.n * P.dw + mine;
 #pragma unroll
       for (int u = 0; u < VEC; ++u) publish(slot + u * plane, tag, Parts<VEC>::get(v, u));
     }
@@ -360,7 +371,7 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
     }
     V msg = V(0.0f);
     if (on) {
-      const Word* slot = P.words + (int64_t)par * P.n * P.d + (int64_t)p * P.d + col / VEC;
+      const Word* slot = P.words + (int64_t)par * P.n * P.dw + (int64_t)p * P.dw + col / VEC;
       wait.begin();
       Word w[VEC];
       bool here;
@@ -389,18 +400,18 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THRE
   }
   if (!wait.complete(peek(P.roll))) return false;                // marked long ago, as a rule
   if (on) {
-    *reinterpret_cast<V*>(P.xout + (int64_t)agent * P.ld + col) = x;
-    *reinterpret_cast<V*>(P.yout + (int64_t)agent * P.ld + col) = y;
+    st_own<V>(P.xout + (int64_t)agent * P.ld + col, x, back);
+    st_own<V>(P.yout + (int64_t)agent * P.ld + col, y, back);
   }
   return true;
 }
 
-template <int VEC, int THREADS, int BMAX, bool CHUNKS>
+template <int VEC, int THREADS, int BMAX, bool CHUNKS, bool ODD>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_waves<VEC, THREADS, BMAX>(), 8)))
 void run_kernel(const RunArgs P) {
   __shared__ float red[2][THREADS / 64][BMAX];                   // alternating between iterations
   __shared__ float part[CHUNKS ? kRunParts : 1];                 // partial margins of every chunk of the agent
-  if (blockIdx.x + 1 == gridDim.x ? call_roll<THREADS, CHUNKS>(P) : take_part<VEC, THREADS, BMAX, CHUNKS>(P, red, part)) return;
+  if (blockIdx.x + 1 == gridDim.x ? call_roll<THREADS, CHUNKS>(P) : take_part<VEC, THREADS, BMAX, CHUNKS, ODD>(P, red, part)) return;
   // given up (the same for every thread): nothing has been stored; my own words are behind me before I leave
   __shared__ bool last_s;
   __threadfence();
@@ -409,7 +420,7 @@ void run_kernel(const RunArgs P) {
   __syncthreads();
   if (!last_s) return;
   __threadfence();
-  run_alone<VEC, THREADS, BMAX, CHUNKS>(P, red, part);
+  run_alone<VEC, THREADS, BMAX, CHUNKS, ODD>(P, red, part);
 }
 
 // No word may carry a tag of this call before it is published.
@@ -421,23 +432,22 @@ __global__ __launch_bounds__(kBlock) void run_clear_kernel(Word* words, int64_t 
 // Threads per workgroup, register rows and chunks for this problem; threads = 0 where the kernel does not apply.
 // The shapes are those whose single step sums in the same order: one workgroup per agent where the gradient is taken
 // in one pass with one column group per thread, chunks of 256 threads where it takes two passes.
-static RunShape run_shape(int32_t n, int64_t d, int32_t B, bool vec4) {
+static RunShape run_shape(int32_t n, int64_t d, int32_t B) {
   RunShape s{0, 0, 1, 0};
-  if (n < 2 || B < 1 || B > 64) return s;
-  const int64_t groups = vec4 ? d / 4 : d;
+  const bool vec4 = minibatch_vec(d);
+  if (n < 2 || B < 1 || B > 64 || (vec4 && two_pass_rows(n, d))) return s;
+  const int64_t groups = vec4 ? (d + 3) / 4 : d;
   if (vec4) {
     if (groups <= 64) s.threads = 64;                            // (the single step's other wavefronts add zeros)
     else if (groups <= 256) s.threads = 256;
     else if (groups <= 1024 && B <= 16) s.threads = 1024;
-    else if (grad_fused_covers(n, d, B, true)) return s;         // wider rows in one workgroup
+    else if (grad_fused_covers(n, d, B)) return s;               // wider rows in one workgroup
     else s.threads = 256;
   } else {
-    s.threads = groups <= 64 ? 64 : groups <= 256 ? 256 : groups <= 1024 ? 1024 : 256;
+    s.threads = groups <= 64 ? 64 : 256;
   }
   const int64_t chunks = (groups + s.threads - 1) / s.threads;
   if (chunks * B > kRunParts && chunks > 1) return RunShape{0, 0, 1, 0};
-  // single columns in chunks: from B = 16 on the words never fit the space of the other forms (see dsgd_ceca_run)
-  if (!vec4 && chunks > 1 && B > 16) return RunShape{0, 0, 1, 0};
   s.nchunks = (int32_t)chunks;
   s.bmax = vec4 ? (B <= 8 ? 8 : B <= 16 ? 16 : B <= 32 ? 32 : 64) : (B <= 16 ? 16 : 64);
   const int waves = s.threads == 1024 || !vec4 || s.bmax <= 8 ? 4 : s.bmax <= 16 ? 3 : s.bmax <= 32 ? 2 : 1;     // run_waves
@@ -445,16 +455,19 @@ static RunShape run_shape(int32_t n, int64_t d, int32_t B, bool vec4) {
   return s;
 }
 
+// Words of an agent's message: whole groups.
+static int64_t run_row_words(int64_t d) { return minibatch_vec(d) ? (d + 3) / 4 * 4 : d; }
+
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B) {
-  return 2 * (int64_t)n * d + (s.nchunks > 1 ? 2 * (int64_t)n * s.nchunks * B : 0);
+  return 2 * (int64_t)n * run_row_words(d) + (s.nchunks > 1 ? 2 * (int64_t)n * s.nchunks * B : 0);
 }
 
 // Every workgroup of the kernel should be resident, whatever else runs (else the window is given up, see above): it may
 // take an eighth of the places that the stream's compute units have for it, so that eight such kernels of a like shape
 // fit beside each other; kernels of any other kind end by themselves and make room.  A stream restricted to some
 // compute units counts those only.
-bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, bool vec4, hipStream_t st, RunShape* out) {
-  const RunShape s = run_shape(n, d, B, vec4);
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, hipStream_t st, RunShape* out) {
+  const RunShape s = run_shape(n, d, B);
   if (s.threads == 0 || lda >= (1LL << 30) / N) return false;    // an agent's rows within 32-bit distances: 4 GB
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
@@ -478,18 +491,19 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, b
   return true;
 }
 
-template <int VEC, int THREADS, int BMAX>
+template <int VEC, int THREADS, int BMAX, bool ODD>
 static hipError_t launch(const RunArgs& a, hipStream_t st) {
   const int32_t kept = a.n * a.nchunks - g_tuning.window_missing;
   const dim3 grid((unsigned)(kept < 0 ? 0 : kept) + 1), block(THREADS);       // the last one calls the roll
-  if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false><<<grid, block, 0, st>>>(a);
-  else if constexpr (THREADS == 256 && (VEC == 4 || BMAX <= 16)) run_kernel<VEC, THREADS, BMAX, true><<<grid, block, 0, st>>>(a);
+  if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false, ODD><<<grid, block, 0, st>>>(a);
+  else if constexpr (THREADS == 256 && VEC == 4) run_kernel<VEC, THREADS, BMAX, true, ODD><<<grid, block, 0, st>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_run(const RunArgs& a0, const RunShape& s, bool vec4, hipStream_t st) {
+hipError_t launch_run(const RunArgs& a0, const RunShape& s, hipStream_t st) {
   RunArgs a = a0;
+  a.dw = run_row_words(a.d);
   a.roll = a.words + run_kernel_words(s, a.n, a.d, a.B);
   const int64_t words = run_kernel_words(s, a.n, a.d, a.B) + 1;
   const int64_t blocks = (words + kBlock - 1) / kBlock;
@@ -498,14 +512,13 @@ hipError_t launch_run(const RunArgs& a0, const RunShape& s, bool vec4, hipStream
   run_clear_kernel<<<dim3((unsigned)blocks), dim3(kBlock), 0, st>>>(a.words, words);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  switch ((vec4 ? 1 << 20 : 0) + s.threads * 64 + s.bmax - 1) {
-#define CECA_RUN(VEC, T, BM) case (VEC == 4 ? 1 << 20 : 0) + T * 64 + BM - 1: return launch<VEC, T, BM>(a, st)
+  switch ((minibatch_vec(a.d) ? 1 << 20 : 0) + s.threads * 64 + s.bmax - 1) {
+#define CECA_RUN(VEC, T, BM) case (VEC == 4 ? 1 << 20 : 0) + T * 64 + BM - 1: return VEC == 4 && a.d % 4 ? launch<VEC, T, BM, VEC == 4>(a, st) : launch<VEC, T, BM, false>(a, st)
     CECA_RUN(4, 64, 8); CECA_RUN(4, 64, 16); CECA_RUN(4, 64, 32); CECA_RUN(4, 64, 64);
     CECA_RUN(4, 256, 8); CECA_RUN(4, 256, 16); CECA_RUN(4, 256, 32); CECA_RUN(4, 256, 64);
     CECA_RUN(4, 1024, 8); CECA_RUN(4, 1024, 16);
     CECA_RUN(1, 64, 16); CECA_RUN(1, 64, 64);
     CECA_RUN(1, 256, 16); CECA_RUN(1, 256, 64);
-    CECA_RUN(1, 1024, 16); CECA_RUN(1, 1024, 64);
 #undef CECA_RUN
   }
   return hipErrorInvalidValue;

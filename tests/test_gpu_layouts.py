@@ -127,3 +127,57 @@ def test_consensus(env, n, d, extra, offset):
     assert np.allclose(out.cpu().numpy(), want, rtol=1e-12, atol=0)
     got = xbar.cpu().numpy()
     assert np.allclose(got[:d], m.astype(np.float32), rtol=2e-7, atol=1e-7) and (got[d:] == PAD).all()
+
+
+@pytest.mark.parametrize("kind", ["lsq", "logistic"])
+@pytest.mark.parametrize("n,d,B", [(3, 5, 3), (6, 63, 64), (6, 65, 9), (4, 66, 64), (40, 67, 17), (5, 255, 33), (6, 257, 8), (7, 1001, 40), (130, 1001, 33),
+                                   (5, 1027, 16), (4, 1030, 40), (6, 2051, 9), (130, 2051, 9), (130, 4099, 16), (3, 5000, 40), (130, 9001, 5)])
+def test_minibatch_losses(env, kind, n, d, B):
+    """Steps and windows (full batches that come again, and random ones), in place and out of place, on rows of the state
+    and of the samples at odd bases and pitches: the bits of 16-byte aligned rows."""
+    torch, P = env
+    from paper_2306_00256_amd import binding as Bn
+    gen = torch.Generator(device="cuda").manual_seed(n * d + B)
+    N, iters, lr, tau = B, 6, 0.02 / (d * B) ** 0.5, P.ceca_tau(n)
+    A = torch.randn((n, N, d), generator=gen, device="cuda")
+    t = torch.randn((n, N), generator=gen, device="cuda").sign()
+    full = torch.arange(N, dtype=torch.int32, device="cuda").expand(iters, n, -1).contiguous()
+    some = torch.randint(-1, N + 1, (iters, n, B), dtype=torch.int32, device="cuda", generator=gen)
+    x0 = 0.1 * torch.randn((2 * n, d), generator=gen, device="cuda")
+
+    def rows(shape, extra, offset):
+        flat = torch.full((offset + int(np.prod(shape)) * (d + extra) + 64,), float("inf"), device="cuda")
+        return flat, flat[offset:offset + int(np.prod(shape)) * (d + extra)].view(*shape, d + extra)
+
+    def outputs(extra, offset, idx):
+        _, a = rows((n, N), extra, offset)
+        a[..., :d] = A
+        loss = Bn.make_minibatch_loss(Bn.LOSS_LSQ if kind == "lsq" else Bn.LOSS_LOGISTIC, a, t, N, B, noise_std=0.02, seed=4, k=2)
+        out = []
+        for call in ("step", "run"):
+            size = P.dsgd_ceca_workspace_bytes if call == "step" else P.dsgd_ceca_run_workspace_bytes
+            ws = torch.empty(size(n, d, loss), dtype=torch.uint8, device="cuda")
+            for in_place in (False, True):
+                src_flat, src = rows((2 * n,), extra, offset)
+                src[:, :d] = x0
+                flat, dst = (src_flat, src) if in_place else rows((2 * n,), extra, (offset + 1) % 4 if offset else 0)
+                for two_kernels in (0, 1):
+                    src[:, :d] = x0
+                    Bn.ceca_set_option(Bn.OPT_HALF_STEP_RUN, 1 - two_kernels)
+                    if call == "step":
+                        P.dsgd_ceca_step(src, dst, n, d, loss, idx[0], lr, 1 % tau, 2, workspace=ws)
+                    else:
+                        P.dsgd_ceca_run(src, dst, n, d, loss, idx, lr, 1 % tau, iters, 2, workspace=ws)
+                    out.append(dst[:, :d].clone())
+                Bn.ceca_reset_options()
+                assert bool(torch.isinf(dst[:, d:]).all()) and bool(torch.isinf(flat[:dst.storage_offset()]).all())
+                assert bool(torch.isinf(flat[dst.storage_offset() + 2 * n * (d + extra):]).all())
+        return out
+
+    for idx in (full, some):
+        ref = outputs(-d % 4, 0, idx)
+        assert all(bool(torch.isfinite(r).all()) for r in ref)
+        assert all(torch.equal(a, ref[0]) for a in ref[:4]) and all(torch.equal(a, ref[4]) for a in ref[4:])
+        for extra, offset in ((0, 0), (1, 3), (3, 1)):
+            for got, want in zip(outputs(extra, offset, idx), ref):
+                assert torch.equal(got, want), (extra, offset)
