@@ -447,12 +447,19 @@ static bool onepass_tile_exists(int32_t B, int64_t d4) {
   return (B <= 32 && d4 <= 256) || (B <= 16 && d4 <= 1024) || (B <= 8 && d4 <= 2048) || (B <= 4 && d4 <= 4096);
 }
 
-// Where the chunked kernel is the default for a single step: single columns, and many agents with long rows.
-static bool chunked_by_default(int32_t n, int64_t d, int32_t) {
+// Where the chunked kernel is the default for a single step (rows of up to 16384 columns, any batch): single columns; many
+// agents with long rows, two workgroups per compute unit; and batches for which no register tile exists on rows of up to 1024
+// columns, which margins and half step would read twice (n = 746, d = 188, B = 64 29 us per iteration against 15, n = 841, d =
+// 528, B = 55 45 against 23, n = 26, d = 250, B = 41 equal).
+// How many agents are many, two-pass against chunked, 20 iterations of B = 17 / 32 / 64: n = 96 at d = 2500 284 / 347 / 582
+// us against 254 / 325 / 569, at d = 12000 819 / 1197 / - against 651 / 1069; n = 80 at d = 2500 252 / 291 / 449 against 250 /
+// 319 / 560; on rows of little more than 1024 columns workgroups are too few for large batches (n = 112, d = 1200 241 / 283 /
+// 428 against 215 / 270 / 473).
+static bool chunked_by_default(int32_t n, int64_t d, int32_t B) {
   const int64_t d4 = (d + 3) / 4;
   if (!minibatch_vec(d)) return true;
   if (d4 > 4096) return false;
-  return d4 > 256 && n >= 128;
+  return d4 <= 256 ? B > 32 : n >= 128 || (n >= 96 && (d > 2048 || B <= 32));
 }
 
 // Rows of more than 2048 columns that are no whole groups, on few agents: margins and half step, in 16-byte groups.  (The
