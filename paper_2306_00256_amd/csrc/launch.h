@@ -123,6 +123,7 @@ struct RunShape {
   int32_t bmax;            // sampled rows in registers
   int32_t nchunks;         // workgroups per agent
   int32_t wg_per_cu;       // workgroups a compute unit holds at least
+  bool one_xcd;            // the workgroups are placed on one XCD
 };
 
 struct RunArgs {
@@ -139,6 +140,7 @@ struct RunArgs {
   unsigned long long* roll;   // the word after them: complete or given up (set by the launcher)
   int64_t d;
   int64_t dw;              // words of an agent's message (set by the launcher)
+  int32_t one_xcd, xcd;    // 1: the window plays on that XCD (set by the launcher)
   int32_t n, N, B, kind, nchunks, port, iters, tau, r0;
   float lr, scale, noise_std;
   uint32_t seed, k;

@@ -34,8 +34,9 @@ namespace ceca {
 // a call with 426 agents, 73 -> 76 us.
 //
 // What bounds it: the latency of the chain rows -> margins -> barrier -> coefficients -> message -> peer, once per
-// iteration (an exchange between workgroups takes about 1.3 us), and a compute unit's intake of sampled rows, 75 GB/s.
-// Per iteration, one launch (two in chunks) each before and here: n = 5, d = 1000, B = 8: 3.9 -> 1.9 us; n = 258, d = 10,
+// iteration (a store and the load that sees it take 0.83 us between two workgroups on different XCDs, 0.58 us on one), and
+// a compute unit's intake of sampled rows, 75 GB/s.
+// Per iteration, one launch (two in chunks) each before and here: n = 5, d = 1000, B = 8: 3.9 -> 1.9 us, on one XCD 1.7; n = 258, d = 10,
 // B = N = 50 with noise: 7.6 -> 2.5 us; n = 6, d = 10000, B = 32 in ten chunks: 13.4 -> 5.9 us; n = 256, d = 256, B = 32:
 // 8.4 -> 2.6 us.
 // Messages packed as four floats in three words were slower (n = 5: 2.2 -> 2.5 us in the same loop), and 128-thread
@@ -224,16 +225,16 @@ __device__ __forceinline__ bool call_roll(const RunArgs& P) {
   return wait.complete(0);
 }
 
-// A workgroup's part of the window.  True if the window is complete and the results are stored.
+// Workgroup `wg`'s part of the window.  True if the window is complete and the results are stored.
 template <int VEC, int THREADS, int BMAX, bool CHUNKS, bool ODD>
-__device__ __forceinline__ bool take_part(const RunArgs& P, float (&red)[2][THREADS / 64][BMAX], float* part) {
+__device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)[2][THREADS / 64][BMAX], float* part) {
   using V = typename VecOf<VEC>::T;
   constexpr int WAVES = THREADS / 64;
   constexpr int CH = kRowGroup;            // rows are requested and added up in groups, as in the single-step kernels
   constexpr int MG = BMAX < 16 ? BMAX : 16;    // samples per wavefront sum (any number gives the same bits)
   static_assert(BMAX % CH == 0 && BMAX <= 64, "whole groups of samples, one lane per sample");
-  const int agent = CHUNKS ? (int)(blockIdx.x / (uint32_t)P.nchunks) : (int)blockIdx.x;
-  const int chunk = CHUNKS ? (int)(blockIdx.x % (uint32_t)P.nchunks) : 0;
+  const int agent = CHUNKS ? (int)((uint32_t)wg / (uint32_t)P.nchunks) : wg;
+  const int chunk = CHUNKS ? (int)((uint32_t)wg % (uint32_t)P.nchunks) : 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // lanes past the last column carry z = 0; they publish and wait for nothing
   const int64_t c = ((int64_t)chunk * THREADS + tid) * VEC;
@@ -411,12 +412,15 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_wav
 void run_kernel(const RunArgs P) {
   __shared__ float red[2][THREADS / 64][BMAX];                   // alternating between iterations
   __shared__ float part[CHUNKS ? kRunParts : 1];                 // partial margins of every chunk of the agent
-  if (blockIdx.x + 1 == gridDim.x ? call_roll<THREADS, CHUNKS>(P) : take_part<VEC, THREADS, BMAX, CHUNKS, ODD>(P, red, part)) return;
+  // workgroups go round-robin over the XCDs: of a window on one of them, only every eighth plays
+  if (P.one_xcd && (blockIdx.x & 7) != (uint32_t)P.xcd) return;
+  const int wg = (int)(P.one_xcd ? blockIdx.x >> 3 : blockIdx.x), wgs = (int)(P.one_xcd ? gridDim.x >> 3 : gridDim.x);
+  if (wg + 1 == wgs ? call_roll<THREADS, CHUNKS>(P) : take_part<VEC, THREADS, BMAX, CHUNKS, ODD>(P, wg, red, part)) return;
   // given up (the same for every thread): nothing has been stored; my own words are behind me before I leave
   __shared__ bool last_s;
   __threadfence();
   __syncthreads();
-  if (threadIdx.x == 0) last_s = (uint32_t)((__hip_atomic_fetch_add(P.roll, kLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kGivenUp) >> 32) + 1 == gridDim.x;
+  if (threadIdx.x == 0) last_s = (uint32_t)((__hip_atomic_fetch_add(P.roll, kLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kGivenUp) >> 32) + 1 == (uint32_t)wgs;
   __syncthreads();
   if (!last_s) return;
   __threadfence();
@@ -433,7 +437,7 @@ __global__ __launch_bounds__(kBlock) void run_clear_kernel(Word* words, int64_t 
 // The shapes are those whose single step sums in the same order: one workgroup per agent where the gradient is taken
 // in one pass with one column group per thread, chunks of 256 threads where it takes two passes.
 static RunShape run_shape(int32_t n, int64_t d, int32_t B) {
-  RunShape s{0, 0, 1, 0};
+  RunShape s{0, 0, 1, 0, false};
   const bool vec4 = minibatch_vec(d);
   if (n < 2 || B < 1 || B > 64 || (vec4 && two_pass_rows(n, d))) return s;
   const int64_t groups = vec4 ? (d + 3) / 4 : d;
@@ -447,7 +451,7 @@ static RunShape run_shape(int32_t n, int64_t d, int32_t B) {
     s.threads = groups <= 64 ? 64 : 256;
   }
   const int64_t chunks = (groups + s.threads - 1) / s.threads;
-  if (chunks * B > kRunParts && chunks > 1) return RunShape{0, 0, 1, 0};
+  if (chunks * B > kRunParts && chunks > 1) return RunShape{0, 0, 1, 0, false};
   s.nchunks = (int32_t)chunks;
   s.bmax = vec4 ? (B <= 8 ? 8 : B <= 16 ? 16 : B <= 32 ? 32 : 64) : (B <= 16 ? 16 : 64);
   const int waves = s.threads == 1024 || !vec4 || s.bmax <= 8 ? 4 : s.bmax <= 16 ? 3 : s.bmax <= 32 ? 2 : 1;     // run_waves
@@ -488,13 +492,18 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, h
   if (usable < cus) cus = usable;
   if ((int64_t)n * s.nchunks * 8 > (int64_t)cus * s.wg_per_cu) return false;
   *out = s;
+  // Windows that need an eighth of one XCD's places (eight of a like shape fit there) play on one: n = 5, d = 1000, B = 8 1.92 ->
+  // 1.68 us per iteration, n = 17, d = 180, B = 8 1.57 -> 1.38, n = 5, B = 32 3.2 -> 2.9.  Which one follows the workspace's
+  // address, so that windows side by side spread.  Not on streams restricted to some compute units.
+  out->one_xcd = usable >= cus && (int64_t)n * s.nchunks * 64 <= (int64_t)cus * s.wg_per_cu;
   return true;
 }
 
 template <int VEC, int THREADS, int BMAX, bool ODD>
 static hipError_t launch(const RunArgs& a, hipStream_t st) {
   const int32_t kept = a.n * a.nchunks - g_tuning.window_missing;
-  const dim3 grid((unsigned)(kept < 0 ? 0 : kept) + 1), block(THREADS);       // the last one calls the roll
+  const unsigned wgs = (unsigned)(kept < 0 ? 0 : kept) + 1;                   // the last one calls the roll
+  const dim3 grid(a.one_xcd ? wgs * 8 : wgs), block(THREADS);
   if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false, ODD><<<grid, block, 0, st>>>(a);
   else if constexpr (THREADS == 256 && VEC == 4) run_kernel<VEC, THREADS, BMAX, true, ODD><<<grid, block, 0, st>>>(a);
   else return hipErrorInvalidValue;
@@ -504,6 +513,8 @@ static hipError_t launch(const RunArgs& a, hipStream_t st) {
 hipError_t launch_run(const RunArgs& a0, const RunShape& s, hipStream_t st) {
   RunArgs a = a0;
   a.dw = run_row_words(a.d);
+  a.one_xcd = s.one_xcd;
+  a.xcd = (int32_t)((reinterpret_cast<uintptr_t>(a.words) >> 12 ^ reinterpret_cast<uintptr_t>(a.words) >> 21) & 7);
   a.roll = a.words + run_kernel_words(s, a.n, a.d, a.B);
   const int64_t words = run_kernel_words(s, a.n, a.d, a.B) + 1;
   const int64_t blocks = (words + kBlock - 1) / kBlock;
