@@ -496,7 +496,7 @@ TileShape steps_tile(int32_t n, bool vec4, int32_t steps) {
 // peers in some round.
 TileShape mix_tile(int32_t n, bool vec4, bool heavy) {
   // Measured on MI355X (n = 31 ... 4096, all three topologies; x alone in registers, 67 registers at 9 rows
-  // per thread).  What counts is how many workgroups a compute unit holds: the LDS tile is n x tile row.
+  // per thread; many peers before they took blocks of consecutive rows, which keep these tiles).  What counts is how many workgroups a compute unit holds: the LDS tile is n x tile row.
   // Up to 256 agents: 256 threads, up to 12 rows per thread (n = 64 ring: 0.20 against 0.25 ms with 16,
   // n = 100: 0.215 against 0.24).  257 to 512 agents: one or two peers per round run 512-thread workgroups
   // with up to 9 rows (n = 258 ring: 0.33 against 0.40 ms), many peers per round (LDS-read bound) 256 threads

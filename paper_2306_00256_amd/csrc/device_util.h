@@ -94,17 +94,20 @@ template <typename V> __device__ __forceinline__ void st_own(float* p, V v, int 
   else st_plain<V>(p, v);
 }
 
-// RT rows of a tile, `step` rows apart, the last one clamped to row `last`, into registers: x from p and, with a second
-// pointer, c from pc, row by row.  (The compiler must neither merge the two kinds of access, which would drop the
-// streaming, nor work all addresses out in front of the branch.)
-template <typename V, int RT, bool TWO = true>
+// RT rows of a tile, `step` rows apart, into registers: x from p and, with a second pointer, c from pc, row by row.
+// Rows past row `last` hold what it does or, on a RING, those from row 0 on.  (The compiler must neither merge the two
+// kinds of access, which would drop the streaming, nor work all addresses out in front of the branch.)
+template <bool RING> __device__ __forceinline__ int row_of(int i, int last) {
+  return RING ? (i > last ? i - last - 1 : i) : min(i, last);
+}
+template <typename V, int RT, bool TWO = true, bool RING = false>
 __device__ __forceinline__ void load_rows(V (&x)[RT], const float* p, int64_t ld, V (&c)[RT], const float* pc, int64_t ldc, int row, int step,
                                           int last, bool cached) {
   if (cached) {
     asm volatile("; cached" : "+v"(row));
 #pragma unroll
     for (int k = 0; k < RT; ++k) {
-      const int64_t i = min(row + k * step, last);
+      const int64_t i = row_of<RING>(row + k * step, last);
       x[k] = ld_plain<V>(p + i * ld);
       if (TWO) c[k] = ld_plain<V>(pc + i * ldc);
     }
@@ -113,15 +116,15 @@ __device__ __forceinline__ void load_rows(V (&x)[RT], const float* p, int64_t ld
     asm volatile("; streamed" : "+v"(row));
 #pragma unroll
     for (int k = 0; k < RT; ++k) {
-      const int64_t i = min(row + k * step, last);
+      const int64_t i = row_of<RING>(row + k * step, last);
       x[k] = ld_stream<V>(p + i * ld);
       if (TWO) c[k] = ld_stream<V>(pc + i * ldc);
     }
   }
 }
-template <typename V, int RT>
+template <typename V, int RT, bool RING = false>
 __device__ __forceinline__ void load_rows(V (&x)[RT], const float* p, int64_t ld, int row, int step, int last, bool cached) {
-  load_rows<V, RT, false>(x, p, ld, x, nullptr, 0, row, step, last, cached);
+  load_rows<V, RT, false, RING>(x, p, ld, x, nullptr, 0, row, step, last, cached);
 }
 // The same rows out of registers, those up to `last`; a short group's own columns one by one.
 // x at p and, unless py is null (the same for every thread), y at py, row by row: all of x's rows before the first of y's
@@ -384,6 +387,9 @@ __device__ __forceinline__ uint32_t lds_address(const void* shared) {
 }
 template <typename V> __device__ __forceinline__ V lds_load(uint32_t address) {
   return *(__attribute__((address_space(3))) const V*)(uintptr_t)address;
+}
+template <typename V> __device__ __forceinline__ void lds_store(uint32_t address, V v) {
+  *(__attribute__((address_space(3))) V*)(uintptr_t)address = v;
 }
 
 // w * self + wp * msg, with one fixed rounding order wherever it is evaluated: the product with self is

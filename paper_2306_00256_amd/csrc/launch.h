@@ -203,6 +203,7 @@ struct MixArgs {
   int32_t threads;          // threads per workgroup: 0 = 256, or 512 / 1024 (16-byte groups only, at most 16 rows per thread)
   TileMemory mem;
   int32_t start[kMixMaxPeriod + 1];
+  int32_t lead[kMixMaxPeriod];   // so many first peers of the round are 1, 2, 4, 8 rows back (set by the launcher)
   float w_self[kMixMaxPeriod];
   int32_t shift[kMixMaxPeers];
   float w[kMixMaxPeers];

@@ -24,8 +24,7 @@ constexpr int mix_waves() { return THREADS > 256 ? 4 : 1; }
 // Same tiling as the fused CECA rounds: a workgroup keeps a column tile of every agent's x in
 // registers (RT rows per thread) and publishes it in LDS once per round, where each row picks up its
 // peers.  One read and one write of x for any number of rounds.
-// SCALAR: weights in scalar instead of vector registers, see launch_mix.
-template <int VEC, int RT, int THREADS, bool SCALAR>
+template <int VEC, int RT, int THREADS>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(mix_waves<THREADS>())))
 void mix_rounds_kernel(const MixArgs M) {
 #pragma clang fp contract(off)
@@ -60,7 +59,7 @@ void mix_rounds_kernel(const MixArgs M) {
   int spec = M.k0 % M.period;
   for (int t = 0; t < M.rounds; ++t) {
     const int j0 = M.start[spec], j1 = M.start[spec + 1];
-    const float ws = SCALAR ? M.w_self[spec] : in_vgpr(M.w_self[spec]);
+    const float ws = in_vgpr(M.w_self[spec]);
     if (j1 > j0) {                                  // a round without peers is the identity
 #pragma unroll
       for (int k = 0; k < L; ++k) xs[tid + k * THREADS] = x[k];
@@ -81,7 +80,7 @@ void mix_rounds_kernel(const MixArgs M) {
         const int past = shift - rg;               // rows k with k * row_lanes < past start from the far end
         uint32_t near = slot - shift * (lanes * (uint32_t)sizeof(V)), far = near + wrap;
         asm volatile("" : "+v"(near), "+v"(far));  // two addresses to select from, not one and a distance to add
-        const float w = SCALAR ? M.w[j] : in_vgpr(M.w[j]);
+        const float w = in_vgpr(M.w[j]);
         V z[RT];
 #pragma unroll
         for (int k = 0; k < RT; ++k) {
@@ -105,17 +104,139 @@ void mix_rounds_kernel(const MixArgs M) {
   store_rows<V, RT>(x, M.xout + out, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
 }
 
+// x <- w_self x + the terms of the round's first RUN peers, which are 1, 2, 4, 8 rows back: among the block's own rows or the
+// REACH rows in front of it.  From the last row down, a row's own peers still hold their old values when its turn comes.
+constexpr int lead_reach(int run) { return run > 0 ? 1 << (run - 1) : 0; }
+template <int RUN, int RT>
+__device__ __forceinline__ void mix_lead(vf4 (&x)[RT], uint32_t front, uint32_t pitch, float ws, const float* w) {
+#pragma clang fp contract(off)
+  constexpr int REACH = lead_reach(RUN);
+  if constexpr (REACH < RT) {
+    float wj[RUN];
+#pragma unroll
+    for (int j = 0; j < RUN; ++j) wj[j] = in_vgpr(w[j]);
+    vf4 z[REACH];
+#pragma unroll
+    for (int k = 0; k < REACH; ++k) z[k] = lds_load<vf4>(front + k * pitch);
+#pragma unroll
+    for (int k = RT - 1; k >= 0; --k) {
+      x[k] = ws * x[k];
+#pragma unroll
+      for (int j = 0; j < RUN; ++j) x[k] = fma_each(wj[j], k < 1 << j ? z[k - (1 << j) + REACH] : x[k - (1 << j)], x[k]);
+      __builtin_amdgcn_sched_barrier(0);         // row by row: 7 rows then fit three 512-thread workgroups (80 registers, not 82)
+    }
+  }
+}
 
-// Vector registers for the weights are the rule (static exponential, 2^26 elements, vector against scalar: n = 258
-// 304 us against 355, n = 600 336 against 385, n = 1026 427 against 539).  512-thread tiles with 32-byte rows and 6 or 7 rows
-// per thread, which many peers per round take from 1281 agents on, are the exception up to 1664 agents, over five pitches:
-// n = 1300 380 to 660 against 348 to 571, n = 1500 402 to 529 against 359 to 481, n = 1660 464 to 566 against 425 to 521
-// (1281: 327 to 522 against 344 to 548); beyond, vector registers win again (n = 1700 465 to 555 against 496 to 604).
+// Wavefronts per SIMD: two 1024-thread workgroups of up to 5 rows are resident.
+template <int THREADS, int RT>
+constexpr int block_waves() { return THREADS == 1024 && RT <= 5 ? 8 : mix_waves<THREADS>(); }
+
+// The same rounds with RT consecutive rows per thread: agents rg * RT and on.  A peer's rows are then consecutive as well, so
+// one address per peer serves the whole block, its rows' distances being constants of the load instructions (rows row_lanes
+// apart take a comparison and a select each), and the peers 1, 2, 4, 8 rows back are mostly the block's own rows, which are in
+// registers: of static exponential's 99 LDS reads per thread and round at n = 1026 this leaves 71.  The tile is followed by
+// copies of its first RT - 1 rows, so that no block of peers has a wrap inside.
+// What bounds it: vector units (4.2 cycles per wavefront instruction and SIMD, of which 87 % are the rows' products) and
+// LDS (busy 64 % of the time) together, n = 1026.
+// Bank conflicts: lanes of a wavefront that differ in the row are RT rows apart, so rows of the tile that are less than all
+// banks wide (LANES < 16) need an odd RT.  Same order of operations per row as above, same bits.
+// Static exponential, 2^27 elements, rows row_lanes apart -> blocks: n = 100 379 -> 329 us, n = 130 499 -> 401, n = 258 614 ->
+// 511, n = 500 696 -> 567, n = 800 713 -> 610, n = 1026 873 -> 729, n = 1400 1001 -> 739, n = 2050 1193 -> 882.
+template <int THREADS, int LANES, int RT>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(block_waves<THREADS, RT>())))
+void mix_blocks_kernel(const MixArgs M) {
+#pragma clang fp contract(off)
+  extern __shared__ float lds_x[];                 // [n + RT - 1][LANES] groups of 4 floats
+  constexpr uint32_t PITCH = LANES * sizeof(vf4);
+  const int tid = threadIdx.x;
+  const int cg = tid % LANES;
+  const int rg = tid / LANES;
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
+  if (tile * LANES >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
+  const int64_t g = tile * LANES + cg;
+  const bool on = g < M.ngroups;
+  const int64_t col = (on ? g : 0) * 4;            // lanes past the last column shadow column group 0
+
+  // Rows past agent n - 1 hold what the agents from 0 on do, and every block past it starts at agent n - 1.  Such rows are
+  // worked out and published like any other, with the bits of the rows they stand for, so nothing below is conditional: the
+  // first block past the last agent (the launcher sees to it that there is one) publishes the copies behind the tile.
+  // Wavefronts that hold later blocks only just take part in the barriers.
+  const int row0 = min(rg * RT, M.n - 1);
+  const bool idle = (__builtin_amdgcn_readfirstlane(rg) - 1) * RT >= M.n;
+  vf4 x[RT];
+  const int64_t from = col - columns_back(M, col);
+  if (!idle) {
+    load_rows<vf4, RT, true>(x, M.xin + from, M.ld, row0, 1, M.n - 1, M.mem.cached_loads);
+    if (M.mem.short_cols) {
+      const int back = (int)(col - from);
+#pragma unroll
+      for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
+    }
+  }
+  const uint32_t wrap = M.n * PITCH;
+  const uint32_t slot = lds_address(lds_x) + row0 * PITCH + cg * (uint32_t)sizeof(vf4);
+  int spec = M.k0 % M.period;
+  for (int t = 0; t < M.rounds; ++t) {
+    int j = M.start[spec];
+    const int j1 = M.start[spec + 1], run = M.lead[spec];
+    if (j1 > j) {                                   // a round without peers is the identity
+      // the first of the peers that are read from the tile, requested ahead like the ones after it
+      j += run;
+      int shift = M.shift[min(j, kMixMaxPeers - 1)];
+      float weight = M.w[min(j, kMixMaxPeers - 1)];
+      const float ws = in_vgpr(M.w_self[spec]);
+      if (!idle) {
+#pragma unroll
+        for (int k = 0; k < RT; ++k) lds_store(slot + k * PITCH, x[k]);
+      }
+      __syncthreads();
+      if (!idle) {
+        // the block `shift` rows back on the circle
+        auto back = [&](int shift) { return slot - shift * PITCH + (row0 < shift ? wrap : 0u); };
+        switch (run) {
+#define CECA_LEAD(RUN) case RUN: mix_lead<RUN, RT>(x, back(lead_reach(RUN)), PITCH, ws, M.w + M.start[spec]); break
+          CECA_LEAD(1); CECA_LEAD(2); CECA_LEAD(3); CECA_LEAD(4);
+#undef CECA_LEAD
+          default:
+#pragma unroll
+            for (int k = 0; k < RT; ++k) x[k] = ws * x[k];
+        }
+        for (; j < j1; ++j) {
+          const uint32_t q = back(shift);
+          const float w = in_vgpr(weight);
+          shift = M.shift[min(j + 1, kMixMaxPeers - 1)];
+          weight = M.w[min(j + 1, kMixMaxPeers - 1)];
+          // every read of a batch is issued before its first value is used; two batches where registers are short
+          constexpr int KB = RT > 9 ? (RT + 1) / 2 : RT;
+#pragma unroll
+          for (int k0 = 0; k0 < RT; k0 += KB) {
+            vf4 z[KB];
+#pragma unroll
+            for (int k = k0; k < k0 + KB && k < RT; ++k) z[k - k0] = lds_load<vf4>(q + k * PITCH);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = k0; k < k0 + KB && k < RT; ++k) x[k] = fma_each(w, z[k - k0], x[k]);
+            if (KB < RT) __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if (++spec == M.period) spec = 0;
+  }
+  if (!on || rg * RT >= M.n) return;
+  // the row addresses are worked out here, after the rounds: nothing of them occupies registers meanwhile
+  int row_out = row0;
+  int64_t out = col;
+  asm volatile("" : "+v"(row_out), "+v"(out));
+  store_rows<vf4, RT>(x, M.xout + out, M.ld, row_out, 1, M.n - 1, columns_back(M, out), M.mem.cached_stores);
+}
+
+
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_mix(const MixArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
-  auto fn = &mix_rounds_kernel<VEC, RT, THREADS, false>;
-  if constexpr (VEC == 4 && THREADS == 512 && (RT == 6 || RT == 7))
-    if (THREADS / mm.row_lanes * 16 < 64 && mm.n <= 13 * 128) fn = &mix_rounds_kernel<VEC, RT, THREADS, true>;
+  const auto fn = &mix_rounds_kernel<VEC, RT, THREADS>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -151,6 +272,59 @@ static hipError_t launch_mix_wide(const MixArgs& mm, unsigned blocks, size_t lds
   return hipErrorInvalidValue;
 }
 
+// Rows per thread of the form with blocks of consecutive rows for this tile, 0 where there is none: enough that at least one
+// block lies past the last agent; the next odd number where rows of the tile are narrower than 256 bytes (bank conflicts, see the
+// kernel).  For many peers per round from 97 agents on: wider rows of the tile, below that, lose (n = 64 296 us against 322,
+// n = 80 376 against 379), and so do one or two peers, which hide behind the memory traffic (one-peer exponential, n = 1026 294
+// against 321, n = 500 234 against 274).  512-thread tiles of 64-byte rows from 672 agents on only: with 635, 71 % of the blocks
+// are in use, 647 us against 689, with 513 to 634 no difference, n = 700 708 against 672.
+static int block_rows(const MixArgs& m, int threads, int lanes) {
+  int most = 0;
+  for (int q = 0; q < m.period; ++q) most = most > m.start[q + 1] - m.start[q] ? most : m.start[q + 1] - m.start[q];
+  if (most < 4) return 0;
+  int rows = m.n / (threads / lanes - 1) + 1;
+  if (lanes < 16) rows |= 1;
+  switch (threads) {
+    case 256: return lanes == 16 ? (rows >= 7 && rows <= 13 ? rows : 0) : (lanes == 8 && rows >= 7 && rows <= 17 ? rows : 0);
+    case 512: return lanes == 4 ? (m.n >= 672 && rows <= 9 ? rows : 0) : (lanes == 2 && rows >= 7 && rows <= 9 ? rows : 0);
+    case 1024: return lanes == 4 && (rows == 5 || rows == 7) ? rows : 0;
+  }
+  return 0;
+}
+
+template <int THREADS, int LANES, int RT>
+static hipError_t launch_blocks(const MixArgs& mm, unsigned blocks, hipStream_t st) {
+  const auto fn = &mix_blocks_kernel<THREADS, LANES, RT>;
+  const size_t lds = (size_t)(mm.n + RT - 1) * LANES * 16;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  fn<<<dim3(blocks), dim3(THREADS), lds, st>>>(mm);
+  return hipGetLastError();
+}
+static hipError_t launch_mix_blocks(const MixArgs& mm, int lanes, int rows, unsigned blocks, hipStream_t st) {
+  switch (mm.threads << 16 | lanes << 8 | rows) {
+#define CECA_RT(T, L, RT) case T << 16 | L << 8 | RT: return launch_blocks<T, L, RT>(mm, blocks, st)
+    CECA_RT(256, 16, 7); CECA_RT(256, 16, 8); CECA_RT(256, 16, 9); CECA_RT(256, 16, 10); CECA_RT(256, 16, 11); CECA_RT(256, 16, 12); CECA_RT(256, 16, 13);
+    CECA_RT(256, 8, 7); CECA_RT(256, 8, 9); CECA_RT(256, 8, 11); CECA_RT(256, 8, 13); CECA_RT(256, 8, 15); CECA_RT(256, 8, 17);
+    CECA_RT(512, 4, 7); CECA_RT(512, 4, 9);
+    CECA_RT(512, 2, 7); CECA_RT(512, 2, 9);
+    CECA_RT(1024, 4, 5); CECA_RT(1024, 4, 7);
+#undef CECA_RT
+  }
+  return hipErrorInvalidValue;
+}
+
+// How many of the round's first peers are 1, 2, 4, 8 rows back in this order and less than a block of `rows` rows.
+static int lead_of(const MixArgs& m, int spec, int rows) {
+  const int32_t* s = m.shift + m.start[spec];
+  const int peers = m.start[spec + 1] - m.start[spec];
+  int run = 0;
+  while (run < peers && run < 4 && s[run] == 1 << run && 1 << run < rows) ++run;
+  return run;
+}
+
 hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   if (m.ngroups <= 0) return hipSuccess;
   const int threads = m.threads > 0 ? m.threads : kBlock;
@@ -169,6 +343,12 @@ hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
+  mm.threads = threads;
+  const int rows = vec4 ? block_rows(m, threads, lanes) : 0;
+  if (rows) {
+    for (int q = 0; q < m.period; ++q) mm.lead[q] = lead_of(m, q, rows);
+    return launch_mix_blocks(mm, lanes, rows, (unsigned)blocks, st);
+  }
   if (!vec4) return launch_mix_256<1>(mm, (unsigned)blocks, lds, st);
   if (threads == 256) return launch_mix_256<4>(mm, (unsigned)blocks, lds, st);
   if (threads == 512) return launch_mix_wide<512>(mm, (unsigned)blocks, lds, st);
