@@ -281,7 +281,7 @@ static hipError_t launch_mix_wide(const MixArgs& mm, unsigned blocks, size_t lds
 static int block_rows(const MixArgs& m, int threads, int lanes) {
   int most = 0;
   for (int q = 0; q < m.period; ++q) most = most > m.start[q + 1] - m.start[q] ? most : m.start[q + 1] - m.start[q];
-  if (most < 4) return 0;
+  if (most < 4 || lanes > 16) return 0;
   int rows = m.n / (threads / lanes - 1) + 1;
   if (lanes < 16) rows |= 1;
   switch (threads) {

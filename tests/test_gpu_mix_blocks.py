@@ -8,8 +8,8 @@ import workloads as WL
 
 pytestmark = pytest.mark.gpu
 
-# first and last agent counts of every tile of the form, those where the rows per thread change, and counts beside them
-NS = [96, 97, 104, 105, 119, 130, 192, 193, 217, 256, 257, 278, 279, 512, 513, 671, 672, 888, 889, 1026, 1142, 1143, 1152, 1153,
+# a few agents, in one row of lanes, and first and last agent counts of every tile of the form, those where the rows per thread change, and counts beside them
+NS = [9, 12, 16, 31, 96, 97, 104, 105, 119, 130, 192, 193, 217, 256, 257, 278, 279, 512, 513, 671, 672, 888, 889, 1026, 1142, 1143, 1152, 1153,
       1274, 1275, 1280, 1281, 1784, 1785, 2294, 2295]
 
 
@@ -48,8 +48,7 @@ def _oracle(x, seq, rounds):
     return x
 
 
-@pytest.mark.parametrize("kind", ["static", "mixed"])
-@pytest.mark.parametrize("n", NS)
+@pytest.mark.parametrize("n,kind", [(n, kind) for n in NS for kind in ("static", "mixed") if n > 16 or kind == "static"])
 def test_blocks(env, n, kind):
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
