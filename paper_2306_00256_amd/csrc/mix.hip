@@ -141,8 +141,8 @@ constexpr int block_waves() { return THREADS == 1024 && RT <= 5 ? 8 : mix_waves<
 // LDS (busy 64 % of the time) together, n = 1026.
 // Bank conflicts: lanes of a wavefront that differ in the row are RT rows apart, so rows of the tile that are less than all
 // banks wide (LANES < 16) need an odd RT.  Same order of operations per row as above, same bits.
-// Static exponential, 2^27 elements, rows row_lanes apart -> blocks: n = 100 379 -> 329 us, n = 130 499 -> 401, n = 258 614 ->
-// 511, n = 500 696 -> 567, n = 800 713 -> 610, n = 1026 873 -> 729, n = 1400 1001 -> 739, n = 2050 1193 -> 882.
+// Static exponential, 2^27 elements, rows row_lanes apart -> blocks: n = 100 401 -> 355 us, n = 130 496 -> 404, n = 258 611 ->
+// 499, n = 500 686 -> 552, n = 800 684 -> 618, n = 1026 852 -> 715, n = 1400 967 -> 759, n = 2050 1010 -> 858.
 template <int THREADS, int LANES, int RT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(block_waves<THREADS, RT>())))
 void mix_blocks_kernel(const MixArgs M) {
@@ -234,6 +234,71 @@ void mix_blocks_kernel(const MixArgs M) {
 }
 
 
+// Ring rounds (peers 1 row back and 1 ahead, in every round): a thread holds RT consecutive rows or one less, and of a block only
+// its first and last row are anyone else's business.  They alone go through LDS, one slot per thread and two buffers in turn, so a
+// round has one barrier and the tile's width is not bound by LDS: its rows are 128 or 256 bytes, where a tile that keeps every row in
+// LDS has 64 from 513 agents on.  A row's new value replaces it from the last one down, with the old value of the row
+// behind carried along.  Same order of operations per row as above, same bits.
+// What bounds it: memory (n = 1026 241 us where the loads and stores alone take 243 in the general form's tile).  Ring, 2^27 elements,
+// general form -> here: n = 130 234 -> 193 us, n = 400 256 -> 217, n = 800 284 -> 217, n = 1026 333 -> 241, n = 1500 550 -> 251,
+// n = 3000 614 -> 356.
+template <int THREADS, int LANES, int RT>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(mix_waves<THREADS>())))
+void mix_ring_kernel(const MixArgs M) {
+#pragma clang fp contract(off)
+  constexpr int ROW_LANES = THREADS / LANES;
+  __shared__ vf4 first_row[2][THREADS], last_row[2][THREADS];
+  const int tid = threadIdx.x;
+  const int cg = tid % LANES;
+  const int rg = tid / LANES;
+  const int64_t tile = tile_of_block(M.mem.xcd_runs);
+  if (tile * LANES >= M.ngroups) return;           // past the last tile (the grid is rounded up to whole runs)
+  const int64_t g = tile * LANES + cg;
+  const bool on = g < M.ngroups;
+  const int64_t col = (on ? g : 0) * 4;            // lanes past the last column shadow column group 0
+
+  const int whole = M.n - (RT - 1) * ROW_LANES;    // blocks of RT rows (1 to ROW_LANES), the others have one less
+  const bool last_mine = rg < whole;
+  const int agent = rg * (RT - 1) + min(rg, whole);
+  const int last = agent + RT - 2 + last_mine;
+  vf4 x[RT];                                       // the row that a shorter block lacks shadows its last one
+  const int64_t from = col - columns_back(M, col);
+  load_rows<vf4, RT>(x, M.xin + from, M.ld, agent, 1, last, M.mem.cached_loads);
+  if (M.mem.short_cols) {
+    const int back = (int)(col - from);
+#pragma unroll
+    for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
+  }
+  const int before = rg > 0 ? tid - LANES : tid + THREADS - LANES;
+  const int behind = rg < ROW_LANES - 1 ? tid + LANES : cg;
+  int spec = M.k0 % M.period;
+  for (int t = 0; t < M.rounds; ++t) {
+    const int j = M.start[spec];
+    const float ws = in_vgpr(M.w_self[spec]), wb = in_vgpr(M.w[j]), wa = in_vgpr(M.w[j + 1]);
+    first_row[t & 1][tid] = x[0];
+    last_row[t & 1][tid] = last_mine ? x[RT - 1] : x[RT - 2];
+    __syncthreads();                               // the buffer's readers of two rounds ago have passed the barrier of the last one
+    const vf4 front = last_row[t & 1][before];
+    vf4 next = first_row[t & 1][behind];
+#pragma unroll
+    for (int k = RT - 1; k >= 0; --k) {
+      const vf4 was = x[k];
+      vf4 v = ws * was;
+      v = fma_each(wb, k > 0 ? x[k > 0 ? k - 1 : 0] : front, v);
+      x[k] = fma_each(wa, next, v);
+      next = k == RT - 1 && !last_mine ? next : was;
+      if (RT > 8) __builtin_amdgcn_sched_barrier(0);       // row by row where registers are short
+    }
+    if (++spec == M.period) spec = 0;
+  }
+  if (!on) return;
+  // the row addresses are worked out here, after the rounds: nothing of them occupies registers meanwhile
+  int row_out = agent;
+  int64_t out = col;
+  asm volatile("" : "+v"(row_out), "+v"(out));
+  store_rows<vf4, RT>(x, M.xout + out, M.ld, row_out, 1, last, columns_back(M, out), M.mem.cached_stores);
+}
+
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_mix(const MixArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
   const auto fn = &mix_rounds_kernel<VEC, RT, THREADS>;
@@ -275,8 +340,8 @@ static hipError_t launch_mix_wide(const MixArgs& mm, unsigned blocks, size_t lds
 // Rows per thread of the form with blocks of consecutive rows for this tile, 0 where there is none: enough that at least one
 // block lies past the last agent; the next odd number where rows of the tile are narrower than 256 bytes (bank conflicts, see the
 // kernel).  For many peers per round from 97 agents on: wider rows of the tile, below that, lose (n = 64 296 us against 322,
-// n = 80 376 against 379), and so do one or two peers, which hide behind the memory traffic (one-peer exponential, n = 1026 294
-// against 321, n = 500 234 against 274).  512-thread tiles of 64-byte rows from 672 agents on only: with 635, 71 % of the blocks
+// n = 80 376 against 379), and so does one peer, which hides behind the memory traffic (one-peer exponential, n = 1026 277
+// against 321, n = 500 236 against 274).  512-thread tiles of 64-byte rows from 672 agents on only: with 635, 71 % of the blocks
 // are in use, 647 us against 689, with 513 to 634 no difference, n = 700 708 against 672.
 static int block_rows(const MixArgs& m, int threads, int lanes) {
   int most = 0;
@@ -325,6 +390,34 @@ static int lead_of(const MixArgs& m, int spec, int rows) {
   return run;
 }
 
+// Threads and column groups per row of the ring kernel's tile; false where the rounds are no ring rounds, the tile is prescribed,
+// or there are so few agents that the general form's rows are as wide.  Rows of the tile as wide as registers allow (about 15 rows
+// per thread in 512-thread workgroups: with 17, n = 1026 410 us against 241 at 9 rows of half the width), 2^27 elements at
+// three pitches, the narrower or the smaller of the two against the choice: n = 130 212 / 198 / 257 us (128-byte rows) against 193 /
+// 194 / 235; n = 300 223 / 203 / 261 (256 threads) against 211 / 210 / 234; n = 917 268 / 264 / 331 (64-byte rows) against 247 / 221 /
+// 271; n = 1500 244 / 235 / 296 (1024 threads) against 251 / 235 / 303; n = 2050 523 / 535 / 581 (512 threads) against 364 / 361 / 424.
+static bool ring_tile(const MixArgs& m, int* threads, int* lanes) {
+  if (m.n <= 64 || g_tuning.rows || g_tuning.tile_threads) return false;
+  for (int q = 0; q < m.period; ++q)
+    if (m.start[q + 1] - m.start[q] != 2 || m.shift[m.start[q]] != 1 || m.shift[m.start[q] + 1] != m.n - 1) return false;
+  *threads = m.n <= 272 ? 256 : m.n <= 1792 ? 512 : 1024;
+  *lanes = m.n <= 448 ? 16 : m.n <= 960 ? 8 : 4;
+  return true;
+}
+
+static hipError_t launch_mix_ring(const MixArgs& mm, int threads, int lanes, unsigned blocks, hipStream_t st) {
+  const int row_lanes = threads / lanes, rows = (mm.n + row_lanes - 1) / row_lanes;
+  switch (threads << 16 | lanes << 8 | rows) {
+#define CECA_RT(T, L, RT) case T << 16 | L << 8 | RT: mix_ring_kernel<T, L, RT><<<dim3(blocks), dim3(T), 0, st>>>(mm); return hipGetLastError()
+#define CECA_RTS(T, L) CECA_RT(T, L, 8); CECA_RT(T, L, 9); CECA_RT(T, L, 10); CECA_RT(T, L, 11); CECA_RT(T, L, 12); CECA_RT(T, L, 13); CECA_RT(T, L, 14)
+    CECA_RT(256, 16, 5); CECA_RT(256, 16, 6); CECA_RT(256, 16, 7); CECA_RTS(256, 16); CECA_RT(256, 16, 15); CECA_RT(256, 16, 16); CECA_RT(256, 16, 17);
+    CECA_RTS(512, 16); CECA_RTS(512, 8); CECA_RT(512, 8, 15); CECA_RTS(512, 4); CECA_RTS(1024, 4); CECA_RT(1024, 4, 15); CECA_RT(1024, 4, 16);
+#undef CECA_RTS
+#undef CECA_RT
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   if (m.ngroups <= 0) return hipSuccess;
   const int threads = m.threads > 0 ? m.threads : kBlock;
@@ -336,11 +429,13 @@ hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   if (m.rows_per_thread < 1 || m.rows_per_thread > 32 ||
       (int64_t)m.rows_per_thread * m.row_lanes < m.n || (int64_t)(m.rows_per_thread - 1) * m.row_lanes >= m.n)
     return hipErrorInvalidValue;
-  const int lanes = threads / m.row_lanes;
+  int lanes = threads / m.row_lanes, ring_threads = 0;
+  const bool ring = vec4 && ring_tile(m, &ring_threads, &lanes);
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MixArgs mm = m;
   tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
+  if (ring) return launch_mix_ring(mm, ring_threads, lanes, (unsigned)blocks, st);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   mm.threads = threads;
