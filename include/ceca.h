@@ -132,7 +132,7 @@ int32_t ceca_gossip_round(const float* S_in, float* S_out, int32_t n, int64_t d,
  * more than about 1150 agents (where the fused pass costs more than that many streaming rounds) take one
  * launch per round instead (in place on S_out after the first).  With more than about 100 agents a row of
  * a workgroup's tile is 64-256 bytes wide: an ld that is a multiple of 32 floats keeps those rows on
- * 128-byte lines (up to 1.7x faster than an odd ld at n = 130-400). */
+ * 128-byte lines (up to 1.3x faster than an odd ld). */
 int32_t ceca_gossip_rounds(const float* S_in, float* S_out, int32_t n, int64_t d, int64_t ld,
                            int32_t rounds, int32_t port, void* hip_stream);
 
