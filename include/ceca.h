@@ -71,6 +71,9 @@ typedef struct {
  *               row when ceca_schedule's exchange_y is 0, the y row when it is 1) and passes it in;
  *               N, B, seed, k, noise_std, grad_scale, A, t are ignored
  * eps_i ~ N(0, I) comes from the counter-based generator below, keyed by (seed, k, agent, column).
+ * Sampled rows should be finite.  With the logistic loss an infinite feature gives an infinite margin and a finite coefficient, so
+ * only its own column is lost -- except in the first columns of the rows (four of them where d is a multiple of 4, else one on
+ * rows of up to 256), which spare lanes multiply by zero: there the margin becomes NaN, and with it the agent's whole message.
  *
  * Noise generator (uint32 arithmetic, wrapping; agent and column 0-based):
  *   mix(h):   h ^= h >> 16; h *= 0x7feb352d; h ^= h >> 15; h *= 0x846ca68b; h ^= h >> 16

@@ -70,6 +70,20 @@ __device__ __forceinline__ vf4 last_columns(vf4 v, int back) {
   return v;
 }
 __device__ __forceinline__ float last_columns(float v, int) { return v; }
+// What a lane read of a row, with zeros for columns that are not its own, when `left` columns of the row are left from its first one
+// on (fewer than four: it read the row's last four; none: anything).  Times z = 0 an infinite one would be NaN.
+__device__ __forceinline__ vf4 own_of_row(vf4 a, int left) {
+  return vf4{left < 4 ? 0.0f : a.x, left < 3 ? 0.0f : a.y, left < 2 ? 0.0f : a.z, left < 1 ? 0.0f : a.w};
+}
+__device__ __forceinline__ float own_of_row(float a, int) { return a; }
+__device__ __forceinline__ int columns_left(int64_t col, int64_t d) { return (int)min(d - col, (int64_t)1 << 20); }
+// Whether some lane of the wavefront has a NaN among its numbers.
+template <int CH> __device__ __forceinline__ bool some_nan(const float (&m)[CH]) {
+  float s = m[0];                          // (infinities of both signs ask for nothing but a second look)
+#pragma unroll
+  for (int j = 1; j < CH; ++j) s += m[j];
+  return __any(s != s);
+}
 
 // That distance for the group at column col.
 template <typename Args> __device__ __forceinline__ int columns_back(const Args& M, int64_t col) {

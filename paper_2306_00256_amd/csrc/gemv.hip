@@ -17,9 +17,11 @@ __device__ __forceinline__ int32_t uniform_i32(int32_t v) { return __builtin_amd
 // Sampled rows are not moved where a row's last group is short (own_columns): the lane takes the row's last four columns
 // as they lie, its z is moved to meet them for the dot products (zeros for its neighbour's columns), and its gradient is
 // moved to its own columns once it is summed.  Both are skipped by wavefronts without such a lane.
+// Zero times an infinite feature is NaN, and a NaN margin makes the whole message NaN where an infinite one loses that feature's
+// column alone.  So where the products of a wavefront have a NaN they are taken again with zeros for what is not the
+// lane's own (own_of_row).  (Rows of whole groups keep one way to a NaN: lanes past the last column read the row's first group.)
 template <bool ODD, typename V> __device__ __forceinline__ V z_for_rows(V z, int back) { return ODD && __any(back != 0) ? last_columns(z, back) : z; }
 template <bool ODD, typename V> __device__ __forceinline__ V own_gradient(V e, int back) { return ODD && __any(back != 0) ? own_columns(e, back) : e; }
-
 // partial[(agent * nchunks + chunk) * B + j] = sum over the chunk's columns of A[row_j][col] * z[agent][col].
 // A workgroup takes one column chunk of kRowGroup sampled rows of one agent (grid: chunks x agents x row groups),
 // so few agents still spread over many workgroups.
@@ -87,6 +89,10 @@ __global__ __launch_bounds__(kBlock) void margins_kernel(const GemvArgs G) {
   float acc[kRowGroup];
 #pragma unroll
   for (int jj = 0; jj < kRowGroup; ++jj) acc[jj] = dot_v(a[jj], z);
+  if (ODD && some_nan(acc)) {
+#pragma unroll
+    for (int jj = 0; jj < kRowGroup; ++jj) acc[jj] = dot_v(own_of_row(a[jj], columns_left(c, G.d)), z);
+  }
   int jj;
   bool owner;
   const float s = wave_sum_many<kRowGroup>(acc, lane, jj, owner);
@@ -207,6 +213,14 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
       m[j] = 0.0f;
 #pragma unroll
       for (int u = 0; u < G; ++u) m[j] += dot_v(a[j][u], zr[u]);
+    }
+    if (ODD && some_nan(m)) {
+#pragma unroll
+      for (int j = 0; j < BMAX; ++j) {
+        m[j] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < G; ++u) m[j] += dot_v(own_of_row(a[j][u], columns_left(((int64_t)u * THREADS + threadIdx.x) * 4, P.d)), zr[u]);
+      }
     }
     constexpr int CH = BMAX < 16 ? BMAX : 16;        // margins are summed across the wavefront 16 at a time
 #pragma unroll
@@ -367,6 +381,14 @@ void grad_chunked_kernel(const GemvArgs P) {
       m[j] = 0.0f;
 #pragma unroll
       for (int u = 0; u < G; ++u) m[j] += dot_v(a[j][u], z[u]);
+    }
+    if (ODD && some_nan(m)) {
+#pragma unroll
+      for (int j = 0; j < CH; ++j) {
+        m[j] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < G; ++u) m[j] += dot_v(own_of_row(a[j][u], columns_left(((int64_t)u * THREADS + threadIdx.x) * VEC, P.d)), z[u]);
+      }
     }
     int jrow;
     bool owner;

@@ -151,7 +151,7 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
           float m[CH];
 #pragma unroll
           for (int j = 0; j < CH; ++j)
-            m[j] = dot_v(ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c - back : first)), zr);
+            m[j] = dot_v(own_of_row(ld_plain<V>(Abase + (int64_t)__builtin_amdgcn_readlane(myidx, c0 + j) * P.lda + (on ? c - back : first)), ODD ? columns_left(c, P.d) : 4), zr);
           int jrow;
           bool owner;
           const float msum = wave_sum_many<CH>(m, lane, jrow, owner);
@@ -297,6 +297,10 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
       float m[MG];
 #pragma unroll
       for (int j = 0; j < MG; ++j) m[j] = dot_v(a[c0 + j], zr);
+      if (ODD && some_nan(m)) {
+#pragma unroll
+        for (int j = 0; j < MG; ++j) m[j] = dot_v(own_of_row(a[c0 + j], columns_left(c, P.d)), zr);
+      }
       int jrow;
       bool owner;
       const float msum = wave_sum_many<MG>(m, lane, jrow, owner);
