@@ -83,6 +83,9 @@ enum { CECA_FORM_NONE = 0, CECA_FORM_STEP_SINGLE = 1, CECA_FORM_STEP_ONE_PASS = 
        CECA_FORM_RUN_STEPS = 8 };
 int32_t ceca_last_form(void);
 
+/* 1 if the workgroups of the calling thread's last one-kernel window (RUN_WINDOW) were placed on one XCD, else 0. */
+int32_t ceca_last_window_on_one_xcd(void);
+
 /* Launch shape the library picks (under the calling thread's overrides) for the state-updating kernel of one
  * ceca_gossip_round (kind = 0), of one dsgd_ceca_step with the quadratic-centre loss (kind = 1) or of one
  * dsgd_ceca_step with a minibatch loss (kind = 2: the combine from stored messages) on a 16-byte aligned

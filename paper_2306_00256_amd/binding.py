@@ -23,7 +23,7 @@ EXPORTS = (
     "consensus_error_workspace_bytes", "consensus_error", "consensus_error_noalloc", "ceca_state_consensus", "ceca_topology_round", "ceca_mix_rounds", "ceca_graph_rounds", "ceca_last_error", "ceca_last_hip_error",
 )
 # include/ceca_test.h: launch-shape overrides and probe kernels for tests and measurement, not the product ABI
-TEST_EXPORTS = ("ceca_set_option", "ceca_reset_options", "ceca_stream_probe", "ceca_describe_step_launch", "ceca_last_form")
+TEST_EXPORTS = ("ceca_set_option", "ceca_reset_options", "ceca_stream_probe", "ceca_describe_step_launch", "ceca_last_form", "ceca_last_window_on_one_xcd")
 
 
 class CecaError(RuntimeError):
@@ -116,6 +116,8 @@ def lib():
         L.ceca_describe_step_launch.restype = C.c_int32
         L.ceca_last_form.argtypes = []
         L.ceca_last_form.restype = C.c_int32
+        L.ceca_last_window_on_one_xcd.argtypes = []
+        L.ceca_last_window_on_one_xcd.restype = C.c_int32
         L.ceca_reset_options.argtypes = []
         L.ceca_reset_options.restype = C.c_int32
         L.ceca_last_error.restype = C.c_char_p
@@ -273,6 +275,11 @@ def ceca_describe_step_launch(n: int, d: int, ld: int, r: int, port: int, kind: 
 def ceca_last_form() -> int:
     """The form (FORM_*) that this thread's last minibatch step or run took (ceca_test.h)."""
     return int(lib().ceca_last_form())
+
+
+def ceca_last_window_on_one_xcd() -> bool:
+    """Whether this thread's last one-kernel window played on one XCD (ceca_test.h)."""
+    return bool(lib().ceca_last_window_on_one_xcd())
 
 
 def ceca_set_option(option: int, value: int) -> None:

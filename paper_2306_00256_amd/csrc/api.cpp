@@ -24,6 +24,7 @@ using ceca::g_tuning;
 thread_local char g_msg[256] = "";
 thread_local int32_t g_hip = 0;
 thread_local int32_t g_form = CECA_FORM_NONE;     // ceca_last_form
+thread_local int32_t g_window_on_one_xcd = 0;      // ceca_last_window_on_one_xcd
 
 int32_t fail(int32_t code, const char* fmt, ...) {
   va_list ap;
@@ -662,6 +663,7 @@ int32_t ceca_reset_options(void) {
 }
 
 int32_t ceca_last_form(void) { return g_form; }
+int32_t ceca_last_window_on_one_xcd(void) { return g_window_on_one_xcd; }
 
 int32_t ceca_tau(int32_t n) {
   if (n < 1) return fail(CECA_EINVAL, "n = %d: need at least one agent", n);
@@ -955,6 +957,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     const hipError_t e = ceca::launch_run(a, shape, st);
     if (e != hipSuccess) return hip_fail(e, "window kernel launch");
     g_form = CECA_FORM_RUN_WINDOW;
+    g_window_on_one_xcd = shape.one_xcd;
     return CECA_OK;
   }
   const bool fused = n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&

@@ -493,13 +493,15 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, h
   }
   int usable = 0;
   for (uint32_t m : mask) usable += __builtin_popcount(m);
-  if (usable < cus) cus = usable;
+  const bool all_units = usable >= cus;
+  if (!all_units) cus = usable;
   if ((int64_t)n * s.nchunks * 8 > (int64_t)cus * s.wg_per_cu) return false;
   *out = s;
   // Windows that need an eighth of one XCD's places (eight of a like shape fit there) play on one: n = 5, d = 1000, B = 8 1.92 ->
   // 1.68 us per iteration, n = 17, d = 180, B = 8 1.57 -> 1.38, n = 5, B = 32 3.2 -> 2.9.  Which one follows the workspace's
-  // address, so that windows side by side spread.  Not on streams restricted to some compute units.
-  out->one_xcd = usable >= cus && (int64_t)n * s.nchunks * 64 <= (int64_t)cus * s.wg_per_cu;
+  // address, so that windows side by side spread.  Not on streams restricted to some compute units: that XCD may have too few of
+  // them, and the window is then given up after its roll call.
+  out->one_xcd = all_units && (int64_t)n * s.nchunks * 64 <= (int64_t)cus * s.wg_per_cu;
   return true;
 }
 
