@@ -500,8 +500,11 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, h
   // Windows that need an eighth of one XCD's places (eight of a like shape fit there) play on one: n = 5, d = 1000, B = 8 1.92 ->
   // 1.68 us per iteration, n = 17, d = 180, B = 8 1.57 -> 1.38, n = 5, B = 32 3.2 -> 2.9.  Which one follows the workspace's
   // address, so that windows side by side spread.  Not on streams restricted to some compute units: that XCD may have too few of
-  // them, and the window is then given up after its roll call.
-  out->one_xcd = all_units && (int64_t)n * s.nchunks * 64 <= (int64_t)cus * s.wg_per_cu;
+  // them, and the window is then given up after its roll call.  Nor where the words of several agents share a line and many
+  // workgroups of that XCD poll it: messages of one group (d = 4) gain 5 to 15 % up to 25 agents and lose up to 23 % from 35
+  // on, other messages shorter than a line gain up to 45 and are even, 0.93 to 1.09 of the time, from 50 on.
+  const int64_t message = run_row_words(d) * (int64_t)sizeof(unsigned long long);
+  out->one_xcd = all_units && n <= (message == 32 ? 30 : message < 128 ? 48 : 64) && (int64_t)n * s.nchunks * 64 <= (int64_t)cus * s.wg_per_cu;
   return true;
 }
 

@@ -8,7 +8,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,d,B,one_xcd", [(2, 1000, 8, True), (16, 1000, 8, True), (17, 1000, 8, False), (2, 1000, 32, True), (8, 1000, 32, True), (9, 1000, 32, False)])
+@pytest.mark.parametrize("n,d,B,one_xcd", [(2, 1000, 8, True), (16, 1000, 8, True), (17, 1000, 8, False), (2, 1000, 32, True), (8, 1000, 32, True), (9, 1000, 32, False),
+                                         (30, 4, 4, True), (31, 4, 4, False), (48, 8, 8, True), (49, 8, 8, False), (64, 16, 8, True), (48, 3, 8, True), (49, 3, 8, False)])
 def test_windows_on_masked_streams_are_spread(n, d, B, one_xcd):
     import torch
     import paper_2306_00256_amd as P
