@@ -139,12 +139,12 @@ struct RunArgs {
   unsigned long long* words;  // {tag, value} words: two message slots [n][dw], then two slots of partial margins [n][nchunks][B]
   unsigned long long* roll;   // the word after them: complete or given up (set by the launcher)
   int64_t d;
-  int64_t dw;              // words of an agent's message (set by the launcher)
-  int32_t one_xcd, xcd;    // 1: the window plays on that XCD (set by the launcher)
   int32_t n, N, B, kind, nchunks, port, iters, tau, r0;
   float lr, scale, noise_std;
   uint32_t seed, k;
   MultiRound round[kRunMaxTau];
+  int64_t dw;              // words of an agent's message (set by the launcher)
+  int32_t xcd;             // the XCD that a window on one plays on (set by the launcher)
 };
 
 struct ConsensusArgs {

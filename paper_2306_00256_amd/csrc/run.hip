@@ -118,6 +118,9 @@ __device__ __forceinline__ int peer_of(const RunArgs& P, const MultiRound& R, in
   return p;
 }
 
+// Words of an agent's message (RunArgs::dw; rows of whole groups have as many as columns: one number fewer in scalar registers).
+template <bool ODD> __device__ __forceinline__ int64_t row_words(const RunArgs& P) { return ODD ? P.dw : P.d; }
+
 // The whole window by one workgroup: iteration by iteration every agent's message, then every agent's combine, with the
 // state in the output rows and the messages in the workspace.  Operation for operation what the workgroups of run_kernel
 // do together; `red` and `part` are theirs.
@@ -211,12 +214,12 @@ __device__ __forceinline__ void run_alone(const RunArgs& P, float (&red)[2][THRE
 
 // The roll: a workgroup is there when its first word has a tag -- the margin of sample 0 of its chunk, or the first word
 // of its agent's message.  True if the window is complete.
-template <int THREADS, bool CHUNKS>
+template <int THREADS, bool CHUNKS, bool ODD>
 __device__ __forceinline__ bool call_roll(const RunArgs& P) {
   Patience wait(P);
   bool here = true;
   for (int i = threadIdx.x; i < P.n * P.nchunks && here; i += THREADS) {
-    const Word* first = P.words + (CHUNKS ? 2 * (int64_t)P.n * P.dw + (int64_t)i * P.B : (int64_t)i * P.dw);
+    const Word* first = P.words + (CHUNKS ? 2 * (int64_t)P.n * row_words<ODD>(P) + (int64_t)i * P.B : (int64_t)i * row_words<ODD>(P));
     wait.begin();
     do here = (peek(first) >> 32) != 0;
     while (!here && wait.again());
@@ -242,8 +245,8 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
   const int64_t col = on ? c : 0;
   const int back = short_back<ODD>(col, P.d);
   // message words of an agent: VEC planes of a word per group, so that neighbouring lanes touch neighbouring words
-  const int64_t plane = P.dw / VEC;
-  const int64_t mine = (int64_t)agent * P.dw + col / VEC;
+  // (all of a window's words are far fewer than 2^31)
+  const uint32_t words = (uint32_t)row_words<ODD>(P), plane = words / VEC, group = (uint32_t)col / VEC;
 
   V x = ld_own<V>(P.xin + (int64_t)agent * P.ld + col, back);
   V y = ld_own<V>(P.yin + (int64_t)agent * P.ld + col, back);
@@ -275,7 +278,8 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
     }
   };
   request_rows();
-  int32_t idx_next = idx[P.iters > 1 ? nb : 0];
+  idx += P.iters > 1 ? nb : 0;
+  int32_t idx_next = *idx;
   Patience wait(P);
   int r = P.r0;
   int reader = agent;                      // who read my message two iterations ago (after the shifts below)
@@ -284,8 +288,11 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
     const int par = t & 1;
     const MultiRound& R = P.round[r];
     const uint32_t tag = (uint32_t)t + 1;
+    const int p = peer_of(P, R, agent);    // whose message I read, and who reads mine
+    int to = p;
+    if (P.port == 2) { to = agent + R.shift; if (to >= P.n) to -= P.n; }
     // the look at the reader of my message of iteration t - 2: has it published iteration t - 1?
-    const Word* seen = P.words + (int64_t)(par ^ 1) * P.n * P.dw + (int64_t)reader * P.dw + col / VEC;
+    const Word* seen = P.words + ((uint32_t)((par ^ 1) * P.n + reader) * words + group);
     Word ack = 0;
     if (t >= 2 && on) ack = peek(seen);
 
@@ -309,7 +316,7 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
     __syncthreads();
     float mj = 0.0f;
     if (CHUNKS) {
-      Word* ring = P.words + 2 * (int64_t)P.n * P.dw + ((int64_t)par * P.n + agent) * P.nchunks * P.B;
+      Word* ring = P.words + (2 * (uint32_t)P.n * words + (uint32_t)(par * P.n + agent) * (uint32_t)(P.nchunks * P.B));
       if (tid < P.B) {
         float s = 0.0f;
 #pragma unroll
@@ -355,15 +362,12 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
     if (P.noise_std != 0.0f) e = add_noise<V>(e, P.noise_std, col, noise_keys(P.seed, P.k + (uint32_t)t, (uint32_t)agent));
     const V v = z - P.lr * e;
 
-    const int p = peer_of(P, R, agent);    // whose message I read, and who reads mine
-    int to = p;
-    if (P.port == 2) { to = agent + R.shift; if (to >= P.n) to -= P.n; }
     if (t >= 2 && on) {
       wait.begin();
       while ((uint32_t)(ack >> 32) < (uint32_t)t && wait.again()) ack = peek(seen);
     }
     if (on) {
-      Word* slot = P.words + (int64_t)par * P.n * P.dw + mine;
+      Word* slot = P.words + ((uint32_t)(par * P.n + agent) * words + group);
 #pragma unroll
       for (int u = 0; u < VEC; ++u) publish(slot + u * plane, tag, Parts<VEC>::get(v, u));
     }
@@ -372,11 +376,12 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
       const int32_t now = myidx;
       myidx = min(max(idx_next, 0), P.N - 1);
       if (__any(now != myidx)) request_rows();                   // the same in every wavefront
-      idx_next = idx[(int64_t)min(t + 2, P.iters - 1) * nb];
+      idx += t + 2 < P.iters ? nb : 0;
+      idx_next = *idx;
     }
     V msg = V(0.0f);
     if (on) {
-      const Word* slot = P.words + (int64_t)par * P.n * P.dw + (int64_t)p * P.dw + col / VEC;
+      const Word* slot = P.words + ((uint32_t)(par * P.n + p) * words + group);
       wait.begin();
       Word w[VEC];
       bool here;
@@ -411,15 +416,16 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
   return true;
 }
 
-template <int VEC, int THREADS, int BMAX, bool CHUNKS, bool ODD>
+// ONE_XCD is a template parameter because the chunked instances are at the limit of their scalar registers.
+template <int VEC, int THREADS, int BMAX, bool CHUNKS, bool ODD, bool ONE_XCD>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(run_waves<VEC, THREADS, BMAX>(), 8)))
 void run_kernel(const RunArgs P) {
   __shared__ float red[2][THREADS / 64][BMAX];                   // alternating between iterations
   __shared__ float part[CHUNKS ? kRunParts : 1];                 // partial margins of every chunk of the agent
   // workgroups go round-robin over the XCDs: of a window on one of them, only every eighth plays
-  if (P.one_xcd && (blockIdx.x & 7) != (uint32_t)P.xcd) return;
-  const int wg = (int)(P.one_xcd ? blockIdx.x >> 3 : blockIdx.x), wgs = (int)(P.one_xcd ? gridDim.x >> 3 : gridDim.x);
-  if (wg + 1 == wgs ? call_roll<THREADS, CHUNKS>(P) : take_part<VEC, THREADS, BMAX, CHUNKS, ODD>(P, wg, red, part)) return;
+  if (ONE_XCD && (blockIdx.x & 7) != (uint32_t)P.xcd) return;
+  const int wg = (int)(ONE_XCD ? blockIdx.x >> 3 : blockIdx.x), wgs = (int)(ONE_XCD ? gridDim.x >> 3 : gridDim.x);
+  if (wg + 1 == wgs ? call_roll<THREADS, CHUNKS, ODD>(P) : take_part<VEC, THREADS, BMAX, CHUNKS, ODD>(P, wg, red, part)) return;
   // given up (the same for every thread): nothing has been stored; my own words are behind me before I leave
   __shared__ bool last_s;
   __threadfence();
@@ -508,13 +514,13 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, h
   return true;
 }
 
-template <int VEC, int THREADS, int BMAX, bool ODD>
+template <int VEC, int THREADS, int BMAX, bool ODD, bool ONE_XCD>
 static hipError_t launch(const RunArgs& a, hipStream_t st) {
   const int32_t kept = a.n * a.nchunks - g_tuning.window_missing;
   const unsigned wgs = (unsigned)(kept < 0 ? 0 : kept) + 1;                   // the last one calls the roll
-  const dim3 grid(a.one_xcd ? wgs * 8 : wgs), block(THREADS);
-  if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false, ODD><<<grid, block, 0, st>>>(a);
-  else if constexpr (THREADS == 256 && VEC == 4) run_kernel<VEC, THREADS, BMAX, true, ODD><<<grid, block, 0, st>>>(a);
+  const dim3 grid(ONE_XCD ? wgs * 8 : wgs), block(THREADS);
+  if (a.nchunks == 1) run_kernel<VEC, THREADS, BMAX, false, ODD, ONE_XCD><<<grid, block, 0, st>>>(a);
+  else if constexpr (THREADS == 256 && VEC == 4) run_kernel<VEC, THREADS, BMAX, true, ODD, ONE_XCD><<<grid, block, 0, st>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -522,7 +528,6 @@ static hipError_t launch(const RunArgs& a, hipStream_t st) {
 hipError_t launch_run(const RunArgs& a0, const RunShape& s, hipStream_t st) {
   RunArgs a = a0;
   a.dw = run_row_words(a.d);
-  a.one_xcd = s.one_xcd;
   a.xcd = (int32_t)((reinterpret_cast<uintptr_t>(a.words) >> 12 ^ reinterpret_cast<uintptr_t>(a.words) >> 21) & 7);
   a.roll = a.words + run_kernel_words(s, a.n, a.d, a.B);
   const int64_t words = run_kernel_words(s, a.n, a.d, a.B) + 1;
@@ -533,13 +538,15 @@ hipError_t launch_run(const RunArgs& a0, const RunShape& s, hipStream_t st) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   switch ((minibatch_vec(a.d) ? 1 << 20 : 0) + s.threads * 64 + s.bmax - 1) {
-#define CECA_RUN(VEC, T, BM) case (VEC == 4 ? 1 << 20 : 0) + T * 64 + BM - 1: return VEC == 4 && a.d % 4 ? launch<VEC, T, BM, VEC == 4>(a, st) : launch<VEC, T, BM, false>(a, st)
+#define CECA_RUN_XCD(VEC, T, BM, ODD) s.one_xcd ? launch<VEC, T, BM, ODD, true>(a, st) : launch<VEC, T, BM, ODD, false>(a, st)
+#define CECA_RUN(VEC, T, BM) case (VEC == 4 ? 1 << 20 : 0) + T * 64 + BM - 1: if (VEC == 4 && a.d % 4) return CECA_RUN_XCD(VEC, T, BM, VEC == 4); return CECA_RUN_XCD(VEC, T, BM, false)
     CECA_RUN(4, 64, 8); CECA_RUN(4, 64, 16); CECA_RUN(4, 64, 32); CECA_RUN(4, 64, 64);
     CECA_RUN(4, 256, 8); CECA_RUN(4, 256, 16); CECA_RUN(4, 256, 32); CECA_RUN(4, 256, 64);
     CECA_RUN(4, 1024, 8); CECA_RUN(4, 1024, 16);
     CECA_RUN(1, 64, 16); CECA_RUN(1, 64, 64);
     CECA_RUN(1, 256, 16); CECA_RUN(1, 256, 64);
 #undef CECA_RUN
+#undef CECA_RUN_XCD
   }
   return hipErrorInvalidValue;
 }
