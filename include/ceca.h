@@ -20,7 +20,9 @@
  *   - Agents and rounds are 0-based: row i is the paper's agent i+1, r = k mod tau
  *     is the ordinary remainder in [0, tau) (Algorithm 1).
  *   - Any base pointer / leading dimension is accepted, with identical results (rows that
- *     lie on 128-byte boundaries are the fastest).
+ *     lie on 128-byte boundaries are the fastest).  The minibatch losses sum rows of up to 256
+ *     columns in an order that depends on whether they lie on 16-byte boundaries: identical up
+ *     to rounding there.
  *   - The functions declared here keep no mutable state between calls beyond the calling
  *     thread's last error (ceca_last_error, ceca_last_hip_error) and may be called from
  *     several threads at once.  Launch shapes are the library's own; the per-thread
@@ -72,8 +74,9 @@ typedef struct {
  *               N, B, seed, k, noise_std, grad_scale, A, t are ignored
  * eps_i ~ N(0, I) comes from the counter-based generator below, keyed by (seed, k, agent, column).
  * Sampled rows should be finite.  With the logistic loss an infinite feature gives an infinite margin and a finite coefficient, so
- * only its own column is lost -- except in the first columns of the rows (four of them where d is a multiple of 4, else one on
- * rows of up to 256), which spare lanes multiply by zero: there the margin becomes NaN, and with it the agent's whole message.
+ * only its own column is lost -- except in the first columns of a row (of a workgroup's share of it), up to four, which spare
+ * lanes multiply by zero: there the margin becomes NaN, and with it the agent's whole message.  (Not on rows of more than 256
+ * columns whose length is no multiple of 4.)
  *
  * Noise generator (uint32 arithmetic, wrapping; agent and column 0-based):
  *   mix(h):   h ^= h >> 16; h *= 0x7feb352d; h ^= h >> 15; h *= 0x846ca68b; h ^= h >> 16
@@ -185,8 +188,8 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * rows batch_idx + t * n * B (device, iters * n * B int32) and the one step size lr; the result has the
  * same bits as `iters` calls of dsgd_ceca_step.  Small problems run the
  * whole window as one kernel whose workgroups wait for each other's messages: those whose workgroups fit an
- * eighth of the device's 256 compute units (d a multiple of 4 up to 256: 512, 384, 256 and 128
- * agents for B <= 8, 16, 32 and 64; other d: 512 up to 64, 128 up to 256; a few dozen agents at d <= 4096, about
+ * eighth of the device's 256 compute units (d a multiple of 4 up to 256 on 16-byte boundaries: 512, 384, 256 and 128
+ * agents for B <= 8, 16, 32 and 64; others: 512 up to d = 64, 128 or more up to 256; a few dozen agents at d <= 4096, about
  * six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096 with B <= 8, nor rows
  * of more than 2048 columns that are no multiple of 4; a
  * stream restricted to some compute units counts those).  Where several workgroups share an agent's columns

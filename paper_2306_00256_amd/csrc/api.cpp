@@ -187,6 +187,11 @@ GemvPlan gemv_plan(int32_t n, int64_t d, int32_t B) {
   return p;
 }
 
+// Whether this call's rows go in 16-byte groups.
+bool minibatch_vec(const float* S, int64_t ld, int64_t d, const ceca_loss_t& loss) {
+  return ceca::minibatch_vec(d, loss.B, aligned16(S) && ld % 4 == 0 && aligned16(loss.A) && loss.lda % 4 == 0);
+}
+
 int32_t check_loss(const ceca_loss_t* loss, int64_t d, bool need_batch, const int32_t* batch_idx) {
   if (!loss) return fail(CECA_EINVAL, "null loss");
   switch (loss->kind) {
@@ -847,7 +852,8 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
   g.noise_std = loss->noise_std;
   g.seed = loss->seed;
   g.k = loss->k;
-  g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (ceca::minibatch_vec(d) ? 4 : 1);
+  g.vec = minibatch_vec(S_in, ld, d, *loss);
+  g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (g.vec ? 4 : 1);
   g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
   hipError_t e = hipSuccess;
   // small problems: one launch, in which every agent's workgroup also evaluates its peer's message (with two ports out
@@ -919,6 +925,9 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   const int32_t tau = ceca::tau_of(n);
   char* w = reinterpret_cast<char*>(workspace);
   const int64_t nb = (int64_t)n * loss->B;
+  // the gradient kernel of an iteration is chosen by the layout of the state that it reads, S_in first, then S_out: the forms
+  // of more than one iteration need the two to agree
+  const bool vec = minibatch_vec(S_in, ld, d, *loss), same_layout = vec == minibatch_vec(S_out, ld, d, *loss);
   // (a workspace of the size before the roll was added to it is still taken, with another form where the words fill it)
   auto window_roll_fits = [&](int64_t words) {
     return words + 8 <= workspace_bytes && !overlaps(workspace, words + 8, S_out, sbytes) && !overlaps(workspace, words + 8, S_in, sbytes);
@@ -930,8 +939,8 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   // floats leaves, so it depends on the length.  Of all lengths to 12,000 that are multiples of 4, with up to 40 agents: 87 % or
   // more to B = 16, 68 % at B = 32, 43 % at B = 64.
   ceca::RunShape shape{};
-  if (n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
-      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, loss->N, loss->lda, st, &shape) &&
+  if (same_layout && n > 1 && iters > 1 && tau <= ceca::kRunMaxTau && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
+      !g_tuning.no_half_step && ceca::run_kernel_shape(n, d, loss->B, vec, loss->N, loss->lda, st, &shape) &&
       ceca::run_kernel_words(shape, n, d, loss->B) * 8 <= need && window_roll_fits(ceca::run_kernel_words(shape, n, d, loss->B) * 8)) {
     ceca::RunArgs a{};
     a.xin = S_in;  a.yin = S_in + (int64_t)n * ld;
@@ -960,15 +969,15 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     g_window_on_one_xcd = shape.one_xcd;
     return CECA_OK;
   }
-  const bool fused = n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
-                     ceca::grad_fused_covers(n, d, loss->B);
+  const bool fused = same_layout && n > 1 && iters > 1 && !g_tuning.two_pass_gradient && !g_tuning.never_chunked &&
+                     ceca::grad_fused_covers(n, d, loss->B, vec);
   // Shapes whose single step takes the two-pass gradient (margins, then half step): the combine of the
   // iteration before becomes the prologue of the margins kernel -- two launches per iteration instead of
   // three, same bits.  The row groups of that kernel all read the old rows while one of them stores the
   // new ones, so the state alternates between S_out and a copy in the workspace.
-  const bool two_pass = g_tuning.two_pass_gradient || !ceca::grad_fused_covers(n, d, loss->B);
+  const bool two_pass = g_tuning.two_pass_gradient || !ceca::grad_fused_covers(n, d, loss->B, vec);
   const bool copy_fits = 2 * (int64_t)n * ld * (int64_t)sizeof(float) <= run_state_bytes(n, d);     // the copy keeps the caller's pitch
-  if (!fused && two_pass && copy_fits && n > 1 && iters > 1 && n <= 65535) {
+  if (!fused && two_pass && same_layout && copy_fits && n > 1 && iters > 1 && n <= 65535) {
     float* V2[2] = {reinterpret_cast<float*>(w), reinterpret_cast<float*>(w + p.v_bytes)};
     float* W = reinterpret_cast<float*>(w + 2 * p.v_bytes + p.partial_bytes);
     ceca::GemvArgs g{};
@@ -981,7 +990,8 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     g.scale = loss->grad_scale > 0.0f ? loss->grad_scale : 1.0f / (float)loss->B;
     g.noise_std = loss->noise_std;
     g.seed = loss->seed;
-    g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (ceca::minibatch_vec(d) ? 4 : 1);
+    g.vec = vec;
+    g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * (vec ? 4 : 1);
     g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
     // where the state lives before iteration t's prologue: S_in, then the copy and S_out in turn
     const float* cur = S_in;
@@ -1055,6 +1065,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     g.ldv = p.ldv;
     g.d = d;
     g.n = n;  g.N = loss->N;  g.B = loss->B;  g.kind = loss->kind;
+    g.vec = vec;
     g.lr = lr;
     g.scale = loss->grad_scale > 0.0f ? loss->grad_scale : 1.0f / (float)loss->B;
     g.noise_std = loss->noise_std;
@@ -1101,6 +1112,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
   g.scale = loss->grad_scale > 0.0f ? loss->grad_scale : 1.0f / (float)loss->B;
   g.noise_std = loss->noise_std;
   g.seed = loss->seed;
+  g.vec = vec;
   g.chunk_cols = ceca::kBlock * ceca::kChunkGroups * 4;
   g.nchunks = (int32_t)((d + g.chunk_cols - 1) / g.chunk_cols);
   const float* xin = S_in;

@@ -435,8 +435,13 @@ void grad_chunked_kernel(const GemvArgs P) {
 // are no whole groups: 64 or 256 threads hold those in single columns, with a quarter of the registers (window of n = 125, d = 199,
 // B = 46: 2.8 us per iteration against 3.7 in groups; n = 360, d = 95, B = 25 7.6 against 8.2).  Longer ones gain: n = 60, d =
 // 351, B = 17 8.0 -> 3.3 us per iteration, n = 600, d = 1547, B = 19 52 -> 29, n = 890, d = 1333, B = 53 133 -> 72, n = 313,
-// d = 4510, B = 11 53 -> 26.  The length alone decides, so every layout has the same bits.
-bool minibatch_vec(int64_t d) { return d % 4 == 0 || d > 256; }
+// d = 4510, B = 11 53 -> 26.
+// Whole groups of up to 256 columns that do not lie on 16-byte boundaries take single columns too where a batch over 32 leaves
+// groups few resident agents and no single-launch step, and up to 64 columns, which one wavefront holds: n = 391, d = 56, B = 40 6.9 us
+// per iteration in groups against 2.8, n = 448, d = 12, B = 13 6.2 against 2.6, single steps of n = 12, d = 8, B = 56 10.0
+// against 4.8; with 65 to 256 columns and B <= 32 groups take 0.8 to 1.0 of the time.  (Such rows on 16-byte boundaries stay in
+// groups; their last bits may differ from those of other layouts.)
+bool minibatch_vec(int64_t d, int32_t B, bool aligned) { return d > 256 || (d % 4 == 0 && (aligned || (d > 64 && B <= 32))); }
 
 // The chunked kernel for rows of d columns.  Workgroup size and column groups per thread are a
 // function of d alone and equal those of the one-pass variant for the same d, so either kernel (and
@@ -451,7 +456,7 @@ static hipError_t launch_chunked(const GemvArgs& g, hipStream_t st) {
     if (odd) grad_chunked_kernel<4, T, CH, G, FUSE, true><<<grid, dim3(T), 0, st>>>(g);     \
     else grad_chunked_kernel<4, T, CH, G, FUSE, false><<<grid, dim3(T), 0, st>>>(g);        \
   } while (0)
-  if (!minibatch_vec(g.d)) {
+  if (!g.vec) {
     if (g.d <= 64) grad_chunked_kernel<1, 64, 8, 1, FUSE, false><<<grid, dim3(64), 0, st>>>(g);
     else grad_chunked_kernel<1, 256, 8, 1, FUSE, false><<<grid, dim3(256), 0, st>>>(g);
   }
@@ -477,9 +482,9 @@ static bool onepass_tile_exists(int32_t B, int64_t d4) {
 // us against 254 / 325 / 569, at d = 12000 819 / 1197 / - against 651 / 1069; n = 80 at d = 2500 252 / 291 / 449 against 250 /
 // 319 / 560; on rows of little more than 1024 columns workgroups are too few for large batches (n = 112, d = 1200 241 / 283 /
 // 428 against 215 / 270 / 473).
-static bool chunked_by_default(int32_t n, int64_t d, int32_t B) {
+static bool chunked_by_default(int32_t n, int64_t d, int32_t B, bool vec) {
   const int64_t d4 = (d + 3) / 4;
-  if (!minibatch_vec(d)) return true;
+  if (!vec) return true;
   if (d4 > 4096) return false;
   return d4 <= 256 ? B > 32 : n >= 128 || (n >= 96 && (d > 2048 || B <= 32));
 }
@@ -494,19 +499,19 @@ bool two_pass_rows(int32_t n, int64_t d) { return d % 4 != 0 && d > 2048 && n <=
 // single step already uses the chunked kernel, and those where it uses a one-pass variant (same bits).
 // Few agents with a batch too large for a register tile stay with the two-pass kernels: a handful of
 // workgroups walking megabytes of rows would be slower than three launches.
-bool grad_fused_covers(int32_t n, int64_t d, int32_t B) {
-  return n >= 2 && (chunked_by_default(n, d, B) || (onepass_tile_exists(B, (d + 3) / 4) && !two_pass_rows(n, d)));
+bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec) {
+  return n >= 2 && (chunked_by_default(n, d, B, vec) || (onepass_tile_exists(B, (d + 3) / 4) && !two_pass_rows(n, d)));
 }
 
 bool launch_grad_fused(const GemvArgs& g, hipStream_t st, hipError_t* err) {
-  if (!grad_fused_covers(g.n, g.d, g.B)) return false;
+  if (!grad_fused_covers(g.n, g.d, g.B, g.vec)) return false;
   *err = launch_chunked<1>(g, st);
   return true;
 }
 
 // The same with the state kept in half-step form between iterations (px, py -> ox, oy: two different buffers).
 bool launch_grad_half(const GemvArgs& g, hipStream_t st, hipError_t* err) {
-  if (!grad_fused_covers(g.n, g.d, g.B)) return false;
+  if (!grad_fused_covers(g.n, g.d, g.B, g.vec)) return false;
   if (g.px == g.ox && !g.p_first) { *err = hipErrorInvalidValue; return true; }     // peers' rows are read while rows are written
   *err = launch_chunked<2>(g, st);
   return true;
@@ -518,7 +523,7 @@ bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err) {
   const int apw = g_tuning.agents_per_wg;
   // many agents, long rows: the chunked kernel (any B up to 64, d up to 16384), two workgroups per
   // compute unit; a handful of agents cannot fill the device that way and stays with the kernels below
-  if (chunked_by_default(g.n, g.d, g.B) && (!g_tuning.never_chunked || !minibatch_vec(g.d))) {
+  if (chunked_by_default(g.n, g.d, g.B, g.vec) && (!g_tuning.never_chunked || !g.vec)) {
     *err = launch_chunked<0>(g, st);
     return true;
   }
@@ -643,7 +648,7 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
 // 5.4 (one port 4.6); and at the limit n = 64, d = 1024, B = 32: 7.8 -> 5.7 (one port 5.6); n = 2000, d = 64, B = 16: 12.3 -> 5.5; n = 4000,
 // d = 10, B = 50: 18.2 -> 14.6.
 bool launch_pair_step(const GemvArgs& g, hipStream_t st, hipError_t* err) {
-  const bool both = g.p_port == 1, vec4 = minibatch_vec(g.d);
+  const bool both = g.p_port == 1, vec4 = g.vec;
   if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20)) return false;
   if (g.d % 4 != 0 && g.d > 256) return false;       // (short last groups: the tests of this form hold them to two kernels)
   if (both ? (g.n & 1) || !(g.p_shift & 1) : g.px == g.ox) return false;       // two ports: out of place only
@@ -671,7 +676,7 @@ bool launch_pair_step(const GemvArgs& g, hipStream_t st, hipError_t* err) {
 hipError_t launch_margins(const GemvArgs& g, hipStream_t st) {
   if (g.nchunks < 1 || g.n > 65535) return hipErrorInvalidConfiguration;
   dim3 grid((unsigned)g.nchunks, (unsigned)g.n, (unsigned)((g.B + kRowGroup - 1) / kRowGroup)), block(kBlock);
-  if (!minibatch_vec(g.d)) margins_kernel<1, false, false><<<grid, block, 0, st>>>(g);
+  if (!g.vec) margins_kernel<1, false, false><<<grid, block, 0, st>>>(g);
   else if (g.d % 4) margins_kernel<4, true, false><<<grid, block, 0, st>>>(g);
   else margins_kernel<4, false, false><<<grid, block, 0, st>>>(g);
   return hipGetLastError();
@@ -682,19 +687,19 @@ hipError_t launch_margins_fused(const GemvArgs& g, hipStream_t st) {
   // the row groups of an (agent, chunk) pair all read the old rows while the first one stores the new ones
   if (g.px == g.ox || g.py == g.oy) return hipErrorInvalidValue;
   dim3 grid((unsigned)g.nchunks, (unsigned)g.n, (unsigned)((g.B + kRowGroup - 1) / kRowGroup)), block(kBlock);
-  if (!minibatch_vec(g.d)) margins_kernel<1, false, true><<<grid, block, 0, st>>>(g);
+  if (!g.vec) margins_kernel<1, false, true><<<grid, block, 0, st>>>(g);
   else if (g.d % 4) margins_kernel<4, true, true><<<grid, block, 0, st>>>(g);
   else margins_kernel<4, false, true><<<grid, block, 0, st>>>(g);
   return hipGetLastError();
 }
 
 hipError_t launch_halfstep(const GemvArgs& g, hipStream_t st) {
-  const int vec = minibatch_vec(g.d) ? 4 : 1;
+  const int vec = g.vec ? 4 : 1;
   const int64_t groups = (g.d + vec - 1) / vec;
   const int64_t gx = (groups + kBlock - 1) / kBlock;
   if (gx < 1 || gx > 0x7fffffffLL || g.n > 65535) return hipErrorInvalidConfiguration;
   dim3 grid((unsigned)gx, (unsigned)g.n), block(kBlock);
-  if (!minibatch_vec(g.d)) halfstep_kernel<1, false><<<grid, block, 0, st>>>(g);
+  if (!g.vec) halfstep_kernel<1, false><<<grid, block, 0, st>>>(g);
   else if (g.d % 4) halfstep_kernel<4, true><<<grid, block, 0, st>>>(g);
   else halfstep_kernel<4, false><<<grid, block, 0, st>>>(g);
   return hipGetLastError();

@@ -94,6 +94,7 @@ struct GemvArgs {
   int64_t ldv;
   int64_t d;
   int32_t n, N, B, kind;
+  int32_t vec;            // 1: rows in 16-byte groups (minibatch_vec), 0: in single columns
   int32_t nchunks;
   int32_t chunk_cols;
   float lr;
@@ -119,6 +120,7 @@ constexpr int kRunMaxTau = 16;
 constexpr int kRunParts = 2048;      // most chunks x samples of an agent
 
 struct RunShape {
+  bool vec;                // rows in 16-byte groups
   int32_t threads;         // per workgroup: 64, 256 or 1024
   int32_t bmax;            // sampled rows in registers
   int32_t nchunks;         // workgroups per agent
@@ -260,21 +262,22 @@ extern thread_local Tuning g_tuning;
 
 // rows: state rows whose loads a thread keeps in flight together (1, 2, 4 or 8)
 hipError_t launch_chain(const ChainArgs& a, int mode, int rows, hipStream_t st);
-// whether a minibatch loss takes rows of d columns in 16-byte groups (else in single columns)
-bool minibatch_vec(int64_t d);
+// whether a minibatch loss takes rows of d columns in 16-byte groups (else in single columns); aligned: rows of the state and
+// of the samples lie on 16-byte boundaries
+bool minibatch_vec(int64_t d, int32_t B, bool aligned);
 // whether rows of that length keep to margins and half step
 bool two_pass_rows(int32_t n, int64_t d);
 // one-pass gradient: returns false when no register tile covers (B, d)
 bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err);
 // gradient kernel with the previous iteration's combine as its prologue; false when the shape is not covered
 bool launch_grad_fused(const GemvArgs& g, hipStream_t st, hipError_t* err);
-bool grad_fused_covers(int32_t n, int64_t d, int32_t B);
+bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec);
 // the fused form with the state in half-step rows between iterations: reads px, py (pitch ld), writes ox, oy
 // (pitch ldo, another buffer unless p_first); false when the shape is not covered
 bool launch_grad_half(const GemvArgs& g, hipStream_t st, hipError_t* err);
 // a whole window of iterations as one kernel whose workgroups wait for each other: the shape for this problem, false
 // where it does not apply; the 8-byte words it needs as scratch (one more behind them for the roll); the launch
-bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, hipStream_t st, RunShape* out);
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, bool vec, int32_t N, int64_t lda, hipStream_t st, RunShape* out);
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B);
 hipError_t launch_run(const RunArgs& a, const RunShape& s, hipStream_t st);
 // gradient, message and combine of one iteration as one kernel (px, py -> ox, oy; two ports: another buffer); false

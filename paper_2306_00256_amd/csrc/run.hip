@@ -446,22 +446,21 @@ __global__ __launch_bounds__(kBlock) void run_clear_kernel(Word* words, int64_t 
 // Threads per workgroup, register rows and chunks for this problem; threads = 0 where the kernel does not apply.
 // The shapes are those whose single step sums in the same order: one workgroup per agent where the gradient is taken
 // in one pass with one column group per thread, chunks of 256 threads where it takes two passes.
-static RunShape run_shape(int32_t n, int64_t d, int32_t B) {
-  RunShape s{0, 0, 1, 0, false};
-  const bool vec4 = minibatch_vec(d);
+static RunShape run_shape(int32_t n, int64_t d, int32_t B, bool vec4) {
+  RunShape s{vec4, 0, 0, 1, 0, false};
   if (n < 2 || B < 1 || B > 64 || (vec4 && two_pass_rows(n, d))) return s;
   const int64_t groups = vec4 ? (d + 3) / 4 : d;
   if (vec4) {
     if (groups <= 64) s.threads = 64;                            // (the single step's other wavefronts add zeros)
     else if (groups <= 256) s.threads = 256;
     else if (groups <= 1024 && B <= 16) s.threads = 1024;
-    else if (grad_fused_covers(n, d, B)) return s;               // wider rows in one workgroup
+    else if (grad_fused_covers(n, d, B, true)) return s;               // wider rows in one workgroup
     else s.threads = 256;
   } else {
     s.threads = groups <= 64 ? 64 : 256;
   }
   const int64_t chunks = (groups + s.threads - 1) / s.threads;
-  if (chunks * B > kRunParts && chunks > 1) return RunShape{0, 0, 1, 0, false};
+  if (chunks * B > kRunParts && chunks > 1) return RunShape{vec4, 0, 0, 1, 0, false};
   s.nchunks = (int32_t)chunks;
   s.bmax = vec4 ? (B <= 8 ? 8 : B <= 16 ? 16 : B <= 32 ? 32 : 64) : (B <= 16 ? 16 : 64);
   const int waves = s.threads == 1024 || !vec4 || s.bmax <= 8 ? 4 : s.bmax <= 16 ? 3 : s.bmax <= 32 ? 2 : 1;     // run_waves
@@ -470,18 +469,18 @@ static RunShape run_shape(int32_t n, int64_t d, int32_t B) {
 }
 
 // Words of an agent's message: whole groups.
-static int64_t run_row_words(int64_t d) { return minibatch_vec(d) ? (d + 3) / 4 * 4 : d; }
+static int64_t run_row_words(const RunShape& s, int64_t d) { return s.vec ? (d + 3) / 4 * 4 : d; }
 
 int64_t run_kernel_words(const RunShape& s, int32_t n, int64_t d, int32_t B) {
-  return 2 * (int64_t)n * run_row_words(d) + (s.nchunks > 1 ? 2 * (int64_t)n * s.nchunks * B : 0);
+  return 2 * (int64_t)n * run_row_words(s, d) + (s.nchunks > 1 ? 2 * (int64_t)n * s.nchunks * B : 0);
 }
 
 // Every workgroup of the kernel should be resident, whatever else runs (else the window is given up, see above): it may
 // take an eighth of the places that the stream's compute units have for it, so that eight such kernels of a like shape
 // fit beside each other; kernels of any other kind end by themselves and make room.  A stream restricted to some
 // compute units counts those only.
-bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, hipStream_t st, RunShape* out) {
-  const RunShape s = run_shape(n, d, B);
+bool run_kernel_shape(int32_t n, int64_t d, int32_t B, bool vec, int32_t N, int64_t lda, hipStream_t st, RunShape* out) {
+  const RunShape s = run_shape(n, d, B, vec);
   if (s.threads == 0 || lda >= (1LL << 30) / N) return false;    // an agent's rows within 32-bit distances: 4 GB
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
@@ -509,7 +508,7 @@ bool run_kernel_shape(int32_t n, int64_t d, int32_t B, int32_t N, int64_t lda, h
   // them, and the window is then given up after its roll call.  Nor where the words of several agents share a line and many
   // workgroups of that XCD poll it: messages of one group (d = 4) gain 5 to 15 % up to 25 agents and lose up to 23 % from 35
   // on, other messages shorter than a line gain up to 45 and are even, 0.93 to 1.09 of the time, from 50 on.
-  const int64_t message = run_row_words(d) * (int64_t)sizeof(unsigned long long);
+  const int64_t message = run_row_words(s, d) * (int64_t)sizeof(unsigned long long);
   out->one_xcd = all_units && n <= (message == 32 ? 30 : message < 128 ? 48 : 64) && (int64_t)n * s.nchunks * 64 <= (int64_t)cus * s.wg_per_cu;
   return true;
 }
@@ -527,7 +526,7 @@ static hipError_t launch(const RunArgs& a, hipStream_t st) {
 
 hipError_t launch_run(const RunArgs& a0, const RunShape& s, hipStream_t st) {
   RunArgs a = a0;
-  a.dw = run_row_words(a.d);
+  a.dw = run_row_words(s, a.d);
   a.xcd = (int32_t)((reinterpret_cast<uintptr_t>(a.words) >> 12 ^ reinterpret_cast<uintptr_t>(a.words) >> 21) & 7);
   a.roll = a.words + run_kernel_words(s, a.n, a.d, a.B);
   const int64_t words = run_kernel_words(s, a.n, a.d, a.B) + 1;
@@ -537,7 +536,7 @@ hipError_t launch_run(const RunArgs& a0, const RunShape& s, hipStream_t st) {
   run_clear_kernel<<<dim3((unsigned)blocks), dim3(kBlock), 0, st>>>(a.words, words);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  switch ((minibatch_vec(a.d) ? 1 << 20 : 0) + s.threads * 64 + s.bmax - 1) {
+  switch ((s.vec ? 1 << 20 : 0) + s.threads * 64 + s.bmax - 1) {
 #define CECA_RUN_XCD(VEC, T, BM, ODD) s.one_xcd ? launch<VEC, T, BM, ODD, true>(a, st) : launch<VEC, T, BM, ODD, false>(a, st)
 #define CECA_RUN(VEC, T, BM) case (VEC == 4 ? 1 << 20 : 0) + T * 64 + BM - 1: if (VEC == 4 && a.d % 4) return CECA_RUN_XCD(VEC, T, BM, VEC == 4); return CECA_RUN_XCD(VEC, T, BM, false)
     CECA_RUN(4, 64, 8); CECA_RUN(4, 64, 16); CECA_RUN(4, 64, 32); CECA_RUN(4, 64, 64);
