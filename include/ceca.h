@@ -190,8 +190,8 @@ int64_t dsgd_ceca_run_workspace_bytes(int32_t n, int64_t d, const ceca_loss_t* l
  * whole window as one kernel whose workgroups wait for each other's messages: those whose workgroups fit an
  * eighth of the device's 256 compute units (d a multiple of 4 up to 256 on 16-byte boundaries: 512, 384, 256 and 128
  * agents for B <= 8, 16, 32 and 64; others: 512 up to d = 64, 128 or more up to 256; a few dozen agents at d <= 4096, about
- * six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096 with B <= 8, nor rows
- * of more than 2048 columns that are no multiple of 4; a
+ * six at d = 10000; not the wide rows of small batches that one workgroup takes, d > 4096 with B <= 8 and a multiple
+ * of 4, nor batches of 8 and more on rows of more than 2048 columns that are no multiple of 4; a
  * stream restricted to some compute units counts those).  Where several workgroups share an agent's columns
  * (d > 1024 and B > 16, or d > 4096) their words also have to fit
  * the workspace, which depends on the length: up to B = 16 nine in ten lengths do, at B = 32 two in

@@ -489,10 +489,12 @@ static bool chunked_by_default(int32_t n, int64_t d, int32_t B, bool vec) {
   return d4 <= 256 ? B > 32 : n >= 128 || (n >= 96 && (d > 2048 || B <= 32));
 }
 
-// Rows of more than 2048 columns that are no whole groups, on few agents: margins and half step, in 16-byte groups.  (The
-// one-pass forms and windows of whole groups would take them too, n = 6, d = 2051, B = 9 4.6 us per iteration against 8.0, n = 3, d =
-// 9001, B = 4 12.8 against 7.8; tests of the two-pass form hold them to it.)  With more agents than a window takes the other
-// forms' rules apply (n = 100, d = 2101, B = 16 13.2 -> 10.4).
+// Rows of more than 2048 columns that are no whole groups, on few agents: margins and half step, in 16-byte groups, and windows
+// in chunks for batches of up to kTwoPassWindow samples, which single columns had before (where their words fitted the workspace: per
+// iteration n = 8, d = 2265, B = 2 3.3 us against 6.9 with two kernels, n = 2, d = 5702, B = 2 3.7 against 6.4).  One workgroup per
+// agent is not better throughout (n = 6, d = 2051, B = 9 4.6 us per iteration in a window of such workgroups against 8.0, n = 3, d =
+// 9001, B = 4 12.8 with one kernel per iteration against 7.8), and where the line lies has not been measured.  With more
+// agents than a window takes the other forms' rules apply (n = 100, d = 2101, B = 16 13.2 -> 10.4).
 bool two_pass_rows(int32_t n, int64_t d) { return d % 4 != 0 && d > 2048 && n <= 32; }
 
 // Shapes whose iterations can run as one fused kernel each with the bits of single steps: those where a

@@ -265,8 +265,9 @@ hipError_t launch_chain(const ChainArgs& a, int mode, int rows, hipStream_t st);
 // whether a minibatch loss takes rows of d columns in 16-byte groups (else in single columns); aligned: rows of the state and
 // of the samples lie on 16-byte boundaries
 bool minibatch_vec(int64_t d, int32_t B, bool aligned);
-// whether rows of that length keep to margins and half step
+// whether rows of that length keep to margins and half step; the largest batch whose windows run as one kernel all the same
 bool two_pass_rows(int32_t n, int64_t d);
+constexpr int32_t kTwoPassWindow = 7;
 // one-pass gradient: returns false when no register tile covers (B, d)
 bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err);
 // gradient kernel with the previous iteration's combine as its prologue; false when the shape is not covered

@@ -448,11 +448,13 @@ __global__ __launch_bounds__(kBlock) void run_clear_kernel(Word* words, int64_t 
 // in one pass with one column group per thread, chunks of 256 threads where it takes two passes.
 static RunShape run_shape(int32_t n, int64_t d, int32_t B, bool vec4) {
   RunShape s{vec4, 0, 0, 1, 0, false};
-  if (n < 2 || B < 1 || B > 64 || (vec4 && two_pass_rows(n, d))) return s;
+  const bool two_pass = vec4 && two_pass_rows(n, d);
+  if (n < 2 || B < 1 || B > 64 || (two_pass && B > kTwoPassWindow)) return s;
   const int64_t groups = vec4 ? (d + 3) / 4 : d;
   if (vec4) {
     if (groups <= 64) s.threads = 64;                            // (the single step's other wavefronts add zeros)
     else if (groups <= 256) s.threads = 256;
+    else if (two_pass) s.threads = 256;
     else if (groups <= 1024 && B <= 16) s.threads = 1024;
     else if (grad_fused_covers(n, d, B, true)) return s;               // wider rows in one workgroup
     else s.threads = 256;
