@@ -872,7 +872,7 @@ int32_t dsgd_ceca_step(const float* S_in, float* S_out, int32_t n, int64_t d, in
       return CECA_OK;
     }
   }
-  const bool onepass = !g_tuning.two_pass_gradient && ceca::launch_grad_onepass(g, st, &e);
+  const bool onepass = !g_tuning.two_pass_gradient && ceca::launch_grad_onepass(g, /*alone=*/true, st, &e);
   if (onepass) {
     if (e != hipSuccess) return hip_fail(e, "one-pass gradient kernel launch");
   } else {
@@ -1128,7 +1128,7 @@ int32_t dsgd_ceca_run(const float* S_in, float* S_out, int32_t n, int64_t d, int
     g.v = V[t & 1];
     if (t == 0) {
       g.zin = rd.exchange_y ? yin : xin;
-      if (!ceca::launch_grad_onepass(g, st, &e))
+      if (!ceca::launch_grad_onepass(g, /*alone=*/false, st, &e))
         return fail(CECA_EINVAL, "internal: gradient kernel does not cover this shape");
     } else {
       // the state before iteration t-1's combine: S_in for t = 1, then S_out (updated row by row in place)

@@ -519,8 +519,18 @@ bool launch_grad_half(const GemvArgs& g, hipStream_t st, hipError_t* err) {
   return true;
 }
 
+// Batches over 32 on rows of up to 1024 columns, in a step of its own: a workgroup walks them in dependent groups of eight rows,
+// where two passes have a workgroup per group, and few agents leave compute units idle.  Two passes against one, step in a captured
+// graph: d = 400, B = 64 n = 4 9.9 us against 12.6, n = 128 11.8 against 13.4, n = 256 14.7 against 15.3; B = 40 n = 4 9.0
+// against 9.9, n = 96 10.3 against 10.5, n = 128 11.2 against 10.9; d <= 256 (64 threads) B = 64 n = 8 10.0 against 11.1, n = 96
+// 11.4 against 11.5, B = 48 9.7 against 9.5, B = 33 9.2 against 8.6.  (Runs fuse one-pass iterations into one kernel each.)
+static bool two_passes_alone(const GemvArgs& g) {
+  return g.vec && g.d <= 1024 && g.B > 32 && (g.d <= 256 ? g.B > 48 && g.n < 96 : g.n < (g.B > 48 ? 256 : 128));
+}
+
 // Picks the one-pass variant whose register tile covers (B, d); false if none does.
-bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err) {
+bool launch_grad_onepass(const GemvArgs& g, bool alone, hipStream_t st, hipError_t* err) {
+  if (alone && two_passes_alone(g)) return false;
   const int64_t d4 = (g.d + 3) / 4;
   const int apw = g_tuning.agents_per_wg;
   // many agents, long rows: the chunked kernel (any B up to 64, d up to 16384), two workgroups per

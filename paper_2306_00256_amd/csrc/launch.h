@@ -268,8 +268,9 @@ bool minibatch_vec(int64_t d, int32_t B, bool aligned);
 // whether rows of that length keep to margins and half step; the largest batch whose windows run as one kernel all the same
 bool two_pass_rows(int32_t n, int64_t d);
 constexpr int32_t kTwoPassWindow = 7;
-// one-pass gradient: returns false when no register tile covers (B, d)
-bool launch_grad_onepass(const GemvArgs& g, hipStream_t st, hipError_t* err);
+// one-pass gradient: returns false when no register tile covers (B, d), and for a step of its own (alone) where two passes are
+// faster
+bool launch_grad_onepass(const GemvArgs& g, bool alone, hipStream_t st, hipError_t* err);
 // gradient kernel with the previous iteration's combine as its prologue; false when the shape is not covered
 bool launch_grad_fused(const GemvArgs& g, hipStream_t st, hipError_t* err);
 bool grad_fused_covers(int32_t n, int64_t d, int32_t B, bool vec);
