@@ -540,6 +540,12 @@ bool launch_grad_onepass(const GemvArgs& g, bool alone, hipStream_t st, hipError
     return true;
   }
   if (two_pass_rows(g.n, g.d)) return false;
+  // Rows of odd length where the looping kernel requests more than the batch (16 rows for one to eight, d <= 1024: a step 0.96 of the
+  // time, d = 385 6.7 us -> 6.4) or its tile spills (d > 8192, four groups per thread; n = 40, d = 9001, B = 2 19 -> 11 us).
+  if (g.d % 4 != 0 && !g_tuning.never_chunked && apw == 0 && (d4 <= 256 ? g.B <= 8 : d4 > 2048 && g.B <= 4)) {
+    *err = launch_chunked<0>(g, st);
+    return true;
+  }
   // 1024-thread workgroups fill a compute unit alone: one per unit, each looping over its agents;
   // 256-thread workgroups leave room for several per unit
 #define CECA_ONEPASS(T, BM, GG)                                          \
