@@ -404,7 +404,14 @@ struct TileShape {
 // kinds and leave rows of the tile a quarter as wide: with rows that are not 16-byte aligned, 2^26 elements, tiles of
 // single columns -> groups: exact averaging n = 9 164 -> 107 us, n = 130 295 -> 210, n = 1026 2181 -> 362; with aligned
 // rows of a length that is no multiple of four, one launch instead of two (n = 130, d = 8067: 18 -> 11.5 us).
+// Small problems on rows that are not 16-byte aligned take single columns: four times the workgroups, and the device is not
+// full.  Groups against single columns, geometric means over n = 3 to 4000 (and the largest): 2^17 elements exact averaging 1.48
+// times the time (2.4), fused rounds 1.44 (2.3), fused iterations 1.34 (1.6), one-peer rounds 1.41 (1.8); 2^19 elements 1.27 (1.7), 1.18
+// (1.5), 1.03 (1.3), 1.25 (1.6); 2^21 elements 0.88 (1.1), 0.83 (1.2), 0.80 (1.2), 0.93 (1.1).  Fused iterations, even at 2^19, change
+// there, the others at 2^20.  (Graph rounds keep groups, 0.87 of the time at 2^17.)
 constexpr int64_t kTileVecCols = 4;
+constexpr int64_t kSmallTiles = 1LL << 20, kSmallSteps = 1LL << 19;
+bool tile_groups(int32_t n, int64_t d, bool aligned, int64_t small = kSmallTiles) { return d >= kTileVecCols && (aligned || n * d >= small); }
 
 // The tile with at most `cap` rows per thread: the fewest row lanes that cover n give the widest rows.
 TileShape shape_tile(int32_t n, bool vec4, int32_t threads, int32_t cap) {
@@ -712,7 +719,7 @@ int32_t ceca_gossip_rounds(const float* S_in, float* S_out, int32_t n, int64_t d
   hipStream_t st = (hipStream_t)hip_stream;
   const int32_t tau = ceca::tau_of(n);
   const TileShape tv = rounds_tile(n, true), ts = rounds_tile(n, false);
-  const TileShape& tile = d >= kTileVecCols ? tv : ts;
+  const TileShape& tile = tile_groups(n, d, aligned16(S_in) && aligned16(S_out) && ld % 4 == 0) ? tv : ts;
   // A single round is the streaming kernel's job, and tiles with rows narrower than a 128-byte line pay
   // off only over a few rounds (measured: the fused pass costs about 1.5, 2.5 and 4.7 single rounds at
   // n = 1026, 2050 and 4096).
@@ -768,7 +775,7 @@ int32_t ceca_average(const float* X_in, float* X_out, int32_t n, int64_t d, int6
   const int32_t tau = ceca::tau_of(n);
   const TileShape tv = rounds_tile(n, true, false), ts = rounds_tile(n, false, false);
   if (!tv.ok || !ts.ok) return fail(CECA_EINVAL, "internal: no tile holds n = %d agents", n);
-  const TileShape& tile = d >= kTileVecCols ? tv : ts;
+  const TileShape& tile = tile_groups(n, d, aligned16(X_in) && aligned16(X_out) && ld % 4 == 0) ? tv : ts;
   ceca::MultiArgs m{};
   m.xin = X_in;
   m.xout = X_out;  m.yout = nullptr;
@@ -1174,7 +1181,7 @@ int32_t dsgd_ceca_steps(const float* S_in, float* S_out, int32_t n, int64_t d, i
   hipStream_t st = (hipStream_t)hip_stream;
   const int32_t tau = ceca::tau_of(n);
   const TileShape tv = steps_tile(n, true, steps), ts = steps_tile(n, false, steps);
-  const TileShape& tile = d >= kTileVecCols ? tv : ts;
+  const TileShape& tile = tile_groups(n, d, aligned16(S_in) && aligned16(S_out) && ld % 4 == 0 && aligned16(loss->c) && loss->ldc % 4 == 0, kSmallSteps) ? tv : ts;
   // A tile row narrower than a 128-byte line reads and writes HBM several times less efficiently than
   // the streaming single-step kernel, which only pays off over enough iterations (measured at n = 1026,
   // 2050, 4096: the fused pass costs about 2, 6 and 11 single steps at 64, 32 and 16 bytes).
@@ -1261,7 +1268,11 @@ int32_t ceca_mix_rounds(const float* X_in, float* X_out, int32_t n, int64_t d, i
   const TileShape tv = mix_tile(n, true, most >= 4), ts = mix_tile(n, false, most >= 4);
   if (!tv.ok || !ts.ok) return fail(CECA_EINVAL, "internal: no tile holds n = %d agents", n);
   hipStream_t st = (hipStream_t)hip_stream;
-  const TileShape& tile = d >= kTileVecCols ? tv : ts;
+  // small problems off 16-byte boundaries keep groups where rounds run in blocks of consecutive rows (2^17 elements 0.64 to 1.06 of the
+  // time of single columns, beyond 3072 agents up to 1.5)
+  tv.fill(d, &m);
+  const bool groups = tile_groups(n, d, aligned16(X_in) && aligned16(X_out) && ld % 4 == 0) || (d >= kTileVecCols && n <= 3072 && ceca::mix_in_blocks(m));
+  const TileShape& tile = groups ? tv : ts;
   tile.fill(d, &m);
   const hipError_t e = ceca::launch_mix_rounds(m, tile.vec4, st);
   if (e != hipSuccess) return hip_fail(e, "mixing kernel launch");

@@ -287,6 +287,8 @@ hipError_t launch_run(const RunArgs& a, const RunShape& s, hipStream_t st);
 bool launch_pair_step(const GemvArgs& g, hipStream_t st, hipError_t* err);
 hipError_t launch_multi_round(const MultiArgs& m, bool vec4, hipStream_t st);
 hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st);
+// whether these rounds on tiles of 16-byte groups run in blocks of consecutive rows
+bool mix_in_blocks(const MixArgs& m);
 hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st);
 hipError_t launch_graph_rounds(const GraphArgs& m, bool vec4, hipStream_t st);
 hipError_t launch_margins(const GemvArgs& g, hipStream_t st);

@@ -418,6 +418,11 @@ static hipError_t launch_mix_ring(const MixArgs& mm, int threads, int lanes, uns
   return hipErrorInvalidValue;
 }
 
+bool mix_in_blocks(const MixArgs& m) {
+  int threads, lanes;
+  return ring_tile(m, &threads, &lanes) || block_rows(m, m.threads, m.threads / m.row_lanes) > 0;
+}
+
 hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   if (m.ngroups <= 0) return hipSuccess;
   const int threads = m.threads > 0 ? m.threads : kBlock;

@@ -1,0 +1,33 @@
+"""The register-tile kernels on both sides of the line between single columns and 16-byte groups, 2^20 elements (fused iterations 2^19)
+on rows off 16-byte boundaries: the bits of aligned rows."""
+import pytest
+
+from test_gpu_large_layouts import _calls
+from test_gpu_layouts import _compare, env  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [3, 64, 65, 97, 531, 2200, 3073])
+@pytest.mark.parametrize("over", [-1, 0])
+@pytest.mark.parametrize("extra,offset", [(1, 0), (0, 3)])
+def test_both_sides_of_the_line(env, n, over, extra, offset):  # noqa: F811
+    torch, P = env
+    d = -(-(1 << 20) // n) + over
+    extra = extra or -d % 4                                     # (0, 3): the base alone is off a boundary
+    for halves, call in _calls(torch, P, n, d).values():
+        _compare(torch, call, halves * n, d, extra, offset, False)
+
+
+@pytest.mark.parametrize("n", [3, 64, 130, 531, 2200])
+@pytest.mark.parametrize("over", [-1, 0])
+def test_fused_iterations_on_both_sides_of_the_line(env, n, over):  # noqa: F811
+    torch, P = env
+    from paper_2306_00256_amd import binding as B
+    d = -(-(1 << 19) // n) + over
+    c = torch.randn((n, d + 1 + (d + 1) % 2), device="cuda")[:, :d]
+
+    def fused(src, dst, ld):
+        P.dsgd_ceca_steps(src, dst, n, d, B.make_quad_center_loss(c, 0.3, 5), 0.1, 0, 9, 2, ld=ld)
+
+    _compare(torch, fused, 2 * n, d, 1, 3, False)
