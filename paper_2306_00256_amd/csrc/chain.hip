@@ -154,11 +154,13 @@ __device__ __forceinline__ void walk_stretch(const ChainArgs& A, uint32_t seg, i
 
 template <int MODE, bool EXCH_Y, bool READ_Y, int R>
 __global__ __launch_bounds__(kBlock) void chain_kernel(const ChainArgs A) {
-  // The last workgroups, one per stretch, take the 1 to 3 columns past the last whole group (or a row of fewer than
-  // four), a column per thread: in a launch of their own they took a small call 3 to 4 us.
+  // The last workgroups take the 1 to 3 columns past the last whole group (or a row of fewer than four, or all columns of a
+  // small problem), a column per thread: in a launch of their own they took a small call 3 to 4 us.
   if (blockIdx.x >= A.vec_blocks) {
-    const int64_t col = A.ngroups * 4 + threadIdx.x;
-    if (col < A.d) walk_stretch<float, MODE, EXCH_Y, READ_Y, 2>(A, blockIdx.x - A.vec_blocks, col);
+    const uint32_t b = blockIdx.x - A.vec_blocks;
+    const uint32_t seg = A.tail_tiles == 1 ? b : b / A.tail_tiles;
+    const int64_t col = A.ngroups * 4 + (int64_t)(b - seg * A.tail_tiles) * kBlock + threadIdx.x;
+    if (col < A.d) walk_stretch<float, MODE, EXCH_Y, READ_Y, 2>(A, seg, col);
     return;
   }
   // Which stretch of which cycle this workgroup walks.  Workgroups are numbered band by band: a band
@@ -178,15 +180,17 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(const ChainArgs A) {
 
 template <int MODE, int R>
 static hipError_t launch_chain_t(ChainArgs a, hipStream_t st) {
-  a.ngroups = a.d / 4;
+  a.ngroups = a.singles ? 0 : a.d / 4;
   const int64_t tiles = (a.ngroups + kBlock - 1) / kBlock;
   const int64_t ncyc = (int64_t)a.n / a.cyc_len;   // cycles are equal-length and cover all agents
   const int64_t nsegs = ncyc * a.segs_per_cycle;
-  const int64_t whole = tiles * nsegs, tail = a.d % 4 ? nsegs : 0;
+  const int64_t tail_tiles = (a.d - 4 * a.ngroups + kBlock - 1) / kBlock;
+  const int64_t whole = tiles * nsegs, tail = tail_tiles * nsegs;
   // the runtime addresses at most 2^32 threads per launch
   constexpr int64_t most = 1LL << 24;
   if (whole >= most || tail >= most) return hipErrorInvalidConfiguration;
   a.tiles = (uint32_t)tiles;
+  a.tail_tiles = (uint32_t)tail_tiles;
   a.nsegs = (uint32_t)nsegs;
   if (a.band == 0 || a.band > a.tiles) a.band = a.tiles;
   // Unused dynamic LDS caps the workgroups resident on a CU (160 KiB of LDS each): fewer, fatter

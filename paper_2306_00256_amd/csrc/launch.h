@@ -27,9 +27,11 @@ struct ChainArgs {
   const float* aux;   // MODE_QUAD: centres c;  MODE_FROMV: messages v;  MODE_GRAD: gradients e
   int64_t ldaux;
   int64_t d;
-  int64_t ngroups;    // whole 16-byte column groups of a row (set by the launcher)
+  bool singles;       // every column by itself
+  int64_t ngroups;    // whole 16-byte column groups of a row, 0 with `singles` (set by the launcher)
   uint32_t tiles;     // workgroups per chain stretch that take them (set by the launcher)
   uint32_t vec_blocks;   // ... over all stretches (set by the launcher)
+  uint32_t tail_tiles;   // workgroups per chain stretch that take the columns past them (set by the launcher)
   uint32_t nsegs;     // stretches over all cycles (set by the launcher)
   uint32_t band;      // column tiles per band of the launch order (0 = all tiles in one band)
   int32_t wg_per_cu;  // cap on resident workgroups per CU (0 = whatever fits)

@@ -1,5 +1,5 @@
 """The register-tile kernels on both sides of the line between single columns and 16-byte groups, 2^20 elements (fused iterations 2^19)
-on rows off 16-byte boundaries: the bits of aligned rows."""
+on rows off 16-byte boundaries, and the streaming kernel on both sides of its own, 2^17: the bits of aligned rows."""
 import pytest
 
 from test_gpu_large_layouts import _calls
@@ -31,3 +31,21 @@ def test_fused_iterations_on_both_sides_of_the_line(env, n, over):  # noqa: F811
         P.dsgd_ceca_steps(src, dst, n, d, B.make_quad_center_loss(c, 0.3, 5), 0.1, 0, 9, 2, ld=ld)
 
     _compare(torch, fused, 2 * n, d, 1, 3, False)
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("n,port", [(2, 1), (3, 2), (130, 1), (417, 2), (2500, 2)])
+@pytest.mark.parametrize("over", [0, 1])
+def test_single_rounds_and_steps_on_both_sides_of_the_line(env, n, port, over, in_place):  # noqa: F811
+    torch, P = env
+    from paper_2306_00256_amd import binding as B
+    d = (1 << 17) // n + over
+    c = torch.randn((n, d + 1 + (d + 1) % 2), device="cuda")[:, :d]
+    last = P.ceca_tau(n) - 1
+    assert P.ceca_describe_step_launch(n, d, d + 1 + d % 2, last, port, 0, in_place)["vec"] == (4 if over else 1)
+    assert P.ceca_describe_step_launch(n, d, -(-d // 4) * 4, last, port, 0, in_place)["vec"] == 4
+
+    for r in (0, last):
+        _compare(torch, lambda src, dst, ld: P.ceca_gossip_round(src, dst, n, d, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
+        _compare(torch, lambda src, dst, ld: P.dsgd_ceca_step(src, dst, n, d, B.make_quad_center_loss(c, 0.3, 5, r), None, 0.1, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
+        _compare(torch, lambda src, dst, ld: P.dsgd_ceca_step(src, dst, n, d, B.make_gradient_loss(c), None, 0.1, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
