@@ -1378,18 +1378,25 @@ int32_t run_consensus(const float* X, int32_t n, int64_t d, int64_t ld, double* 
   c.X = X;  c.ld = ld;  c.d = d;  c.n = n;
   c.out = out;
   c.xbar = xbar_or_null;
-  // The strip forms take rows of any base, pitch and length from four columns on in 16-byte groups, the others rows
-  // of whole groups.
+  // Rows that are not whole 16-byte groups on 16-byte boundaries: the strip forms take them in groups from four columns on, the
+  // others only whole groups.  Small problems take single columns, in wavefront strips or workgroup tiles: groups leave a
+  // quarter of the workgroups, and the workgroup form's long-lived ones have nothing to walk.  Groups against single columns, geometric
+  // means over n = 2 to 4000 (and the largest): 2^13 elements 1.13 times the time (1.64), 2^17 1.06 (1.56), 2^19 0.98 (1.45), 2^20 0.89
+  // (1.03), 2^22 0.63.
+  constexpr int64_t kSmallCons = 1LL << 19;
+  const bool aligned = aligned16(X) && ld % 4 == 0 && d % 4 == 0;
+  const bool groups = aligned || (d >= 4 && n * d > kSmallCons);
   const int32_t forced = g_tuning.cons_form;
   int form = CONS_TWO_PASS;
   const bool by_default = p.group_default && !(p.group_spills && have >= p.two_pass_total);
-  if (p.group_threads > 0 && d >= 4 && (forced == CONS_GROUP || (forced == 0 && by_default))) form = CONS_GROUP;
+  if (p.group_threads > 0 && (forced == CONS_GROUP ? d >= 4 : forced == 0 && by_default && groups)) form = CONS_GROUP;
   else if (forced == CONS_WAVE ? p.wave_cgs > 0 : (forced == 0 && p.wave_cgs > 0 && p.wave_default)) form = CONS_WAVE;
   else if (forced != CONS_TWO_PASS && p.rows_per_thread > 0) form = CONS_TILE;
-  const bool vec = form == CONS_GROUP || form == CONS_WAVE ? d >= 4 : d % 4 == 0;
-  if (form != CONS_WAVE && forced == 0 && !(aligned16(X) && ld % 4 == 0 && d % 4 == 0)) {
-    // What a scratch size holds on layouts that are not 16-byte aligned is stated for single columns in workgroup tiles
-    // or two passes; calls beyond that are refused in the other forms as well.
+  const bool vec = form == CONS_GROUP || (groups && (form == CONS_WAVE || d % 4 == 0));
+  if (form != CONS_WAVE && forced == 0 && !aligned) {
+    // The sizes that the allocation-free entry point takes on such layouts are part of its interface, stated for single columns in
+    // workgroup tiles or two passes.  They do not follow the form: a program that sizes its problems by them is told the same whatever
+    // form takes the call.
     *need = p.rows_per_thread > 0 ? p.tile_total : p.two_pass_total;
     if (have < *need) return CECA_EWORKSPACE;
   }

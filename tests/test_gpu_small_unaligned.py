@@ -1,5 +1,6 @@
 """The register-tile kernels on both sides of the line between single columns and 16-byte groups, 2^20 elements (fused iterations 2^19)
-on rows off 16-byte boundaries, and the streaming kernel on both sides of its own, 2^17: the bits of aligned rows."""
+on rows off 16-byte boundaries, and the streaming kernel on both sides of its own, 2^17: the bits of aligned rows.  The consensus
+observables (2^19): fp64 sums in another order, 1e-12."""
 import pytest
 
 from test_gpu_large_layouts import _calls
@@ -49,3 +50,29 @@ def test_single_rounds_and_steps_on_both_sides_of_the_line(env, n, port, over, i
         _compare(torch, lambda src, dst, ld: P.ceca_gossip_round(src, dst, n, d, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
         _compare(torch, lambda src, dst, ld: P.dsgd_ceca_step(src, dst, n, d, B.make_quad_center_loss(c, 0.3, 5, r), None, 0.1, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
         _compare(torch, lambda src, dst, ld: P.dsgd_ceca_step(src, dst, n, d, B.make_gradient_loss(c), None, 0.1, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
+
+
+@pytest.mark.parametrize("n", [5, 64, 108, 130, 531, 1532, 2900, 3090])
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("extra,offset", [(0, 1), (1, 0)])
+def test_consensus_on_both_sides_of_the_line(env, n, over, extra, offset):  # noqa: F811
+    torch, P = env
+    d = (1 << 19) // n + over
+    ld = d + extra
+    flat = torch.full((offset + n * ld + 64,), 1e30, device="cuda")
+    X = flat[offset:offset + n * ld].view(n, ld)
+    X[:, :d] = torch.randn((n, d), device="cuda") + 2.0
+    ws = torch.empty(P.consensus_error_workspace_bytes(n, d), dtype=torch.uint8, device="cuda")
+    x = X[:, :d].double()
+    m = x.mean(dim=0)
+    dev = ((x - m) ** 2).sum(dim=1)
+    want = torch.stack([dev.sum(), dev.sqrt().sum(), dev.sqrt().max(), (m * m).sum().sqrt()])
+    for noalloc in (False, True):
+        out = torch.zeros(5, dtype=torch.float64, device="cuda")
+        xbar = torch.full((d + 8,), 7.0, device="cuda")
+        if noalloc:
+            P.consensus_error_noalloc(X, n, d, out, xbar=xbar, ld=ld)
+        else:
+            P.consensus_error(X, n, d, out, xbar=xbar, workspace=ws, ld=ld)
+        assert torch.allclose(out[:4], want, rtol=1e-12, atol=0) and float(out[4]) == n
+        assert torch.allclose(xbar[:d].double(), m, rtol=2e-7, atol=1e-7) and bool((xbar[d:] == 7.0).all())
