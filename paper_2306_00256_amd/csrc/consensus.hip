@@ -175,7 +175,9 @@ __global__ __launch_bounds__(kBlock) void cons_tile_kernel(const ConsensusArgs C
 // (fp64, fixed order).  A wavefront takes strips w, w + nwaves, ... and adds up every row's squared
 // distance to the column means over all of them before it reduces across lanes once.
 // Writes devpart[agent][wave] (row n: the wavefront's share of ||xbar||^2) and, if asked, xbar.
-template <int VEC, int RT>
+// ODD: the length is no multiple of VEC; whole groups have instances without the short one's instructions (n = 2, 2^25 elements 64.0
+// us with them, 57.5 without).
+template <int VEC, int RT, bool ODD>
 __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C) {
   using V = typename VecOf<VEC>::T;
   constexpr int RTP = RT <= 1 ? 1 : RT <= 2 ? 2 : RT <= 4 ? 4 : RT <= 8 ? 8 : RT <= 16 ? 16 : 32;
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
   const int rg = lane >> C.cg_shift;
   const int row_lanes = 64 >> C.cg_shift;
   const int64_t ngroups = (C.d + VEC - 1) / VEC;
-  const int short_cols = (int)(ngroups * VEC - C.d);   // columns that a row's last group lacks: zeros add nothing below
+  const int short_cols = ODD ? (int)(ngroups * VEC - C.d) : 0;   // columns that a row's last group lacks: zeros add nothing below
   double acc[RTP];
 #pragma unroll
   for (int k = 0; k < RTP; ++k) acc[k] = 0.0;
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
     on = g < ngroups;
     col = (on ? g : 0) * VEC;
     // my rows lie row_lanes rows apart: one address, stepped (only the last row may need the clamp)
-    const int64_t from = col - (g == ngroups - 1 ? short_cols : 0);
+    const int64_t from = col - (ODD && g == ngroups - 1 ? short_cols : 0);
     const float* p = C.X + (int64_t)rg * C.ld + from;
     const int64_t step = (int64_t)row_lanes * C.ld;
 #pragma unroll
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
   while (true) {
     const int64_t next = strip + C.nwaves;
     const bool more = next < C.strips;              // the same for the whole wavefront
-    if (short_cols && strip == C.strips - 1) {
+    if (ODD && strip == C.strips - 1) {
       const int back = strip * cgs + cg == ngroups - 1 ? short_cols : 0;
 #pragma unroll
       for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(kBlock) void cons_wave_kernel(const ConsensusArgs C
       if (C.xbar) {
 #pragma unroll
         for (int q = 0; q < VEC; ++q)
-          if (col + q < C.d) C.xbar[col + q] = (float)m[q];
+          if (!ODD || col + q < C.d) C.xbar[col + q] = (float)m[q];
       }
     }
     if (!more) break;
@@ -305,7 +307,7 @@ __device__ __forceinline__ double div_by(double s, double n, double r) {
 // call in two passes, 126 us in this form (122 us for the kernel, 4.4 TB/s, bound by the 128-byte reads of 1026 rows a
 // strip).
 // Writes devpart[agent][workgroup] (row n: the workgroup's share of ||xbar||^2) and, if asked, xbar.
-template <int RT, int THREADS>
+template <int RT, int THREADS, bool ODD>
 __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs C) {
   constexpr int WAVES = THREADS / 64;
   constexpr int RTP = RT <= 1 ? 1 : RT <= 2 ? 2 : RT <= 4 ? 4 : RT <= 8 ? 8 : RT <= 16 ? 16 : 32;
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
   const int rg = tid >> C.cg_shift;
   const int row_lanes = THREADS >> C.cg_shift;
   const int64_t ngroups = (C.d + 3) / 4;
-  const int short_cols = (int)(ngroups * 4 - C.d);  // columns that a row's last group lacks: zeros add nothing below
+  const int short_cols = ODD ? (int)(ngroups * 4 - C.d) : 0;     // columns that a row's last group lacks: zeros add nothing below
   const bool last_mine = rg + (RT - 1) * row_lanes < C.n;      // rows per thread is the least that covers n
   const double n = (double)C.n, rn = 1.0 / n;
   double acc[RTP];
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
   const int64_t last_step = last_mine ? step : (int64_t)(C.n - 1 - (rg + (RT - 2) * row_lanes)) * C.ld;
   auto first_row = [&](int64_t tile) {
     const int64_t g = tile * cgs + cg;
-    return C.X + (int64_t)(RT > 1 ? rg : min(rg, C.n - 1)) * C.ld + (g < ngroups ? g * 4 - (g == ngroups - 1 ? short_cols : 0) : 0);
+    return C.X + (int64_t)(RT > 1 ? rg : min(rg, C.n - 1)) * C.ld + (g < ngroups ? g * 4 - (ODD && g == ngroups - 1 ? short_cols : 0) : 0);
   };
   vf4 x[RT];
   {
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
   }
   int buf = 0;
   for (int64_t tile = blockIdx.x; tile < C.strips; tile += gridDim.x, buf ^= 1) {
-    if (short_cols && tile == C.strips - 1) {
+    if (ODD && tile == C.strips - 1) {
       const int back = tile * cgs + cg == ngroups - 1 ? short_cols : 0;
 #pragma unroll
       for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
@@ -391,7 +393,7 @@ __global__ __launch_bounds__(THREADS) void cons_group_kernel(const ConsensusArgs
       if (C.xbar) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (g * 4 + q < C.d) C.xbar[g * 4 + q] = (float)m[q];
+          if (!ODD || g * 4 + q < C.d) C.xbar[g * 4 + q] = (float)m[q];
       }
     }
   }
@@ -533,6 +535,7 @@ static hipError_t launch_cons_tile(ConsensusArgs c, bool vec4, hipStream_t st) {
 
 static hipError_t launch_cons_wave(const ConsensusArgs& c0, bool vec4, hipStream_t st) {
   ConsensusArgs c = c0;
+  const bool odd = c.d % 4 != 0;
   const int cgs = c.wave_cgs;
   if (cgs < 1 || cgs > 64 || (cgs & (cgs - 1)) != 0 || (1 << c.cg_shift) != cgs) return hipErrorInvalidValue;
   const int row_lanes = 64 / cgs;
@@ -548,8 +551,8 @@ static hipError_t launch_cons_wave(const ConsensusArgs& c0, bool vec4, hipStream
   c.ntiles = c.nwaves;            // row length of devpart for the reduction kernels
   c.normpart = c.dev2 + c.n;      // devsum's row n is ||xbar||^2
   c.norm_count = 1;
-#define CECA_CW4(RT) case RT: cons_wave_kernel<4, RT><<<grid, dim3(block), 0, st>>>(c); break
-#define CECA_CW1(RT) case RT: cons_wave_kernel<1, RT><<<grid, dim3(block), 0, st>>>(c); break
+#define CECA_CW4(RT) case RT: if (odd) cons_wave_kernel<4, RT, true><<<grid, dim3(block), 0, st>>>(c); else cons_wave_kernel<4, RT, false><<<grid, dim3(block), 0, st>>>(c); break
+#define CECA_CW1(RT) case RT: cons_wave_kernel<1, RT, false><<<grid, dim3(block), 0, st>>>(c); break
   if (vec4) {
     switch (c.rows_per_thread) {
       CECA_CW4(1); CECA_CW4(2); CECA_CW4(3); CECA_CW4(4); CECA_CW4(5); CECA_CW4(6); CECA_CW4(7); CECA_CW4(8);
@@ -573,11 +576,13 @@ static hipError_t launch_cons_wave(const ConsensusArgs& c0, bool vec4, hipStream
 
 template <int THREADS, int MOST>
 static hipError_t launch_group_rt(const ConsensusArgs& c, size_t lds, hipStream_t st) {
+  const bool odd = c.d % 4 != 0;
   switch (c.rows_per_thread) {
 #define CECA_CG(RT)                                                                                       \
   case RT:                                                                                                \
     if constexpr (RT <= MOST) {                                                                           \
-      cons_group_kernel<RT, THREADS><<<dim3((unsigned)c.nwaves), dim3(THREADS), lds, st>>>(c);            \
+      if (odd) cons_group_kernel<RT, THREADS, true><<<dim3((unsigned)c.nwaves), dim3(THREADS), lds, st>>>(c);  \
+      else cons_group_kernel<RT, THREADS, false><<<dim3((unsigned)c.nwaves), dim3(THREADS), lds, st>>>(c);     \
       return hipGetLastError();                                                                           \
     }                                                                                                     \
     break;
