@@ -348,7 +348,7 @@ hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   StepsArgs ss = s;
-  tile_memory(&ss.m.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
+  tile_memory(&ss.m.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, 2 * (int64_t)m.n, &blocks, s.c, s.ldc);
   size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (s.noise_std != 0.0f) lds = ((lds + 7) & ~(size_t)7) + (size_t)m.n * sizeof(uint64_t);   // the noise keys behind the tile
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
@@ -396,7 +396,7 @@ hipError_t launch_multi_round(const MultiArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MultiArgs mm = m;
-  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, &blocks);
+  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, m.yout ? 2 * (int64_t)m.n : m.n, &blocks);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
   if (!vec4) return launch_rounds_rt<1, 256>(mm, (unsigned)blocks, lds, st);
