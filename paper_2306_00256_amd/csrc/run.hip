@@ -339,7 +339,15 @@ __device__ __forceinline__ bool take_part(const RunArgs& P, int wg, float (&red)
       }
       __syncthreads();
       const int j = min(lane, P.B - 1);
-      for (int ch = 0; ch < P.nchunks; ++ch) mj += part[ch * P.B + j];
+      int ch = 0;                          // four words of LDS on their way at a time, added in order (490 -> 485 us in ten chunks)
+      for (; ch + 4 <= P.nchunks; ch += 4) {
+        float q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = part[(ch + u) * P.B + j];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) mj += q[u];
+      }
+      for (; ch < P.nchunks; ++ch) mj += part[ch * P.B + j];
     } else {
       const int j = min(lane, BMAX - 1);
 #pragma unroll
