@@ -148,17 +148,19 @@ ChainPlan plan_chain(ceca::ChainArgs* a, int mode, int64_t d, int32_t port) {
 // Small problems on rows off 16-byte boundaries take single columns: four times the threads, and what bounds them is one thread's
 // walk.  Groups against single columns, geometric means over n = 2 to 2500 (and the largest): 2^13 elements rounds 1.06 times the
 // time (1.2), noisy steps 1.16 (1.4), in place, where a thread walks whole cycles, 1.1 (2.3); 2^17 elements 0.98, 1.01 and 1.0 (1.4);
-// 2^19 elements 0.82, 0.81 and 0.94.
+// 2^19 elements 0.82, 0.81 and 0.94.  In place, rows of odd length on such boundaries do too: the walks over the groups and over the
+// last columns, in two workgroups, would write parts of the same lines (n = 417, d = 13, in-place rounds 110 us, 50 in single
+// columns).
 constexpr int64_t kSmallChain = 1LL << 17;
-bool chain_singles(const ceca::ChainArgs& a, int64_t d) {
+bool chain_singles(const ceca::ChainArgs& a, int64_t d, bool cycles) {
   const bool aligned = aligned16(a.xin) && aligned16(a.xout) && a.ld % 4 == 0 && aligned16(a.aux) && a.ldaux % 4 == 0;
-  return !aligned && a.n * d <= kSmallChain;
+  return (!aligned || (cycles && d % 4 != 0)) && a.n * d <= kSmallChain;
 }
 
 int32_t run_chain(ceca::ChainArgs a, int mode, int64_t d, const ceca_round_t& rd, int32_t port, hipStream_t st) {
   const ChainPlan pl = plan_chain(&a, mode, d, port);
   a.d = d;
-  a.singles = chain_singles(a, d);
+  a.singles = chain_singles(a, d, pl.in_place && port == 2);
   shape_chain(rd, a.n, port, pl.in_place, pl.default_seg, d, &a);
   const hipError_t e = ceca::launch_chain(a, mode, pl.rows, st);
   if (e != hipSuccess) return hip_fail(e, "chain kernel launch");
@@ -1346,7 +1348,7 @@ int32_t ceca_describe_step_launch(int32_t n, int64_t d, int64_t ld, int32_t r, i
   out[2] = a.wg_per_cu;
   out[3] = a.seg_len;
   out[4] = a.segs_per_cycle;
-  out[5] = d >= 4 && !chain_singles(a, d) ? 4 : 1;
+  out[5] = d >= 4 && !chain_singles(a, d, pl.in_place && port == 2) ? 4 : 1;
   return CECA_OK;
 }
 

@@ -44,7 +44,8 @@ def test_single_rounds_and_steps_on_both_sides_of_the_line(env, n, port, over, i
     c = torch.randn((n, d + 1 + (d + 1) % 2), device="cuda")[:, :d]
     last = P.ceca_tau(n) - 1
     assert P.ceca_describe_step_launch(n, d, d + 1 + d % 2, last, port, 0, in_place)["vec"] == (4 if over else 1)
-    assert P.ceca_describe_step_launch(n, d, -(-d // 4) * 4, last, port, 0, in_place)["vec"] == 4
+    cycles = in_place and port == 2 and d % 4 != 0 and not over  # walks of odd rows that share lines
+    assert P.ceca_describe_step_launch(n, d, -(-d // 4) * 4, last, port, 0, in_place)["vec"] == (1 if cycles else 4)
 
     for r in (0, last):
         _compare(torch, lambda src, dst, ld: P.ceca_gossip_round(src, dst, n, d, r, port, ld=ld), 2 * n, d, 1 + d % 2, 3, in_place)
