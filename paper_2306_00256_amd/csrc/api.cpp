@@ -522,28 +522,30 @@ TileShape steps_tile(int32_t n, bool vec4, int32_t steps) {
 // peers in some round.
 TileShape mix_tile(int32_t n, bool vec4, bool heavy) {
   // Measured on MI355X (n = 31 ... 4096, all three topologies; x alone in registers, 67 registers at 9 rows
-  // per thread; many peers before they took blocks of consecutive rows, which keep these tiles).  What counts is how many workgroups a compute unit holds: the LDS tile is n x tile row.
+  // per thread) with rows row_lanes apart.  Rings of more than 64 agents have tiles of their own since (mix.hip) and many
+  // peers mostly blocks of consecutive rows, which keep these tiles; figures of rings below are of that form, for one or two
+  // peers.  What counts is how many workgroups a compute unit holds: the LDS tile is n x tile row.
   // Up to 256 agents: 256 threads, up to 12 rows per thread (n = 64 ring: 0.20 against 0.25 ms with 16,
   // n = 100: 0.215 against 0.24).  257 to 512 agents: one or two peers per round run 512-thread workgroups
   // with up to 9 rows (n = 258 ring: 0.33 against 0.40 ms), many peers per round (LDS-read bound) 256 threads
   // with up to 16.  Up to 9 x 128 agents: 512 threads x at most 9 rows, i.e. 64-byte tile rows and three
   // workgroups per compute unit rather than 128-byte rows and one (n = 800: ring 0.31 against 0.50 ms, static
   // exponential 0.81 against 1.20).  Beyond: 512 threads x 13 rows up to 13 x 128 agents and 1024 threads
-  // after that for few peers; many peers take 1024 threads x 5 rows up to 1280 agents (64-byte rows: n = 1160, 2^26
-  // elements, two pitches 476 us against 601 to 640 with 512 x 9, n = 1280: 440 against 602 to 619) and keep 512 threads x 9
-  // rows up to 2304 agents (n = 1500: 0.98 against 1.51 ms, n = 2050: 1.34 against 1.59).
+  // after that for few peers; many peers take 1024 threads x 5 rows as long as a block of five lies past the last agent (1274;
+  // 64-byte rows, static exponential n = 1270, 2^27 elements 683 us; n = 1276 in blocks of seven 967, as 512 x 7 rows 730) and keep 512
+  // threads x 9 rows up to 2304 agents (n = 1500: 0.98 against 1.51 ms, n = 2050: 1.34 against 1.59).
   return pick_tile(n, vec4, 4, 32, 16,
                    [heavy](int32_t m) {
                      if (m <= 256) return ceca::kBlock;
                      if (m <= 512) return heavy ? ceca::kBlock : 512;
                      if (m <= 9 * 128) return 512;
-                     if (heavy) return m > 5 * 256 && m <= 9 * 256 ? 512 : 1024;
+                     if (heavy) return m >= 5 * 255 && m <= 9 * 256 ? 512 : 1024;
                      return m <= 13 * 128 ? 512 : 1024;
                    },
                    [n, heavy](int32_t threads) {
                      if (threads == ceca::kBlock) return n <= 256 ? 12 : (n <= 512 ? 16 : (heavy ? 16 : 24));
                      if (threads == 512) return (heavy || n <= 9 * 128) ? 9 : 13;
-                     return heavy && n <= 5 * 256 ? 5 : 13;
+                     return heavy && n < 5 * 255 ? 5 : 13;
                    });
 }
 

@@ -352,7 +352,7 @@ static int block_rows(const MixArgs& m, int threads, int lanes) {
   switch (threads) {
     case 256: return lanes == 16 ? (rows >= 7 && rows <= 13 ? rows : 0) : (lanes == 8 && rows >= 7 && rows <= 17 ? rows : 0);
     case 512: return lanes == 4 ? (m.n >= 672 && rows <= 9 ? rows : 0) : (lanes == 2 && rows >= 7 && rows <= 9 ? rows : 0);
-    case 1024: return lanes == 4 && (rows == 5 || rows == 7) ? rows : 0;
+    case 1024: return lanes == 4 && rows == 5 ? rows : 0;
   }
   return 0;
 }
@@ -375,7 +375,7 @@ static hipError_t launch_mix_blocks(const MixArgs& mm, int lanes, int rows, unsi
     CECA_RT(256, 8, 7); CECA_RT(256, 8, 9); CECA_RT(256, 8, 11); CECA_RT(256, 8, 13); CECA_RT(256, 8, 15); CECA_RT(256, 8, 17);
     CECA_RT(512, 4, 7); CECA_RT(512, 4, 9);
     CECA_RT(512, 2, 7); CECA_RT(512, 2, 9);
-    CECA_RT(1024, 4, 5); CECA_RT(1024, 4, 7);
+    CECA_RT(1024, 4, 5);
 #undef CECA_RT
   }
   return hipErrorInvalidValue;
