@@ -35,8 +35,8 @@ extern "C" {
  *   CECA_OPT_CONS_SINGLE_PASS  consensus observables: 1 (default) the library's choice; 0 always the two-pass
  *                     kernels; 2 the single pass with workgroup tiles (LDS) where a tile holds n agents;
  *                     3 the single pass with one wavefront per column strip (up to 64 x rows agents);
- *                     4 the single pass with long-lived workgroups (16-byte layouts, up to 6144 agents)
- *   CECA_OPT_XCD_TILE_ORDER  1 (default): register-tile kernels whose tile rows are narrower than 128 bytes give
+ *                     4 the single pass with long-lived workgroups (rows of four columns and more, up to 6144 agents)
+ *   CECA_OPT_XCD_TILE_ORDER  1 (default): register-tile kernels whose tile rows are not whole 128-byte lines give
  *                     each of the 8 XCDs runs of 16 adjacent tiles in turn; 0: plain order
  *   CECA_OPT_TILE_THREADS  threads per workgroup of the fused rounds, fused iterations and mixing kernels:
  *                     256, 512 or 1024; more threads make the rows of a tile wider.  A tile shape that cannot

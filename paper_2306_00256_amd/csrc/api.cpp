@@ -230,7 +230,8 @@ int32_t check_loss(const ceca_loss_t* loss, int64_t d, bool need_batch, const in
 }
 
 // Consensus observables come in four forms (all deterministic, fp64 accumulation):
-//   GROUP     one pass, a long-lived workgroup holds a column strip of every agent: up to 3072 agents, 16-byte layouts
+//   GROUP     one pass, a long-lived workgroup holds a column strip of every agent: up to 3072 agents; off 16-byte boundaries from
+//             kSmallCons elements on (run_consensus)
 //   WAVE      one pass, a wavefront holds a column strip of every agent (no LDS): up to 64 x 32 agents
 //   TILE      one pass, a workgroup holds a column tile of every agent and reduces through LDS
 //   TWO_PASS  column sums, mean, then per-agent squared deviations (x read twice)

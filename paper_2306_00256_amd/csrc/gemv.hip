@@ -273,7 +273,8 @@ __global__ __launch_bounds__(THREADS) void grad_onepass_kernel(const GemvArgs P)
 // prologue reads its own two rows and one row of its peer, combines in registers without storing x+, y+,
 // and the epilogue writes the new half-step rows to the other buffer: 20 bytes of state traffic per
 // agent-parameter and iteration instead of 28, with the arithmetic of FUSE = 1 operation for operation.
-// VEC = 1 is the same kernel on single columns (see minibatch_vec).
+// VEC = 1 is the same kernel on single columns (see minibatch_vec).  Of the instances only <4, 1024, 2, 4, 2, true> spills (9 registers:
+// half-step runs on rows of more than 8192 columns that are no whole groups).
 template <int VEC, int THREADS, int CH, int G, int FUSE, bool ODD>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(G == 1 ? 8 : 4, 8)))
 void grad_chunked_kernel(const GemvArgs P) {
@@ -668,7 +669,7 @@ __global__ __launch_bounds__(2 * THREADS) void pair_step_kernel(const GemvArgs P
 bool launch_pair_step(const GemvArgs& g, hipStream_t st, hipError_t* err) {
   const bool both = g.p_port == 1, vec4 = g.vec;
   if ((int64_t)g.n * g.B * g.d * 4 > (8LL << 20)) return false;
-  if (g.d % 4 != 0 && g.d > 256) return false;       // (short last groups: the tests of this form hold them to two kernels)
+  if (g.d % 4 != 0 && g.d > 256) return false;       // pair_step_kernel has no instructions for a short last group, and single columns end at 256
   if (both ? (g.n & 1) || !(g.p_shift & 1) : g.px == g.ox) return false;       // two ports: out of place only
   const dim3 grid((unsigned)(both ? g.n / 2 : g.n));
 #define CECA_PAIR(VEC, T, BM)                                                \

@@ -141,8 +141,10 @@ constexpr int block_waves() { return THREADS == 1024 && RT <= 5 ? 8 : mix_waves<
 // LDS (busy 64 % of the time) together, n = 1026.
 // Bank conflicts: lanes of a wavefront that differ in the row are RT rows apart, so rows of the tile that are less than all
 // banks wide (LANES < 16) need an odd RT.  Same order of operations per row as above, same bits.
-// Static exponential, 2^27 elements, rows row_lanes apart -> blocks: n = 100 401 -> 355 us, n = 130 496 -> 404, n = 258 611 ->
-// 499, n = 500 686 -> 552, n = 800 684 -> 618, n = 1026 852 -> 715, n = 1400 967 -> 759, n = 2050 1010 -> 858.
+// Static exponential, 2^27 elements at pitches that are no power of two, rows row_lanes apart -> blocks: n = 100 401 -> 355 us,
+// n = 130 496 -> 404, n = 258 611 -> 499, n = 500 686 -> 552, n = 800 684 -> 618, n = 1026 852 -> 715, n = 1400 967 -> 759, n = 2050 1010 -> 858.
+// (At powers of two: n = 130, d = 2^20 520 -> 440, n = 1026, d = 2^17 901 -> 798.)  <1024, 4, 5> spills one register, for two resident
+// workgroups.
 template <int THREADS, int LANES, int RT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(block_waves<THREADS, RT>())))
 void mix_blocks_kernel(const MixArgs M) {
@@ -236,12 +238,13 @@ void mix_blocks_kernel(const MixArgs M) {
 
 // Ring rounds (peers 1 row back and 1 ahead, in every round): a thread holds RT consecutive rows or one less, and of a block only
 // its first and last row are anyone else's business.  They alone go through LDS, one slot per thread and two buffers in turn, so a
-// round has one barrier and the tile's width is not bound by LDS: its rows are 128 or 256 bytes, where a tile that keeps every row in
-// LDS has 64 from 513 agents on.  A row's new value replaces it from the last one down, with the old value of the row
+// round has one barrier and the tile's width is not bound by LDS: its rows are 256 bytes up to 448 agents, 128 up to 960 and 64 beyond,
+// where a tile that keeps every row in LDS has 64 from 513 agents on.  A row's new value replaces it from the last one down, with the old value of the row
 // behind carried along.  Same order of operations per row as above, same bits.
-// What bounds it: memory (n = 1026 241 us where the loads and stores alone take 243 in the general form's tile).  Ring, 2^27 elements,
-// general form -> here: n = 130 234 -> 193 us, n = 400 256 -> 217, n = 800 284 -> 217, n = 1026 333 -> 241, n = 1500 550 -> 251,
-// n = 3000 614 -> 356.
+// What bounds it: memory (n = 1026 241 us where the loads and stores alone take 243 in the general form's tile).  Ring, 2^27 elements at
+// pitches that are no power of two, general form -> here: n = 130 234 -> 193 us, n = 400 256 -> 217, n = 800 284 -> 217, n = 1026 333 ->
+// 241, n = 1500 550 -> 251, n = 3000 614 -> 356.  (Powers of two: n = 130, d = 2^20 256 -> 212, n = 1026, d = 2^17 407 -> 309.)  Blocks of
+// 15 rows spill 2 registers, those of 16 rows in 1024-thread workgroups (3841 agents on) 10.
 template <int THREADS, int LANES, int RT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(mix_waves<THREADS>())))
 void mix_ring_kernel(const MixArgs M) {

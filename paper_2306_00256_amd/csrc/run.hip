@@ -106,7 +106,7 @@ template <> struct Parts<4> {
 };
 
 // wavefronts per SIMD the kernel is compiled for (the host's residency rule counts on them): BMAX rows of VEC
-// columns and about 70 more registers per thread, nothing spilled
+// columns and about 70 more registers per thread, nothing spilled to memory (scalar registers go to spare vector registers)
 template <int VEC, int THREADS, int BMAX>
 constexpr int run_waves() { return THREADS == 1024 || VEC == 1 || BMAX <= 8 ? 4 : BMAX <= 16 ? 3 : BMAX <= 32 ? 2 : 1; }
 

@@ -37,7 +37,7 @@ CASES = [("hypercube", 64, 0), ("hypercube", 1024, 0), ("torus", 15, 3), ("torus
 def test_graph_rounds_match_the_oracle(env, kind, n, rows):
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
-    d = (4 * 9 + 3) if n > 1000 else (4 * 150 + 3)           # 16-byte groups and a scalar tail
+    d = (4 * 9 + 3) if n > 1000 else (4 * 150 + 3)           # 16-byte groups, the last one short
     rounds = 5
     edges = WL.edges_of(kind, n, rows)
     host = WL.graph_table(n, edges)

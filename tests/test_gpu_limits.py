@@ -246,7 +246,7 @@ def test_more_rounds_than_one_kernel_takes(env):
 def test_workgroup_widths_of_the_fused_rounds_give_the_same_bits(env, n, port):
     """256-, 512- and 1024-thread workgroups of the fused-rounds kernel (tile rows of different widths, up
     to 144 KB of LDS), with the library's rows per thread and with fewer: same bits as single rounds, for
-    16-byte column groups with a scalar tail and for an unaligned layout; exact averaging, fused iterations
+    16-byte column groups with a short last one and for an unaligned layout; exact averaging, fused iterations
     and the mixing rounds of the comparison topologies likewise (those against the oracle too)."""
     torch, P = env
     from paper_2306_00256_amd import binding as Bn
