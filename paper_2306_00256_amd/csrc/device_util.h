@@ -85,6 +85,13 @@ template <int CH> __device__ __forceinline__ bool some_nan(const float (&m)[CH])
   return __any(s != s);
 }
 
+// How a register-tile kernel's tile goes about memory (TileMemory).  WHOLE: rows of whole groups that are streamed, the instance without
+// the instructions for anything else.
+template <bool WHOLE, typename Args> __device__ __forceinline__ auto tile_of(const Args& M) {
+  auto mem = M.mem;
+  if (WHOLE) mem.cached_loads = mem.cached_stores = mem.short_cols = 0;
+  return mem;
+}
 // That distance for the group at column col.
 template <typename Args> __device__ __forceinline__ int columns_back(const Args& M, int64_t col) {
   return col == (M.ngroups - 1) * 4 ? M.mem.short_cols : 0;

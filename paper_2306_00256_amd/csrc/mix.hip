@@ -24,7 +24,7 @@ constexpr int mix_waves() { return THREADS > 256 ? 4 : 1; }
 // Same tiling as the fused CECA rounds: a workgroup keeps a column tile of every agent's x in
 // registers (RT rows per thread) and publishes it in LDS once per round, where each row picks up its
 // peers.  One read and one write of x for any number of rounds.
-template <int VEC, int RT, int THREADS>
+template <int VEC, int RT, int THREADS, bool WHOLE>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(mix_waves<THREADS>())))
 void mix_rounds_kernel(const MixArgs M) {
 #pragma clang fp contract(off)
@@ -41,9 +41,10 @@ void mix_rounds_kernel(const MixArgs M) {
   const int64_t col = (on ? g : 0) * VEC;          // lanes past the last column shadow column group 0
 
   V x[RT];                                         // rows past the last agent shadow it
-  const int64_t from = col - columns_back(M, col);
-  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
-  if (M.mem.short_cols) {
+  const auto mem = tile_of<WHOLE>(M);
+  const int64_t from = col - (WHOLE ? 0 : columns_back(M, col));
+  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, mem.cached_loads);
+  if (mem.short_cols) {
     const int back = (int)(col - from);
 #pragma unroll
     for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
@@ -101,7 +102,7 @@ void mix_rounds_kernel(const MixArgs M) {
   int rg_out = rg;
   int64_t out = col;
   asm volatile("" : "+v"(rg_out), "+v"(out));
-  store_rows<V, RT>(x, M.xout + out, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
+  store_rows<V, RT>(x, M.xout + out, M.ld, rg_out, M.row_lanes, M.n - 1, WHOLE ? 0 : columns_back(M, out), mem.cached_stores);
 }
 
 // x <- w_self x + the terms of the round's first RUN peers, which are 1, 2, 4, 8 rows back: among the block's own rows or the
@@ -245,7 +246,7 @@ void mix_blocks_kernel(const MixArgs M) {
 // pitches that are no power of two, general form -> here: n = 130 234 -> 193 us, n = 400 256 -> 217, n = 800 284 -> 217, n = 1026 333 ->
 // 241, n = 1500 550 -> 251, n = 3000 614 -> 356.  (Powers of two: n = 130, d = 2^20 256 -> 212, n = 1026, d = 2^17 407 -> 309.)  Blocks of
 // 15 rows spill 2 registers, those of 16 rows in 1024-thread workgroups (3841 agents on) 10.
-template <int THREADS, int LANES, int RT>
+template <int THREADS, int LANES, int RT, bool WHOLE>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(mix_waves<THREADS>())))
 void mix_ring_kernel(const MixArgs M) {
 #pragma clang fp contract(off)
@@ -265,9 +266,10 @@ void mix_ring_kernel(const MixArgs M) {
   const int agent = rg * (RT - 1) + min(rg, whole);
   const int last = agent + RT - 2 + last_mine;
   vf4 x[RT];                                       // the row that a shorter block lacks shadows its last one
-  const int64_t from = col - columns_back(M, col);
-  load_rows<vf4, RT>(x, M.xin + from, M.ld, agent, 1, last, M.mem.cached_loads);
-  if (M.mem.short_cols) {
+  const auto mem = tile_of<WHOLE>(M);
+  const int64_t from = col - (WHOLE ? 0 : columns_back(M, col));
+  load_rows<vf4, RT>(x, M.xin + from, M.ld, agent, 1, last, mem.cached_loads);
+  if (mem.short_cols) {
     const int back = (int)(col - from);
 #pragma unroll
     for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
@@ -299,12 +301,14 @@ void mix_ring_kernel(const MixArgs M) {
   int row_out = agent;
   int64_t out = col;
   asm volatile("" : "+v"(row_out), "+v"(out));
-  store_rows<vf4, RT>(x, M.xout + out, M.ld, row_out, 1, last, columns_back(M, out), M.mem.cached_stores);
+  store_rows<vf4, RT>(x, M.xout + out, M.ld, row_out, 1, last, WHOLE ? 0 : columns_back(M, out), mem.cached_stores);
 }
 
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_mix(const MixArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
-  const auto fn = &mix_rounds_kernel<VEC, RT, THREADS>;
+  auto fn = &mix_rounds_kernel<VEC, RT, THREADS, false>;
+  if constexpr (VEC == 4 && THREADS <= 512)
+    if (mm.mem.whole()) fn = &mix_rounds_kernel<VEC, RT, THREADS, true>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -411,7 +415,7 @@ static bool ring_tile(const MixArgs& m, int* threads, int* lanes) {
 static hipError_t launch_mix_ring(const MixArgs& mm, int threads, int lanes, unsigned blocks, hipStream_t st) {
   const int row_lanes = threads / lanes, rows = (mm.n + row_lanes - 1) / row_lanes;
   switch (threads << 16 | lanes << 8 | rows) {
-#define CECA_RT(T, L, RT) case T << 16 | L << 8 | RT: mix_ring_kernel<T, L, RT><<<dim3(blocks), dim3(T), 0, st>>>(mm); return hipGetLastError()
+#define CECA_RT(T, L, RT) case T << 16 | L << 8 | RT: (mm.mem.whole() ? &mix_ring_kernel<T, L, RT, true> : &mix_ring_kernel<T, L, RT, false>)<<<dim3(blocks), dim3(T), 0, st>>>(mm); return hipGetLastError()
 #define CECA_RTS(T, L) CECA_RT(T, L, 8); CECA_RT(T, L, 9); CECA_RT(T, L, 10); CECA_RT(T, L, 11); CECA_RT(T, L, 12); CECA_RT(T, L, 13); CECA_RT(T, L, 14)
     CECA_RT(256, 16, 5); CECA_RT(256, 16, 6); CECA_RT(256, 16, 7); CECA_RTS(256, 16); CECA_RT(256, 16, 15); CECA_RT(256, 16, 16); CECA_RT(256, 16, 17);
     CECA_RTS(512, 16); CECA_RTS(512, 8); CECA_RT(512, 8, 15); CECA_RTS(512, 4); CECA_RTS(1024, 4); CECA_RT(1024, 4, 15); CECA_RT(1024, 4, 16);

@@ -43,7 +43,7 @@ __device__ __forceinline__ int wrap_slot(int s, int wrap) {   // s in (-wrap, 2 
   return (int)min((unsigned)s, (unsigned)(s - wrap));
 }
 
-template <int VEC, int RT, int THREADS, int LEAN>
+template <int VEC, int RT, int THREADS, int LEAN, bool WHOLE>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(rounds_waves<THREADS, LEAN>())))
 void multi_round_kernel(const MultiArgs M) {
   using V = typename VecOf<VEC>::T;
@@ -61,9 +61,10 @@ void multi_round_kernel(const MultiArgs M) {
   V x[RT], y[RT];
   // rows past the last agent shadow the last one (their values are never stored): no branch
   // surrounds a load, so all of a thread's rows are in flight together
-  const int64_t from = col - columns_back(M, col);
-  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
-  if (M.mem.short_cols) {
+  const auto mem = tile_of<WHOLE>(M);
+  const int64_t from = col - (WHOLE ? 0 : columns_back(M, col));
+  load_rows<V, RT>(x, M.xin + from, M.ld, rg, M.row_lanes, M.n - 1, mem.cached_loads);
+  if (mem.short_cols) {
     const int back = (int)(col - from);
 #pragma unroll
     for (int k = 0; k < RT; ++k) x[k] = own_columns(x[k], back);
@@ -145,8 +146,8 @@ void multi_round_kernel(const MultiArgs M) {
   int rg_out = rg;
   int64_t out = col;
   asm volatile("" : "+v"(rg_out), "+v"(out));
-  store_rows<V, RT>(x, M.xout + out, y, M.yout ? M.yout + out : nullptr, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out),
-                    M.mem.cached_stores);
+  store_rows<V, RT>(x, M.xout + out, y, M.yout ? M.yout + out : nullptr, M.ld, rg_out, M.row_lanes, M.n - 1, WHOLE ? 0 : columns_back(M, out),
+                    mem.cached_stores);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -157,7 +158,7 @@ void multi_round_kernel(const MultiArgs M) {
 // Eqs. (8), (9)), `rounds` times.  20 bytes per agent-parameter for any number of iterations.  The
 // arithmetic per iteration is that of the single-step kernel, operation for operation.
 // ---------------------------------------------------------------------------------------------
-template <int VEC, int RT, int THREADS, bool NOISY>
+template <int VEC, int RT, int THREADS, bool NOISY, bool WHOLE>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(multi_round_waves<THREADS>())))
 void multi_step_kernel(const StepsArgs S) {
 #pragma clang fp contract(off)
@@ -176,16 +177,17 @@ void multi_step_kernel(const StepsArgs S) {
 
   V x[RT], y[RT], c[RT];
   const bool first_reads_y = M.round[0].read_y != 0;
-  const int64_t from = col - columns_back(M, col);
+  const auto mem = tile_of<WHOLE>(M);
+  const int64_t from = col - (WHOLE ? 0 : columns_back(M, col));
   // rows past the last agent shadow it
-  load_rows<V, RT>(x, M.xin + from, M.ld, c, S.c + from, S.ldc, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
+  load_rows<V, RT>(x, M.xin + from, M.ld, c, S.c + from, S.ldc, rg, M.row_lanes, M.n - 1, mem.cached_loads);
   if (first_reads_y) {                             // a first round with b = 0 never uses y(0)
-    load_rows<V, RT>(y, S.yin + from, M.ld, rg, M.row_lanes, M.n - 1, M.mem.cached_loads);
+    load_rows<V, RT>(y, S.yin + from, M.ld, rg, M.row_lanes, M.n - 1, mem.cached_loads);
   } else {
 #pragma unroll
     for (int k = 0; k < RT; ++k) y[k] = V(0.0f);
   }
-  if (M.mem.short_cols) {
+  if (mem.short_cols) {
     const int back = (int)(col - from);
 #pragma unroll
     for (int k = 0; k < RT; ++k) {
@@ -294,12 +296,14 @@ void multi_step_kernel(const StepsArgs S) {
   int rg_out = rg;
   int64_t out = col;
   asm volatile("" : "+v"(rg_out), "+v"(out));
-  store_rows<V, RT>(x, M.xout + out, y, M.yout + out, M.ld, rg_out, M.row_lanes, M.n - 1, columns_back(M, out), M.mem.cached_stores);
+  store_rows<V, RT>(x, M.xout + out, y, M.yout + out, M.ld, rg_out, M.row_lanes, M.n - 1, WHOLE ? 0 : columns_back(M, out), mem.cached_stores);
 }
 
 template <int VEC, int RT, int THREADS>
 static hipError_t launch_steps(const StepsArgs& ss, unsigned blocks, size_t lds, hipStream_t st) {
-  const auto fn = ss.noise_std != 0.0f ? &multi_step_kernel<VEC, RT, THREADS, true> : &multi_step_kernel<VEC, RT, THREADS, false>;
+  auto fn = ss.noise_std != 0.0f ? &multi_step_kernel<VEC, RT, THREADS, true, false> : &multi_step_kernel<VEC, RT, THREADS, false, false>;
+  if constexpr (VEC == 4 && THREADS == 256)
+    if (ss.m.mem.whole()) fn = ss.noise_std != 0.0f ? &multi_step_kernel<VEC, RT, THREADS, true, true> : &multi_step_kernel<VEC, RT, THREADS, false, true>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -360,13 +364,15 @@ hipError_t launch_multi_step(const StepsArgs& s, bool vec4, hipStream_t st) {
 
 template <int VEC, int RT, int THREADS, int LEAN>
 static hipError_t launch_rounds(const MultiArgs& mm, unsigned blocks, size_t lds, hipStream_t st) {
+  auto fn = &multi_round_kernel<VEC, RT, THREADS, LEAN, false>;
+  if constexpr (VEC == 4 && THREADS <= 512 && LEAN < 6)
+    if (mm.mem.whole()) fn = &multi_round_kernel<VEC, RT, THREADS, LEAN, true>;
   if (lds > 64 * 1024) {
     // more than 64 KB of LDS per workgroup has to be asked for
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&multi_round_kernel<VEC, RT, THREADS, LEAN>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  multi_round_kernel<VEC, RT, THREADS, LEAN><<<dim3(blocks), dim3(THREADS), lds, st>>>(mm);
+  fn<<<dim3(blocks), dim3(THREADS), lds, st>>>(mm);
   return hipGetLastError();
 }
 
