@@ -321,7 +321,8 @@ hipError_t launch_phi(double* out, hipStream_t st);
 // rows) 482 / 382 -> 387 / 358.  Cached stores alone bring two thirds of it for the rounds and all for the averaging.
 // Not everywhere.  Outputs of up to 48 MB (the L2s hold 32 MB together): where pitch and base are whole lines and only the tile's
 // rows are narrower, 64 bytes, they are streamed (n = 800, 2^23 elements, exact averaging 30.2 us against 32.9, one-peer rounds
-// 22.7 against 25.7; narrower rows gain 1.3 to 1.5 times from the caches).  Rows of 512 bytes and more share few lines: their
+// 22.7 against 25.7; narrower rows gain 1.3 to 1.5 times from the caches).  Ring tiles are not, `narrow_streamed` false (n = 1000, 2^20 elements
+// 7.65 us cached, 8.89 streamed, 2^22 15.1, 12.9, 2^23 23.8, 30.1).  Rows of 512 bytes and more share few lines: their
 // stores are streamed from 12 MB to 48 MB (n = 10 and 31, 2^23 elements at pitches of 16 bytes: ring 14.5 against 17.7,
 // one-peer 13.4 against 15.6; 2^24 elements cached stores win again, 0.85 against 0.94), those of rows of 2048 bytes from 200 MB on
 // (n = 3, 2^26 elements, exact averaging 79 against 98, ring 80 against 99).
@@ -333,12 +334,12 @@ inline bool on_lines(const void* a, const void* b, int64_t ld) {
   return ld % 32 == 0 && ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 127) == 0;
 }
 inline void tile_memory(TileMemory* mem, int row_bytes, const void* in, const void* out, int64_t ld, int64_t out_rows, int64_t* blocks,
-                        const void* aux = nullptr, int64_t ldaux = 0) {
+                        const void* aux = nullptr, int64_t ldaux = 0, bool narrow_streamed = true) {
   const bool pitch_lines = on_lines(in, out, ld), aux_lines = on_lines(aux, aux, ldaux);
   const bool whole_lines = row_bytes % 128 == 0 && pitch_lines;
   const int64_t out_bytes = out_rows * ld * (int64_t)sizeof(float);
   const bool small = out_bytes <= (48LL << 20);
-  const bool streamed = whole_lines || (small && pitch_lines && row_bytes >= 64);
+  const bool streamed = whole_lines || (narrow_streamed && small && pitch_lines && row_bytes >= 64);
   const bool wide = !pitch_lines && ((row_bytes >= 512 && small && out_bytes >= (12LL << 20)) || (row_bytes >= 2048 && out_bytes >= (200LL << 20)));
   mem->xcd_runs = 0;
   mem->cached_loads = !streamed || (!aux_lines && !small);

@@ -446,7 +446,7 @@ hipError_t launch_mix_rounds(const MixArgs& m, bool vec4, hipStream_t st) {
   int64_t blocks = (m.ngroups + lanes - 1) / lanes;
   if (blocks < 1 || blocks >= (1LL << 24)) return hipErrorInvalidConfiguration;
   MixArgs mm = m;
-  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, m.n, &blocks);
+  tile_memory(&mm.mem, lanes * (vec4 ? 16 : 4), m.xin, m.xout, m.ld, m.n, &blocks, nullptr, 0, /*narrow_streamed=*/!ring);
   if (ring) return launch_mix_ring(mm, ring_threads, lanes, (unsigned)blocks, st);
   const size_t lds = (size_t)m.n * lanes * (vec4 ? 16 : 4);
   if (lds > kMultiMaxLds) return hipErrorInvalidValue;
